@@ -203,6 +203,21 @@ void launch_segments(uint32_t *keys, uint32_t *vals, uint32_t *tk, uint32_t *tv,
 void launch_batched(uint32_t *keys, uint32_t *vals, const uint32_t *offsets, uint32_t num_segments,
                     const SegLayout &L, char *ws, hipStream_t stream);
 
+// Most items one block sorts whole in LDS (rt_block_sort.h): 32-bit keys, and
+// 64-bit keys with values of up to 8 bytes.
+constexpr size_t kBlockSortMax32 = 16384;
+constexpr size_t kBlockSortMax64 = 8192;
+// A whole array of 2 to that many items in one launch; vals NULL: keys only
+// (value_words 0, 1 or 2 with 64-bit keys).
+void launch_block_sort(uint32_t *keys, uint32_t *vals, uint32_t n, hipStream_t stream);
+void launch_block_sort64(uint64_t *keys, uint32_t *vals, uint32_t value_words, uint32_t n, hipStream_t stream);
+// Whether cfg leaves the method to the library: no digits, shape or flags
+// but RT_FLAG_VALIDATE.
+bool default_method(const rt_config *cfg);
+// The end of a call that ran no kernel which can raise a device error:
+// finish_call, and with RT_FLAG_VALIDATE the wait it asks for.
+rt_status finish_waited(const rt_config *cfg, hipStream_t stream, const char *what);
+
 // Kernel timing marks (see rt_profile_start); cheap no-ops when disabled.
 void prof_begin(hipStream_t stream);
 void prof_mark(hipStream_t stream, uint32_t kind);

@@ -585,7 +585,12 @@ extern "C" rt_status rt_sort_pairs_ex(uint32_t *keys, uint32_t *vals, size_t n, 
                              workspace_bytes, L.total);
         if (reinterpret_cast<uintptr_t>(ws) & 255u)
             return set_error(RT_ERR_INVALID_ARG, "rt_sort_pairs_ex: workspace must be 256-byte aligned");
-    } else {
+    }
+    if (default_method(cfg) && n <= kBlockSortMax32) {
+        launch_block_sort(keys, vals, static_cast<uint32_t>(n), stream);
+        return finish_waited(cfg, stream, "rt_sort_pairs_ex");
+    }
+    if (ws == nullptr) {
         s = cached_workspace(L.total, stream, &ws);
         if (s != RT_OK) return s;
     }
@@ -652,6 +657,10 @@ extern "C" rt_status rt_sort_pairs_noalloc(uint32_t *keys, uint32_t *vals, size_
                          "rt_sort_pairs_noalloc: %zu items need %zu bytes of workspace; the static scratch holds %zu "
                          "(use rt_sort_pairs_ex)",
                          n, L.total, kNoAllocScratchBytes);
+    if (default_method(cfg) && n <= kBlockSortMax32) {
+        launch_block_sort(keys, vals, static_cast<uint32_t>(n), stream);
+        return finish_waited(cfg, stream, "rt_sort_pairs_noalloc");
+    }
     void *ws = nullptr;
     s = noalloc_scratch(&ws, "rt_sort_pairs_noalloc");
     if (s != RT_OK) return s;

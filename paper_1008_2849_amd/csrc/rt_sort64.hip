@@ -408,7 +408,12 @@ extern "C" rt_status rt_sort64_ex(uint64_t *keys, void *vals, uint32_t value_byt
                              L.total);
         if (reinterpret_cast<uintptr_t>(ws) & 255u)
             return set_error(RT_ERR_INVALID_ARG, "rt_sort64_ex: workspace must be 256-byte aligned");
-    } else {
+    }
+    if (default_method(cfg) && n <= kBlockSortMax64) {
+        launch_block_sort64(keys, static_cast<uint32_t *>(vals), vw, static_cast<uint32_t>(n), stream);
+        return finish_waited(cfg, stream, "rt_sort64_ex");
+    }
+    if (ws == nullptr) {
         s = cached_workspace(L.total, stream, &ws);
         if (s != RT_OK) return s;
     }
