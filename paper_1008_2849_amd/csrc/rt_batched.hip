@@ -36,6 +36,17 @@ bool seg_tile_shape_supported(int block, int ipt) {
     return false;
 }
 
+template <int BLOCK, int IPT, bool VALS, int BITS>
+static void launch_seg_small_shape(uint32_t grid, hipStream_t stream, const SegDesc *descs, const uint32_t *list,
+                                   const SegHeader *h, int which, int key_bits, int to_temp) {
+    if constexpr (BITS == 8)
+        hipLaunchKernelGGL((k_seg_small<BLOCK, IPT, VALS>), dim3(grid), dim3(BLOCK), 0, stream, descs, list, h, which,
+                           to_temp);
+    else
+        hipLaunchKernelGGL((k_seg_small_digits<BLOCK, IPT, VALS, BITS>), dim3(grid), dim3(BLOCK), 0, stream, descs,
+                           list, h, which, key_bits, to_temp);
+}
+
 void launch_seg_small(const SegClass &c, bool vals, uint32_t max_listed, hipStream_t stream, const SegDesc *descs,
                       const uint32_t *list, const SegHeader *h, int which, int key_bits, int to_temp) {
     // enough blocks to fill the CUs: more per CU for smaller shapes, as many
@@ -46,15 +57,11 @@ void launch_seg_small(const SegClass &c, bool vals, uint32_t max_listed, hipStre
     const uint32_t per_cu = std::max<uint32_t>(
         {1u, kSegLdsMax / static_cast<uint32_t>(c.block * c.ipt), kLdsBytesPerCu / lds});
     const uint32_t grid = std::max<uint32_t>(1u, std::min<uint32_t>(max_listed, cus * per_cu));
-#define RT_SEG_SHAPE_LAUNCH(BLK, I, B)                                                                           \
-    if (c.block == BLK && c.ipt == I && c.bits == B) {                                                           \
-        if (vals)                                                                                                \
-            hipLaunchKernelGGL((k_seg_small<BLK, I, true, B>), dim3(grid), dim3(BLK), 0, stream, descs, list, h, \
-                               which, key_bits, to_temp);                                                        \
-        else                                                                                                     \
-            hipLaunchKernelGGL((k_seg_small<BLK, I, false, B>), dim3(grid), dim3(BLK), 0, stream, descs, list,   \
-                               h, which, key_bits, to_temp);                                                     \
-        return;                                                                                                  \
+#define RT_SEG_SHAPE_LAUNCH(BLK, I, B)                                             \
+    if (c.block == BLK && c.ipt == I && c.bits == B) {                             \
+        if (vals) launch_seg_small_shape<BLK, I, true, B>(grid, stream, descs, list, h, which, key_bits, to_temp); \
+        else launch_seg_small_shape<BLK, I, false, B>(grid, stream, descs, list, h, which, key_bits, to_temp);     \
+        return;                                                                    \
     }
     RT_FOR_EACH_SEG_SMALL_SHAPE(RT_SEG_SHAPE_LAUNCH)
 #undef RT_SEG_SHAPE_LAUNCH

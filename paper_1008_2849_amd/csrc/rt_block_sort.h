@@ -28,6 +28,8 @@ namespace rt {
 // cost less than two digit passes.  For n uniform keys in NB >= n / 1.1 bins
 // the fullest bin holds 6 to 8 items.
 constexpr uint32_t kBinLimit = 24;
+constexpr int kSlotGroup = 4;  // slots whose LDS reads go out together
+constexpr int kCrowded = 8;  // of 64 sampled keys in one of 256 cells
 
 constexpr int floor_log2(int x) { return x <= 1 ? 0 : 1 + floor_log2(x / 2); }
 constexpr int ceil_log2(int x) { return x <= 1 ? 0 : 1 + floor_log2(x - 1); }
@@ -44,7 +46,7 @@ struct BlockSortLds {
     union {
         struct {
             uint32_t bin[NB + 4];          // counts, then starts; bin[NB] = n
-            K word[CAP + kBinLimit];       // a rank may read past its bin, never past this
+            K word[CAP + kBinLimit + 2];   // a rank may read past its bin, never past this; the last: past the end
         } b;
         struct {
             K k[CAP];
@@ -91,48 +93,111 @@ __device__ __forceinline__ T wave_fold(T x, F op) {
     return last_lane(x);
 }
 
-// Sorts items [0, n) of in_k/in_v (n <= BLOCK * IPT) into out_k/out_v, which
-// may be the same arrays.  Every thread of the block must call it; the LDS
-// is free again after the next barrier.
+// Makes x opaque: what was derived from it is derived again, not kept in
+// registers across a phase.
+__device__ __forceinline__ void forget(uint32_t &x) { asm volatile("" : "+v"(x)); }
+__device__ __forceinline__ void forget(uint64_t &x) { asm volatile("" : "+v"(x)); }
+
+// The staged items, each key plus lo, to out_k/out_v: GRP slots' LDS reads go
+// out together.
+template <int BLOCK, int IPT, typename K, typename V, bool VALS>
+__device__ __forceinline__ void block_store(const BlockSortLds<BLOCK, IPT, K, V, VALS> &lds, uint32_t tid, uint32_t n,
+                                            K lo, K *out_k, V *out_v) {
+    constexpr int GRP = kSlotGroup;
+#pragma unroll
+    for (int g = 0; g < IPT; g += GRP) {
+        if (static_cast<uint32_t>(g * BLOCK) >= n) break;
+        K k[GRP];
+        V v[VALS ? GRP : 1];
+#pragma unroll
+        for (int q = 0; q < GRP; ++q) {
+            if (g + q >= IPT) continue;
+            k[q] = lds.s.k[(g + q) * BLOCK + tid] + lo;
+            if constexpr (VALS) v[q] = lds.s.v[(g + q) * BLOCK + tid];
+        }
+#pragma unroll
+        for (int q = 0; q < GRP; ++q) {
+            const uint32_t i = (g + q) * BLOCK + tid;
+            if (g + q >= IPT || i >= n) continue;
+            *gptr<K, true>(out_k, i) = k[q];
+            if constexpr (VALS) *gptr<V, true>(out_v, i) = v[q];
+        }
+    }
+}
+
+// Sorts items [0, n) of in_k/in_v (1 <= n <= BLOCK * IPT) into out_k/out_v,
+// which may be the same arrays.  Every thread of the block must call it; the
+// LDS is free again after the next barrier.
+//
+// Each wave owns `slots` * 64 consecutive items, lane l the items l, l + 64,
+// ... of them: the items are spread over all waves whatever n is, and slot by
+// slot, lane by lane is input order.  Where an LDS read is followed by its
+// use, kSlotGroup slots are taken together and without a test per item, so
+// that their reads overlap: past the end, a lane writes to a spare place.
 template <int BLOCK, int IPT, typename K, typename V, bool VALS>
 __device__ __forceinline__ void block_sort(const K *in_k, const V *in_v, uint32_t n, K *out_k, V *out_v,
                                            BlockSortLds<BLOCK, IPT, K, V, VALS> &lds) {
     typedef BlockSortLds<BLOCK, IPT, K, V, VALS> L;
     constexpr int WAVES = L::WAVES;
     constexpr int PER = L::PER;
+    constexpr int GRP = kSlotGroup;
     constexpr uint32_t NB = L::NB;
-    const uint32_t tid = threadIdx.x;
+    uint32_t tid = threadIdx.x;
+    forget(tid);
     const uint32_t lane = tid & 63u;
-    const uint32_t wave = tid >> 6;
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    n = __builtin_amdgcn_readfirstlane(n);
+    const int slots = static_cast<int>((n + BLOCK - 1) / BLOCK);
+    const uint32_t slot0 = wave * 64u * slots;
+    uint32_t item0 = slot0 + lane;
+    // whether slot j holds an item of this lane
+#define RT_LIVE(j) (item0 + (j) * 64 < ((j) < slots ? n : 0u))
 
-    // ---- load (item j * BLOCK + tid in slot j), clear the bins, key range
+    // ---- load, clear the bins, key range
     K key[IPT];
-    V val[VALS ? IPT : 1];
     K lo = ~K(0), hi = 0;
 #pragma unroll
-    for (int j = 0; j < IPT; ++j) {
-        const uint32_t i = j * BLOCK + tid;
-        if (i < n) key[j] = in_k[i];
-    }
-    if constexpr (VALS) {
+    for (int g = 0; g < IPT; g += GRP)
+        if (g < slots) {
 #pragma unroll
-        for (int j = 0; j < IPT; ++j) {
-            const uint32_t i = j * BLOCK + tid;
-            if (i < n) val[j] = in_v[i];
+            for (int j = g; j < g + GRP && j < IPT; ++j) key[j] = *gptr<K, true>(in_k, min(item0 + j * 64, n - 1u));
         }
-    }
     for (uint32_t i = tid; i < NB / 4; i += BLOCK) reinterpret_cast<uint4 *>(lds.b.bin)[i] = make_uint4(0u, 0u, 0u, 0u);
 #pragma unroll
-    for (int j = 0; j < IPT; ++j) {
-        if (j * BLOCK + tid >= n) continue;
-        lo = key[j] < lo ? key[j] : lo;
-        hi = key[j] > hi ? key[j] : hi;
-    }
+    for (int g = 0; g < IPT; g += GRP)
+        if (g < slots) {
+#pragma unroll
+            for (int j = g; j < g + GRP && j < IPT; ++j) {
+                lo = key[j] < lo ? key[j] : lo;
+                hi = key[j] > hi ? key[j] : hi;
+            }
+        }
     lo = wave_fold(lo, [](K x, K y) { return x < y ? x : y; });
     hi = wave_fold(hi, [](K x, K y) { return x < y ? y : x; });
+    // Keys that crowd a few bins go straight to the digit passes, which would
+    // otherwise start after a bin count in vain: of one key per lane (from two
+    // slots, so that a sorted input looks spread), more than kCrowded share
+    // one of 128 to 256 cells of the wave's own range with one of six of them
+    // (spread keys: hardly ever more than 4).
+    bool crowded = false;
+    {
+        K pick = key[0];
+        if (IPT / 2 < slots) {
+            K other = key[IPT / 2];
+            forget(other);  // (a choice of two elements would put the keys in scratch memory)
+            if ((lane & 1u) && item0 + IPT / 2 * 64 < n) pick = other;
+        }
+        const uint32_t wbits = key_bits_of(static_cast<K>(hi - lo));
+        uint32_t cell = static_cast<uint32_t>((pick - lo) >> (wbits > 8 ? wbits - 8 : 0u));
+        if (item0 >= n) cell = 256u + lane;
+#pragma unroll
+        for (int q = 0; q < 6; ++q)
+            crowded |= __popcll(__builtin_amdgcn_ballot_w64(cell == __builtin_amdgcn_readlane(cell, 11 * q))) > kCrowded;
+    }
     if (lane == 0) {
         lds.wlo[wave] = lo;
         lds.whi[wave] = hi;
+        lds.wmax[wave] = crowded ? 1u : 0u;
     }
     __syncthreads();
 #pragma unroll
@@ -140,28 +205,30 @@ __device__ __forceinline__ void block_sort(const K *in_k, const V *in_v, uint32_
         const K a = lds.wlo[w], b = lds.whi[w];
         lo = a < lo ? a : lo;
         hi = b > hi ? b : hi;
+        crowded = crowded || lds.wmax[w] != 0u;
     }
-    const uint32_t bits = key_bits_of(static_cast<K>(hi - lo));
+    const uint32_t bits = __builtin_amdgcn_readfirstlane(key_bits_of(static_cast<K>(hi - lo)));
     if (bits == 0) {  // one key value: the input order stands
         if (out_k != in_k) {
-#pragma unroll
-            for (int j = 0; j < IPT; ++j) {
-                const uint32_t i = j * BLOCK + tid;
-                if (i >= n) continue;
-                out_k[i] = key[j];
-                if constexpr (VALS) out_v[i] = val[j];
+            for (uint32_t i = tid; i < n; i += BLOCK) {
+                *gptr<K, true>(out_k, i) = *gptr<K, true>(in_k, i);
+                if constexpr (VALS) *gptr<V, true>(out_v, i) = *gptr<V, true>(in_v, i);
             }
         }
         return;
     }
     const uint32_t shift = bits > static_cast<uint32_t>(L::LOG_NB) ? bits - L::LOG_NB : 0u;
+    V val[VALS ? IPT : 1];
 
     // ---- bin sort, if an item's word holds its bits below the bin and its index
-    if (shift + L::IDX_BITS <= 8 * sizeof(K)) {
-        uint32_t at[IPT];  // slot in the bin, then the bin's start
+    if (!crowded && shift + L::IDX_BITS <= 8 * sizeof(K)) {
+        uint32_t at[IPT];  // slot in the bin, then the final position
 #pragma unroll
         for (int j = 0; j < IPT; ++j)
-            if (j * BLOCK + tid < n) at[j] = atomicAdd(&lds.b.bin[static_cast<uint32_t>((key[j] - lo) >> shift)], 1u);
+        {
+            at[j] = 0;
+            if (RT_LIVE(j)) at[j] = atomicAdd(&lds.b.bin[static_cast<uint32_t>((key[j] - lo) >> shift)], 1u);
+        }
         __syncthreads();
         // exclusive prefix sum: wave w owns bins [w, w + 1) * 64 * PER, four
         // consecutive bins a lane and step
@@ -191,79 +258,96 @@ __device__ __forceinline__ void block_sort(const K *in_k, const V *in_v, uint32_
             if (w < static_cast<int>(wave)) before += lds.wsum[w];
             most = max(most, lds.wmax[w]);
         }
+        most = __builtin_amdgcn_readfirstlane(most);
         if (most <= kBinLimit) {
 #pragma unroll
             for (int q = 0; q < PER / 4; ++q)
                 row[q * 64 + lane] = make_uint4(c[q].x + before, c[q].y + before, c[q].z + before, c[q].w + before);
             if (tid == 0) lds.b.bin[NB] = n;
             __syncthreads();
-            // ---- one word per item, in its bin's slots
-            K mine[IPT];
-            uint32_t cnt[IPT], pos[IPT];
+            // ---- one word per item, in its bin's slots: the key's bits below
+            // the bin, then the item's index; and the values on their way
+            const K below = (K(1) << shift) - 1u;
+            forget(item0);
 #pragma unroll
-            for (int j = 0; j < IPT; ++j) {
-                const uint32_t i = j * BLOCK + tid;
-                cnt[j] = 0;
-                mine[j] = 0;
-                if (i >= n) {
-                    at[j] = 0;
-                    continue;
+            for (int g = 0; g < IPT; g += GRP)
+                if (g < slots) {
+#pragma unroll
+                    for (int j = g; j < g + GRP && j < IPT; ++j) {
+                        forget(key[j]);
+                        const uint32_t i = item0 + j * 64;
+                        const K rel = key[j] - lo;
+                        uint32_t p = lds.b.bin[static_cast<uint32_t>(rel >> shift)] + at[j];
+                        if (!RT_LIVE(j)) p = L::CAP + kBinLimit;
+                        lds.b.word[p] = ((rel & below) << L::IDX_BITS) | i;
+                        if constexpr (VALS) val[j] = *gptr<V, true>(in_v, min(i, n - 1u));
+                    }
                 }
-                const K rel = key[j] - lo;
-                const uint32_t b = static_cast<uint32_t>(rel >> shift);
-                const uint32_t first = lds.b.bin[b];
-                cnt[j] = lds.b.bin[b + 1] - first;
-                mine[j] = ((rel & ((K(1) << shift) - 1u)) << L::IDX_BITS) | i;
-                lds.b.word[first + at[j]] = mine[j];
-                at[j] = first;
-                pos[j] = first;
-            }
             __syncthreads();
-            // ---- rank in the bin: the smaller words among its slots (the
-            // reads past a shorter bin hit later words and do not count)
-            for (uint32_t t = 0; t < most; ++t) {
+            // ---- rank in the bin: the smaller words among its slots.  The
+            // bins are read again, so that only keys, values and positions stay
+            // in registers across the groups.  Reads past a shorter bin hit
+            // later words and do not count.
 #pragma unroll
-                for (int j = 0; j < IPT; ++j) {
-                    if (j * BLOCK >= n) continue;
-                    const K w = lds.b.word[at[j] + t];
-                    pos[j] += static_cast<uint32_t>((t < cnt[j]) & (w < mine[j]));
+            for (int g = 0; g < IPT; g += GRP)
+                if (g < slots) {
+                    uint32_t first[GRP], cnt[GRP], r[GRP];
+                    K mine[GRP];
+                    forget(item0);
+#pragma unroll
+                    for (int q = 0; q < GRP; ++q) {
+                        if (g + q >= IPT) continue;
+                        forget(key[g + q]);
+                        const K rel = key[g + q] - lo;
+                        const uint32_t b = static_cast<uint32_t>(rel >> shift);
+                        first[q] = lds.b.bin[b];
+                        cnt[q] = lds.b.bin[b + 1];
+                        mine[q] = ((rel & below) << L::IDX_BITS) | (item0 + (g + q) * 64);
+                        r[q] = first[q];
+                    }
+#pragma unroll
+                    for (int q = 0; q < GRP; ++q)
+                        if (g + q < IPT) cnt[q] -= first[q];
+                    for (uint32_t t = 0; t < most; t += 2) {
+#pragma unroll
+                        for (int q = 0; q < GRP; ++q) {
+                            if (g + q >= IPT) continue;
+                            const K w0 = lds.b.word[first[q] + t], w1 = lds.b.word[first[q] + t + 1];
+                            r[q] += static_cast<uint32_t>((t < cnt[q]) & (w0 < mine[q]));
+                            r[q] += static_cast<uint32_t>((t + 1 < cnt[q]) & (w1 < mine[q]));
+                        }
+                    }
+#pragma unroll
+                    for (int q = 0; q < GRP; ++q)
+                        if (g + q < IPT) at[g + q] = r[q];
                 }
-            }
             __syncthreads();
             // ---- gather by position, then write consecutive addresses
+            forget(item0);
 #pragma unroll
             for (int j = 0; j < IPT; ++j) {
-                if (j * BLOCK + tid >= n) continue;
-                lds.s.k[pos[j]] = key[j];
-                if constexpr (VALS) lds.s.v[pos[j]] = val[j];
+                if (!RT_LIVE(j)) continue;
+                lds.s.k[at[j]] = key[j];
+                if constexpr (VALS) lds.s.v[at[j]] = val[j];
             }
             __syncthreads();
-#pragma unroll
-            for (int j = 0; j < IPT; ++j) {
-                const uint32_t i = j * BLOCK + tid;
-                if (i >= n) continue;
-                out_k[i] = lds.s.k[i];
-                if constexpr (VALS) out_v[i] = lds.s.v[i];
-            }
+            forget(tid);
+            block_store<BLOCK, IPT, K, V, VALS>(lds, tid, n, K(0), out_k, out_v);
             return;
         }
-        __syncthreads();  // the bins are read: the digit passes reuse the LDS
     }
+    __syncthreads();  // the digit passes reuse the LDS
 
-    // ---- digit passes.  Wave w owns items [w, w + 1) * 64 * IPT and lane l
-    // holds item s * 64 + l of them in slot s, so that slot-by-slot,
-    // lane-by-lane ranking follows input order.  Slots wholly past the end
-    // are neither ranked nor staged; the empty lanes of the slot that holds
-    // the end take the highest digit, behind every item.
-    constexpr int WAVE_ITEMS = 64 * IPT;
-    const uint32_t wslot0 = wave * WAVE_ITEMS + lane;
+    // ---- digit passes, ranked in input order.  Slots wholly past the end are
+    // neither ranked nor staged; the empty lanes of the slot that holds the
+    // end take the highest digit, behind every item.
+    forget(item0);
     uint32_t *wh = lds.whist + wave * 256;
     uint32_t *scratch = lds.whist + WAVES * 256 + wave * 64 + lane;
 #pragma unroll
     for (int j = 0; j < IPT; ++j) {
-        const uint32_t i = wslot0 + j * 64;
-        key[j] = i < n ? static_cast<K>(in_k[i] - lo) : ~K(0);
-        if constexpr (VALS) val[j] = i < n ? in_v[i] : V(0);
+        key[j] = RT_LIVE(j) ? static_cast<K>(key[j] - lo) : ~K(0);
+        if constexpr (VALS) val[j] = RT_LIVE(j) ? *gptr<V, true>(in_v, item0 + j * 64) : V(0);
     }
     for (uint32_t sh = 0; sh < bits; sh += 8) {
         for (uint32_t i = lane; i < 256; i += 64) wh[i] = 0u;
@@ -271,7 +355,7 @@ __device__ __forceinline__ void block_sort(const K *in_k, const V *in_v, uint32_
         uint32_t rnk[IPT];
 #pragma unroll
         for (int j = 0; j < IPT; ++j) {
-            if (wave * WAVE_ITEMS + j * 64 >= n) continue;
+            if (j >= slots || slot0 + j * 64 >= n) continue;
             const uint32_t dg = static_cast<uint32_t>(key[j] >> sh) & 255u;
             uint32_t mlo, mhi;
             match_digit<8>(dg, mlo, mhi);
@@ -321,7 +405,7 @@ __device__ __forceinline__ void block_sort(const K *in_k, const V *in_v, uint32_
         __syncthreads();
 #pragma unroll
         for (int j = 0; j < IPT; ++j) {
-            if (wave * WAVE_ITEMS + j * 64 >= n) continue;
+            if (j >= slots || slot0 + j * 64 >= n) continue;
             const uint32_t r = wh[static_cast<uint32_t>(key[j] >> sh) & 255u] + rnk[j];
             lds.s.k[r] = key[j];
             if constexpr (VALS) lds.s.v[r] = val[j];
@@ -330,17 +414,15 @@ __device__ __forceinline__ void block_sort(const K *in_k, const V *in_v, uint32_
         if (sh + 8 < bits) {
 #pragma unroll
             for (int j = 0; j < IPT; ++j) {
-                const uint32_t i = wslot0 + j * 64;
-                key[j] = i < n ? lds.s.k[i] : ~K(0);
-                if constexpr (VALS) val[j] = i < n ? lds.s.v[i] : V(0);
+                const uint32_t i = item0 + j * 64;
+                key[j] = RT_LIVE(j) ? lds.s.k[i] : ~K(0);
+                if constexpr (VALS) val[j] = RT_LIVE(j) ? lds.s.v[i] : V(0);
             }
             // the stage is rewritten only after the next pass's first barrier
         }
     }
-    for (uint32_t i = tid; i < n; i += BLOCK) {
-        out_k[i] = lds.s.k[i] + lo;
-        if constexpr (VALS) out_v[i] = lds.s.v[i];
-    }
+    block_store<BLOCK, IPT, K, V, VALS>(lds, tid, n, lo, out_k, out_v);
+#undef RT_LIVE
 }
 
 // A whole array of at most BLOCK * IPT items, sorted in place by one block:

@@ -16,7 +16,7 @@
 // Each pass is Section 3's counting sort (histogram, exclusive prefix sum,
 // stable scatter) and the pass sequence is Section 4's LSD order; a segment
 // is sorted exactly as a single array of its own would be.
-#include "rt_kernels.h"
+#include "rt_block_sort.h"
 
 namespace rt {
 
@@ -200,9 +200,27 @@ static __global__ __launch_bounds__(256) void k_seg_tilemap(const SegDesc *__res
 // whole segment in one block
 // ---------------------------------------------------------------------------
 
-// Sorts segments of at most BLOCK * IPT items, one per block at a time.  The
-// segment is loaded once from k/v, taken through the digits of passes
-// 0..passes-1 in LDS, and stored once: to k/v, or to tk/tv when to_temp is
+// Sorts segments of at most BLOCK * IPT items, one per block at a time: bin
+// sort, or 8-bit digit passes for crowded bins (rt_block_sort.h).  A segment
+// is loaded once from k/v and stored once: to k/v, or to tk/tv when to_temp
+// is set (where the tiled passes leave an odd pass count's result).
+template <int BLOCK, int IPT, bool VALS>
+__global__ __launch_bounds__(BLOCK, 4) void k_seg_small(const SegDesc *__restrict__ descs,
+                                                     const uint32_t *__restrict__ list,
+                                                     const SegHeader *__restrict__ h, int which, int to_temp) {
+    __shared__ BlockSortLds<BLOCK, IPT, uint32_t, uint32_t, VALS> lds;
+    const uint32_t count = h->count[which];
+    for (uint32_t e = blockIdx.x; e < count; e += gridDim.x) {
+        const SegDesc d = descs[list[e]];
+        block_sort<BLOCK, IPT, uint32_t, uint32_t, VALS>(d.k, d.v, d.n, to_temp ? d.tk : d.k, to_temp ? d.tv : d.v,
+                                                         lds);
+        __syncthreads();  // the LDS is reused by the next segment
+    }
+}
+
+// The same with BITS-bit digit passes only (the 11-bit classes of a tuning
+// table), on the low key_bits bits of the keys.  The
+// segment is loaded once from k/v, taken through its digits in LDS, and stored once: to k/v, or to tk/tv when to_temp is
 // set (where the tiled passes leave an odd pass count's result).  Slots
 // wholly past the segment's end are neither ranked nor staged; the empty
 // lanes of the slot that holds the end take all-ones keys, which rank behind
@@ -211,7 +229,7 @@ static __global__ __launch_bounds__(256) void k_seg_tilemap(const SegDesc *__res
 // pass is the onesweep ranking: wave-local ballot match plus per-wave digit
 // counters, then digit offsets across the block.
 template <int BLOCK, int IPT, bool VALS, int BITS>
-__global__ __launch_bounds__(BLOCK) void k_seg_small(const SegDesc *__restrict__ descs,
+__global__ __launch_bounds__(BLOCK) void k_seg_small_digits(const SegDesc *__restrict__ descs,
                                                      const uint32_t *__restrict__ list,
                                                      const SegHeader *__restrict__ h, int which, int key_bits,
                                                      int to_temp) {
