@@ -20,6 +20,8 @@
 //
 // The bin sort counts first and gives way to the digit passes when some bin
 // holds more than kBinLimit items.
+#pragma once
+
 #include "rt_kernels.h"
 
 namespace rt {
@@ -98,35 +100,53 @@ __device__ __forceinline__ T wave_fold(T x, F op) {
 __device__ __forceinline__ void forget(uint32_t &x) { asm volatile("" : "+v"(x)); }
 __device__ __forceinline__ void forget(uint64_t &x) { asm volatile("" : "+v"(x)); }
 
-// The staged items, each key plus lo, to out_k/out_v: GRP slots' LDS reads go
-// out together.
-template <int BLOCK, int IPT, typename K, typename V, bool VALS>
+// Where block_sort reads its items and puts the sorted ones.
+template <typename K, typename V>
+struct ArraySource {
+    const K *k;
+    const V *v;
+    __device__ __forceinline__ K key(uint32_t i) const { return *gptr<K, true>(k, i); }
+    __device__ __forceinline__ V val(uint32_t i) const { return *gptr<V, true>(v, i); }
+};
+template <typename K, typename V, bool VALS>
+struct ArraySink {
+    K *k;
+    V *v;
+    __device__ __forceinline__ void put(uint32_t i, K key, V val) const {
+        *gptr<K, true>(k, i) = key;
+        if constexpr (VALS) *gptr<V, true>(v, i) = val;
+    }
+};
+
+// The staged items, each key plus lo, to the sink: kSlotGroup slots' LDS reads
+// go out together.
+template <int BLOCK, int IPT, typename K, typename V, bool VALS, typename Sink>
 __device__ __forceinline__ void block_store(const BlockSortLds<BLOCK, IPT, K, V, VALS> &lds, uint32_t tid, uint32_t n,
-                                            K lo, K *out_k, V *out_v) {
+                                            K lo, const Sink &sink) {
     constexpr int GRP = kSlotGroup;
 #pragma unroll
     for (int g = 0; g < IPT; g += GRP) {
         if (static_cast<uint32_t>(g * BLOCK) >= n) break;
         K k[GRP];
-        V v[VALS ? GRP : 1];
+        V v[GRP];
 #pragma unroll
         for (int q = 0; q < GRP; ++q) {
             if (g + q >= IPT) continue;
             k[q] = lds.s.k[(g + q) * BLOCK + tid] + lo;
+            v[q] = 0;
             if constexpr (VALS) v[q] = lds.s.v[(g + q) * BLOCK + tid];
         }
 #pragma unroll
         for (int q = 0; q < GRP; ++q) {
             const uint32_t i = (g + q) * BLOCK + tid;
             if (g + q >= IPT || i >= n) continue;
-            *gptr<K, true>(out_k, i) = k[q];
-            if constexpr (VALS) *gptr<V, true>(out_v, i) = v[q];
+            sink.put(i, k[q], v[q]);
         }
     }
 }
 
-// Sorts items [0, n) of in_k/in_v (1 <= n <= BLOCK * IPT) into out_k/out_v,
-// which may be the same arrays.  Every thread of the block must call it; the
+// Sorts items [0, n) of src (1 <= n <= BLOCK * IPT) into sink, which may be
+// the same arrays (in_place).  Every thread of the block must call it; the
 // LDS is free again after the next barrier.
 //
 // Each wave owns `slots` * 64 consecutive items, lane l the items l, l + 64,
@@ -134,8 +154,8 @@ __device__ __forceinline__ void block_store(const BlockSortLds<BLOCK, IPT, K, V,
 // slot, lane by lane is input order.  Where an LDS read is followed by its
 // use, kSlotGroup slots are taken together and without a test per item, so
 // that their reads overlap: past the end, a lane writes to a spare place.
-template <int BLOCK, int IPT, typename K, typename V, bool VALS>
-__device__ __forceinline__ void block_sort(const K *in_k, const V *in_v, uint32_t n, K *out_k, V *out_v,
+template <int BLOCK, int IPT, typename K, typename V, bool VALS, typename Source, typename Sink>
+__device__ __forceinline__ void block_sort(const Source &src, uint32_t n, const Sink &sink, bool in_place,
                                            BlockSortLds<BLOCK, IPT, K, V, VALS> &lds) {
     typedef BlockSortLds<BLOCK, IPT, K, V, VALS> L;
     constexpr int WAVES = L::WAVES;
@@ -160,7 +180,7 @@ __device__ __forceinline__ void block_sort(const K *in_k, const V *in_v, uint32_
     for (int g = 0; g < IPT; g += GRP)
         if (g < slots) {
 #pragma unroll
-            for (int j = g; j < g + GRP && j < IPT; ++j) key[j] = *gptr<K, true>(in_k, min(item0 + j * 64, n - 1u));
+            for (int j = g; j < g + GRP && j < IPT; ++j) key[j] = src.key(min(item0 + j * 64, n - 1u));
         }
     for (uint32_t i = tid; i < NB / 4; i += BLOCK) reinterpret_cast<uint4 *>(lds.b.bin)[i] = make_uint4(0u, 0u, 0u, 0u);
 #pragma unroll
@@ -209,11 +229,11 @@ __device__ __forceinline__ void block_sort(const K *in_k, const V *in_v, uint32_
     }
     const uint32_t bits = __builtin_amdgcn_readfirstlane(key_bits_of(static_cast<K>(hi - lo)));
     if (bits == 0) {  // one key value: the input order stands
-        if (out_k != in_k) {
-            for (uint32_t i = tid; i < n; i += BLOCK) {
-                *gptr<K, true>(out_k, i) = *gptr<K, true>(in_k, i);
-                if constexpr (VALS) *gptr<V, true>(out_v, i) = *gptr<V, true>(in_v, i);
-            }
+        if (in_place) return;
+        for (uint32_t i = tid; i < n; i += BLOCK) {
+            V v = 0;
+            if constexpr (VALS) v = src.val(i);
+            sink.put(i, lo, v);
         }
         return;
     }
@@ -280,7 +300,7 @@ __device__ __forceinline__ void block_sort(const K *in_k, const V *in_v, uint32_
                         uint32_t p = lds.b.bin[static_cast<uint32_t>(rel >> shift)] + at[j];
                         if (!RT_LIVE(j)) p = L::CAP + kBinLimit;
                         lds.b.word[p] = ((rel & below) << L::IDX_BITS) | i;
-                        if constexpr (VALS) val[j] = *gptr<V, true>(in_v, min(i, n - 1u));
+                        if constexpr (VALS) val[j] = src.val(min(i, n - 1u));
                     }
                 }
             __syncthreads();
@@ -332,7 +352,7 @@ __device__ __forceinline__ void block_sort(const K *in_k, const V *in_v, uint32_
             }
             __syncthreads();
             forget(tid);
-            block_store<BLOCK, IPT, K, V, VALS>(lds, tid, n, K(0), out_k, out_v);
+            block_store<BLOCK, IPT, K, V, VALS>(lds, tid, n, K(0), sink);
             return;
         }
     }
@@ -347,7 +367,7 @@ __device__ __forceinline__ void block_sort(const K *in_k, const V *in_v, uint32_
 #pragma unroll
     for (int j = 0; j < IPT; ++j) {
         key[j] = RT_LIVE(j) ? static_cast<K>(key[j] - lo) : ~K(0);
-        if constexpr (VALS) val[j] = RT_LIVE(j) ? *gptr<V, true>(in_v, item0 + j * 64) : V(0);
+        if constexpr (VALS) val[j] = RT_LIVE(j) ? src.val(item0 + j * 64) : V(0);
     }
     for (uint32_t sh = 0; sh < bits; sh += 8) {
         for (uint32_t i = lane; i < 256; i += 64) wh[i] = 0u;
@@ -421,7 +441,7 @@ __device__ __forceinline__ void block_sort(const K *in_k, const V *in_v, uint32_
             // the stage is rewritten only after the next pass's first barrier
         }
     }
-    block_store<BLOCK, IPT, K, V, VALS>(lds, tid, n, lo, out_k, out_v);
+    block_store<BLOCK, IPT, K, V, VALS>(lds, tid, n, lo, sink);
 #undef RT_LIVE
 }
 
@@ -433,7 +453,7 @@ __device__ __forceinline__ void block_sort(const K *in_k, const V *in_v, uint32_
 template <int BLOCK, int IPT, typename K, typename V, bool VALS>
 __global__ __launch_bounds__(BLOCK) void k_block_sort(K *__restrict__ keys, V *__restrict__ vals, uint32_t n) {
     __shared__ BlockSortLds<BLOCK, IPT, K, V, VALS> lds;
-    block_sort<BLOCK, IPT, K, V, VALS>(keys, vals, n, keys, vals, lds);
+    block_sort<BLOCK, IPT, K, V, VALS>(ArraySource<K, V>{keys, vals}, n, ArraySink<K, V, VALS>{keys, vals}, true, lds);
 }
 
 }  // namespace rt

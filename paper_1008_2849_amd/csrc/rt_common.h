@@ -211,6 +211,16 @@ constexpr size_t kBlockSortMax64 = 8192;
 // (value_words 0, 1 or 2 with 64-bit keys).
 void launch_block_sort(uint32_t *keys, uint32_t *vals, uint32_t n, hipStream_t stream);
 void launch_block_sort64(uint64_t *keys, uint32_t *vals, uint32_t value_words, uint32_t n, hipStream_t stream);
+// The splitter sort (rt_split_kernels.h) takes the sizes above those, up to
+// these.  tk/tv: temporaries of n items; scratch: split_scratch_bytes() bytes,
+// 256-byte aligned.
+constexpr size_t kSplitMax32 = static_cast<size_t>(1) << 20;
+constexpr size_t kSplitMax64 = static_cast<size_t>(1) << 19;
+size_t split_scratch_bytes(size_t n, size_t key_bytes);
+void launch_split(uint32_t *keys, uint32_t *vals, uint32_t n, uint32_t *tk, uint32_t *tv, char *scratch,
+                  hipStream_t stream);
+void launch_split64(uint64_t *keys, uint32_t *vals, uint32_t value_words, uint32_t n, uint64_t *tk, uint32_t *tv,
+                    char *scratch, hipStream_t stream);
 // Whether cfg leaves the method to the library: no digits, shape or flags
 // but RT_FLAG_VALIDATE.
 bool default_method(const rt_config *cfg);

@@ -18,6 +18,8 @@
 // output leaves the chip in runs of consecutive addresses instead of one
 // scattered word per item, and the tiles are large (16K items) so that a
 // digit's run is 256 bytes long on average for uniform keys.
+#pragma once
+
 #include "rt_internal.h"
 
 namespace rt {

@@ -212,8 +212,9 @@ __global__ __launch_bounds__(BLOCK, 4) void k_seg_small(const SegDesc *__restric
     const uint32_t count = h->count[which];
     for (uint32_t e = blockIdx.x; e < count; e += gridDim.x) {
         const SegDesc d = descs[list[e]];
-        block_sort<BLOCK, IPT, uint32_t, uint32_t, VALS>(d.k, d.v, d.n, to_temp ? d.tk : d.k, to_temp ? d.tv : d.v,
-                                                         lds);
+        block_sort<BLOCK, IPT, uint32_t, uint32_t, VALS>(
+            ArraySource<uint32_t, uint32_t>{d.k, d.v}, d.n,
+            ArraySink<uint32_t, uint32_t, VALS>{to_temp ? d.tk : d.k, to_temp ? d.tv : d.v}, !to_temp, lds);
         __syncthreads();  // the LDS is reused by the next segment
     }
 }

@@ -570,6 +570,17 @@ static rt_status check_ranges(const uint32_t *keys, const uint32_t *vals, size_t
     return RT_OK;
 }
 
+// Takes the splitter sort where the method is the library's to choose and the
+// size suits it: its tables lie in the workspace below the first temporary.
+static bool try_split(uint32_t *keys, uint32_t *vals, size_t n, const rt_config *cfg, const Layout &L, void *ws,
+                      hipStream_t stream) {
+    if (!default_method(cfg) || n > kSplitMax32 || split_scratch_bytes(n, sizeof(uint32_t)) > L.t1k) return false;
+    char *w = static_cast<char *>(ws);
+    launch_split(keys, vals, static_cast<uint32_t>(n), reinterpret_cast<uint32_t *>(w + L.t1k),
+                 vals ? reinterpret_cast<uint32_t *>(w + L.t1v) : nullptr, w, stream);
+    return true;
+}
+
 extern "C" rt_status rt_sort_pairs_ex(uint32_t *keys, uint32_t *vals, size_t n, const rt_config *cfg,
                                 void *workspace, size_t workspace_bytes, hipStream_t stream) {
     rt_status s = check_ranges(keys, vals, n, "rt_sort_pairs_ex");
@@ -594,6 +605,7 @@ extern "C" rt_status rt_sort_pairs_ex(uint32_t *keys, uint32_t *vals, size_t n, 
         s = cached_workspace(L.total, stream, &ws);
         if (s != RT_OK) return s;
     }
+    if (try_split(keys, vals, n, cfg, L, ws, stream)) return finish_waited(cfg, stream, "rt_sort_pairs_ex");
     launch_sort(keys, vals, static_cast<uint32_t>(n), r, L, static_cast<char *>(ws), false, nullptr, nullptr,
                 stream);
     s = finish_call(stream, "rt_sort_pairs_ex");
@@ -664,6 +676,7 @@ extern "C" rt_status rt_sort_pairs_noalloc(uint32_t *keys, uint32_t *vals, size_
     void *ws = nullptr;
     s = noalloc_scratch(&ws, "rt_sort_pairs_noalloc");
     if (s != RT_OK) return s;
+    if (try_split(keys, vals, n, cfg, L, ws, stream)) return finish_waited(cfg, stream, "rt_sort_pairs_noalloc");
     // every region that must start at zero (histograms, lookback words,
     // tile counters, error word) is cleared by the sort's own kernels
     launch_sort(keys, vals, static_cast<uint32_t>(n), r, L, static_cast<char *>(ws), false, nullptr, nullptr,

@@ -417,6 +417,13 @@ extern "C" rt_status rt_sort64_ex(uint64_t *keys, void *vals, uint32_t value_byt
         s = cached_workspace(L.total, stream, &ws);
         if (s != RT_OK) return s;
     }
+    if (default_method(cfg) && n <= kSplitMax64 && split_scratch_bytes(n, sizeof(uint64_t)) <= L.t1k) {
+        char *w = static_cast<char *>(ws);
+        launch_split64(keys, static_cast<uint32_t *>(vals), vw, static_cast<uint32_t>(n),
+                       reinterpret_cast<uint64_t *>(w + L.t1k), vw ? reinterpret_cast<uint32_t *>(w + L.t1v) : nullptr,
+                       w, stream);
+        return finish_waited(cfg, stream, "rt_sort64_ex");
+    }
     launch_sort64(keys, static_cast<uint32_t *>(vals), vw, static_cast<uint32_t>(n), r, L, static_cast<char *>(ws),
                   stream);
     s = finish_call(stream, "rt_sort64_ex");
