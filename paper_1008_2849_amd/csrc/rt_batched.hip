@@ -181,8 +181,8 @@ void launch_segments(uint32_t *keys, uint32_t *vals, uint32_t *tk, uint32_t *tv,
                      hipStream_t stream, uint32_t digit0, bool persistent) {
     const SegPointers P = seg_pointers(ws, L);
     const bool vals_on = vals != nullptr;
-    hipLaunchKernelGGL(k_seg_reset, dim3(1), dim3(64), 0, stream, P.header);
-    hipLaunchKernelGGL(k_seg_classify, dim3((num_segments + 255) / 256), dim3(256), 0, stream, offsets,
+    hipLaunchKernelGGL(k_seg_reset, dim3(1), dim3(64), 0, stream, P.header, nullptr, 0u);
+    hipLaunchKernelGGL((k_seg_classify<uint32_t, uint32_t>), dim3((num_segments + 255) / 256), dim3(256), 0, stream, offsets,
                        num_segments, keys, vals, tk, vals_on ? tv : nullptr, L.capacity, L.large_capacity,
                        to_temp, L.classes.limits(), P.descs, P.lists, P.header);
     // XCD chunks of the tile list pay off for long segments only: with a few

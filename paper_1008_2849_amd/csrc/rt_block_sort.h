@@ -286,53 +286,62 @@ __device__ __forceinline__ void block_sort(const Source &src, uint32_t n, const 
             if (tid == 0) lds.b.bin[NB] = n;
             __syncthreads();
             // ---- one word per item, in its bin's slots: the key's bits below
-            // the bin, then the item's index; and the values on their way
+            // the bin, then the item's index; and the values on their way.  at
+            // then holds the bin's start and, above it, its count.
             const K below = (K(1) << shift) - 1u;
             forget(item0);
 #pragma unroll
             for (int g = 0; g < IPT; g += GRP)
                 if (g < slots) {
+                    uint32_t first[GRP], next[GRP];
 #pragma unroll
-                    for (int j = g; j < g + GRP && j < IPT; ++j) {
-                        forget(key[j]);
+                    for (int q = 0; q < GRP; ++q) {
+                        if (g + q >= IPT) continue;
+                        forget(key[g + q]);
+                        const uint32_t b = static_cast<uint32_t>((key[g + q] - lo) >> shift);
+                        first[q] = lds.b.bin[b];
+                        next[q] = lds.b.bin[b + 1];
+                    }
+#pragma unroll
+                    for (int q = 0; q < GRP; ++q) {
+                        const int j = g + q;
+                        if (j >= IPT) continue;
                         const uint32_t i = item0 + j * 64;
-                        const K rel = key[j] - lo;
-                        uint32_t p = lds.b.bin[static_cast<uint32_t>(rel >> shift)] + at[j];
+                        uint32_t p = first[q] + at[j];
                         if (!RT_LIVE(j)) p = L::CAP + kBinLimit;
-                        lds.b.word[p] = ((rel & below) << L::IDX_BITS) | i;
+                        lds.b.word[p] = (((key[j] - lo) & below) << L::IDX_BITS) | i;
+                        at[j] = first[q] | ((next[q] - first[q]) << 16);
                         if constexpr (VALS) val[j] = src.val(min(i, n - 1u));
                     }
                 }
             __syncthreads();
-            // ---- rank in the bin: the smaller words among its slots.  The
-            // bins are read again, so that only keys, values and positions stay
-            // in registers across the groups.  Reads past a shorter bin hit
-            // later words and do not count.
+            // ---- rank in the bin: the smaller words among its slots, two a
+            // step.  An item alone in its bin, or past its bin's end, reads the
+            // first word with the other such lanes (one LDS access).
 #pragma unroll
             for (int g = 0; g < IPT; g += GRP)
                 if (g < slots) {
                     uint32_t first[GRP], cnt[GRP], r[GRP];
                     K mine[GRP];
                     forget(item0);
+                    uint32_t longest = 0;
 #pragma unroll
                     for (int q = 0; q < GRP; ++q) {
-                        if (g + q >= IPT) continue;
-                        forget(key[g + q]);
-                        const K rel = key[g + q] - lo;
-                        const uint32_t b = static_cast<uint32_t>(rel >> shift);
-                        first[q] = lds.b.bin[b];
-                        cnt[q] = lds.b.bin[b + 1];
-                        mine[q] = ((rel & below) << L::IDX_BITS) | (item0 + (g + q) * 64);
-                        r[q] = first[q];
+                        const int j = g + q;
+                        if (j >= IPT) continue;
+                        forget(key[j]);
+                        mine[q] = (((key[j] - lo) & below) << L::IDX_BITS) | (item0 + j * 64);
+                        r[q] = first[q] = at[j] & 0xFFFFu;
+                        cnt[q] = at[j] >> 16;
+                        if (cnt[q] == 1u) cnt[q] = 0u;
+                        longest = max(longest, cnt[q]);
                     }
-#pragma unroll
-                    for (int q = 0; q < GRP; ++q)
-                        if (g + q < IPT) cnt[q] -= first[q];
-                    for (uint32_t t = 0; t < most; t += 2) {
+                    for (uint32_t t = 0; __builtin_amdgcn_ballot_w64(t < longest) != 0u; t += 2) {
 #pragma unroll
                         for (int q = 0; q < GRP; ++q) {
                             if (g + q >= IPT) continue;
-                            const K w0 = lds.b.word[first[q] + t], w1 = lds.b.word[first[q] + t + 1];
+                            const uint32_t p = t < cnt[q] ? first[q] + t : 0u;
+                            const K w0 = lds.b.word[p], w1 = lds.b.word[p + 1];
                             r[q] += static_cast<uint32_t>((t < cnt[q]) & (w0 < mine[q]));
                             r[q] += static_cast<uint32_t>((t + 1 < cnt[q]) & (w1 < mine[q]));
                         }

@@ -24,9 +24,12 @@ namespace rt {
 // set-up of a batched call: descriptors and work lists from the offsets
 // ---------------------------------------------------------------------------
 
-static __global__ __launch_bounds__(64) void k_seg_reset(SegHeader *__restrict__ h) {
+// one set: also the offsets of a single segment of n items.
+static __global__ __launch_bounds__(64) void k_seg_reset(SegHeader *__restrict__ h, uint32_t *__restrict__ one,
+                                                  uint32_t n) {
     uint32_t *w = reinterpret_cast<uint32_t *>(h);
     for (uint32_t i = threadIdx.x; i < sizeof(SegHeader) / 4; i += 64) w[i] = 0u;
+    if (one != nullptr && threadIdx.x < 2) one[threadIdx.x] = threadIdx.x == 0 ? 0u : n;
 }
 
 // One thread per segment.  Segment s is [off[s], off[s+1]) of keys/vals; its
@@ -37,8 +40,9 @@ static __global__ __launch_bounds__(64) void k_seg_reset(SegHeader *__restrict__
 // copied there here, as no later kernel sees it.  List slots are taken per
 // wave: one atomic per class and wave, each lane's slot found from the
 // class's ballot.
+template <typename K = uint32_t, typename V = uint32_t>
 static __global__ __launch_bounds__(256) void k_seg_classify(const uint32_t *__restrict__ off, uint32_t num_segments,
-                                                      uint32_t *keys, uint32_t *vals, uint32_t *tk, uint32_t *tv,
+                                                      K *keys, V *vals, K *tk, V *tv,
                                                       size_t capacity, uint32_t large_capacity, int to_temp,
                                                       SegClassLimits classes, SegDesc *__restrict__ descs,
                                                       uint32_t *__restrict__ lists, SegHeader *__restrict__ h) {
@@ -57,10 +61,10 @@ static __global__ __launch_bounds__(256) void k_seg_classify(const uint32_t *__r
             }
         } else {
             const uint32_t n = b - a;
-            d.k = keys + a;
-            d.v = vals ? vals + a : nullptr;
-            d.tk = tk + (a - o0);
-            d.tv = tv ? tv + (a - o0) : nullptr;
+            d.k = reinterpret_cast<uint32_t *>(keys + a);
+            d.v = reinterpret_cast<uint32_t *>(vals ? vals + a : nullptr);
+            d.tk = reinterpret_cast<uint32_t *>(tk + (a - o0));
+            d.tv = reinterpret_cast<uint32_t *>(tv ? tv + (a - o0) : nullptr);
             d.n = n;
             d.pass = 0;
             d.row = 0;

@@ -417,12 +417,20 @@ extern "C" rt_status rt_sort64_ex(uint64_t *keys, void *vals, uint32_t value_byt
         s = cached_workspace(L.total, stream, &ws);
         if (s != RT_OK) return s;
     }
-    if (default_method(cfg) && n <= kSplitMax64 && split_scratch_bytes(n, sizeof(uint64_t)) <= L.t1k) {
+    if (default_method(cfg)) {
         char *w = static_cast<char *>(ws);
-        launch_split64(keys, static_cast<uint32_t *>(vals), vw, static_cast<uint32_t>(n),
-                       reinterpret_cast<uint64_t *>(w + L.t1k), vw ? reinterpret_cast<uint32_t *>(w + L.t1v) : nullptr,
-                       w, stream);
-        return finish_waited(cfg, stream, "rt_sort64_ex");
+        uint32_t *v = static_cast<uint32_t *>(vals);
+        uint64_t *tk = reinterpret_cast<uint64_t *>(w + L.t1k);
+        uint32_t *tv = vw ? reinterpret_cast<uint32_t *>(w + L.t1v) : nullptr;
+        if (n <= kSplitMax64 && split_scratch_bytes(n, sizeof(uint64_t)) <= L.t1k) {
+            launch_split64(keys, v, vw, static_cast<uint32_t>(n), tk, tv, w, stream);
+            return finish_waited(cfg, stream, "rt_sort64_ex");
+        }
+        if (n > kSplitMax64 && n < kSplitLargeEnd && L.t2k != 0 &&
+            split_large_scratch_bytes64(n, vw) <= L.total - L.t2k) {
+            launch_split_large64(keys, v, vw, static_cast<uint32_t>(n), tk, tv, w + L.t2k, stream);
+            return finish_waited(cfg, stream, "rt_sort64_ex");
+        }
     }
     launch_sort64(keys, static_cast<uint32_t *>(vals), vw, static_cast<uint32_t>(n), r, L, static_cast<char *>(ws),
                   stream);

@@ -37,14 +37,24 @@ namespace rt {
 
 constexpr int kBuckets = 256;
 
+// Splitters are searched in the order of a binary tree (node i's children
+// are 2i and 2i + 1, the root is 1): a level is a run of consecutive LDS
+// words, which lanes read without bank conflicts.  Node i holds the splitter
+// of this index.
+__device__ __forceinline__ uint32_t tree_index(uint32_t i) {
+    const uint32_t level = 31u - __builtin_clz(i);
+    return ((2u * (i - (1u << level)) + 1u) << (7u - level)) - 1u;
+}
+static_assert(kBuckets == 256, "eight levels");
+
 // Bucket of a key: the number of splitters at or below it (kBuckets - 1 of
-// them, ascending).
+// them), from their tree.
 template <typename K>
-__device__ __forceinline__ uint32_t bucket_of(K key, const K *split) {
-    uint32_t p = 0;
+__device__ __forceinline__ uint32_t bucket_of(K key, const K *tree) {
+    uint32_t i = 1;
 #pragma unroll
-    for (uint32_t step = kBuckets / 2; step >= 1; step /= 2) p += key >= split[p + step - 1] ? step : 0u;
-    return p;
+    for (int level = 0; level < 8; ++level) i = 2u * i + (key >= tree[i] ? 1u : 0u);
+    return i - kBuckets;
 }
 
 // Sample key i of M: a pseudo-random item of the i-th of M equal stretches.
@@ -78,6 +88,7 @@ __global__ __launch_bounds__(BLOCK) void k_split_count(const K *__restrict__ key
     constexpr int M = BLOCK * SIPT;  // 2048 or 4096 sample keys
     __shared__ BlockSortLds<BLOCK, SIPT, K, uint32_t, false> sort;
     __shared__ K picked[kBuckets];
+    __shared__ K sorted[kBuckets];
     __shared__ K split[kBuckets];
     __shared__ uint32_t count[kBuckets];
     const uint32_t tid = threadIdx.x;
@@ -92,9 +103,11 @@ __global__ __launch_bounds__(BLOCK) void k_split_count(const K *__restrict__ key
         // v the first time, v + 1 from then on (at the largest key: v)
         const K v = picked[tid];
         const K s = tid > 0 && picked[tid - 1] == v && v != ~K(0) ? v + 1u : v;
-        split[tid] = s;
+        sorted[tid] = s;
         if (blockIdx.x == 0) splitters[tid] = s;
     }
+    __syncthreads();
+    if (tid > 0 && tid < kBuckets) split[tid] = sorted[tree_index(tid)];
     __syncthreads();
 #pragma unroll
     for (int j = 0; j < IPT; ++j)
@@ -139,7 +152,7 @@ __global__ __launch_bounds__(BLOCK) void k_split_scatter(const K *__restrict__ k
 #pragma unroll
         for (int j = 0; j < IPT; ++j) val[j] = *gptr<V, sizeof(V) == 4>(vals, tile0 + min(slot0 + j * 64, valid - 1u));
     }
-    if (tid < kBuckets - 1) split[tid] = splitters[tid];
+    if (tid > 0 && tid < kBuckets) split[tid] = splitters[tree_index(tid)];
     for (uint32_t i = tid; i < WAVES * kBuckets; i += BLOCK) whist[i] = 0u;
     // the table's column sums: all tiles, and the tiles before this one
     {

@@ -1,0 +1,29 @@
+// rt_split_large64.hip -- the two-pass splitter sort of large arrays of 64-bit
+// keys.
+#include <algorithm>
+
+#include "rt_split_seg.h"
+
+namespace rt {
+
+static SplitSortLayout layout64(size_t n, uint32_t value_words) {
+    return make_split_sort_layout(n, 1024,
+                                  value_words == 2 ? SplitTile<uint64_t, uint64_t, true>::IPT
+                                                   : SplitTile<uint64_t, uint32_t, true>::IPT);
+}
+
+size_t split_large_scratch_bytes64(size_t n, uint32_t value_words) { return layout64(n, value_words).total; }
+
+void launch_split_large64(uint64_t *keys, uint32_t *vals, uint32_t value_words, uint32_t n, uint64_t *tk, uint32_t *tv,
+                          char *scratch, hipStream_t stream) {
+    const SplitSortLayout S = layout64(n, value_words);
+    if (value_words == 2)
+        launch_split_sort<uint64_t, uint64_t, true>(keys, reinterpret_cast<uint64_t *>(vals), n, tk,
+                                                    reinterpret_cast<uint64_t *>(tv), S, scratch, stream);
+    else if (value_words == 1)
+        launch_split_sort<uint64_t, uint32_t, true>(keys, vals, n, tk, tv, S, scratch, stream);
+    else
+        launch_split_sort<uint64_t, uint32_t, false>(keys, nullptr, n, tk, nullptr, S, scratch, stream);
+}
+
+}  // namespace rt

@@ -1,0 +1,151 @@
+// rt_split_seg.h -- host side of the splitter passes over segments: launch
+// sequence, shapes by type, and the two-pass sort of a large array.
+#pragma once
+
+#include "rt_common.h"
+#include "rt_split_seg_kernels.h"
+
+namespace rt {
+
+inline uint32_t split_grid(size_t want, uint32_t cap) {
+    if (want < 1) want = 1;
+    return static_cast<uint32_t>(want < cap ? want : cap);
+}
+
+// Threads and items per thread of a scatter tile: 16K items, staged keys then
+// values through one stage where they do not fit the LDS together (12K with
+// 8-byte keys and values); 32-bit keys alone in 512 x 32 blocks, two to a CU.
+template <typename K, typename V, bool VALS>
+struct SplitTile {
+    static constexpr int BLOCK = sizeof(K) == 4 && !VALS ? 512 : 1024;
+    static constexpr int IPT = BLOCK == 512 ? 32 : (sizeof(K) == 8 && VALS && sizeof(V) == 8) ? 12 : 16;
+    static constexpr bool SEQ = sizeof(K) == 8 && VALS;
+    static constexpr int ITEMS = BLOCK * IPT;
+};
+
+// A pass's tables inside a SegLayout workspace: rows in the histogram rows,
+// the table, chunk rows and leaf lists in the lookback words.
+struct SplitTables {
+    char *rows;
+    uint32_t *table, *chunks;
+    LeafLists *lists;
+    SplitLeaf *leaves;
+    uint32_t leaf_capacity;
+};
+inline SplitTables split_tables(char *ws, const SegLayout &L) {
+    SplitTables t;
+    t.rows = ws + L.hist;
+    t.table = reinterpret_cast<uint32_t *>(ws + L.status);
+    t.chunks = reinterpret_cast<uint32_t *>(ws + L.status + L.status_pass);
+    t.lists = reinterpret_cast<LeafLists *>(ws + L.status + 2 * L.status_pass);
+    t.leaves = reinterpret_cast<SplitLeaf *>(ws + L.status + 2 * L.status_pass + 256);
+    // a segment has at most n / (kLeafAim / 2) buckets, or one
+    t.leaf_capacity = static_cast<uint32_t>(L.capacity / (kLeafAim / 2) + L.large_capacity);
+    return t;
+}
+static_assert(sizeof(LeafLists) <= 256, "the lists' header");
+
+// What becomes of the buckets: the segments of a next pass (sub[0..kBuckets],
+// one listed segment), or leaves, sorted from tk/tv into k/v or in place in
+// tk/tv.
+enum class SplitEnd { kNextPass, kLeavesBack, kLeavesInPlace };
+
+// One splitter pass over the tiled list of a SegLayout whose descriptors,
+// list and tile map are on the device.
+template <typename K, typename V, bool VALS>
+void launch_split_pass(const SegPointers &P, const SegLayout &L, uint32_t list_stride, SplitEnd end, uint32_t *sub,
+                       char *ws, hipStream_t stream) {
+    typedef SplitTile<K, V, VALS> T;
+    const uint32_t cus = static_cast<uint32_t>(device_cu_count());
+    const SplitTables t = split_tables(ws, L);
+    const uint32_t *list = P.lists + static_cast<size_t>(kSegLarge) * list_stride;
+    const uint32_t segs = std::max<uint32_t>(1u, L.large_capacity);
+    const bool leaves = end != SplitEnd::kNextPass;
+    constexpr bool k64 = sizeof(K) == 8;
+    hipLaunchKernelGGL((k_split_sample<1024, 8, K>), dim3(split_grid(segs, cus * 2)), dim3(1024), 0, stream, P.descs,
+                       list, P.header, t.rows, leaves ? 0u : static_cast<uint32_t>(kBuckets));
+    prof_mark(stream, RT_KIND_PROBE);
+    const uint32_t tiles = (L.max_tiles + kChunks - 1) / kChunks * kChunks;
+    hipLaunchKernelGGL((k_split_tile_count<512, K>), dim3(tiles), dim3(512), 0, stream, P.tile_seg, P.header, t.rows,
+                       t.table, static_cast<uint32_t>(T::ITEMS));
+    prof_mark(stream, RT_KIND_HISTOGRAM);
+    hipLaunchKernelGGL(k_split_scan,
+                       dim3(split_grid(static_cast<size_t>(segs) * (kBuckets / 32), cus * 8),
+                            (L.max_tiles + kScanChunk - 1) / kScanChunk),
+                       dim3(1024), 0, stream, P.first_tile, P.header, t.table, t.chunks);
+    if (leaves)
+        hipLaunchKernelGGL(k_leaf_reset, dim3(1), dim3(64), 0, stream, t.lists, 4352u, 8192u, k64 ? 8192u : 16384u,
+                           t.leaf_capacity);
+    hipLaunchKernelGGL((k_split_starts<K>), dim3(split_grid(segs, cus * 4)), dim3(256), 0, stream, P.descs, list,
+                       P.header, P.first_tile, t.rows, t.chunks, leaves ? nullptr : sub, leaves ? t.lists : nullptr,
+                       t.leaves, end == SplitEnd::kLeavesBack ? 1u : 0u);
+    prof_mark(stream, RT_KIND_PLAN);
+    hipLaunchKernelGGL((k_split_tile_scatter<T::BLOCK, T::IPT, K, V, VALS, T::SEQ, sizeof(K) == 4>), dim3(tiles),
+                       dim3(T::BLOCK), 0, stream, P.tile_seg, P.header, t.rows, t.table, t.chunks);
+    prof_mark(stream, RT_KIND_PASS);
+    if (!leaves) return;
+    const int in_place = end == SplitEnd::kLeavesInPlace ? 1 : 0;
+#define RT_SPLIT_LEAVES(BLK, I, C, PER_CU)                                                                         \
+    hipLaunchKernelGGL((k_split_leaves<BLK, I, K, V, VALS>), dim3(split_grid(t.leaf_capacity, cus * (PER_CU))),    \
+                       dim3(BLK), 0, stream, P.descs, t.lists, t.leaves, C, in_place)
+    RT_SPLIT_LEAVES(256, 17, 0, 4);
+    RT_SPLIT_LEAVES(512, 16, 1, 2);
+    if constexpr (!k64) RT_SPLIT_LEAVES(1024, 16, 2, 1);
+#undef RT_SPLIT_LEAVES
+    hipLaunchKernelGGL((k_split_long_leaves<1024, K, V, VALS>), dim3(cus), dim3(1024), 0, stream, P.descs, t.lists,
+                       t.leaves, in_place);
+    prof_mark(stream, RT_KIND_SEG_SMALL);
+}
+
+// Workspace of the two-pass sort of one array: the first pass's buckets as
+// segment offsets, then the passes' tables (one pass at a time), beside the
+// temporaries.
+struct SplitSortLayout {
+    size_t offsets, seg, total;  // offsets: {0, n}, then the first pass's kBuckets + 1
+    SegLayout first, second;
+};
+inline SplitSortLayout make_split_sort_layout(size_t n, int block, int ipt) {
+    SplitSortLayout S{};
+    SegClassTable t = seg_class_table();
+    t.tile_block = block;
+    t.tile_ipt = ipt;
+    S.offsets = 0;
+    S.seg = 2048;
+    S.first = make_seg_layout(1, n, false, false, true, &t);
+    S.second = make_seg_layout(kBuckets, n, false, false, true, &t);
+    S.total = S.seg + std::max(S.first.total, S.second.total);
+    return S;
+}
+
+// Sorts n items of keys/vals in place (n >= 2, n < 2^30).
+template <typename K, typename V, bool VALS>
+void launch_split_sort(K *keys, V *vals, uint32_t n, K *tk, V *tv, const SplitSortLayout &S, char *ws,
+                       hipStream_t stream) {
+    const uint32_t cus = static_cast<uint32_t>(device_cu_count());
+    uint32_t *off1 = reinterpret_cast<uint32_t *>(ws + S.offsets);
+    uint32_t *off2 = off1 + 64;
+    char *seg = ws + S.seg;
+    prof_begin(stream);
+    for (int pass = 0; pass < 2; ++pass) {
+        const SegLayout &L = pass == 0 ? S.first : S.second;
+        const SegPointers P = seg_pointers(seg, L);
+        const uint32_t num = pass == 0 ? 1u : static_cast<uint32_t>(kBuckets);
+        K *a_k = pass == 0 ? keys : tk, *b_k = pass == 0 ? tk : keys;
+        V *a_v = pass == 0 ? vals : tv, *b_v = pass == 0 ? tv : vals;
+        hipLaunchKernelGGL(k_seg_reset, dim3(1), dim3(64), 0, stream, P.header, pass == 0 ? off1 : nullptr, n);
+        hipLaunchKernelGGL((k_seg_classify<K, V>), dim3((num + 255) / 256), dim3(256), 0, stream,
+                           pass == 0 ? off1 : off2, num, a_k, VALS ? a_v : nullptr, b_k, VALS ? b_v : nullptr,
+                           L.capacity, L.large_capacity, 1, L.classes.limits(), P.descs, P.lists, P.header);
+        hipLaunchKernelGGL(k_seg_tiles, dim3(1), dim3(1024), 0, stream, P.descs,
+                           P.lists + static_cast<size_t>(kSegLarge) * num, P.first_tile, P.header, L.large_capacity,
+                           L.max_tiles, L.tile);
+        hipLaunchKernelGGL(k_seg_tilemap, dim3(split_grid((L.max_tiles + 255) / 256, cus * 4)), dim3(256), 0, stream,
+                           P.descs, P.lists + static_cast<size_t>(kSegLarge) * num, P.first_tile, P.header,
+                           P.tile_seg, 1u);
+        prof_mark(stream, RT_KIND_SEGMENTED);
+        launch_split_pass<K, V, VALS>(P, L, num, pass == 0 ? SplitEnd::kNextPass : SplitEnd::kLeavesInPlace, off2, seg,
+                                      stream);
+    }
+}
+
+}  // namespace rt

@@ -1,0 +1,618 @@
+// rt_split_seg_kernels.h -- splitter passes over long segments: the large
+// single-array sorts (two such passes, then leaves) and the long segments of
+// batched calls (one pass, then leaves).
+//
+// A pass cuts every listed segment into up to 256 buckets of neighbouring
+// keys and writes them, stably, to the segment's other arrays.  Against the
+// 8-bit digit passes of the onesweep form:
+//
+// * the buckets are chosen from a sample of the segment, so they come out
+//   about equal for any distribution of keys, and two passes leave ranges
+//   that one block sorts whole in LDS, whatever the key width; four or eight
+//   digit passes become two and a leaf;
+// * the tiles' counts are taken beforehand, one row of a table per tile, so a
+//   tile knows where its runs go without a lookback chain, and tiles may run
+//   in any order: each XCD takes a contiguous share of them, so that
+//   neighbouring runs, which share cache lines, are written through one L2.
+//
+// Launches of a pass: k_split_sample (buckets of each segment),
+// k_split_tile_count (rows), k_split_scan (rows to prefix sums, totals),
+// k_split_starts (bucket bounds: the next pass's segments, or leaf lists) and
+// k_split_tile_scatter; then k_split_leaves per leaf size.
+#pragma once
+
+#include "rt_seg_kernels.h"
+#include "rt_split_kernels.h"
+
+namespace rt {
+
+// A segment's buckets, in its row of the histogram table (kSegPasses *
+// kSegRadix words): the buckets' item totals, this, the splitters.
+struct SplitSeg {
+    uint64_t lo;       // linear: key of bucket 0's start
+    uint32_t scale;    // linear: bucket = umulhi((key - lo) >> shift, scale)
+    uint32_t shift;
+    uint32_t linear;   // 1: equal stretches of the key range; 0: splitters
+    uint32_t buckets;  // a power of two, at most kBuckets
+    uint32_t pad[2];
+};
+constexpr int kSplitRowBytes = kSegPasses * kSegRadix * 4;
+constexpr int kSplitSegAt = 1024, kSplittersAt = 2048;
+static_assert(kSplittersAt + kBuckets * 8 <= kSplitRowBytes, "64-bit splitters fit the row");
+
+// One leaf: items [off, off + n) of segment `seg`'s arrays.  one: a single
+// key value (in order as it stands).
+struct SplitLeaf {
+    uint32_t seg, off, n, one;
+};
+constexpr int kLeafClasses = 4;  // up to 4352, 8192 and 16384 items (64-bit keys: 4352, 8192, none); longer
+struct LeafLists {
+    uint32_t count[kLeafClasses];
+    uint32_t max_n[kLeafClasses - 1];
+    uint32_t capacity;  // entries per list
+};
+
+// Items per leaf aimed at, at most: leaves of equal stretches of spread keys
+// then fit 256 x 17 blocks (4352 items) up to segments of 2^20 items.
+constexpr uint32_t kLeafAim = 3072;
+
+__device__ __forceinline__ uint32_t split_bucket_count(uint32_t n) {
+    uint32_t b = 1;
+    while (b < static_cast<uint32_t>(kBuckets) && n > b * kLeafAim) b *= 2;
+    return b;
+}
+
+// Buckets of a segment's keys, held in a block.
+template <typename K>
+struct Splitter {
+    K lo;
+    uint32_t scale, shift, linear, last;
+    const K *split;  // LDS: the tree of kBuckets - 1 (past the segment's: the largest key)
+    __device__ __forceinline__ uint32_t stretch(K key) const {
+        const K d = key > lo ? static_cast<K>(key - lo) : K(0);
+        const K x = d >> shift;
+        const uint32_t y = sizeof(K) == 8 && (static_cast<uint64_t>(x) >> 32) ? ~0u : static_cast<uint32_t>(x);
+        return min(last, __umulhi(y, scale));
+    }
+    __device__ __forceinline__ uint32_t search(K key) const { return min(last, bucket_of(key, split)); }
+    __device__ __forceinline__ uint32_t operator()(K key) const { return linear ? stretch(key) : search(key); }
+};
+
+// The buckets of the segment with this row; every thread calls it, and a
+// barrier follows before the splitter is used.
+template <int BLOCK, typename K>
+__device__ __forceinline__ Splitter<K> load_splitter(const char *rows, uint32_t row, K *lds_split) {
+    const char *r = rows + static_cast<size_t>(row) * kSplitRowBytes;
+    const SplitSeg *s = reinterpret_cast<const SplitSeg *>(r + kSplitSegAt);
+    Splitter<K> f;
+    f.lo = static_cast<K>(s->lo);
+    f.scale = s->scale;
+    f.shift = s->shift;
+    f.linear = s->linear;
+    f.last = s->buckets - 1u;
+    f.split = lds_split;
+    if (!f.linear)
+        for (uint32_t i = threadIdx.x; i < static_cast<uint32_t>(kBuckets); i += BLOCK)
+            if (i > 0) lds_split[i] = reinterpret_cast<const K *>(r + kSplittersAt)[tree_index(i)];
+    return f;
+}
+
+// Stratified sample of m keys of a segment of n items (m may exceed n).
+template <typename K>
+struct SegSample {
+    const K *k;
+    uint32_t n, m;
+    __device__ __forceinline__ K key(uint32_t i) const {
+        const uint32_t a = static_cast<uint32_t>(static_cast<uint64_t>(i) * n / m);
+        const uint32_t b = static_cast<uint32_t>(static_cast<uint64_t>(i + 1) * n / m);
+        return k[min(a + __umulhi((i + 1u) * 0x9E3779B9u, b - a), n - 1u)];
+    }
+    __device__ __forceinline__ uint32_t val(uint32_t) const { return 0u; }
+};
+template <typename K>
+struct QuantileSink {
+    K *picked;
+    K *ends;
+    uint32_t every, buckets, m;
+    __device__ __forceinline__ void put(uint32_t i, K key, uint32_t) const {
+        if (i % every == every - 1u && i / every + 1u < buckets) picked[i / every] = key;
+        if (i == 0) ends[0] = key;
+        if (i == m - 1u) ends[1] = key;
+    }
+};
+
+// Chooses every listed segment's buckets (fixed_buckets of them if set, from
+// 8192 sample keys; else as many as its leaves need, from 2048, or 4096 from
+// 2^19 items: more random reads cost more than better leaves give): equal stretches of the sampled range if no stretch holds far
+// more of the sample than its share (no bucket much above the mean, and a
+// bucket costs one multiplication), else the sample's quantiles.
+template <int BLOCK, int SIPT, typename K>
+__global__ __launch_bounds__(BLOCK) void k_split_sample(const SegDesc *__restrict__ descs,
+                                                        const uint32_t *__restrict__ list,
+                                                        const SegHeader *__restrict__ h, char *__restrict__ rows,
+                                                        uint32_t fixed_buckets) {
+    __shared__ BlockSortLds<BLOCK, SIPT, K, uint32_t, false> sort;
+    __shared__ K picked[kBuckets];
+    __shared__ K ends[2];
+    __shared__ uint32_t hits[kBuckets];
+    __shared__ SplitSeg seg;
+    const uint32_t tid = threadIdx.x;
+    const uint32_t count = h->count[kSegLarge];
+    for (uint32_t e = blockIdx.x; e < count; e += gridDim.x) {
+        const SegDesc d = descs[list[e]];
+        const uint32_t n = d.n;
+        char *row = rows + static_cast<size_t>(d.row) * kSplitRowBytes;
+        const uint32_t buckets = fixed_buckets ? fixed_buckets : split_bucket_count(n);
+        const uint32_t m = fixed_buckets ? static_cast<uint32_t>(BLOCK * SIPT) : n < (1u << 19) ? 2048u : 4096u;
+        const SegSample<K> src{reinterpret_cast<const K *>(d.k), n, m};
+        if (tid < kBuckets) {
+            picked[tid] = ~K(0);
+            hits[tid] = 0u;
+        }
+        __syncthreads();
+        if (buckets > 1)
+            block_sort<BLOCK, SIPT, K, uint32_t, false>(src, m, QuantileSink<K>{picked, ends, m / buckets, buckets, m},
+                                                        false, sort);
+        __syncthreads();
+        if (tid == 0) {
+            seg.lo = 0;
+            seg.scale = seg.shift = 0u;
+            seg.linear = 1u;
+            seg.buckets = buckets;
+            seg.pad[0] = seg.pad[1] = 0u;
+            if (buckets > 1) {
+                // the sampled range, widened by a sample's mean distance
+                const uint64_t a = ends[0], b = ends[1], top = ~K(0);
+                const uint64_t w = (b - a) / m;
+                const uint64_t lo = a - min(a, w), hi = b + min(top - b, w);
+                const uint32_t bits = key_bits_of(hi - lo);
+                seg.shift = bits > 32u ? bits - 32u : 0u;
+                const uint64_t span = ((hi - lo) >> seg.shift) + 1u;
+                seg.lo = lo;
+                seg.linear = span >= (1u << 16) ? 1u : 0u;
+                seg.scale = seg.linear ? static_cast<uint32_t>((static_cast<uint64_t>(buckets) << 32) / span) : 0u;
+            }
+        }
+        __syncthreads();
+        if (buckets > 1 && seg.linear) {
+            Splitter<K> f;
+            f.lo = static_cast<K>(seg.lo);
+            f.scale = seg.scale;
+            f.shift = seg.shift;
+            f.last = buckets - 1u;
+            for (uint32_t i = tid; i < m; i += BLOCK) atomicAdd(&hits[f.stretch(src.key(i))], 1u);
+            __syncthreads();
+            // a share of mean s: 6 standard deviations, s + 6 sqrt(s)
+            const uint32_t s = m / buckets;
+            if (tid < buckets && hits[tid] > s && (hits[tid] - s) * (hits[tid] - s) > 36u * s) seg.linear = 0u;
+            __syncthreads();
+        }
+        if (tid < kBuckets - 1) {
+            // v the first time, v + 1 from then on (at the largest key: v)
+            const K v = picked[tid];
+            reinterpret_cast<K *>(row + kSplittersAt)[tid] = tid > 0 && picked[tid - 1] == v && v != ~K(0) ? v + 1u : v;
+        }
+        if (tid == 0) *reinterpret_cast<SplitSeg *>(row + kSplitSegAt) = seg;
+        __syncthreads();
+    }
+}
+
+// The tile of this block: each XCD (blocks are dealt to them in turn) takes a
+// contiguous eighth of the tiles.  Any order is correct.
+__device__ __forceinline__ uint32_t split_tile_of(uint32_t block, uint32_t tiles) {
+    const uint32_t per = (tiles + kChunks - 1u) / kChunks;
+    const uint32_t q = block / kChunks;
+    return q < per ? (block % kChunks) * per + q : kNoTile;
+}
+
+// Row t of `table`: tile t's items per bucket.
+template <int BLOCK, typename K>
+__global__ __launch_bounds__(BLOCK) void k_split_tile_count(const SegDesc *__restrict__ tile_desc,
+                                                            const SegHeader *__restrict__ h,
+                                                            const char *__restrict__ rows,
+                                                            uint32_t *__restrict__ table, uint32_t tile_items) {
+    constexpr int C = 8;  // lane-class copies of the counters, as in k_histogram
+    constexpr int U = 16;  // keys in flight per lane
+    __shared__ K split[kBuckets];
+    __shared__ uint32_t count[C][kBuckets + 1];
+    const uint32_t tid = threadIdx.x, lane = tid & 63u;
+    const uint32_t total = h->total_tiles;
+    const uint32_t tile = split_tile_of(blockIdx.x, total);
+    if (tile >= total) return;
+    const SegDesc d = tile_desc[tile];
+    const uint32_t start = (tile - d.pad) * tile_items;
+    const uint32_t valid = min(tile_items, d.n - start);
+    const K *src = reinterpret_cast<const K *>(d.k) + start;
+    // the first keys are on their way while the splitters are read
+    K k[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) k[u] = *gptr<K, true>(src, min(u * BLOCK + tid, valid - 1u));
+    const Splitter<K> f = load_splitter<BLOCK, K>(rows, d.row, split);
+    for (uint32_t i = tid; i < C * (kBuckets + 1); i += BLOCK) (&count[0][0])[i] = 0u;
+    __syncthreads();
+    uint32_t *mine = count[lane % C];
+    for (uint32_t base = 0; base < valid; base += BLOCK * U) {
+        uint32_t b[U];
+        if (f.linear) {
+#pragma unroll
+            for (int u = 0; u < U; ++u) b[u] = f.stretch(k[u]);
+        } else {
+#pragma unroll
+            for (int u = 0; u < U; ++u) b[u] = f.search(k[u]);
+        }
+        if (base + BLOCK * U < valid) {  // the next keys
+#pragma unroll
+            for (int u = 0; u < U; ++u) k[u] = *gptr<K, true>(src, min(base + (U + u) * BLOCK + tid, valid - 1u));
+        }
+        const uint32_t b0 = __builtin_amdgcn_readfirstlane(b[0]);
+        uint32_t differ = base + BLOCK * U <= valid ? 0u : 1u;
+#pragma unroll
+        for (int u = 0; u < U; ++u) differ |= b[u] ^ b0;
+        if (__builtin_amdgcn_ballot_w64(differ != 0u) == 0) {
+            if (lane == 0) atomicAdd(&mine[b0], static_cast<uint32_t>(64 * U));
+        } else {
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                if (base + u * BLOCK + tid < valid) atomicAdd(&mine[b[u]], 1u);
+        }
+    }
+    __syncthreads();
+    for (uint32_t i = tid; i < static_cast<uint32_t>(kBuckets); i += BLOCK) {
+        uint32_t c = 0;
+#pragma unroll
+        for (int w = 0; w < C; ++w) c += count[w][i];
+        table[static_cast<size_t>(tile) * kBuckets + i] = c;
+    }
+}
+
+// The tiles of a segment are summed in chunks of kScanChunk; a chunk's row in
+// the chunk table.
+constexpr uint32_t kScanChunk = 2048;
+__device__ __forceinline__ uint32_t chunk_row(uint32_t first_tile, uint32_t row, uint32_t tile) {
+    return first_tile / kScanChunk + row + (tile - first_tile) / kScanChunk;
+}
+
+// Per listed segment, 32 of its buckets and chunk blockIdx.y of its tiles:
+// the tiles' rows become exclusive prefix sums inside the chunk, and the
+// chunk's totals go to the chunk table.  32 threads share a bucket's rows,
+// eight loads in flight each.
+static __global__ __launch_bounds__(1024) void k_split_scan(const uint32_t *__restrict__ first_tile,
+                                                            const SegHeader *__restrict__ h,
+                                                            uint32_t *__restrict__ table,
+                                                            uint32_t *__restrict__ chunks) {
+    constexpr uint32_t SLICES = kBuckets / 32;
+    constexpr int U = 8;
+    __shared__ uint32_t sums[32][33];
+    const uint32_t b = threadIdx.x & 31u, g = threadIdx.x >> 5;
+    const uint32_t work = h->count[kSegLarge] * SLICES;
+    for (uint32_t w = blockIdx.x; w < work; w += gridDim.x) {
+        const uint32_t e = w / SLICES, col = (w % SLICES) * 32u + b;
+        const uint32_t f = first_tile[e];
+        const uint32_t t0 = f + blockIdx.y * kScanChunk;
+        if (t0 >= first_tile[e + 1]) continue;
+        const uint32_t tiles = min(first_tile[e + 1] - t0, kScanChunk);
+        const uint32_t lo = t0 + g * tiles / 32u, hi = t0 + (g + 1u) * tiles / 32u;
+        uint32_t sum = 0;
+        for (uint32_t t = lo; t < hi; t += U) {
+            uint32_t c[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) c[u] = table[static_cast<size_t>(min(t + u, hi - 1u)) * kBuckets + col];
+#pragma unroll
+            for (int u = 0; u < U; ++u) sum += t + u < hi ? c[u] : 0u;
+        }
+        sums[g][b] = sum;
+        __syncthreads();
+        uint32_t run = 0;
+        for (uint32_t q = 0; q < g; ++q) run += sums[q][b];
+        if (g == 31u) chunks[static_cast<size_t>(chunk_row(f, e, t0)) * kBuckets + col] = run + sum;
+        for (uint32_t t = lo; t < hi; t += U) {
+            uint32_t c[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) c[u] = table[static_cast<size_t>(min(t + u, hi - 1u)) * kBuckets + col];
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                if (t + u < hi) {
+                    table[static_cast<size_t>(t + u) * kBuckets + col] = run;
+                    run += c[u];
+                }
+        }
+        __syncthreads();
+    }
+}
+
+static __global__ __launch_bounds__(64) void k_leaf_reset(LeafLists *__restrict__ l, uint32_t max0, uint32_t max1,
+                                                          uint32_t max2, uint32_t capacity) {
+    if (threadIdx.x < kLeafClasses) l->count[threadIdx.x] = 0u;
+    if (threadIdx.x == 0) {
+        l->max_n[0] = max0;
+        l->max_n[1] = max1;
+        l->max_n[2] = max2;
+        l->capacity = capacity;
+    }
+}
+
+// Per listed segment: its chunks' totals become prefix sums, its buckets'
+// totals go to its row, and where the buckets start: sub set (one segment):
+// to sub[0..kBuckets], the segments of the next pass; lists set: a leaf per
+// bucket that is not in order as it stands (of every bucket, if `all`: the
+// leaves go to other arrays) to the list of its size.
+template <typename K>
+__global__ __launch_bounds__(256) void k_split_starts(const SegDesc *__restrict__ descs,
+                                                      const uint32_t *__restrict__ list,
+                                                      const SegHeader *__restrict__ h,
+                                                      const uint32_t *__restrict__ first_tile, char *__restrict__ rows,
+                                                      uint32_t *__restrict__ chunks, uint32_t *__restrict__ sub,
+                                                      LeafLists *__restrict__ lists,
+                                                      SplitLeaf *__restrict__ leaves, uint32_t all) {
+    __shared__ uint32_t s_wsum[4];
+    const uint32_t tid = threadIdx.x, lane = tid & 63u;
+    const uint32_t count = h->count[kSegLarge];
+    for (uint32_t e = blockIdx.x; e < count; e += gridDim.x) {
+        const uint32_t s = list[e];
+        const SegDesc d = descs[s];
+        char *row = rows + static_cast<size_t>(d.row) * kSplitRowBytes;
+        const uint32_t f = first_tile[e], tiles = first_tile[e + 1] - f;
+        uint32_t c = 0;
+        for (uint32_t t = 0; t < tiles; t += kScanChunk) {
+            uint32_t *p = chunks + static_cast<size_t>(chunk_row(f, e, f + t)) * kBuckets + tid;
+            const uint32_t x = *p;
+            *p = c;
+            c += x;
+        }
+        reinterpret_cast<uint32_t *>(row)[tid] = c;
+        const uint32_t start = block_exclusive_sum<256>(c, s_wsum);
+        if (sub != nullptr) {
+            sub[tid] = start;
+            if (tid == 255) sub[256] = d.n;
+        }
+        if (lists != nullptr) {
+            const SplitSeg *seg = reinterpret_cast<const SplitSeg *>(row + kSplitSegAt);
+            const K *split = reinterpret_cast<const K *>(row + kSplittersAt);
+            uint32_t one = 0;  // the bucket holds one key value
+            if (!seg->linear && tid > 0)
+                one = tid + 1u < seg->buckets ? (static_cast<K>(split[tid] - split[tid - 1]) == K(1))
+                                              : (split[tid - 1] == ~K(0));
+            int q = -1;
+            if (c >= (all ? 1u : 2u) && (all || !one)) {  // (in place, one value is in order already)
+                q = kLeafClasses - 1;
+#pragma unroll
+                for (int i = kLeafClasses - 2; i >= 0; --i)
+                    if (c <= lists->max_n[i]) q = i;
+            }
+#pragma unroll
+            for (int i = 0; i < kLeafClasses; ++i) {
+                const uint64_t mine = __builtin_amdgcn_ballot_w64(q == i);
+                if (mine == 0) continue;
+                uint32_t first = 0;
+                if (lane == 0) first = atomicAdd(&lists->count[i], static_cast<uint32_t>(__popcll(mine)));
+                first = __shfl(first, 0, 64);
+                const uint32_t at = first + __builtin_amdgcn_mbcnt_hi(
+                                                static_cast<uint32_t>(mine >> 32),
+                                                __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(mine), 0u));
+                if (q == i && at < lists->capacity)
+                    leaves[static_cast<size_t>(i) * lists->capacity + at] = SplitLeaf{s, start, c, one};
+            }
+        }
+        __syncthreads();
+    }
+}
+
+// Scatters the tile of this block by bucket from k/v to tk/tv of its segment,
+// stably.  SEQ: the values go through the keys' stage after them.
+template <int BLOCK, int IPT, typename K, typename V, bool VALS, bool SEQ, bool SMALL>
+__global__ __launch_bounds__(BLOCK) void k_split_tile_scatter(const SegDesc *__restrict__ tile_desc,
+                                                              const SegHeader *__restrict__ h,
+                                                              const char *__restrict__ rows,
+                                                              const uint32_t *__restrict__ table,
+                                                              const uint32_t *__restrict__ chunks) {
+    constexpr int WAVES = BLOCK / 64;
+    constexpr uint32_t TILE = BLOCK * IPT;
+    __shared__ K stage_k[TILE];
+    __shared__ V stage_v2[VALS && !SEQ ? TILE : 1];
+    __shared__ uint32_t whist[WAVES * kBuckets + WAVES * 64];
+    __shared__ uint32_t gbase[kBuckets];
+    __shared__ K split[kBuckets];
+    __shared__ uint32_t wsum[2][WAVES];
+    const uint32_t tid = threadIdx.x;
+    const uint32_t lane = tid & 63u;
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const uint32_t tile = split_tile_of(blockIdx.x, h->total_tiles);
+    if (tile >= h->total_tiles) return;
+    const SegDesc d = tile_desc[tile];
+    const uint32_t item0 = (tile - d.pad) * TILE;
+    const uint32_t valid = min(TILE, d.n - item0);
+    const bool full = valid == TILE;
+    const uint32_t slot0 = wave * 64 * IPT + lane;  // slot j of the lane holds tile item slot0 + 64 j
+    const K *src_k = reinterpret_cast<const K *>(d.k) + item0;
+    const V *src_v = reinterpret_cast<const V *>(d.v) + (VALS ? item0 : 0u);
+    K *dst_k = reinterpret_cast<K *>(d.tk);
+    V *dst_v = reinterpret_cast<V *>(d.tv);
+
+    K key[IPT];
+    V val[VALS ? IPT : 1];
+    if (full) {
+#pragma unroll
+        for (int j = 0; j < IPT; ++j) key[j] = *gptr<K, true>(src_k, slot0 + j * 64);
+    } else {
+#pragma unroll
+        for (int j = 0; j < IPT; ++j) key[j] = *gptr<K, true>(src_k, min(slot0 + j * 64, valid - 1u));
+    }
+    const Splitter<K> f = load_splitter<BLOCK, K>(rows, d.row, split);
+    uint32_t total = 0, before = 0;
+    if (tid < kBuckets) {
+        total = reinterpret_cast<const uint32_t *>(rows + static_cast<size_t>(d.row) * kSplitRowBytes)[tid];
+        before = table[static_cast<size_t>(tile) * kBuckets + tid] +
+                 chunks[static_cast<size_t>(chunk_row(d.pad, d.row, tile)) * kBuckets + tid];
+    }
+    uint32_t *wh = whist + wave * kBuckets;
+    uint32_t *scratch = whist + WAVES * kBuckets + wave * 64 + lane;
+    for (uint32_t i = lane; i < static_cast<uint32_t>(kBuckets); i += 64) wh[i] = 0u;
+    __syncthreads();
+
+    // ---- stable rank inside the wave, slot by slot; lanes past the end count
+    // as the last bucket, behind every item.  rb: rank, and the bucket above it
+    uint32_t rb[IPT];
+    if (f.linear) {
+#pragma unroll
+        for (int j = 0; j < IPT; ++j) rb[j] = f.stretch(key[j]);
+    } else {
+#pragma unroll
+        for (int j = 0; j < IPT; ++j) rb[j] = f.search(key[j]);
+    }
+    if (!full) {
+#pragma unroll
+        for (int j = 0; j < IPT; ++j)
+            if (slot0 + j * 64 >= valid) rb[j] = kBuckets - 1;
+    }
+#pragma unroll
+    for (int j = 0; j < IPT; ++j) {
+        const uint32_t b = rb[j];
+        uint32_t lo, hi;
+        match_digit<8>(b, lo, hi);
+        const uint32_t cnt = wh[b];
+        const uint32_t r = __builtin_amdgcn_mbcnt_hi(hi, __builtin_amdgcn_mbcnt_lo(lo, cnt));
+        rb[j] = r | (b << 16);
+        uint32_t *dst = r == cnt ? wh + b : scratch;
+        uint32_t t;
+        asm("v_bcnt_u32_b32 %0, %1, %2" : "=v"(t) : "v"(lo), "v"(cnt));
+        asm("v_bcnt_u32_b32 %0, %1, %2" : "=v"(t) : "v"(hi), "v"(t));
+        *dst = t;
+        compiler_fence();
+        if constexpr (VALS) {
+            if (j == IPT / 2 - 1) {  // the values: on their way while the rest is ranked
+#pragma unroll
+                for (int q = 0; q < IPT; ++q)
+                    val[q] = *gptr<V, true>(src_v, full ? slot0 + q * 64 : min(slot0 + q * 64, valid - 1u));
+            }
+        }
+    }
+    __syncthreads();
+
+    // ---- per bucket: each wave's offset in the tile, and where its run goes
+    uint32_t mine = 0;
+    uint32_t wrun[WAVES];
+    if (tid < kBuckets) {
+#pragma unroll
+        for (int w = 0; w < WAVES; ++w) {
+            wrun[w] = mine;
+            mine += whist[w * kBuckets + tid];
+        }
+    }
+    const uint32_t texcl = block_exclusive_sum<BLOCK>(mine, wsum[0]);
+    const uint32_t start = block_exclusive_sum<BLOCK>(total, wsum[1]);
+    if (tid < kBuckets) {
+#pragma unroll
+        for (int w = 0; w < WAVES; ++w) whist[w * kBuckets + tid] = wrun[w] + texcl;
+        gbase[tid] = start + before - texcl;
+    }
+    __syncthreads();
+
+    // ---- gather by bucket in LDS, then write each bucket's run
+#pragma unroll
+    for (int j = 0; j < IPT; ++j) {
+        const uint32_t r = wh[rb[j] >> 16] + (rb[j] & 0xFFFFu);
+        stage_k[r] = key[j];
+        if constexpr (VALS && !SEQ) stage_v2[r] = val[j];
+        if constexpr (SEQ) rb[j] = r;
+    }
+    __syncthreads();
+    const uint32_t last = d.n - 1u;
+    uint32_t sp[IPT];
+    K sk[IPT];
+#pragma unroll
+    for (int j = 0; j < IPT; ++j) sk[j] = stage_k[j * BLOCK + tid];
+    if (f.linear) {
+#pragma unroll
+        for (int j = 0; j < IPT; ++j) sp[j] = f.stretch(sk[j]);
+    } else {
+#pragma unroll
+        for (int j = 0; j < IPT; ++j) sp[j] = f.search(sk[j]);
+    }
+#pragma unroll
+    for (int j = 0; j < IPT; ++j) sp[j] = min(gbase[sp[j]] + j * BLOCK + tid, last);
+    if (full) {
+#pragma unroll
+        for (int j = 0; j < IPT; ++j) {
+            *gptr<K, SMALL>(dst_k, sp[j]) = sk[j];
+            if constexpr (VALS && !SEQ) *gptr<V, SMALL>(dst_v, sp[j]) = stage_v2[j * BLOCK + tid];
+        }
+    } else {
+#pragma unroll
+        for (int j = 0; j < IPT; ++j) {
+            if (j * BLOCK + tid >= valid) continue;
+            *gptr<K, SMALL>(dst_k, sp[j]) = sk[j];
+            if constexpr (VALS && !SEQ) *gptr<V, SMALL>(dst_v, sp[j]) = stage_v2[j * BLOCK + tid];
+        }
+    }
+    if constexpr (SEQ) {
+        __syncthreads();  // every key out of the stage
+        V *stage_v = reinterpret_cast<V *>(stage_k);
+#pragma unroll
+        for (int j = 0; j < IPT; ++j) stage_v[rb[j]] = val[j];
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < IPT; ++j)
+            if (full || j * BLOCK + tid < valid) *gptr<V, SMALL>(dst_v, sp[j]) = stage_v[j * BLOCK + tid];
+    }
+}
+
+// Sorts the leaves of one list whole in LDS, from tk/tv of their segments (to
+// which the pass wrote) into k/v, or in place in tk/tv.
+template <int BLOCK, int IPT, typename K, typename V, bool VALS>
+__global__ __launch_bounds__(BLOCK, sizeof(K) == 4 ? 4 : 2) void k_split_leaves(const SegDesc *__restrict__ descs,
+                                                           const LeafLists *__restrict__ lists,
+                                                           const SplitLeaf *__restrict__ leaves, int which,
+                                                           int in_place) {
+    __shared__ BlockSortLds<BLOCK, IPT, K, V, VALS> lds;
+    const uint32_t count = min(lists->count[which], lists->capacity);
+    leaves += static_cast<size_t>(which) * lists->capacity;
+    for (uint32_t e = blockIdx.x; e < count; e += gridDim.x) {
+        const SplitLeaf l = leaves[e];
+        const SegDesc d = descs[l.seg];
+        const K *src_k = reinterpret_cast<const K *>(d.tk) + l.off;
+        const V *src_v = VALS ? reinterpret_cast<const V *>(d.tv) + l.off : nullptr;
+        K *dst_k = reinterpret_cast<K *>(in_place ? d.tk : d.k) + l.off;
+        V *dst_v = VALS ? reinterpret_cast<V *>(in_place ? d.tv : d.v) + l.off : nullptr;
+        block_sort<BLOCK, IPT, K, V, VALS>(ArraySource<K, V>{src_k, src_v}, l.n, ArraySink<K, V, VALS>{dst_k, dst_v},
+                                           in_place != 0, lds);
+        __syncthreads();
+    }
+}
+
+// The leaves that no LDS holds: those of one value are copied by all blocks
+// together (not at all in place), others sorted by one block through global
+// memory.
+template <int BLOCK, typename K, typename V, bool VALS>
+__global__ __launch_bounds__(BLOCK) void k_split_long_leaves(const SegDesc *__restrict__ descs,
+                                                             const LeafLists *__restrict__ lists,
+                                                             const SplitLeaf *__restrict__ leaves, int in_place) {
+    __shared__ uint32_t whist[BLOCK / 64 * 256];
+    __shared__ uint32_t wsum[BLOCK / 64];
+    const uint32_t count = min(lists->count[kLeafClasses - 1], lists->capacity);
+    leaves += static_cast<size_t>(kLeafClasses - 1) * lists->capacity;
+    for (uint32_t e = 0; e < count; ++e) {
+        const SplitLeaf l = leaves[e];
+        const SegDesc d = descs[l.seg];
+        K *from_k = reinterpret_cast<K *>(d.tk) + l.off, *to_k = reinterpret_cast<K *>(d.k) + l.off;
+        V *from_v = VALS ? reinterpret_cast<V *>(d.tv) + l.off : nullptr;
+        V *to_v = VALS ? reinterpret_cast<V *>(d.v) + l.off : nullptr;
+        if (l.one) {  // (never in place)
+            for (uint32_t i = blockIdx.x * BLOCK + threadIdx.x; i < l.n; i += gridDim.x * BLOCK) {
+                to_k[i] = from_k[i];
+                if constexpr (VALS) to_v[i] = from_v[i];
+            }
+        } else if (e % gridDim.x == blockIdx.x) {
+            if (!in_place) {
+                for (uint32_t i = threadIdx.x; i < l.n; i += BLOCK) {
+                    to_k[i] = from_k[i];
+                    if constexpr (VALS) to_v[i] = from_v[i];
+                }
+                block_sort_global<BLOCK, K, V, VALS>(to_k, to_v, from_k, from_v, l.n, whist, wsum);
+            } else {
+                block_sort_global<BLOCK, K, V, VALS>(from_k, from_v, to_k, to_v, l.n, whist, wsum);
+            }
+        }
+    }
+}
+
+}  // namespace rt
