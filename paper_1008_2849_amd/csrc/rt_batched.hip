@@ -3,11 +3,12 @@
 // stay on the device: descriptors, size classes and tile maps are all built
 // by kernels, so a call is a fixed sequence of launches (no host sync) that
 // a caller with its own workspace can capture into a HIP graph.
+#include <algorithm>
 #include <cstring>
 #include <mutex>
 
 #include "rt_common.h"
-#include "rt_seg_kernels.h"
+#include "rt_split_seg.h"
 
 namespace rt {
 
@@ -105,6 +106,16 @@ static uint32_t cap_grid(size_t want, uint32_t cap) {
     return static_cast<uint32_t>(want < cap ? want : cap);
 }
 
+template <bool VALS>
+static void launch_small_classes(const SegPointers &P, const SegLayout &L, uint32_t list_stride, int passes, int to_temp,
+                                 hipStream_t stream) {
+    for (uint32_t c = 0; c < L.classes.count; ++c)
+        launch_seg_small(L.classes.cls[c], VALS, list_stride, stream, P.descs,
+                         P.lists + static_cast<size_t>(c) * list_stride, P.header, static_cast<int>(c),
+                         passes * kSegBits, to_temp);
+    prof_mark(stream, RT_KIND_SEG_SMALL);
+}
+
 // Per-segment histograms and prefix sums, whole-in-LDS segments, and passes
 // 0..passes-1 (on digits digit0..digit0 + passes - 1) over the tiled
 // segments.  The lists and the tiled list's counter are already on the
@@ -114,11 +125,13 @@ static uint32_t cap_grid(size_t want, uint32_t cap) {
 template <bool VALS, typename S>
 static void launch_seg_sort_body(const SegPointers &P, const SegLayout &L, uint32_t list_stride, int passes,
                                  int to_temp, uint32_t nchunks, uint32_t digit0, bool persistent,
-                                 hipStream_t stream) {
+                                 hipStream_t stream, int from = kSegLarge) {
     const uint32_t cus = static_cast<uint32_t>(device_cu_count());
     uint32_t *large_list = P.lists + static_cast<size_t>(kSegLarge) * list_stride;
-    hipLaunchKernelGGL(k_seg_tiles, dim3(1), dim3(1024), 0, stream, P.descs, large_list, P.first_tile, P.header,
-                       L.large_capacity, L.max_tiles, L.tile);
+    const bool huge = from == kSegHuge;
+    hipLaunchKernelGGL(k_seg_tiles, dim3(1), dim3(1024), 0, stream, P.descs, huge ? P.huge_list : large_list,
+                       P.first_tile, P.header, L.large_capacity, L.max_tiles, L.tile, from,
+                       huge ? large_list : nullptr, nullptr, 0u);
     hipLaunchKernelGGL(k_seg_tilemap, dim3(cap_grid((L.max_tiles + 255) / 256, cus * 4)), dim3(256), 0, stream,
                        P.descs, large_list, P.first_tile, P.header, P.tile_seg, nchunks);
     prof_mark(stream, RT_KIND_SEGMENTED);
@@ -133,12 +146,7 @@ static void launch_seg_sort_body(const SegPointers &P, const SegLayout &L, uint3
     hipLaunchKernelGGL(k_seg_plan, dim3(cap_grid(L.large_capacity, cus * 4)), dim3(256), 0, stream, P.descs,
                        large_list, P.header, P.hist, P.base);
     prof_mark(stream, RT_KIND_PLAN);
-    // whole-in-LDS classes
-    for (uint32_t c = 0; c < L.classes.count; ++c)
-        launch_seg_small(L.classes.cls[c], VALS, list_stride, stream, P.descs,
-                         P.lists + static_cast<size_t>(c) * list_stride, P.header, static_cast<int>(c),
-                         passes * kSegBits, to_temp);
-    prof_mark(stream, RT_KIND_SEG_SMALL);
+    if (from == kSegLarge) launch_small_classes<VALS>(P, L, list_stride, passes, to_temp, stream);
     for (int p = 0; p < passes; ++p) {
         S *status = reinterpret_cast<S *>(reinterpret_cast<char *>(P.status) + p * L.status_pass);
         uint32_t *ctr = P.header_words + offsetof(SegHeader, chunk_ctr) / 4 + p * kChunks;
@@ -170,6 +178,7 @@ SegPointers seg_pointers(char *ws, const SegLayout &L) {
     P.tile_seg = reinterpret_cast<SegDesc *>(ws + L.tile_seg);
     P.hist = reinterpret_cast<uint32_t *>(ws + L.hist);
     P.base = reinterpret_cast<uint32_t *>(ws + L.base);
+    P.huge_list = P.base;  // (moved out before the rows are written)
     P.status = ws + L.status;
     P.tk = reinterpret_cast<uint32_t *>(ws + L.tk);
     P.tv = L.tv ? reinterpret_cast<uint32_t *>(ws + L.tv) : nullptr;
@@ -181,10 +190,10 @@ void launch_segments(uint32_t *keys, uint32_t *vals, uint32_t *tk, uint32_t *tv,
                      hipStream_t stream, uint32_t digit0, bool persistent) {
     const SegPointers P = seg_pointers(ws, L);
     const bool vals_on = vals != nullptr;
-    hipLaunchKernelGGL(k_seg_reset, dim3(1), dim3(64), 0, stream, P.header, nullptr, 0u);
-    hipLaunchKernelGGL((k_seg_classify<uint32_t, uint32_t>), dim3((num_segments + 255) / 256), dim3(256), 0, stream, offsets,
+    hipLaunchKernelGGL(k_seg_reset, dim3(1), dim3(64), 0, stream, P.header);
+    hipLaunchKernelGGL(k_seg_classify, dim3((num_segments + 255) / 256), dim3(256), 0, stream, offsets,
                        num_segments, keys, vals, tk, vals_on ? tv : nullptr, L.capacity, L.large_capacity,
-                       to_temp, L.classes.limits(), P.descs, P.lists, P.header);
+                       to_temp, L.classes.limits(), P.descs, P.lists, P.header, 0u, nullptr);
     // XCD chunks of the tile list pay off for long segments only: with a few
     // tiles per segment (many partial tiles, short lookback chains) one
     // chunk measured faster.  The segments' mean size bounds their tiles.
@@ -198,11 +207,43 @@ void launch_segments(uint32_t *keys, uint32_t *vals, uint32_t *tk, uint32_t *tv,
     }
 }
 
+// Segments of a batched call, longest first: one splitter pass and leaves;
+// four digit passes for those too long for that, if the call can hold any.
+// Their list waits in the base rows, which the splitter pass does not use.
+constexpr uint32_t kSplitSegMax = 1u << 21;  // mean leaves of 8192 items, half the longest
+
+template <bool VALS>
+static void launch_batched_body(const SegPointers &P, const SegLayout &L, uint32_t num_segments, char *ws,
+                                hipStream_t stream) {
+    launch_small_classes<VALS>(P, L, num_segments, kSegPasses, 0, stream);
+    if (L.large_capacity > 0)
+        launch_split_pass<uint32_t, uint32_t, VALS>(P, L, num_segments, SplitEnd::kLeavesBack, nullptr, ws, stream);
+    if (L.capacity > kSplitSegMax)
+        launch_seg_sort_body<VALS, uint32_t>(P, L, num_segments, kSegPasses, 0, 1u, 0u, true, stream, kSegHuge);
+}
+
 void launch_batched(uint32_t *keys, uint32_t *vals, const uint32_t *offsets, uint32_t num_segments,
                     const SegLayout &L, char *ws, hipStream_t stream) {
     const SegPointers P = seg_pointers(ws, L);
     prof_begin(stream);
-    launch_segments(keys, vals, P.tk, vals ? P.tv : nullptr, offsets, num_segments, L, ws, kSegPasses, 0, stream);
+    uint32_t *tv = vals ? P.tv : nullptr;
+    if (L.tile != kSegTile || L.wide_status) {
+        launch_segments(keys, vals, P.tk, tv, offsets, num_segments, L, ws, kSegPasses, 0, stream);
+        return;
+    }
+    hipLaunchKernelGGL(k_seg_reset, dim3(1), dim3(64), 0, stream, P.header);
+    hipLaunchKernelGGL(k_seg_classify, dim3((num_segments + 255) / 256), dim3(256), 0, stream, offsets, num_segments,
+                       keys, vals, P.tk, tv, L.capacity, L.large_capacity, 0, L.classes.limits(), P.descs, P.lists,
+                       P.header, kSplitSegMax, P.huge_list);
+    if (L.large_capacity > 0) {
+        const SplitTables t = split_tables(ws, L);
+        hipLaunchKernelGGL(k_seg_tiles, dim3(1), dim3(1024), 0, stream, P.descs,
+                           P.lists + static_cast<size_t>(kSegLarge) * num_segments, P.first_tile, P.header,
+                           L.large_capacity, L.max_tiles, L.tile, kSegLarge, nullptr, t.lists, t.leaf_capacity);
+        prof_mark(stream, RT_KIND_SEGMENTED);
+    }
+    if (vals) launch_batched_body<true>(P, L, num_segments, ws, stream);
+    else launch_batched_body<false>(P, L, num_segments, ws, stream);
 }
 
 }  // namespace rt

@@ -82,6 +82,7 @@ constexpr int kSegMaxClasses = 4;    // whole-in-LDS size classes at most
 constexpr uint32_t kSegLdsMax = 1024 * 16;  // largest segment one block sorts in LDS
 constexpr uint32_t kLdsBytesPerCu = 160 * 1024;  // LDS of one gfx950 CU
 constexpr int kSegLarge = kSegMaxClasses;   // list index of the tiled segments
+constexpr int kSegHuge = kSegLarge + 1;     // segments too long for one splitter pass and leaves
 constexpr uint32_t kSegErrBounds = 2u;  // a segment reached past the workspace
 
 // Size limits of the whole-in-LDS classes of a call: class c takes the
@@ -105,7 +106,7 @@ struct SegDesc {
 
 // Device-side counters of a segmented sort.
 struct SegHeader {
-    uint32_t count[kSegMaxClasses + 1];  // list lengths: whole-in-LDS classes, tiled
+    uint32_t count[kSegMaxClasses + 2];  // list lengths: whole-in-LDS classes, tiled, huge
     uint32_t total_tiles;                // tiles of the tiled list
     uint32_t error;
     // XCD chunks of the tile list, cut at segment ends: chunk x holds tiles

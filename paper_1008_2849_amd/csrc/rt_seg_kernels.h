@@ -24,12 +24,9 @@ namespace rt {
 // set-up of a batched call: descriptors and work lists from the offsets
 // ---------------------------------------------------------------------------
 
-// one set: also the offsets of a single segment of n items.
-static __global__ __launch_bounds__(64) void k_seg_reset(SegHeader *__restrict__ h, uint32_t *__restrict__ one,
-                                                  uint32_t n) {
+static __global__ __launch_bounds__(64) void k_seg_reset(SegHeader *__restrict__ h) {
     uint32_t *w = reinterpret_cast<uint32_t *>(h);
     for (uint32_t i = threadIdx.x; i < sizeof(SegHeader) / 4; i += 64) w[i] = 0u;
-    if (one != nullptr && threadIdx.x < 2) one[threadIdx.x] = threadIdx.x == 0 ? 0u : n;
 }
 
 // One thread per segment.  Segment s is [off[s], off[s+1]) of keys/vals; its
@@ -37,15 +34,16 @@ static __global__ __launch_bounds__(64) void k_seg_reset(SegHeader *__restrict__
 // `capacity` elements.  A segment with an end before its start, or reaching
 // past off[0] + capacity, is left untouched and raises kSegErrBounds.  When
 // the result is wanted in the temporaries (to_temp), a one-item segment is
-// copied there here, as no later kernel sees it.  List slots are taken per
+// copied there here, as no later kernel sees it.  Segments of more than
+// huge_min items go to huge_list (NULL: none do).  List slots are taken per
 // wave: one atomic per class and wave, each lane's slot found from the
 // class's ballot.
-template <typename K = uint32_t, typename V = uint32_t>
 static __global__ __launch_bounds__(256) void k_seg_classify(const uint32_t *__restrict__ off, uint32_t num_segments,
-                                                      K *keys, V *vals, K *tk, V *tv,
+                                                      uint32_t *keys, uint32_t *vals, uint32_t *tk, uint32_t *tv,
                                                       size_t capacity, uint32_t large_capacity, int to_temp,
                                                       SegClassLimits classes, SegDesc *__restrict__ descs,
-                                                      uint32_t *__restrict__ lists, SegHeader *__restrict__ h) {
+                                                      uint32_t *__restrict__ lists, SegHeader *__restrict__ h,
+                                                      uint32_t huge_min, uint32_t *__restrict__ huge_list) {
     const uint32_t s = blockIdx.x * 256 + threadIdx.x;
     int c = -1;  // list of this lane's segment (-1: none)
     SegDesc d;
@@ -61,15 +59,15 @@ static __global__ __launch_bounds__(256) void k_seg_classify(const uint32_t *__r
             }
         } else {
             const uint32_t n = b - a;
-            d.k = reinterpret_cast<uint32_t *>(keys + a);
-            d.v = reinterpret_cast<uint32_t *>(vals ? vals + a : nullptr);
-            d.tk = reinterpret_cast<uint32_t *>(tk + (a - o0));
-            d.tv = reinterpret_cast<uint32_t *>(tv ? tv + (a - o0) : nullptr);
+            d.k = keys + a;
+            d.v = vals ? vals + a : nullptr;
+            d.tk = tk + (a - o0);
+            d.tv = tv ? tv + (a - o0) : nullptr;
             d.n = n;
             d.pass = 0;
             d.row = 0;
             d.pad = 0;
-            c = kSegLarge;
+            c = huge_list != nullptr && n > huge_min ? kSegHuge : kSegLarge;
 #pragma unroll
             for (int i = kSegMaxClasses - 1; i >= 0; --i)
                 if (i < static_cast<int>(classes.count) && n <= classes.max_n[i]) c = i;
@@ -77,7 +75,7 @@ static __global__ __launch_bounds__(256) void k_seg_classify(const uint32_t *__r
     }
     uint32_t at = 0;
 #pragma unroll
-    for (int q = 0; q <= kSegLarge; ++q) {
+    for (int q = 0; q <= kSegHuge; ++q) {
         const uint64_t mine = __builtin_amdgcn_ballot_w64(c == q);
         if (mine == 0) continue;
         const uint32_t lane_lo = static_cast<uint32_t>(mine), lane_hi = static_cast<uint32_t>(mine >> 32);
@@ -90,7 +88,7 @@ static __global__ __launch_bounds__(256) void k_seg_classify(const uint32_t *__r
         if (c == q) at = first + below;
     }
     if (c < 0) return;
-    if (c == kSegLarge) {
+    if (c >= kSegLarge) {
         if (at >= large_capacity) {  // only if capacity does not bound the offsets
             atomicOr(&h->error, kSegErrBounds);
             return;
@@ -98,7 +96,8 @@ static __global__ __launch_bounds__(256) void k_seg_classify(const uint32_t *__r
         d.row = at;
     }
     descs[s] = d;
-    lists[static_cast<size_t>(c) * num_segments + at] = s;
+    if (c == kSegHuge) huge_list[at] = s;
+    else lists[static_cast<size_t>(c) * num_segments + at] = s;
 }
 
 // The tiled list as the server builds it on the host has no counter on the
@@ -107,7 +106,17 @@ static __global__ __launch_bounds__(64) void k_seg_set_count(SegHeader *__restri
     if (threadIdx.x == 0) h->count[which] = count;
 }
 
+// The leaf lists of a splitter pass (rt_split_seg_kernels.h).
+constexpr int kLeafClasses = 3;
+struct LeafLists {
+    uint32_t count[kLeafClasses];
+    uint32_t capacity;  // entries per list
+};
+
 // One block: first_tile[i] = tiles of list entries before i, and the total.
+// `from`: whose list it is (count[from]); its length, as far as the workspace
+// holds it, becomes count[kSegLarge], and moved (if set) takes its entries.
+// leaf_lists set: also empties them.
 // Well-formed offsets never list more than large_capacity segments nor more
 // than max_tiles tiles; overlapping (malformed) ones can, and then the list
 // is cut to what the workspace holds (or emptied) and the error is raised,
@@ -115,14 +124,25 @@ static __global__ __launch_bounds__(64) void k_seg_set_count(SegHeader *__restri
 static __global__ __launch_bounds__(1024) void k_seg_tiles(const SegDesc *__restrict__ descs,
                                                            const uint32_t *__restrict__ list,
                                                            uint32_t *__restrict__ first_tile, SegHeader *__restrict__ h,
-                                                           uint32_t large_capacity, uint32_t max_tiles, uint32_t tile) {
+                                                           uint32_t large_capacity, uint32_t max_tiles, uint32_t tile,
+                                                           int from, uint32_t *__restrict__ moved,
+                                                           LeafLists *__restrict__ leaf_lists,
+                                                           uint32_t leaf_capacity) {
     __shared__ uint32_t s_wsum[16];
-    const uint32_t listed = h->count[kSegLarge];
+    const uint32_t listed = h->count[from];
+    if (leaf_lists != nullptr) {
+        if (threadIdx.x < kLeafClasses) leaf_lists->count[threadIdx.x] = 0u;
+        if (threadIdx.x == kLeafClasses) leaf_lists->capacity = leaf_capacity;
+    }
     const uint32_t count = min(listed, large_capacity);
     const uint32_t per = (count + 1023u) / 1024u;
     const uint32_t lo = min(count, threadIdx.x * per), hi = min(count, lo + per);
     uint32_t sum = 0;  // at most 256 entries of at most 2^19 tiles: no overflow
-    for (uint32_t i = lo; i < hi; ++i) sum += (descs[list[i]].n + tile - 1) / tile;
+    for (uint32_t i = lo; i < hi; ++i) {
+        const uint32_t s = list[i];
+        sum += (descs[s].n + tile - 1) / tile;
+        if (moved != nullptr) moved[i] = s;
+    }
     // saturate, so the block total stays exact up to max_tiles and cannot wrap
     uint32_t run = block_exclusive_sum<1024>(min(sum, max_tiles + 1u), s_wsum);
     for (uint32_t i = lo; i < hi; ++i) {

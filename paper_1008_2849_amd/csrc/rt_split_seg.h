@@ -51,7 +51,7 @@ static_assert(sizeof(LeafLists) <= 256, "the lists' header");
 enum class SplitEnd { kNextPass, kLeavesBack, kLeavesInPlace };
 
 // One splitter pass over the tiled list of a SegLayout whose descriptors,
-// list and tile map are on the device.
+// list, first tiles and leaf lists' header are on the device.
 template <typename K, typename V, bool VALS>
 void launch_split_pass(const SegPointers &P, const SegLayout &L, uint32_t list_stride, SplitEnd end, uint32_t *sub,
                        char *ws, hipStream_t stream) {
@@ -61,9 +61,12 @@ void launch_split_pass(const SegPointers &P, const SegLayout &L, uint32_t list_s
     const uint32_t *list = P.lists + static_cast<size_t>(kSegLarge) * list_stride;
     const uint32_t segs = std::max<uint32_t>(1u, L.large_capacity);
     const bool leaves = end != SplitEnd::kNextPass;
-    constexpr bool k64 = sizeof(K) == 8;
-    hipLaunchKernelGGL((k_split_sample<1024, 8, K>), dim3(split_grid(segs, cus * 2)), dim3(1024), 0, stream, P.descs,
-                       list, P.header, t.rows, leaves ? 0u : static_cast<uint32_t>(kBuckets));
+    if (leaves)
+        hipLaunchKernelGGL((k_split_sample<256, 8, K>), dim3(split_grid(segs, cus * 6)), dim3(256), 0, stream, P.descs,
+                           list, P.header, P.first_tile, P.tile_seg, t.rows, 0u);
+    else
+        hipLaunchKernelGGL((k_split_sample<1024, 8, K>), dim3(segs), dim3(1024), 0, stream, P.descs, list, P.header,
+                           P.first_tile, P.tile_seg, t.rows, static_cast<uint32_t>(kBuckets));
     prof_mark(stream, RT_KIND_PROBE);
     const uint32_t tiles = (L.max_tiles + kChunks - 1) / kChunks * kChunks;
     hipLaunchKernelGGL((k_split_tile_count<512, K>), dim3(tiles), dim3(512), 0, stream, P.tile_seg, P.header, t.rows,
@@ -73,9 +76,6 @@ void launch_split_pass(const SegPointers &P, const SegLayout &L, uint32_t list_s
                        dim3(split_grid(static_cast<size_t>(segs) * (kBuckets / 32), cus * 8),
                             (L.max_tiles + kScanChunk - 1) / kScanChunk),
                        dim3(1024), 0, stream, P.first_tile, P.header, t.table, t.chunks);
-    if (leaves)
-        hipLaunchKernelGGL(k_leaf_reset, dim3(1), dim3(64), 0, stream, t.lists, 4352u, 8192u, k64 ? 8192u : 16384u,
-                           t.leaf_capacity);
     hipLaunchKernelGGL((k_split_starts<K>), dim3(split_grid(segs, cus * 4)), dim3(256), 0, stream, P.descs, list,
                        P.header, P.first_tile, t.rows, t.chunks, leaves ? nullptr : sub, leaves ? t.lists : nullptr,
                        t.leaves, end == SplitEnd::kLeavesBack ? 1u : 0u);
@@ -85,15 +85,10 @@ void launch_split_pass(const SegPointers &P, const SegLayout &L, uint32_t list_s
     prof_mark(stream, RT_KIND_PASS);
     if (!leaves) return;
     const int in_place = end == SplitEnd::kLeavesInPlace ? 1 : 0;
-#define RT_SPLIT_LEAVES(BLK, I, C, PER_CU)                                                                         \
-    hipLaunchKernelGGL((k_split_leaves<BLK, I, K, V, VALS>), dim3(split_grid(t.leaf_capacity, cus * (PER_CU))),    \
-                       dim3(BLK), 0, stream, P.descs, t.lists, t.leaves, C, in_place)
-    RT_SPLIT_LEAVES(256, 17, 0, 4);
-    RT_SPLIT_LEAVES(512, 16, 1, 2);
-    if constexpr (!k64) RT_SPLIT_LEAVES(1024, 16, 2, 1);
-#undef RT_SPLIT_LEAVES
-    hipLaunchKernelGGL((k_split_long_leaves<1024, K, V, VALS>), dim3(cus), dim3(1024), 0, stream, P.descs, t.lists,
-                       t.leaves, in_place);
+    hipLaunchKernelGGL((k_split_leaves<256, 17, K, V, VALS>), dim3(split_grid(t.leaf_capacity, cus * 4)), dim3(256), 0,
+                       stream, P.descs, t.lists, t.leaves, in_place);
+    hipLaunchKernelGGL((k_split_long_leaves<1024, sizeof(K) == 4 ? 16 : 8, K, V, VALS>), dim3(cus), dim3(1024), 0,
+                       stream, P.descs, t.lists, t.leaves, in_place);
     prof_mark(stream, RT_KIND_SEG_SMALL);
 }
 
@@ -101,7 +96,7 @@ void launch_split_pass(const SegPointers &P, const SegLayout &L, uint32_t list_s
 // segment offsets, then the passes' tables (one pass at a time), beside the
 // temporaries.
 struct SplitSortLayout {
-    size_t offsets, seg, total;  // offsets: {0, n}, then the first pass's kBuckets + 1
+    size_t offsets, seg, total;
     SegLayout first, second;
 };
 inline SplitSortLayout make_split_sort_layout(size_t n, int block, int ipt) {
@@ -121,9 +116,7 @@ inline SplitSortLayout make_split_sort_layout(size_t n, int block, int ipt) {
 template <typename K, typename V, bool VALS>
 void launch_split_sort(K *keys, V *vals, uint32_t n, K *tk, V *tv, const SplitSortLayout &S, char *ws,
                        hipStream_t stream) {
-    const uint32_t cus = static_cast<uint32_t>(device_cu_count());
-    uint32_t *off1 = reinterpret_cast<uint32_t *>(ws + S.offsets);
-    uint32_t *off2 = off1 + 64;
+    uint32_t *off = reinterpret_cast<uint32_t *>(ws + S.offsets);
     char *seg = ws + S.seg;
     prof_begin(stream);
     for (int pass = 0; pass < 2; ++pass) {
@@ -132,18 +125,13 @@ void launch_split_sort(K *keys, V *vals, uint32_t n, K *tk, V *tv, const SplitSo
         const uint32_t num = pass == 0 ? 1u : static_cast<uint32_t>(kBuckets);
         K *a_k = pass == 0 ? keys : tk, *b_k = pass == 0 ? tk : keys;
         V *a_v = pass == 0 ? vals : tv, *b_v = pass == 0 ? tv : vals;
-        hipLaunchKernelGGL(k_seg_reset, dim3(1), dim3(64), 0, stream, P.header, pass == 0 ? off1 : nullptr, n);
-        hipLaunchKernelGGL((k_seg_classify<K, V>), dim3((num + 255) / 256), dim3(256), 0, stream,
-                           pass == 0 ? off1 : off2, num, a_k, VALS ? a_v : nullptr, b_k, VALS ? b_v : nullptr,
-                           L.capacity, L.large_capacity, 1, L.classes.limits(), P.descs, P.lists, P.header);
-        hipLaunchKernelGGL(k_seg_tiles, dim3(1), dim3(1024), 0, stream, P.descs,
-                           P.lists + static_cast<size_t>(kSegLarge) * num, P.first_tile, P.header, L.large_capacity,
-                           L.max_tiles, L.tile);
-        hipLaunchKernelGGL(k_seg_tilemap, dim3(split_grid((L.max_tiles + 255) / 256, cus * 4)), dim3(256), 0, stream,
-                           P.descs, P.lists + static_cast<size_t>(kSegLarge) * num, P.first_tile, P.header,
-                           P.tile_seg, 1u);
+        const SplitTables t = split_tables(seg, L);
+        hipLaunchKernelGGL((k_split_segments<K, V, VALS>), dim3(1), dim3(256), 0, stream, pass == 0 ? nullptr : off,
+                           num, n, a_k, a_v, b_k, b_v, L.tile, P.descs,
+                           P.lists + static_cast<size_t>(kSegLarge) * num, P.first_tile, P.header, t.lists,
+                           t.leaf_capacity);
         prof_mark(stream, RT_KIND_SEGMENTED);
-        launch_split_pass<K, V, VALS>(P, L, num, pass == 0 ? SplitEnd::kNextPass : SplitEnd::kLeavesInPlace, off2, seg,
+        launch_split_pass<K, V, VALS>(P, L, num, pass == 0 ? SplitEnd::kNextPass : SplitEnd::kLeavesInPlace, off, seg,
                                       stream);
     }
 }

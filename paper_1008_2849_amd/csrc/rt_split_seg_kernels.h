@@ -45,12 +45,13 @@ static_assert(kSplittersAt + kBuckets * 8 <= kSplitRowBytes, "64-bit splitters f
 struct SplitLeaf {
     uint32_t seg, off, n, one;
 };
-constexpr int kLeafClasses = 4;  // up to 4352, 8192 and 16384 items (64-bit keys: 4352, 8192, none); longer
-struct LeafLists {
-    uint32_t count[kLeafClasses];
-    uint32_t max_n[kLeafClasses - 1];
-    uint32_t capacity;  // entries per list
-};
+// Leaf classes (kLeafClasses): what 256 x 17 blocks hold, what the largest
+// blocks hold, longer ones.
+constexpr uint32_t kLeafSmall = 256 * 17;
+template <typename K>
+constexpr uint32_t leaf_max() {
+    return sizeof(K) == 4 ? 1024u * 16u : 1024u * 8u;
+}
 
 // Items per leaf aimed at, at most: leaves of equal stretches of spread keys
 // then fit 256 x 17 blocks (4352 items) up to segments of 2^20 items.
@@ -121,16 +122,21 @@ struct QuantileSink {
     }
 };
 
-// Chooses every listed segment's buckets (fixed_buckets of them if set, from
-// 8192 sample keys; else as many as its leaves need, from 2048, or 4096 from
-// 2^19 items: more random reads cost more than better leaves give): equal stretches of the sampled range if no stretch holds far
+// Chooses every listed segment's buckets (fixed_buckets of them if set, else
+// as many as its leaves need) from BLOCK * SIPT sample keys, and writes its
+// tiles' entries of the tile map (as k_seg_tilemap).  2048 sample keys serve
+// a pass with leaves: 8192 gave better leaves only to keys of uneven density,
+// and cost 60 us more in random reads at 2^28 items.  The buckets are equal stretches of the sampled range if no stretch holds far
 // more of the sample than its share (no bucket much above the mean, and a
-// bucket costs one multiplication), else the sample's quantiles.
+// key's bucket costs one multiplication), else the sample's quantiles.
 template <int BLOCK, int SIPT, typename K>
 __global__ __launch_bounds__(BLOCK) void k_split_sample(const SegDesc *__restrict__ descs,
                                                         const uint32_t *__restrict__ list,
-                                                        const SegHeader *__restrict__ h, char *__restrict__ rows,
+                                                        const SegHeader *__restrict__ h,
+                                                        const uint32_t *__restrict__ first_tile,
+                                                        SegDesc *__restrict__ tile_desc, char *__restrict__ rows,
                                                         uint32_t fixed_buckets) {
+    constexpr uint32_t m = BLOCK * SIPT;
     __shared__ BlockSortLds<BLOCK, SIPT, K, uint32_t, false> sort;
     __shared__ K picked[kBuckets];
     __shared__ K ends[2];
@@ -143,7 +149,12 @@ __global__ __launch_bounds__(BLOCK) void k_split_sample(const SegDesc *__restric
         const uint32_t n = d.n;
         char *row = rows + static_cast<size_t>(d.row) * kSplitRowBytes;
         const uint32_t buckets = fixed_buckets ? fixed_buckets : split_bucket_count(n);
-        const uint32_t m = fixed_buckets ? static_cast<uint32_t>(BLOCK * SIPT) : n < (1u << 19) ? 2048u : 4096u;
+        {
+            SegDesc t = d;
+            t.pad = first_tile[e];
+            const uint32_t end = first_tile[e + 1];
+            for (uint32_t i = t.pad + tid; i < end; i += BLOCK) tile_desc[i] = t;
+        }
         const SegSample<K> src{reinterpret_cast<const K *>(d.k), n, m};
         if (tid < kBuckets) {
             picked[tid] = ~K(0);
@@ -320,17 +331,6 @@ static __global__ __launch_bounds__(1024) void k_split_scan(const uint32_t *__re
     }
 }
 
-static __global__ __launch_bounds__(64) void k_leaf_reset(LeafLists *__restrict__ l, uint32_t max0, uint32_t max1,
-                                                          uint32_t max2, uint32_t capacity) {
-    if (threadIdx.x < kLeafClasses) l->count[threadIdx.x] = 0u;
-    if (threadIdx.x == 0) {
-        l->max_n[0] = max0;
-        l->max_n[1] = max1;
-        l->max_n[2] = max2;
-        l->capacity = capacity;
-    }
-}
-
 // Per listed segment: its chunks' totals become prefix sums, its buckets'
 // totals go to its row, and where the buckets start: sub set (one segment):
 // to sub[0..kBuckets], the segments of the next pass; lists set: a leaf per
@@ -374,10 +374,7 @@ __global__ __launch_bounds__(256) void k_split_starts(const SegDesc *__restrict_
                                               : (split[tid - 1] == ~K(0));
             int q = -1;
             if (c >= (all ? 1u : 2u) && (all || !one)) {  // (in place, one value is in order already)
-                q = kLeafClasses - 1;
-#pragma unroll
-                for (int i = kLeafClasses - 2; i >= 0; --i)
-                    if (c <= lists->max_n[i]) q = i;
+                q = c <= kLeafSmall ? 0 : c <= leaf_max<K>() ? 1 : 2;
             }
 #pragma unroll
             for (int i = 0; i < kLeafClasses; ++i) {
@@ -556,16 +553,14 @@ __global__ __launch_bounds__(BLOCK) void k_split_tile_scatter(const SegDesc *__r
     }
 }
 
-// Sorts the leaves of one list whole in LDS, from tk/tv of their segments (to
-// which the pass wrote) into k/v, or in place in tk/tv.
+// Sorts the leaves of the first list whole in LDS, from tk/tv of their
+// segments (to which the pass wrote) into k/v, or in place in tk/tv.
 template <int BLOCK, int IPT, typename K, typename V, bool VALS>
 __global__ __launch_bounds__(BLOCK, sizeof(K) == 4 ? 4 : 2) void k_split_leaves(const SegDesc *__restrict__ descs,
                                                            const LeafLists *__restrict__ lists,
-                                                           const SplitLeaf *__restrict__ leaves, int which,
-                                                           int in_place) {
+                                                           const SplitLeaf *__restrict__ leaves, int in_place) {
     __shared__ BlockSortLds<BLOCK, IPT, K, V, VALS> lds;
-    const uint32_t count = min(lists->count[which], lists->capacity);
-    leaves += static_cast<size_t>(which) * lists->capacity;
+    const uint32_t count = min(lists->count[0], lists->capacity);
     for (uint32_t e = blockIdx.x; e < count; e += gridDim.x) {
         const SplitLeaf l = leaves[e];
         const SegDesc d = descs[l.seg];
@@ -579,40 +574,90 @@ __global__ __launch_bounds__(BLOCK, sizeof(K) == 4 ? 4 : 2) void k_split_leaves(
     }
 }
 
-// The leaves that no LDS holds: those of one value are copied by all blocks
-// together (not at all in place), others sorted by one block through global
-// memory.
-template <int BLOCK, typename K, typename V, bool VALS>
+// The other leaves: those the largest blocks hold, as above; longer ones of
+// one value are copied by all blocks together (in place they are never
+// listed), others sorted by one block through global memory.
+template <int BLOCK, int IPT, typename K, typename V, bool VALS>
 __global__ __launch_bounds__(BLOCK) void k_split_long_leaves(const SegDesc *__restrict__ descs,
                                                              const LeafLists *__restrict__ lists,
                                                              const SplitLeaf *__restrict__ leaves, int in_place) {
-    __shared__ uint32_t whist[BLOCK / 64 * 256];
-    __shared__ uint32_t wsum[BLOCK / 64];
-    const uint32_t count = min(lists->count[kLeafClasses - 1], lists->capacity);
-    leaves += static_cast<size_t>(kLeafClasses - 1) * lists->capacity;
-    for (uint32_t e = 0; e < count; ++e) {
-        const SplitLeaf l = leaves[e];
-        const SegDesc d = descs[l.seg];
-        K *from_k = reinterpret_cast<K *>(d.tk) + l.off, *to_k = reinterpret_cast<K *>(d.k) + l.off;
-        V *from_v = VALS ? reinterpret_cast<V *>(d.tv) + l.off : nullptr;
-        V *to_v = VALS ? reinterpret_cast<V *>(d.v) + l.off : nullptr;
-        if (l.one) {  // (never in place)
-            for (uint32_t i = blockIdx.x * BLOCK + threadIdx.x; i < l.n; i += gridDim.x * BLOCK) {
-                to_k[i] = from_k[i];
-                if constexpr (VALS) to_v[i] = from_v[i];
-            }
-        } else if (e % gridDim.x == blockIdx.x) {
-            if (!in_place) {
-                for (uint32_t i = threadIdx.x; i < l.n; i += BLOCK) {
+    __shared__ BlockSortLds<BLOCK, IPT, K, V, VALS> lds;
+    static_assert(BLOCK * IPT == leaf_max<K>(), "the largest leaf");
+    for (int which = 1; which < kLeafClasses; ++which) {
+        const uint32_t count = min(lists->count[which], lists->capacity);
+        const SplitLeaf *list = leaves + static_cast<size_t>(which) * lists->capacity;
+        for (uint32_t e = which == 1 ? blockIdx.x : 0u; e < count; e += which == 1 ? gridDim.x : 1u) {
+            const SplitLeaf l = list[e];
+            const SegDesc d = descs[l.seg];
+            K *from_k = reinterpret_cast<K *>(d.tk) + l.off, *to_k = reinterpret_cast<K *>(d.k) + l.off;
+            V *from_v = VALS ? reinterpret_cast<V *>(d.tv) + l.off : nullptr;
+            V *to_v = VALS ? reinterpret_cast<V *>(d.v) + l.off : nullptr;
+            if (which == 1) {
+                block_sort<BLOCK, IPT, K, V, VALS>(
+                    ArraySource<K, V>{from_k, from_v}, l.n,
+                    ArraySink<K, V, VALS>{in_place ? from_k : to_k, in_place ? from_v : to_v}, in_place != 0, lds);
+                __syncthreads();
+            } else if (l.one) {
+                for (uint32_t i = blockIdx.x * BLOCK + threadIdx.x; i < l.n; i += gridDim.x * BLOCK) {
                     to_k[i] = from_k[i];
                     if constexpr (VALS) to_v[i] = from_v[i];
                 }
-                block_sort_global<BLOCK, K, V, VALS>(to_k, to_v, from_k, from_v, l.n, whist, wsum);
-            } else {
-                block_sort_global<BLOCK, K, V, VALS>(from_k, from_v, to_k, to_v, l.n, whist, wsum);
+            } else if (e % gridDim.x == blockIdx.x) {
+                if (!in_place)
+                    for (uint32_t i = threadIdx.x; i < l.n; i += BLOCK) {
+                        to_k[i] = from_k[i];
+                        if constexpr (VALS) to_v[i] = from_v[i];
+                    }
+                if (in_place) block_sort_global<BLOCK, K, V, VALS>(from_k, from_v, to_k, to_v, l.n, lds.whist, lds.wsum);
+                else block_sort_global<BLOCK, K, V, VALS>(to_k, to_v, from_k, from_v, l.n, lds.whist, lds.wsum);
             }
         }
     }
+}
+
+// The segments of a pass of the two-pass sort, in one block: offsets off[0..
+// count] (count <= kBuckets; one segment of n items if off is NULL) become
+// descriptors, the tiled list, first tiles and the header, as k_seg_classify
+// and k_seg_tiles make them.  A one-item segment is copied to tk/tv here.
+template <typename K, typename V, bool VALS>
+__global__ __launch_bounds__(256) void k_split_segments(const uint32_t *__restrict__ off, uint32_t count, uint32_t n,
+                                                        K *k, V *v, K *tk, V *tv, uint32_t tile,
+                                                        SegDesc *__restrict__ descs, uint32_t *__restrict__ list,
+                                                        uint32_t *__restrict__ first_tile, SegHeader *__restrict__ h,
+                                                        LeafLists *__restrict__ leaf_lists, uint32_t leaf_capacity) {
+    __shared__ uint32_t wsum[2][4];
+    const uint32_t s = threadIdx.x;
+    const uint32_t a = off == nullptr || s >= count ? 0u : off[s];
+    const uint32_t e = s >= count ? 0u : off == nullptr ? n : off[s + 1];
+    const uint32_t len = e - a;
+    const uint32_t listed = len >= 2u ? 1u : 0u, tiles = listed ? (len - 1u) / tile + 1u : 0u;
+    const uint32_t at = block_exclusive_sum<256>(listed, wsum[0]);
+    const uint32_t t0 = block_exclusive_sum<256>(tiles, wsum[1]);
+    if (len == 1u) {
+        tk[a] = k[a];
+        if constexpr (VALS) tv[a] = v[a];
+    }
+    if (listed) {
+        SegDesc d;
+        d.k = reinterpret_cast<uint32_t *>(k + a);
+        d.v = VALS ? reinterpret_cast<uint32_t *>(v + a) : nullptr;
+        d.tk = reinterpret_cast<uint32_t *>(tk + a);
+        d.tv = VALS ? reinterpret_cast<uint32_t *>(tv + a) : nullptr;
+        d.n = len;
+        d.pass = 0;
+        d.row = at;
+        d.pad = t0;
+        descs[at] = d;
+        list[at] = at;
+        first_tile[at] = t0;
+    }
+    if (s == 255u) {
+        first_tile[at + listed] = t0 + tiles;
+        h->count[kSegLarge] = at + listed;
+        h->total_tiles = t0 + tiles;
+    }
+    if (s < kLeafClasses) leaf_lists->count[s] = 0u;
+    if (s == kLeafClasses) leaf_lists->capacity = leaf_capacity;
 }
 
 }  // namespace rt

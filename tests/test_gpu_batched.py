@@ -267,3 +267,29 @@ def test_graph_capture_replays():
         rts.sort_pairs_batched(k2, v2, o, n)
         sync()
         check((to_host(k2), to_host(v2)), want, f"eager after replay {rep}")
+
+
+@pytest.mark.parametrize("kind", ["uniform", "and4", "zipf16", "one"])
+def test_long_segments(kind):
+    """Segments around the sizes where the method changes: the LDS's, tile
+    edges, more and fewer buckets, one splitter pass (2^21) and digit passes
+    above it; offsets that start past zero."""
+    import torch
+    sizes = [16384, 16385, 1, 24576, 24577, 0, 32769, 98304, 196609, 786433, (1 << 21), (1 << 21) + 1, 3, 49153]
+    announce(f"batched long segments {kind}")
+    n = sum(sizes)
+    keys = {"uniform": lambda: inputs.uniform_keys(n, 71), "and4": lambda: inputs.and_keys(n, 4, 72),
+            "zipf16": lambda: inputs.zipf16_keys(n, 73), "one": lambda: np.full(n, 7, np.uint32)}[kind]()
+    off = np.concatenate([[0], np.cumsum(sizes)]) + 5
+    base = np.concatenate([np.full(5, 9, np.uint32), keys, np.full(5, 9, np.uint32)])
+    want_k, want_v = base.copy(), np.arange(len(base), dtype=np.uint32)
+    for a, b in zip(off[:-1], off[1:]):
+        order = np.argsort(base[a:b], kind="stable")
+        want_k[a:b], want_v[a:b] = base[a:b][order], want_v[a:b][order]
+    o = to_dev(off.astype(np.uint32))
+    k, v, only = to_dev(base), to_dev(np.arange(len(base), dtype=np.uint32)), to_dev(base)
+    rts.sort_batched_ex(k, v, o, n, validate=True)
+    rts.sort_batched_ex(only, None, o, n, validate=True)
+    sync()
+    assert np.array_equal(to_host(k), want_k) and np.array_equal(to_host(v), want_v)
+    assert np.array_equal(to_host(only), want_k)
