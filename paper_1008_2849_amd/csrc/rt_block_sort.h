@@ -22,6 +22,9 @@
 // holds more than kBinLimit items.
 #pragma once
 
+#include <type_traits>
+#include <utility>
+
 #include "rt_kernels.h"
 
 namespace rt {
@@ -44,11 +47,13 @@ struct BlockSortLds {
     static constexpr int NB = 1 << LOG_NB;
     static constexpr int PER = NB >= BLOCK ? NB / BLOCK : 1;  // bins per thread of the scan
     static constexpr int IDX_BITS = ceil_log2(CAP);
+    static constexpr uint32_t NONE = CAP + kBinLimit;       // word: larger than any (two of them)
+    static constexpr uint32_t SPARE = CAP + kBinLimit + 2;  // word: written by lanes without an item
     static_assert(PER % 4 == 0, "the scan reads four bins at a time");
     union {
         struct {
             uint32_t bin[NB + 4];          // counts, then starts; bin[NB] = n
-            K word[CAP + kBinLimit + 2];   // a rank may read past its bin, never past this; the last: past the end
+            K word[CAP + kBinLimit + 4];   // a rank may read past its bin, and past the end
         } b;
         struct {
             K k[CAP];
@@ -100,21 +105,44 @@ __device__ __forceinline__ T wave_fold(T x, F op) {
 __device__ __forceinline__ void forget(uint32_t &x) { asm volatile("" : "+v"(x)); }
 __device__ __forceinline__ void forget(uint64_t &x) { asm volatile("" : "+v"(x)); }
 
+// f(0), f(1), ..., f(N - 1) with compile-time arguments.  (Loops nested over
+// a register array left it one register tuple, copied whole at each branch.)
+template <int... I, typename F>
+__device__ __forceinline__ void static_for_each(std::integer_sequence<int, I...>, F &&f) {
+    (f(std::integral_constant<int, I>{}), ...);
+}
+template <int N, typename F>
+__device__ __forceinline__ void static_for(F &&f) {
+    static_for_each(std::make_integer_sequence<int, N>{}, f);
+}
+// f of each slot of group g (kSlotGroup of them, fewer in the last group).
+template <int IPT, int G, typename F>
+__device__ __forceinline__ void group_slots(F &&f) {
+    static_for<(IPT - G < kSlotGroup ? IPT - G : kSlotGroup)>(
+        [&](auto q) { f(std::integral_constant<int, G + decltype(q)::value>{}); });
+}
+
 // Where block_sort reads its items and puts the sorted ones.
 template <typename K, typename V>
 struct ArraySource {
     const K *k;
     const V *v;
-    __device__ __forceinline__ K key(uint32_t i) const { return *gptr<K, true>(k, i); }
-    __device__ __forceinline__ V val(uint32_t i) const { return *gptr<V, true>(v, i); }
+    // item i + c; c a constant that the load's immediate offset takes
+    __device__ __forceinline__ K key(uint32_t i, uint32_t c = 0) const {
+        return *((const __attribute__((address_space(1))) K *)((const g_char *)k + static_cast<uint32_t>(i * sizeof(K))) + c);
+    }
+    __device__ __forceinline__ V val(uint32_t i, uint32_t c = 0) const {
+        return *((const __attribute__((address_space(1))) V *)((const g_char *)v + static_cast<uint32_t>(i * sizeof(V))) + c);
+    }
 };
 template <typename K, typename V, bool VALS>
 struct ArraySink {
     K *k;
     V *v;
-    __device__ __forceinline__ void put(uint32_t i, K key, V val) const {
-        *gptr<K, true>(k, i) = key;
-        if constexpr (VALS) *gptr<V, true>(v, i) = val;
+    // item base + i, base uniform
+    __device__ __forceinline__ void put(uint32_t base, uint32_t i, K key, V val) const {
+        *gptr<K, true>(k + base, i) = key;
+        if constexpr (VALS) *gptr<V, true>(v + base, i) = val;
     }
 };
 
@@ -124,25 +152,25 @@ template <int BLOCK, int IPT, typename K, typename V, bool VALS, typename Sink>
 __device__ __forceinline__ void block_store(const BlockSortLds<BLOCK, IPT, K, V, VALS> &lds, uint32_t tid, uint32_t n,
                                             K lo, const Sink &sink) {
     constexpr int GRP = kSlotGroup;
-#pragma unroll
-    for (int g = 0; g < IPT; g += GRP) {
-        if (static_cast<uint32_t>(g * BLOCK) >= n) break;
+    static_for<(IPT + GRP - 1) / GRP>([&](auto group) {
+        constexpr int g = group * GRP;
+        if (static_cast<uint32_t>(g * BLOCK) >= n) return;
         K k[GRP];
         V v[GRP];
-#pragma unroll
-        for (int q = 0; q < GRP; ++q) {
-            if (g + q >= IPT) continue;
-            k[q] = lds.s.k[(g + q) * BLOCK + tid] + lo;
+        group_slots<IPT, g>([&](auto slot) {
+            constexpr int j = slot, q = j - g;
+            k[q] = lds.s.k[j * BLOCK + tid] + lo;
             v[q] = 0;
-            if constexpr (VALS) v[q] = lds.s.v[(g + q) * BLOCK + tid];
+            if constexpr (VALS) v[q] = lds.s.v[j * BLOCK + tid];
+        });
+        if (static_cast<uint32_t>((g + GRP < IPT ? g + GRP : IPT) * BLOCK) <= n) {
+            group_slots<IPT, g>([&](auto slot) { sink.put(slot * BLOCK, tid, k[slot - g], v[slot - g]); });
+        } else {
+            group_slots<IPT, g>([&](auto slot) {
+                if (slot * BLOCK + tid < n) sink.put(slot * BLOCK, tid, k[slot - g], v[slot - g]);
+            });
         }
-#pragma unroll
-        for (int q = 0; q < GRP; ++q) {
-            const uint32_t i = (g + q) * BLOCK + tid;
-            if (g + q >= IPT || i >= n) continue;
-            sink.put(i, k[q], v[q]);
-        }
-    }
+    });
 }
 
 // Sorts items [0, n) of src (1 <= n <= BLOCK * IPT) into sink, which may be
@@ -160,7 +188,7 @@ __device__ __forceinline__ void block_sort(const Source &src, uint32_t n, const 
     typedef BlockSortLds<BLOCK, IPT, K, V, VALS> L;
     constexpr int WAVES = L::WAVES;
     constexpr int PER = L::PER;
-    constexpr int GRP = kSlotGroup;
+    constexpr int GRP = kSlotGroup, GROUPS = (IPT + GRP - 1) / GRP;
     constexpr uint32_t NB = L::NB;
     uint32_t tid = threadIdx.x;
     forget(tid);
@@ -172,26 +200,27 @@ __device__ __forceinline__ void block_sort(const Source &src, uint32_t n, const 
     uint32_t item0 = slot0 + lane;
     // whether slot j holds an item of this lane
 #define RT_LIVE(j) (item0 + (j) * 64 < ((j) < slots ? n : 0u))
+    // whether the slots of group g all hold an item in every lane of the wave
+    const int full_slots = min(slots, static_cast<int>((max(n, slot0) - slot0) / 64u));
+#define RT_FULL(g) (((g) + GRP < IPT ? (g) + GRP : IPT) <= full_slots)
 
     // ---- load, clear the bins, key range
     K key[IPT];
     K lo = ~K(0), hi = 0;
-#pragma unroll
-    for (int g = 0; g < IPT; g += GRP)
-        if (g < slots) {
-#pragma unroll
-            for (int j = g; j < g + GRP && j < IPT; ++j) key[j] = src.key(min(item0 + j * 64, n - 1u));
-        }
+    static_for<GROUPS>([&](auto group) {
+        constexpr int g = group * GRP;
+        if (RT_FULL(g)) group_slots<IPT, g>([&](auto j) { key[j] = src.key(item0, j * 64); });
+        else if (g < slots) group_slots<IPT, g>([&](auto j) { key[j] = src.key(min(item0 + j * 64, n - 1u)); });
+    });
     for (uint32_t i = tid; i < NB / 4; i += BLOCK) reinterpret_cast<uint4 *>(lds.b.bin)[i] = make_uint4(0u, 0u, 0u, 0u);
-#pragma unroll
-    for (int g = 0; g < IPT; g += GRP)
-        if (g < slots) {
-#pragma unroll
-            for (int j = g; j < g + GRP && j < IPT; ++j) {
+    static_for<GROUPS>([&](auto group) {
+        constexpr int g = group * GRP;
+        if (g < slots)
+            group_slots<IPT, g>([&](auto j) {
                 lo = key[j] < lo ? key[j] : lo;
                 hi = key[j] > hi ? key[j] : hi;
-            }
-        }
+            });
+    });
     lo = wave_fold(lo, [](K x, K y) { return x < y ? x : y; });
     hi = wave_fold(hi, [](K x, K y) { return x < y ? y : x; });
     // Keys that crowd a few bins go straight to the digit passes, which would
@@ -233,7 +262,7 @@ __device__ __forceinline__ void block_sort(const Source &src, uint32_t n, const 
         for (uint32_t i = tid; i < n; i += BLOCK) {
             V v = 0;
             if constexpr (VALS) v = src.val(i);
-            sink.put(i, lo, v);
+            sink.put(0, i, lo, v);
         }
         return;
     }
@@ -243,12 +272,18 @@ __device__ __forceinline__ void block_sort(const Source &src, uint32_t n, const 
     // ---- bin sort, if an item's word holds its bits below the bin and its index
     if (!crowded && shift + L::IDX_BITS <= 8 * sizeof(K)) {
         uint32_t at[IPT];  // slot in the bin, then the final position
-#pragma unroll
-        for (int j = 0; j < IPT; ++j)
-        {
-            at[j] = 0;
-            if (RT_LIVE(j)) at[j] = atomicAdd(&lds.b.bin[static_cast<uint32_t>((key[j] - lo) >> shift)], 1u);
-        }
+        static_for<GROUPS>([&](auto group) {
+            constexpr int g = group * GRP;
+            if (RT_FULL(g))
+                group_slots<IPT, g>([&](auto j) {
+                    at[j] = atomicAdd(&lds.b.bin[static_cast<uint32_t>((key[j] - lo) >> shift)], 1u);
+                });
+            else if (g < slots)
+                group_slots<IPT, g>([&](auto j) {
+                    at[j] = 0;
+                    if (RT_LIVE(j)) at[j] = atomicAdd(&lds.b.bin[static_cast<uint32_t>((key[j] - lo) >> shift)], 1u);
+                });
+        });
         __syncthreads();
         // exclusive prefix sum: wave w owns bins [w, w + 1) * 64 * PER, four
         // consecutive bins a lane and step
@@ -284,81 +319,101 @@ __device__ __forceinline__ void block_sort(const Source &src, uint32_t n, const 
             for (int q = 0; q < PER / 4; ++q)
                 row[q * 64 + lane] = make_uint4(c[q].x + before, c[q].y + before, c[q].z + before, c[q].w + before);
             if (tid == 0) lds.b.bin[NB] = n;
+            // words past the end compare as larger than any
+            if (tid < kBinLimit) lds.b.word[n + tid] = ~K(0);
+            if (tid < 2) lds.b.word[L::NONE + tid] = ~K(0);
             __syncthreads();
             // ---- one word per item, in its bin's slots: the key's bits below
-            // the bin, then the item's index; and the values on their way.  at
-            // then holds the bin's start and, above it, its count.
-            const K below = (K(1) << shift) - 1u;
+            // the bin (all its bits, if they fit), then the item's index; and
+            // the values on their way.  at then holds the bin's start and,
+            // above it, its count.
+            const bool whole = bits + L::IDX_BITS <= 8 * sizeof(K);
+            const K below = whole ? ~K(0) : (K(1) << shift) - 1u;
             forget(item0);
-#pragma unroll
-            for (int g = 0; g < IPT; g += GRP)
-                if (g < slots) {
-                    uint32_t first[GRP], next[GRP];
-#pragma unroll
-                    for (int q = 0; q < GRP; ++q) {
-                        if (g + q >= IPT) continue;
-                        forget(key[g + q]);
-                        const uint32_t b = static_cast<uint32_t>((key[g + q] - lo) >> shift);
-                        first[q] = lds.b.bin[b];
-                        next[q] = lds.b.bin[b + 1];
-                    }
-#pragma unroll
-                    for (int q = 0; q < GRP; ++q) {
-                        const int j = g + q;
-                        if (j >= IPT) continue;
-                        const uint32_t i = item0 + j * 64;
-                        uint32_t p = first[q] + at[j];
-                        if (!RT_LIVE(j)) p = L::CAP + kBinLimit;
-                        lds.b.word[p] = (((key[j] - lo) & below) << L::IDX_BITS) | i;
-                        at[j] = first[q] | ((next[q] - first[q]) << 16);
-                        if constexpr (VALS) val[j] = src.val(min(i, n - 1u));
-                    }
+            static_for<GROUPS>([&](auto group) {
+                constexpr int g = group * GRP;
+                if (g >= slots) return;
+                uint32_t first[GRP], next[GRP];
+                group_slots<IPT, g>([&](auto j) {
+                    forget(key[j]);
+                    const uint32_t b = static_cast<uint32_t>((key[j] - lo) >> shift);
+                    first[j - g] = lds.b.bin[b];
+                    next[j - g] = lds.b.bin[b + 1];
+                });
+                const auto word = [&](auto j) { return (((key[j] - lo) & below) << L::IDX_BITS) | (item0 + j * 64); };
+                if (RT_FULL(g)) {
+                    group_slots<IPT, g>([&](auto j) {
+                        lds.b.word[first[j - g] + at[j]] = word(j);
+                        if constexpr (VALS) val[j] = src.val(item0, j * 64);
+                    });
+                } else {
+                    group_slots<IPT, g>([&](auto j) {
+                        lds.b.word[RT_LIVE(j) ? first[j - g] + at[j] : static_cast<uint32_t>(L::SPARE)] = word(j);
+                        if constexpr (VALS) val[j] = src.val(min(item0 + j * 64, n - 1u));
+                    });
                 }
+                group_slots<IPT, g>([&](auto j) { at[j] = first[j - g] | ((next[j - g] - first[j - g]) << 16); });
+            });
             __syncthreads();
             // ---- rank in the bin: the smaller words among its slots, two a
-            // step.  An item alone in its bin, or past its bin's end, reads the
-            // first word with the other such lanes (one LDS access).
-#pragma unroll
-            for (int g = 0; g < IPT; g += GRP)
-                if (g < slots) {
-                    uint32_t first[GRP], cnt[GRP], r[GRP];
-                    K mine[GRP];
-                    forget(item0);
-                    uint32_t longest = 0;
-#pragma unroll
-                    for (int q = 0; q < GRP; ++q) {
-                        const int j = g + q;
-                        if (j >= IPT) continue;
-                        forget(key[j]);
-                        mine[q] = (((key[j] - lo) & below) << L::IDX_BITS) | (item0 + j * 64);
-                        r[q] = first[q] = at[j] & 0xFFFFu;
-                        cnt[q] = at[j] >> 16;
-                        if (cnt[q] == 1u) cnt[q] = 0u;
-                        longest = max(longest, cnt[q]);
-                    }
-                    for (uint32_t t = 0; __builtin_amdgcn_ballot_w64(t < longest) != 0u; t += 2) {
-#pragma unroll
-                        for (int q = 0; q < GRP; ++q) {
-                            if (g + q >= IPT) continue;
-                            const uint32_t p = t < cnt[q] ? first[q] + t : 0u;
+            // step.  An item alone in its bin, or past its bin's end, reads a
+            // word that never counts, with the other such lanes (one LDS
+            // access).  Words of whole keys need no test for the bin's end:
+            // what follows it is larger.
+            static_for<GROUPS>([&](auto group) {
+                constexpr int g = group * GRP;
+                if (g >= slots) return;
+                uint32_t first[GRP], cnt[GRP], r[GRP];
+                K mine[GRP];
+                forget(item0);
+                uint32_t longest = 0;
+                group_slots<IPT, g>([&](auto j) {
+                    constexpr int q = j - g;
+                    forget(key[j]);
+                    mine[q] = (((key[j] - lo) & below) << L::IDX_BITS) | (item0 + j * 64);
+                    r[q] = first[q] = at[j] & 0xFFFFu;
+                    cnt[q] = at[j] >> 16;
+                    if (cnt[q] == 1u) cnt[q] = 0u;
+                    longest = max(longest, cnt[q]);
+                });
+                if (whole) {
+                    for (uint32_t t = 0; __builtin_amdgcn_ballot_w64(t < longest) != 0u; t += 2)
+                        group_slots<IPT, g>([&](auto j) {
+                            constexpr int q = j - g;
+                            const uint32_t p = t < cnt[q] ? first[q] + t : static_cast<uint32_t>(L::NONE);
                             const K w0 = lds.b.word[p], w1 = lds.b.word[p + 1];
-                            r[q] += static_cast<uint32_t>((t < cnt[q]) & (w0 < mine[q]));
+                            r[q] += static_cast<uint32_t>(w0 < mine[q]);
+                            r[q] += static_cast<uint32_t>(w1 < mine[q]);
+                        });
+                } else {
+                    for (uint32_t t = 0; __builtin_amdgcn_ballot_w64(t < longest) != 0u; t += 2)
+                        group_slots<IPT, g>([&](auto j) {
+                            constexpr int q = j - g;
+                            const uint32_t p = t < cnt[q] ? first[q] + t : static_cast<uint32_t>(L::NONE);
+                            const K w0 = lds.b.word[p], w1 = lds.b.word[p + 1];
+                            r[q] += static_cast<uint32_t>(w0 < mine[q]);
                             r[q] += static_cast<uint32_t>((t + 1 < cnt[q]) & (w1 < mine[q]));
-                        }
-                    }
-#pragma unroll
-                    for (int q = 0; q < GRP; ++q)
-                        if (g + q < IPT) at[g + q] = r[q];
+                        });
                 }
+                group_slots<IPT, g>([&](auto j) { at[j] = r[j - g]; });
+            });
             __syncthreads();
             // ---- gather by position, then write consecutive addresses
             forget(item0);
-#pragma unroll
-            for (int j = 0; j < IPT; ++j) {
-                if (!RT_LIVE(j)) continue;
-                lds.s.k[at[j]] = key[j];
-                if constexpr (VALS) lds.s.v[at[j]] = val[j];
-            }
+            static_for<GROUPS>([&](auto group) {
+                constexpr int g = group * GRP;
+                if (RT_FULL(g))
+                    group_slots<IPT, g>([&](auto j) {
+                        lds.s.k[at[j]] = key[j];
+                        if constexpr (VALS) lds.s.v[at[j]] = val[j];
+                    });
+                else if (g < slots)
+                    group_slots<IPT, g>([&](auto j) {
+                        if (!RT_LIVE(j)) return;
+                        lds.s.k[at[j]] = key[j];
+                        if constexpr (VALS) lds.s.v[at[j]] = val[j];
+                    });
+            });
             __syncthreads();
             forget(tid);
             block_store<BLOCK, IPT, K, V, VALS>(lds, tid, n, K(0), sink);
@@ -452,6 +507,7 @@ __device__ __forceinline__ void block_sort(const Source &src, uint32_t n, const 
     }
     block_store<BLOCK, IPT, K, V, VALS>(lds, tid, n, lo, sink);
 #undef RT_LIVE
+#undef RT_FULL
 }
 
 // A whole array of at most BLOCK * IPT items, sorted in place by one block:

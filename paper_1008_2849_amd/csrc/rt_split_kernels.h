@@ -62,18 +62,20 @@ template <typename K, int M>
 struct SampleSource {
     const K *k;
     uint32_t n;
-    __device__ __forceinline__ K key(uint32_t i) const {
+    __device__ __forceinline__ K key(uint32_t i, uint32_t c = 0) const {
+        i += c;
         const uint32_t a = static_cast<uint32_t>(static_cast<uint64_t>(i) * n / M);
         const uint32_t b = static_cast<uint32_t>(static_cast<uint64_t>(i + 1) * n / M);
         return *gptr<K, sizeof(K) == 4>(k, a + __umulhi((i + 1u) * 0x9E3779B9u, b - a));
     }
-    __device__ __forceinline__ uint32_t val(uint32_t) const { return 0u; }
+    __device__ __forceinline__ uint32_t val(uint32_t, uint32_t = 0) const { return 0u; }
 };
 // Every (M / kBuckets)-th sorted sample key.
 template <typename K, int M>
 struct SplitterSink {
     K *split;
-    __device__ __forceinline__ void put(uint32_t i, K key, uint32_t) const {
+    __device__ __forceinline__ void put(uint32_t base, uint32_t i, K key, uint32_t) const {
+        i += base;
         constexpr uint32_t EVERY = M / kBuckets;
         if (i % EVERY == EVERY - 1u && i / EVERY < kBuckets - 1u) split[i / EVERY] = key;
     }

@@ -103,19 +103,21 @@ template <typename K>
 struct SegSample {
     const K *k;
     uint32_t n, m;
-    __device__ __forceinline__ K key(uint32_t i) const {
+    __device__ __forceinline__ K key(uint32_t i, uint32_t c = 0) const {
+        i += c;
         const uint32_t a = static_cast<uint32_t>(static_cast<uint64_t>(i) * n / m);
         const uint32_t b = static_cast<uint32_t>(static_cast<uint64_t>(i + 1) * n / m);
         return k[min(a + __umulhi((i + 1u) * 0x9E3779B9u, b - a), n - 1u)];
     }
-    __device__ __forceinline__ uint32_t val(uint32_t) const { return 0u; }
+    __device__ __forceinline__ uint32_t val(uint32_t, uint32_t = 0) const { return 0u; }
 };
 template <typename K>
 struct QuantileSink {
     K *picked;
     K *ends;
     uint32_t every, buckets, m;
-    __device__ __forceinline__ void put(uint32_t i, K key, uint32_t) const {
+    __device__ __forceinline__ void put(uint32_t base, uint32_t i, K key, uint32_t) const {
+        i += base;
         if (i % every == every - 1u && i / every + 1u < buckets) picked[i / every] = key;
         if (i == 0) ends[0] = key;
         if (i == m - 1u) ends[1] = key;
