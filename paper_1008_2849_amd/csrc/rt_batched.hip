@@ -213,11 +213,14 @@ void launch_segments(uint32_t *keys, uint32_t *vals, uint32_t *tk, uint32_t *tv,
 constexpr uint32_t kSplitSegMax = 1u << 21;  // mean leaves of 8192 items, half the longest
 
 template <bool VALS>
-static void launch_batched_body(const SegPointers &P, const SegLayout &L, uint32_t num_segments, char *ws,
-                                hipStream_t stream) {
+static void launch_batched_body(uint32_t *keys, uint32_t *vals, const SegPointers &P, const SegLayout &L,
+                                uint32_t num_segments, char *ws, hipStream_t stream) {
     launch_small_classes<VALS>(P, L, num_segments, kSegPasses, 0, stream);
+    typedef SplitTile<uint32_t, uint32_t, VALS> T;
+    static_assert(T::ITEMS == kSegTile, "the tile map is made for these tiles");
     if (L.large_capacity > 0)
-        launch_split_pass<uint32_t, uint32_t, VALS>(P, L, num_segments, SplitEnd::kLeavesBack, nullptr, ws, stream);
+        launch_split_pass<T, uint32_t, uint32_t, VALS>(P, L, num_segments, SplitEnd::kLeavesBack, nullptr,
+                                                    LeafArrays<uint32_t, uint32_t>{keys, vals, P.tk, P.tv}, ws, stream);
     if (L.capacity > kSplitSegMax)
         launch_seg_sort_body<VALS, uint32_t>(P, L, num_segments, kSegPasses, 0, 1u, 0u, true, stream, kSegHuge);
 }
@@ -242,8 +245,8 @@ void launch_batched(uint32_t *keys, uint32_t *vals, const uint32_t *offsets, uin
                            L.large_capacity, L.max_tiles, L.tile, kSegLarge, nullptr, t.lists, t.leaf_capacity);
         prof_mark(stream, RT_KIND_SEGMENTED);
     }
-    if (vals) launch_batched_body<true>(P, L, num_segments, ws, stream);
-    else launch_batched_body<false>(P, L, num_segments, ws, stream);
+    if (vals) launch_batched_body<true>(keys, vals, P, L, num_segments, ws, stream);
+    else launch_batched_body<false>(keys, vals, P, L, num_segments, ws, stream);
 }
 
 }  // namespace rt

@@ -376,24 +376,34 @@ __device__ __forceinline__ void block_sort(const Source &src, uint32_t n, const 
                     if (cnt[q] == 1u) cnt[q] = 0u;
                     longest = max(longest, cnt[q]);
                 });
+                K w0[GRP], w1[GRP];
+                const auto read = [&](uint32_t t) {
+                    group_slots<IPT, g>([&](auto j) {
+                        constexpr int q = j - g;
+                        const uint32_t p = t < cnt[q] ? first[q] + t : static_cast<uint32_t>(L::NONE);
+                        w0[q] = lds.b.word[p];
+                        w1[q] = lds.b.word[p + 1];
+                    });
+                    __builtin_amdgcn_sched_barrier(0);  // all reads out before the first is waited for
+                };
                 if (whole) {
-                    for (uint32_t t = 0; __builtin_amdgcn_ballot_w64(t < longest) != 0u; t += 2)
+                    for (uint32_t t = 0; __builtin_amdgcn_ballot_w64(t < longest) != 0u; t += 2) {
+                        read(t);
                         group_slots<IPT, g>([&](auto j) {
                             constexpr int q = j - g;
-                            const uint32_t p = t < cnt[q] ? first[q] + t : static_cast<uint32_t>(L::NONE);
-                            const K w0 = lds.b.word[p], w1 = lds.b.word[p + 1];
-                            r[q] += static_cast<uint32_t>(w0 < mine[q]);
-                            r[q] += static_cast<uint32_t>(w1 < mine[q]);
+                            r[q] += static_cast<uint32_t>(w0[q] < mine[q]);
+                            r[q] += static_cast<uint32_t>(w1[q] < mine[q]);
                         });
+                    }
                 } else {
-                    for (uint32_t t = 0; __builtin_amdgcn_ballot_w64(t < longest) != 0u; t += 2)
+                    for (uint32_t t = 0; __builtin_amdgcn_ballot_w64(t < longest) != 0u; t += 2) {
+                        read(t);
                         group_slots<IPT, g>([&](auto j) {
                             constexpr int q = j - g;
-                            const uint32_t p = t < cnt[q] ? first[q] + t : static_cast<uint32_t>(L::NONE);
-                            const K w0 = lds.b.word[p], w1 = lds.b.word[p + 1];
-                            r[q] += static_cast<uint32_t>(w0 < mine[q]);
-                            r[q] += static_cast<uint32_t>((t + 1 < cnt[q]) & (w1 < mine[q]));
+                            r[q] += static_cast<uint32_t>(w0[q] < mine[q]);
+                            r[q] += static_cast<uint32_t>((t + 1 < cnt[q]) & (w1[q] < mine[q]));
                         });
+                    }
                 }
                 group_slots<IPT, g>([&](auto j) { at[j] = r[j - g]; });
             });

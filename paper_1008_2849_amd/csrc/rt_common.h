@@ -224,7 +224,7 @@ void launch_split64(uint64_t *keys, uint32_t *vals, uint32_t value_words, uint32
                     char *scratch, hipStream_t stream);
 // The two-pass splitter sort (rt_split_seg_kernels.h), for larger arrays of
 // fewer than 2^30 items.  scratch as above, split_large_scratch_bytes() long.
-constexpr size_t kSplitLargeMin32 = static_cast<size_t>(1) << 30;  // four digit passes are as fast below
+constexpr size_t kSplitLargeMin32 = static_cast<size_t>(1) << 20;  // four digit passes are as fast below
 constexpr size_t kSplitLargeEnd = static_cast<size_t>(1) << 30;
 size_t split_large_scratch_bytes(size_t n, bool vals);
 size_t split_large_scratch_bytes64(size_t n, uint32_t value_words);

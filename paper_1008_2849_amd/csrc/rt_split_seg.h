@@ -39,8 +39,8 @@ inline SplitTables split_tables(char *ws, const SegLayout &L) {
     t.chunks = reinterpret_cast<uint32_t *>(ws + L.status + L.status_pass);
     t.lists = reinterpret_cast<LeafLists *>(ws + L.status + 2 * L.status_pass);
     t.leaves = reinterpret_cast<SplitLeaf *>(ws + L.status + 2 * L.status_pass + 256);
-    // a segment has at most n / (kLeafAim / 2) buckets, or one
-    t.leaf_capacity = static_cast<uint32_t>(L.capacity / (kLeafAim / 2) + L.large_capacity);
+    // a segment of n items has at most n / kLeafAim + 1 buckets
+    t.leaf_capacity = static_cast<uint32_t>(L.capacity / kLeafAim + L.large_capacity);
     return t;
 }
 static_assert(sizeof(LeafLists) <= 256, "the lists' header");
@@ -50,12 +50,12 @@ static_assert(sizeof(LeafLists) <= 256, "the lists' header");
 // tk/tv.
 enum class SplitEnd { kNextPass, kLeavesBack, kLeavesInPlace };
 
+// arrays: those the segments lie in.
 // One splitter pass over the tiled list of a SegLayout whose descriptors,
 // list, first tiles and leaf lists' header are on the device.
-template <typename K, typename V, bool VALS>
+template <typename T, typename K, typename V, bool VALS>
 void launch_split_pass(const SegPointers &P, const SegLayout &L, uint32_t list_stride, SplitEnd end, uint32_t *sub,
-                       char *ws, hipStream_t stream) {
-    typedef SplitTile<K, V, VALS> T;
+                       const LeafArrays<K, V> &arrays, char *ws, hipStream_t stream) {
     const uint32_t cus = static_cast<uint32_t>(device_cu_count());
     const SplitTables t = split_tables(ws, L);
     const uint32_t *list = P.lists + static_cast<size_t>(kSegLarge) * list_stride;
@@ -77,7 +77,7 @@ void launch_split_pass(const SegPointers &P, const SegLayout &L, uint32_t list_s
                             (L.max_tiles + kScanChunk - 1) / kScanChunk),
                        dim3(1024), 0, stream, P.first_tile, P.header, t.table, t.chunks);
     hipLaunchKernelGGL((k_split_starts<K>), dim3(split_grid(segs, cus * 4)), dim3(256), 0, stream, P.descs, list,
-                       P.header, P.first_tile, t.rows, t.chunks, leaves ? nullptr : sub, leaves ? t.lists : nullptr,
+                       P.header, P.first_tile, t.rows, t.chunks, leaves ? nullptr : sub, arrays.k, arrays.tk, leaves ? t.lists : nullptr,
                        t.leaves, end == SplitEnd::kLeavesBack ? 1u : 0u);
     prof_mark(stream, RT_KIND_PLAN);
     hipLaunchKernelGGL((k_split_tile_scatter<T::BLOCK, T::IPT, K, V, VALS, T::SEQ, sizeof(K) == 4>), dim3(tiles),
@@ -86,9 +86,9 @@ void launch_split_pass(const SegPointers &P, const SegLayout &L, uint32_t list_s
     if (!leaves) return;
     const int in_place = end == SplitEnd::kLeavesInPlace ? 1 : 0;
     hipLaunchKernelGGL((k_split_leaves<256, 17, K, V, VALS>), dim3(split_grid(t.leaf_capacity, cus * 4)), dim3(256), 0,
-                       stream, P.descs, t.lists, t.leaves, in_place);
+                       stream, arrays, t.lists, t.leaves, in_place);
     hipLaunchKernelGGL((k_split_long_leaves<1024, sizeof(K) == 4 ? 16 : 8, K, V, VALS>), dim3(cus), dim3(1024), 0,
-                       stream, P.descs, t.lists, t.leaves, in_place);
+                       stream, arrays, t.lists, t.leaves, in_place);
     prof_mark(stream, RT_KIND_SEG_SMALL);
 }
 
@@ -131,8 +131,8 @@ void launch_split_sort(K *keys, V *vals, uint32_t n, K *tk, V *tv, const SplitSo
                            P.lists + static_cast<size_t>(kSegLarge) * num, P.first_tile, P.header, t.lists,
                            t.leaf_capacity);
         prof_mark(stream, RT_KIND_SEGMENTED);
-        launch_split_pass<K, V, VALS>(P, L, num, pass == 0 ? SplitEnd::kNextPass : SplitEnd::kLeavesInPlace, off, seg,
-                                      stream);
+        launch_split_pass<SplitTile<K, V, VALS>, K, V, VALS>(P, L, num, pass == 0 ? SplitEnd::kNextPass : SplitEnd::kLeavesInPlace, off,
+                                      LeafArrays<K, V>{a_k, a_v, b_k, b_v}, seg, stream);
     }
 }
 

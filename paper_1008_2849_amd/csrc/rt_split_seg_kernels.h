@@ -33,17 +33,26 @@ struct SplitSeg {
     uint32_t scale;    // linear: bucket = umulhi((key - lo) >> shift, scale)
     uint32_t shift;
     uint32_t linear;   // 1: equal stretches of the key range; 0: splitters
-    uint32_t buckets;  // a power of two, at most kBuckets
+    uint32_t buckets;  // at most kBuckets
     uint32_t pad[2];
 };
 constexpr int kSplitRowBytes = kSegPasses * kSegRadix * 4;
 constexpr int kSplitSegAt = 1024, kSplittersAt = 2048;
 static_assert(kSplittersAt + kBuckets * 8 <= kSplitRowBytes, "64-bit splitters fit the row");
 
-// One leaf: items [off, off + n) of segment `seg`'s arrays.  one: a single
-// key value (in order as it stands).
+// One leaf of n items: where it starts in the arrays that hold the segments'
+// k/v and tk/tv, and whether it holds a single key value (in order as it
+// stands).
 struct SplitLeaf {
-    uint32_t seg, off, n, one;
+    uint32_t at_k, at_tk, n, one;
+};
+// Those arrays.
+template <typename K, typename V>
+struct LeafArrays {
+    K *k;
+    V *v;
+    K *tk;
+    V *tv;
 };
 // Leaf classes (kLeafClasses): what 256 x 17 blocks hold, what the largest
 // blocks hold, longer ones.
@@ -53,14 +62,15 @@ constexpr uint32_t leaf_max() {
     return sizeof(K) == 4 ? 1024u * 16u : 1024u * 8u;
 }
 
-// Items per leaf aimed at, at most: leaves of equal stretches of spread keys
-// then fit 256 x 17 blocks (4352 items) up to segments of 2^20 items.
-constexpr uint32_t kLeafAim = 3072;
+// Items per leaf aimed at: leaves of equal stretches of spread keys then stay
+// within four standard deviations of what 256 x 17 blocks hold (4352 items) up
+// to segments of 2^20 items.  Fuller leaves cost less per item (a leaf's bins
+// are scanned whole): 2^27 pairs in segments of up to 2^20 took 577 us in
+// leaves of 1536 to 3072 items.
+constexpr uint32_t kLeafAim = 3900;
 
 __device__ __forceinline__ uint32_t split_bucket_count(uint32_t n) {
-    uint32_t b = 1;
-    while (b < static_cast<uint32_t>(kBuckets) && n > b * kLeafAim) b *= 2;
-    return b;
+    return min((n + kLeafAim - 1u) / kLeafAim, static_cast<uint32_t>(kBuckets));
 }
 
 // Buckets of a segment's keys, held in a block.
@@ -115,10 +125,12 @@ template <typename K>
 struct QuantileSink {
     K *picked;
     K *ends;
-    uint32_t every, buckets, m;
+    uint32_t buckets, m;
     __device__ __forceinline__ void put(uint32_t base, uint32_t i, K key, uint32_t) const {
         i += base;
-        if (i % every == every - 1u && i / every + 1u < buckets) picked[i / every] = key;
+        // the first key to complete q + 1 of the buckets' equal shares of m
+        const uint32_t q = (i + 1u) * buckets / m;
+        if (q != i * buckets / m && q < buckets) picked[q - 1u] = key;
         if (i == 0) ends[0] = key;
         if (i == m - 1u) ends[1] = key;
     }
@@ -164,7 +176,7 @@ __global__ __launch_bounds__(BLOCK) void k_split_sample(const SegDesc *__restric
         }
         __syncthreads();
         if (buckets > 1)
-            block_sort<BLOCK, SIPT, K, uint32_t, false>(src, m, QuantileSink<K>{picked, ends, m / buckets, buckets, m},
+            block_sort<BLOCK, SIPT, K, uint32_t, false>(src, m, QuantileSink<K>{picked, ends, buckets, m},
                                                         false, sort);
         __syncthreads();
         if (tid == 0) {
@@ -344,7 +356,7 @@ __global__ __launch_bounds__(256) void k_split_starts(const SegDesc *__restrict_
                                                       const SegHeader *__restrict__ h,
                                                       const uint32_t *__restrict__ first_tile, char *__restrict__ rows,
                                                       uint32_t *__restrict__ chunks, uint32_t *__restrict__ sub,
-                                                      LeafLists *__restrict__ lists,
+                                                      const K *k0, const K *tk0, LeafLists *__restrict__ lists,
                                                       SplitLeaf *__restrict__ leaves, uint32_t all) {
     __shared__ uint32_t s_wsum[4];
     const uint32_t tid = threadIdx.x, lane = tid & 63u;
@@ -370,6 +382,8 @@ __global__ __launch_bounds__(256) void k_split_starts(const SegDesc *__restrict_
         if (lists != nullptr) {
             const SplitSeg *seg = reinterpret_cast<const SplitSeg *>(row + kSplitSegAt);
             const K *split = reinterpret_cast<const K *>(row + kSplittersAt);
+            const uint32_t at_k = static_cast<uint32_t>(reinterpret_cast<const K *>(d.k) - k0);
+            const uint32_t at_tk = static_cast<uint32_t>(reinterpret_cast<const K *>(d.tk) - tk0);
             uint32_t one = 0;  // the bucket holds one key value
             if (!seg->linear && tid > 0)
                 one = tid + 1u < seg->buckets ? (static_cast<K>(split[tid] - split[tid - 1]) == K(1))
@@ -389,15 +403,19 @@ __global__ __launch_bounds__(256) void k_split_starts(const SegDesc *__restrict_
                                                 static_cast<uint32_t>(mine >> 32),
                                                 __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(mine), 0u));
                 if (q == i && at < lists->capacity)
-                    leaves[static_cast<size_t>(i) * lists->capacity + at] = SplitLeaf{s, start, c, one};
+                    leaves[static_cast<size_t>(i) * lists->capacity + at] =
+                        SplitLeaf{at_k + start, at_tk + start, c, one};
             }
         }
         __syncthreads();
     }
 }
 
-// Scatters the tile of this block by bucket from k/v to tk/tv of its segment,
-// stably.  SEQ: the values go through the keys' stage after them.
+// Scatters the tile of this block by bucket from k/v to tk/tv of its segment:
+// stably with values; keys alone, where equal keys cannot be told apart, in
+// any order inside a bucket, so that an LDS add ranks an item (3 vector
+// instructions against about 50 of ballot matching).  SEQ: the values go
+// through the keys' stage after them.
 template <int BLOCK, int IPT, typename K, typename V, bool VALS, bool SEQ, bool SMALL>
 __global__ __launch_bounds__(BLOCK) void k_split_tile_scatter(const SegDesc *__restrict__ tile_desc,
                                                               const SegHeader *__restrict__ h,
@@ -443,7 +461,7 @@ __global__ __launch_bounds__(BLOCK) void k_split_tile_scatter(const SegDesc *__r
         before = table[static_cast<size_t>(tile) * kBuckets + tid] +
                  chunks[static_cast<size_t>(chunk_row(d.pad, d.row, tile)) * kBuckets + tid];
     }
-    uint32_t *wh = whist + wave * kBuckets;
+    uint32_t *wh = whist + (VALS ? wave * kBuckets : 0);
     uint32_t *scratch = whist + WAVES * kBuckets + wave * 64 + lane;
     for (uint32_t i = lane; i < static_cast<uint32_t>(kBuckets); i += 64) wh[i] = 0u;
     __syncthreads();
@@ -463,8 +481,28 @@ __global__ __launch_bounds__(BLOCK) void k_split_tile_scatter(const SegDesc *__r
         for (int j = 0; j < IPT; ++j)
             if (slot0 + j * 64 >= valid) rb[j] = kBuckets - 1;
     }
+    if constexpr (!VALS) {
 #pragma unroll
-    for (int j = 0; j < IPT; ++j) {
+        for (int j = 0; j < IPT; ++j) {
+            const uint32_t b = rb[j];
+            if (!full && slot0 + j * 64 >= valid) continue;
+            // a slot of one bucket (sorted or repeated keys) takes one add
+            uint32_t r;
+            if (__builtin_amdgcn_ballot_w64(b != __builtin_amdgcn_readfirstlane(b)) == 0) {
+                const uint64_t live = __builtin_amdgcn_ballot_w64(true);
+                const uint32_t below = __builtin_amdgcn_mbcnt_hi(
+                    static_cast<uint32_t>(live >> 32), __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(live), 0u));
+                uint32_t first = 0;
+                if (below == 0) first = atomicAdd(&whist[b], static_cast<uint32_t>(__popcll(live)));
+                r = __builtin_amdgcn_readfirstlane(first) + below;
+            } else {
+                r = atomicAdd(&whist[b], 1u);
+            }
+            rb[j] = r | (b << 16);
+        }
+    }
+#pragma unroll
+    for (int j = 0; VALS && j < IPT; ++j) {
         const uint32_t b = rb[j];
         uint32_t lo, hi;
         match_digit<8>(b, lo, hi);
@@ -488,11 +526,12 @@ __global__ __launch_bounds__(BLOCK) void k_split_tile_scatter(const SegDesc *__r
     __syncthreads();
 
     // ---- per bucket: each wave's offset in the tile, and where its run goes
+    constexpr int TABLES = VALS ? WAVES : 1;
     uint32_t mine = 0;
-    uint32_t wrun[WAVES];
+    uint32_t wrun[TABLES];
     if (tid < kBuckets) {
 #pragma unroll
-        for (int w = 0; w < WAVES; ++w) {
+        for (int w = 0; w < TABLES; ++w) {
             wrun[w] = mine;
             mine += whist[w * kBuckets + tid];
         }
@@ -501,7 +540,7 @@ __global__ __launch_bounds__(BLOCK) void k_split_tile_scatter(const SegDesc *__r
     const uint32_t start = block_exclusive_sum<BLOCK>(total, wsum[1]);
     if (tid < kBuckets) {
 #pragma unroll
-        for (int w = 0; w < WAVES; ++w) whist[w * kBuckets + tid] = wrun[w] + texcl;
+        for (int w = 0; w < TABLES; ++w) whist[w * kBuckets + tid] = wrun[w] + texcl;
         gbase[tid] = start + before - texcl;
     }
     __syncthreads();
@@ -509,6 +548,7 @@ __global__ __launch_bounds__(BLOCK) void k_split_tile_scatter(const SegDesc *__r
     // ---- gather by bucket in LDS, then write each bucket's run
 #pragma unroll
     for (int j = 0; j < IPT; ++j) {
+        if (!VALS && !full && slot0 + j * 64 >= valid) continue;
         const uint32_t r = wh[rb[j] >> 16] + (rb[j] & 0xFFFFu);
         stage_k[r] = key[j];
         if constexpr (VALS && !SEQ) stage_v2[r] = val[j];
@@ -555,23 +595,29 @@ __global__ __launch_bounds__(BLOCK) void k_split_tile_scatter(const SegDesc *__r
     }
 }
 
-// Sorts the leaves of the first list whole in LDS, from tk/tv of their
-// segments (to which the pass wrote) into k/v, or in place in tk/tv.
+// Sorts the leaves of the first list whole in LDS, from the arrays the pass
+// wrote into the others, or in place.  The next leaf's bounds are read while
+// this one is sorted.
 template <int BLOCK, int IPT, typename K, typename V, bool VALS>
-__global__ __launch_bounds__(BLOCK, sizeof(K) == 4 ? 4 : 2) void k_split_leaves(const SegDesc *__restrict__ descs,
-                                                           const LeafLists *__restrict__ lists,
-                                                           const SplitLeaf *__restrict__ leaves, int in_place) {
+__global__ __launch_bounds__(BLOCK, sizeof(K) == 4 ? 4 : 2) void k_split_leaves(LeafArrays<K, V> a,
+                                                                               const LeafLists *__restrict__ lists,
+                                                                               const SplitLeaf *__restrict__ leaves,
+                                                                               int in_place) {
     __shared__ BlockSortLds<BLOCK, IPT, K, V, VALS> lds;
     const uint32_t count = min(lists->count[0], lists->capacity);
-    for (uint32_t e = blockIdx.x; e < count; e += gridDim.x) {
-        const SplitLeaf l = leaves[e];
-        const SegDesc d = descs[l.seg];
-        const K *src_k = reinterpret_cast<const K *>(d.tk) + l.off;
-        const V *src_v = VALS ? reinterpret_cast<const V *>(d.tv) + l.off : nullptr;
-        K *dst_k = reinterpret_cast<K *>(in_place ? d.tk : d.k) + l.off;
-        V *dst_v = VALS ? reinterpret_cast<V *>(in_place ? d.tv : d.v) + l.off : nullptr;
-        block_sort<BLOCK, IPT, K, V, VALS>(ArraySource<K, V>{src_k, src_v}, l.n, ArraySink<K, V, VALS>{dst_k, dst_v},
-                                           in_place != 0, lds);
+    uint32_t e = blockIdx.x;
+    if (e >= count) return;
+    SplitLeaf l = leaves[e];
+    for (;;) {
+        e += gridDim.x;
+        const SplitLeaf next = leaves[min(e, count - 1u)];
+        const uint32_t to = in_place ? l.at_tk : l.at_k;
+        block_sort<BLOCK, IPT, K, V, VALS>(
+            ArraySource<K, V>{a.tk + l.at_tk, VALS ? a.tv + l.at_tk : nullptr}, l.n,
+            ArraySink<K, V, VALS>{(in_place ? a.tk : a.k) + to, VALS ? (in_place ? a.tv : a.v) + to : nullptr},
+            in_place != 0, lds);
+        if (e >= count) return;
+        l = next;
         __syncthreads();
     }
 }
@@ -580,8 +626,7 @@ __global__ __launch_bounds__(BLOCK, sizeof(K) == 4 ? 4 : 2) void k_split_leaves(
 // one value are copied by all blocks together (in place they are never
 // listed), others sorted by one block through global memory.
 template <int BLOCK, int IPT, typename K, typename V, bool VALS>
-__global__ __launch_bounds__(BLOCK) void k_split_long_leaves(const SegDesc *__restrict__ descs,
-                                                             const LeafLists *__restrict__ lists,
+__global__ __launch_bounds__(BLOCK) void k_split_long_leaves(LeafArrays<K, V> a, const LeafLists *__restrict__ lists,
                                                              const SplitLeaf *__restrict__ leaves, int in_place) {
     __shared__ BlockSortLds<BLOCK, IPT, K, V, VALS> lds;
     static_assert(BLOCK * IPT == leaf_max<K>(), "the largest leaf");
@@ -590,10 +635,9 @@ __global__ __launch_bounds__(BLOCK) void k_split_long_leaves(const SegDesc *__re
         const SplitLeaf *list = leaves + static_cast<size_t>(which) * lists->capacity;
         for (uint32_t e = which == 1 ? blockIdx.x : 0u; e < count; e += which == 1 ? gridDim.x : 1u) {
             const SplitLeaf l = list[e];
-            const SegDesc d = descs[l.seg];
-            K *from_k = reinterpret_cast<K *>(d.tk) + l.off, *to_k = reinterpret_cast<K *>(d.k) + l.off;
-            V *from_v = VALS ? reinterpret_cast<V *>(d.tv) + l.off : nullptr;
-            V *to_v = VALS ? reinterpret_cast<V *>(d.v) + l.off : nullptr;
+            K *from_k = a.tk + l.at_tk, *to_k = a.k + l.at_k;
+            V *from_v = VALS ? a.tv + l.at_tk : nullptr;
+            V *to_v = VALS ? a.v + l.at_k : nullptr;
             if (which == 1) {
                 block_sort<BLOCK, IPT, K, V, VALS>(
                     ArraySource<K, V>{from_k, from_v}, l.n,
