@@ -158,7 +158,10 @@ __device__ __forceinline__ void status_store(S *p, S v) {
 // fill
 // ---------------------------------------------------------------------------
 
-static __global__ __launch_bounds__(256) void k_fill_zero(uint32_t *__restrict__ p, size_t words) {
+// one (if set): a word that starts at 1.
+static __global__ __launch_bounds__(256) void k_fill_zero(uint32_t *__restrict__ p, size_t words,
+                                                          uint32_t *__restrict__ one = nullptr) {
+    if (one != nullptr && blockIdx.x == 0 && threadIdx.x == 0) *one = 1u;
     const size_t stride = static_cast<size_t>(gridDim.x) * 256;
     for (size_t i = static_cast<size_t>(blockIdx.x) * 256 + threadIdx.x; i < words; i += stride)
         p[i] = 0u;
@@ -343,6 +346,9 @@ __device__ __forceinline__ T wave_reduce(T v, F op) {
     return v;
 }
 
+//
+// Block p looks at pass p and clears *mode, which starts at 1, if it finds a
+// reason: one block for all passes, one after the other, took 27 us.
 template <int BLOCK, typename K = uint32_t>
 __global__ __launch_bounds__(BLOCK) void k_chunk_probe(const K *__restrict__ keys, uint32_t n, HistArgs ha,
                                                        uint32_t *__restrict__ mode) {
@@ -351,9 +357,10 @@ __global__ __launch_bounds__(BLOCK) void k_chunk_probe(const K *__restrict__ key
     constexpr int PER = RUNS / WAVES;  // runs per wave = keys per lane
     __shared__ uint32_t s_tab[kChunks * kChunkRadix];
     __shared__ uint32_t s_chunk[kChunks];
-    __shared__ uint32_t s_lo[kMaxPasses], s_hi[kMaxPasses];
-    __shared__ uint32_t s_max, s_bad;
+    __shared__ uint32_t s_lo[2], s_hi[2];  // of digit p - 1, of digit p
+    __shared__ uint32_t s_max;
     const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
+    const uint32_t p = blockIdx.x;
     // runs of consecutive keys: a few hundred pages touched, not thousands
     K k[PER];  // 32- or 64-bit keys
 #pragma unroll
@@ -361,64 +368,59 @@ __global__ __launch_bounds__(BLOCK) void k_chunk_probe(const K *__restrict__ key
         const uint64_t start = static_cast<uint64_t>(wave * PER + j) * n / RUNS;
         k[j] = keys[min(start + lane, static_cast<uint64_t>(n) - 1u)];
     }
-    if (tid < kMaxPasses) {
+    for (uint32_t i = tid; i < kChunks * kChunkRadix; i += BLOCK) s_tab[i] = 0u;
+    if (tid < kChunks) s_chunk[tid] = 0u;
+    if (tid < 2) {
         s_lo[tid] = ~0u;
         s_hi[tid] = 0u;
     }
-    if (tid == 0) s_bad = 0u;
+    if (tid == 0) s_max = 0u;
     __syncthreads();
-    for (uint32_t p = 0; p < ha.num_passes; ++p) {
+    for (uint32_t q = p == 0 ? 1u : 0u; q < 2u; ++q) {
+        const uint32_t dp = p + q - 1u;
         uint32_t lo = ~0u, hi = 0u;
 #pragma unroll
         for (int j = 0; j < PER; ++j) {
-            const uint32_t d = static_cast<uint32_t>(k[j] >> ha.shift[p]) & ha.mask[p];
+            const uint32_t d = static_cast<uint32_t>(k[j] >> ha.shift[dp]) & ha.mask[dp];
             lo = min(lo, d);
             hi = max(hi, d);
         }
         lo = wave_reduce(lo, [](uint32_t x, uint32_t y) { return min(x, y); });
         hi = wave_reduce(hi, [](uint32_t x, uint32_t y) { return max(x, y); });
         if (lane == 0) {
-            atomicMin(&s_lo[p], lo);
-            atomicMax(&s_hi[p], hi);
+            atomicMin(&s_lo[q], lo);
+            atomicMax(&s_hi[q], hi);
         }
     }
-    for (uint32_t p = 0; p < ha.num_passes; ++p) {
-        for (uint32_t i = tid; i < kChunks * kChunkRadix; i += BLOCK) s_tab[i] = 0u;
-        if (tid < kChunks) s_chunk[tid] = 0u;
-        if (tid == 0) s_max = 0u;
-        __syncthreads();
-        const uint32_t w = 32u - __builtin_clz(ha.mask[p]);
+    const uint32_t w = 32u - __builtin_clz(ha.mask[p]);
 #pragma unroll
-        for (int j = 0; j < PER; ++j) {
-            const uint32_t x = p == 0 ? 0u : (static_cast<uint32_t>(k[j] >> ha.shift[p - 1]) & ha.mask[p - 1]) >> ha.cshift[p - 1];
-            atomicAdd(&s_tab[(x << w) | (static_cast<uint32_t>(k[j] >> ha.shift[p]) & ha.mask[p])], 1u);
-        }
-        __syncthreads();
-        uint32_t m = 0;
-        for (uint32_t i = tid; i < (static_cast<uint32_t>(kChunks) << w); i += BLOCK) {
-            const uint32_t c = s_tab[i];
-            m = max(m, c);
-            if (w >= 6u) {  // a wave's 64 entries share a chunk: one add per wave
-                const uint32_t t = wave_reduce(c, [](uint32_t x, uint32_t y) { return x + y; });
-                if (lane == 0) atomicAdd(&s_chunk[i >> w], t);
-            } else if (c != 0u) {
-                atomicAdd(&s_chunk[i >> w], c);
-            }
-        }
-        m = wave_reduce(m, [](uint32_t x, uint32_t y) { return max(x, y); });
-        if (lane == 0) atomicMax(&s_max, m);
-        __syncthreads();
-        if (tid == 0) {
-            if (s_lo[p] != s_hi[p] && s_max > kProbeSamples / 64) s_bad = 1u;
-            if (p > 0 && s_lo[p - 1] != s_hi[p - 1]) {
-                uint32_t mc = 0;
-                for (int x = 0; x < kChunks; ++x) mc = max(mc, s_chunk[x]);
-                if (mc > kProbeSamples / 4) s_bad = 1u;
-            }
-        }
-        __syncthreads();
+    for (int j = 0; j < PER; ++j) {
+        const uint32_t x = p == 0 ? 0u : (static_cast<uint32_t>(k[j] >> ha.shift[p - 1]) & ha.mask[p - 1]) >> ha.cshift[p - 1];
+        atomicAdd(&s_tab[(x << w) | (static_cast<uint32_t>(k[j] >> ha.shift[p]) & ha.mask[p])], 1u);
     }
-    if (tid == 0) *mode = s_bad ? 0u : 1u;
+    __syncthreads();
+    uint32_t m = 0;
+    for (uint32_t i = tid; i < (static_cast<uint32_t>(kChunks) << w); i += BLOCK) {
+        const uint32_t c = s_tab[i];
+        m = max(m, c);
+        if (w >= 6u) {  // a wave's 64 entries share a chunk: one add per wave
+            const uint32_t t = wave_reduce(c, [](uint32_t x, uint32_t y) { return x + y; });
+            if (lane == 0) atomicAdd(&s_chunk[i >> w], t);
+        } else if (c != 0u) {
+            atomicAdd(&s_chunk[i >> w], c);
+        }
+    }
+    m = wave_reduce(m, [](uint32_t x, uint32_t y) { return max(x, y); });
+    if (lane == 0) atomicMax(&s_max, m);
+    __syncthreads();
+    if (tid != 0) return;
+    bool bad = s_lo[1] != s_hi[1] && s_max > kProbeSamples / 64;
+    if (p > 0 && s_lo[0] != s_hi[0]) {
+        uint32_t mc = 0;
+        for (int x = 0; x < kChunks; ++x) mc = max(mc, s_chunk[x]);
+        bad = bad || mc > kProbeSamples / 4;
+    }
+    if (bad) *mode = 0u;
 }
 
 // ---------------------------------------------------------------------------
@@ -462,7 +464,10 @@ __device__ inline void plan_chunks(const PlanArgs &a, bool chunked, const uint32
     pp->ctile[kChunks] = t;
 }
 
-// One block of 256 threads; thread t covers bins [8t, 8t + 8) of a pass.
+// One block of 256 threads; thread t covers bins [8t, 8t + 8) of a pass (with
+// per-chunk counts: digit t).  The counts of all passes are loaded together,
+// and thread p writes pass p's plan: read and written one after the other,
+// pass by pass, the same work took 10 us for four passes and 16 us for eight.
 // Also clears the tile counters of the passes and the error word after them.
 //
 // Chunks (a.chunk_ctr set): with a.chunked the histograms are per chunk (see
@@ -476,7 +481,7 @@ __device__ inline void plan_chunks(const PlanArgs &a, bool chunked, const uint32
 static __global__ __launch_bounds__(256) void k_plan(PlanArgs a, const uint32_t *__restrict__ hist,
                                               uint32_t *__restrict__ base, SortPlan *__restrict__ plan,
                                               uint32_t *__restrict__ tile_counters, uint32_t direct) {
-    __shared__ uint32_t s_wsum[4];
+    __shared__ uint32_t s_wsum[kMaxPasses][4];
     __shared__ uint32_t s_constant[kMaxPasses];
     __shared__ uint32_t s_cstart[kMaxPasses + 1][kChunks];  // [p][x]: base of pass p - 1 at chunk x's first digit
     const uint32_t tid = threadIdx.x;
@@ -490,104 +495,91 @@ static __global__ __launch_bounds__(256) void k_plan(PlanArgs a, const uint32_t 
     if (tid == kMaxPasses) tile_counters[kMaxPasses] = 0u;  // the error word
     if (a.chunk_ctr != nullptr)
         for (uint32_t i = tid; i < kMaxPasses * kChunks; i += 256) a.chunk_ctr[i] = 0u;
-    __syncthreads();
-    for (uint32_t p = 0; p < a.num_passes; ++p) {
-        const uint32_t bins = 1u << a.width[p];
-        if (chunked) {
-            // digits of at most 8 bits: thread t owns digit t, its chunk
-            // counts loaded together
-            const uint32_t d = tid;
-            uint32_t h[kChunks];
-            uint32_t c = 0;
+    uint32_t c[kMaxPasses][8];  // bins 8t..8t + 7, or chunks 0..7 of digit t
+    static_assert(kChunks == 8, "a digit's chunk counts take a thread's bins");
 #pragma unroll
-            for (int x = 0; x < kChunks; ++x) {
-                h[x] = d < bins ? hist[(p * kChunks + x) * kChunkRadix + d] : 0u;
-                c += h[x];
-            }
-            if (c == a.n) s_constant[p] = 1u;  // every key has this digit
-            const uint32_t run = block_exclusive_sum<256>(c, s_wsum);
-            base[p * kMaxRadix + d] = d < bins ? run : a.n;
-            for (uint32_t i = d + 256; i < static_cast<uint32_t>(kMaxRadix); i += 256) base[p * kMaxRadix + i] = a.n;
+    for (int p = 0; p < kMaxPasses; ++p) {
+        if (p >= static_cast<int>(a.num_passes)) break;
+        const uint32_t bins = 1u << a.width[p];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            if (chunked) c[p][i] = tid < bins ? hist[(p * kChunks + i) * kChunkRadix + tid] : 0u;
+            else c[p][i] = tid * 8 + i < bins ? hist[p * kMaxRadix + tid * 8 + i] : 0u;
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int p = 0; p < kMaxPasses; ++p) {
+        if (p >= static_cast<int>(a.num_passes)) break;
+        const uint32_t bins = 1u << a.width[p];
+        uint32_t sum = 0;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            sum += c[p][i];
+            if (!chunked && c[p][i] == a.n) s_constant[p] = 1u;  // every key has this digit
+        }
+        if (chunked && sum == a.n) s_constant[p] = 1u;
+        uint32_t run = block_exclusive_sum<256>(sum, s_wsum[p]);
+        uint32_t *out = base + p * kMaxRadix;
+        if (chunked) {
+            // digits of at most 8 bits: thread t owns digit t
+            const uint32_t d = tid;
+            out[d] = d < bins ? run : a.n;
+            for (uint32_t i = d + 256; i < static_cast<uint32_t>(kMaxRadix); i += 256) out[i] = a.n;
             if (d < bins) {
                 uint32_t r = run;
 #pragma unroll
                 for (int x = 0; x < kChunks; ++x) {
                     a.cbase[(p * kChunks + x) * kChunkRadix + d] = r;
-                    r += h[x];
+                    r += c[p][x];
                 }
                 // pass p + 1's chunk x starts where digit x << cshift of this pass starts
                 const uint32_t cshift = a.width[p] > 3u ? a.width[p] - 3u : 0u;
                 if ((d & ((1u << cshift) - 1u)) == 0u && (d >> cshift) < kChunks) s_cstart[p + 1][d >> cshift] = run;
             }
-            __syncthreads();  // s_wsum is reused by the next pass; s_cstart is read below
-            continue;
-        }
-        uint32_t c[8];
-        uint32_t sum = 0;
+        } else {
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            const uint32_t d = tid * 8 + i;
-            c[i] = d < bins ? hist[p * kMaxRadix + d] : 0u;
-            sum += c[i];
-            if (c[i] == a.n) s_constant[p] = 1u;  // every key has this digit
+            for (int i = 0; i < 8; ++i) {  // bins past the digit's range start at n
+                out[tid * 8 + i] = run;
+                run += c[p][i];
+            }
         }
-        uint32_t run = block_exclusive_sum<256>(sum, s_wsum);
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {  // bins past the digit's range start at n
-            base[p * kMaxRadix + tid * 8 + i] = run;
-            run += c[i];
-        }
-        __syncthreads();  // s_wsum is reused by the next pass
     }
-    if (tid != 0) return;
+    __syncthreads();
+    if (tid >= kMaxPasses) return;
 
-    uint32_t active[kMaxPasses];
-    uint32_t executed = 0;
-    for (uint32_t p = 0; p < kMaxPasses; ++p) {
-        active[p] = p < a.num_passes && (direct || a.no_skip || !s_constant[p]);
-        executed += active[p];
-    }
+    uint32_t active = 0;  // bit p: pass p runs
+    for (uint32_t p = 0; p < a.num_passes; ++p)
+        if (direct || a.no_skip || !s_constant[p]) active |= 1u << p;
+    const uint32_t executed = static_cast<uint32_t>(__popc(active));
     // Buffers: U = caller's arrays, A/B = temporaries.  The last executed pass
     // must write U: an even count alternates U->A->U...; an odd count >= 3
     // starts U->A->B->U and then alternates; a single pass goes U->A and is
     // copied back.  `direct` (one explicit pass) reads U and writes A.
-    const uint32_t *src_k = a.user_k, *src_v = a.user_v;
-    uint32_t j = 0;
-    for (uint32_t p = 0; p < kMaxPasses; ++p) {
-        PassPlan pp;
-        pp.active = active[p];
-        pp.shift = a.shift[p];
-        pp.width = a.width[p];
-        pp.pad[0] = pp.pad[1] = 0;
-        pp.src_k = src_k;
-        pp.src_v = src_v;
-        pp.dst_k = nullptr;
-        pp.dst_v = nullptr;
-        if (active[p]) {
-            uint32_t *dk, *dv;
-            if (direct) {
-                dk = a.t1_k; dv = a.t1_v;
-            } else if (executed == 1) {
-                dk = a.t1_k; dv = a.t1_v;
-            } else if ((executed & 1u) && j < 3) {
-                dk = j == 0 ? a.t1_k : (j == 1 ? a.t2_k : a.user_k);
-                dv = j == 0 ? a.t1_v : (j == 1 ? a.t2_v : a.user_v);
-            } else {
-                const uint32_t k = (executed & 1u) ? j - 3 : j;  // position in the alternation
-                dk = (k & 1u) ? a.user_k : a.t1_k;
-                dv = (k & 1u) ? a.user_v : a.t1_v;
-            }
-            pp.dst_k = dk;
-            pp.dst_v = dv;
-            src_k = dk;
-            src_v = dv;
-            ++j;
-        }
-        plan->pass[p] = pp;
-        plan_chunks(a, chunked, s_cstart[p], base, p, &plan->pass[p]);  // in place: no indexed local copy
+    // Where the j-th executed pass writes: 0 = U, 1 = A, 2 = B.
+    const auto writes = [&](uint32_t j) -> uint32_t {
+        if (direct || executed == 1) return 1u;
+        if ((executed & 1u) && j < 3u) return (j + 1u) % 3u;
+        const uint32_t k = (executed & 1u) ? j - 3u : j;  // position in the alternation
+        return (k & 1u) ? 0u : 1u;
+    };
+    const uint32_t p = tid, j = static_cast<uint32_t>(__popc(active & ((1u << p) - 1u)));
+    const uint32_t from = j == 0 ? 0u : writes(j - 1u), to = writes(j);
+    PassPlan pp;
+    pp.active = (active >> p) & 1u;
+    pp.shift = a.shift[p];
+    pp.width = a.width[p];
+    pp.pad[0] = pp.pad[1] = 0;
+    pp.src_k = from == 0u ? a.user_k : from == 1u ? a.t1_k : a.t2_k;
+    pp.src_v = from == 0u ? a.user_v : from == 1u ? a.t1_v : a.t2_v;
+    pp.dst_k = to == 0u ? a.user_k : to == 1u ? a.t1_k : a.t2_k;
+    pp.dst_v = to == 0u ? a.user_v : to == 1u ? a.t1_v : a.t2_v;
+    plan->pass[p] = pp;
+    plan_chunks(a, chunked, s_cstart[p], base, p, &plan->pass[p]);  // in place: no indexed local copy
+    if (p == 0) {
+        plan->executed = executed;
+        plan->copy_back = (!direct && executed == 1) ? 1u : 0u;
     }
-    plan->executed = executed;
-    plan->copy_back = (!direct && executed == 1) ? 1u : 0u;
 }
 
 // Fused next-digit histogram (RT_FLAG_FUSED_HISTOGRAM): a pass counts the

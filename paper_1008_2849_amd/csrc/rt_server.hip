@@ -341,7 +341,7 @@ rt_status enqueue_step(rt_server *s, StepSlot &slot, const StepPlan &P) {
     }
     if (P.tiled) {  // one pass of every tiled request, each at its own pass
         hipLaunchKernelGGL(k_fill_zero, dim3(grid((P.tiles * kSegRadix + 4095) / 4096, 4096)), dim3(256), 0, st,
-                           d_status, P.tiles * kSegRadix);
+                           d_status, P.tiles * kSegRadix, nullptr);
         hipLaunchKernelGGL(k_seg_tiles, dim3(1), dim3(1024), 0, st, d_descs, d_plist, d_first_p, d_hp, stride,
                            m.max_tiles, static_cast<uint32_t>(kSegTile), kSegLarge, nullptr, nullptr, 0u);
         // XCD chunks when the step's tiled requests are long (see seg_chunk_count)

@@ -442,21 +442,21 @@ static bool sample_decides(const Resolved &r, uint32_t n) {
 
 // hist_zeroed: the caller has cleared the counters already.  chunked: the
 // per-chunk counts of a sort with r.chunked, in place of the plain ones;
-// with mode set (r.probe) the probe kernel chooses between the two and
-// writes its choice to *mode.  Returns whether it did (else the counts are
+// with mode set (r.probe; *mode starts at 1) the probe kernel chooses between
+// the two and writes its choice to *mode.  Returns whether it did (else the counts are
 // per chunk exactly when chunked is set).
 bool launch_histograms(const uint32_t *keys, uint32_t n, const Resolved &r, uint32_t *hist, hipStream_t stream,
                        bool hist_zeroed, bool chunked, uint32_t *mode) {
     const HistArgs ha = hist_args(r, n, chunked);
     if (!hist_zeroed) {
         hipLaunchKernelGGL(k_fill_zero, dim3(16), dim3(256), 0, stream, hist,
-                           static_cast<size_t>(r.num_passes) * kMaxRadix);
+                           static_cast<size_t>(r.num_passes) * kMaxRadix, nullptr);
         prof_mark(stream, RT_KIND_FILL);
     }
     const HistArgs hp = hist_args(r, n, false);
     const bool probe = chunked && mode != nullptr && sample_decides(r, n);
     if (probe) {
-        hipLaunchKernelGGL(k_chunk_probe<1024>, dim3(1), dim3(1024), 0, stream, keys, n, ha, mode);
+        hipLaunchKernelGGL(k_chunk_probe<1024>, dim3(ha.num_passes), dim3(1024), 0, stream, keys, n, ha, mode);
         prof_mark(stream, RT_KIND_PROBE);
         switch (hist_copies(ha.total_bins)) {
             case 16: launch_histogram_auto_copies<16>(keys, n, hp, ha, mode, hist, stream); break;
@@ -489,10 +489,10 @@ void launch_sort(uint32_t *keys, uint32_t *vals, uint32_t n, const Resolved &r, 
     // the histogram counters and the lookback words of every pass ("not
     // published") start at zero: one fill over both (adjacent in the layout)
     const size_t fill_words = (L.status + L.status_bytes - L.hist) / 4;
-    hipLaunchKernelGGL(k_fill_zero, dim3(grid_for(fill_words, 256 * 16, 4096)), dim3(256), 0, stream, hist,
-                       fill_words);
-    prof_mark(stream, RT_KIND_FILL);
     uint32_t *mode = ctr + kMaxPasses + 1 + kMaxPasses * kChunks;
+    hipLaunchKernelGGL(k_fill_zero, dim3(grid_for(fill_words, 256 * 16, 4096)), dim3(256), 0, stream, hist,
+                       fill_words, mode);
+    prof_mark(stream, RT_KIND_FILL);
     // fused: the upfront read counts only the first pass's digit; each pass
     // counts the next one's
     Resolved rh = r;
@@ -742,8 +742,9 @@ extern "C" rt_status rt_chunk_decision(const uint32_t *keys, size_t n, int with_
     if (s != RT_OK) return s;
     prof_begin(stream);
     if (n >= 2 && sample_decides(r, static_cast<uint32_t>(n))) {
-        hipLaunchKernelGGL(k_chunk_probe<1024>, dim3(1), dim3(1024), 0, stream, keys, static_cast<uint32_t>(n),
-                           hist_args(r, n, true), mode);
+        hipLaunchKernelGGL(k_set_word, dim3(1), dim3(64), 0, stream, mode, 1u);
+        hipLaunchKernelGGL(k_chunk_probe<1024>, dim3(r.num_passes), dim3(1024), 0, stream, keys,
+                           static_cast<uint32_t>(n), hist_args(r, n, true), mode);
         prof_mark(stream, RT_KIND_PROBE);
     } else {
         hipLaunchKernelGGL(k_set_word, dim3(1), dim3(64), 0, stream, mode, (n >= 2 && r.chunked) ? 1u : 0u);

@@ -281,19 +281,19 @@ void launch_sort64(uint64_t *keys, uint32_t *vals, uint32_t vw, uint32_t n, cons
     prof_begin(stream);
     // histogram counters and lookback words, adjacent in the layout
     const size_t fill_words = (L.status + L.status_bytes - L.hist) / 4;
+    uint32_t *mode = ctr + kMaxPasses + 1 + kMaxPasses * kChunks;
     hipLaunchKernelGGL(k_fill_zero, dim3(grid_for(fill_words, 256 * 16, 4096)), dim3(256), 0, stream, hist,
-                       fill_words);
+                       fill_words, mode);
     prof_mark(stream, RT_KIND_FILL);
 
     const HistArgs ha = hist_args(r, n, false);
-    uint32_t *mode = ctr + kMaxPasses + 1 + kMaxPasses * kChunks;
     uint32_t pos_bound[kChunks + 1] = {};
     if (r.chunked) pos_bounds(n, r, pos_bound);
     bool probed = false;
     if (r.chunked) {
         const HistArgs hc = hist_args(r, n, true);
         if (sample_decides64(r, n)) {
-            hipLaunchKernelGGL((k_chunk_probe<1024, uint64_t>), dim3(1), dim3(1024), 0, stream, keys, n, hc, mode);
+            hipLaunchKernelGGL((k_chunk_probe<1024, uint64_t>), dim3(hc.num_passes), dim3(1024), 0, stream, keys, n, hc, mode);
             prof_mark(stream, RT_KIND_PROBE);
             switch (copies64(hc.total_bins)) {
                 case 8: launch_histogram64_auto<8>(keys, n, ha, hc, mode, hist, stream); break;
@@ -458,7 +458,8 @@ extern "C" rt_status rt_chunk_decision64(const uint64_t *keys, size_t n, uint32_
     chunk_mode64(n, &r);
     prof_begin(stream);
     if (n >= 2 && sample_decides64(r, static_cast<uint32_t>(n))) {
-        hipLaunchKernelGGL((k_chunk_probe<1024, uint64_t>), dim3(1), dim3(1024), 0, stream, keys,
+        hipLaunchKernelGGL(k_set_word, dim3(1), dim3(64), 0, stream, mode, 1u);
+        hipLaunchKernelGGL((k_chunk_probe<1024, uint64_t>), dim3(r.num_passes), dim3(1024), 0, stream, keys,
                            static_cast<uint32_t>(n), hist_args(r, n, true), mode);
         prof_mark(stream, RT_KIND_PROBE);
     } else {
