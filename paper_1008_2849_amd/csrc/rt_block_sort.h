@@ -34,7 +34,8 @@ namespace rt {
 // the fullest bin holds 6 to 8 items.
 constexpr uint32_t kBinLimit = 24;
 constexpr int kSlotGroup = 4;  // slots whose LDS reads go out together
-constexpr int kCrowded = 8;  // of 64 sampled keys in one of 256 cells
+constexpr int kCrowded = 8;    // of 64 sampled keys in one of 256 cells
+constexpr uint32_t kDense = 8;  // items per value of a small key range
 
 constexpr int floor_log2(int x) { return x <= 1 ? 0 : 1 + floor_log2(x / 2); }
 constexpr int ceil_log2(int x) { return x <= 1 ? 0 : 1 + floor_log2(x - 1); }
@@ -267,6 +268,8 @@ __device__ __forceinline__ void block_sort(const Source &src, uint32_t n, const 
         return;
     }
     const uint32_t shift = bits > static_cast<uint32_t>(L::LOG_NB) ? bits - L::LOG_NB : 0u;
+    // few values, each many times: the bins would overflow
+    if (bits < 16u && (n >> bits) >= kDense) crowded = true;
     V val[VALS ? IPT : 1];
 
     // ---- bin sort, if an item's word holds its bits below the bin and its index

@@ -222,14 +222,27 @@ void launch_split(uint32_t *keys, uint32_t *vals, uint32_t n, uint32_t *tk, uint
                   hipStream_t stream);
 void launch_split64(uint64_t *keys, uint32_t *vals, uint32_t value_words, uint32_t n, uint64_t *tk, uint32_t *tv,
                     char *scratch, hipStream_t stream);
-// The two-pass splitter sort (rt_split_seg_kernels.h), for larger arrays of
-// fewer than 2^30 items.  scratch as above, split_large_scratch_bytes() long.
-constexpr size_t kSplitLargeMin32 = static_cast<size_t>(1) << 20;  // four digit passes are as fast below
+// The splitter passes over a large array of 64-bit keys
+// (rt_split_seg_kernels.h): one pass and leaves up to kSplitOneMax64, two and
+// leaves from kSplitTwoMin64 to kSplitLargeEnd.  scratch as above,
+// split_large_scratch_bytes64() long.  us, the digit passes against these,
+// pairs with 4-byte values:
+//
+//             spread keys  ANDs of two   below 2^32   below 2^20
+//   600000     156    83    154   145    101    82    86    81
+//   2^20       183   100    182   194    115    99    95    99   (one pass)
+//   2^21       227   154    223   292                117   142   (two)
+//   2^22       367   189    365   308    221   209   179   193
+//   2^24       998   508    981   878                461   510
+//   2^26      3311  1814   3414  3096   2338  1830  1577  1814
+//
+// The lines are where keys of all eight digits gain whatever their
+// distribution.  Two passes do not gain where the digit passes skip five of
+// eight, which only a pass over the keys can tell.
+constexpr size_t kSplitOneMax64 = 256 * 3650;  // (full leaves)
+constexpr size_t kSplitTwoMin64 = static_cast<size_t>(1) << 22;
 constexpr size_t kSplitLargeEnd = static_cast<size_t>(1) << 30;
-size_t split_large_scratch_bytes(size_t n, bool vals);
 size_t split_large_scratch_bytes64(size_t n, uint32_t value_words);
-void launch_split_large(uint32_t *keys, uint32_t *vals, uint32_t n, uint32_t *tk, uint32_t *tv, char *scratch,
-                        hipStream_t stream);
 void launch_split_large64(uint64_t *keys, uint32_t *vals, uint32_t value_words, uint32_t n, uint64_t *tk, uint32_t *tv,
                           char *scratch, hipStream_t stream);
 // Whether cfg leaves the method to the library: no digits, shape or flags

@@ -570,23 +570,14 @@ static rt_status check_ranges(const uint32_t *keys, const uint32_t *vals, size_t
     return RT_OK;
 }
 
-// Takes a splitter sort where the method is the library's to choose and the
-// size suits it.  Both use the first temporary; the tables lie below it, or
-// where the digit passes would have the second temporary.
+// Takes the splitter sort where the method is the library's to choose and the
+// size suits it: the first temporary is its temporary, the tables lie below.
 static bool try_split(uint32_t *keys, uint32_t *vals, size_t n, const rt_config *cfg, const Layout &L, void *ws,
                       hipStream_t stream) {
-    if (!default_method(cfg)) return false;
+    if (!default_method(cfg) || n > kSplitMax32 || split_scratch_bytes(n, sizeof(uint32_t)) > L.t1k) return false;
     char *w = static_cast<char *>(ws);
-    uint32_t *tk = reinterpret_cast<uint32_t *>(w + L.t1k);
-    uint32_t *tv = vals ? reinterpret_cast<uint32_t *>(w + L.t1v) : nullptr;
-    if (n <= kSplitMax32) {
-        if (split_scratch_bytes(n, sizeof(uint32_t)) > L.t1k) return false;
-        launch_split(keys, vals, static_cast<uint32_t>(n), tk, tv, w, stream);
-        return true;
-    }
-    if (n < kSplitLargeMin32 || n >= kSplitLargeEnd || L.t2k == 0 || split_large_scratch_bytes(n, vals != nullptr) > L.total - L.t2k)
-        return false;
-    launch_split_large(keys, vals, static_cast<uint32_t>(n), tk, tv, w + L.t2k, stream);
+    launch_split(keys, vals, static_cast<uint32_t>(n), reinterpret_cast<uint32_t *>(w + L.t1k),
+                 vals ? reinterpret_cast<uint32_t *>(w + L.t1v) : nullptr, w, stream);
     return true;
 }
 

@@ -39,8 +39,10 @@ inline SplitTables split_tables(char *ws, const SegLayout &L) {
     t.chunks = reinterpret_cast<uint32_t *>(ws + L.status + L.status_pass);
     t.lists = reinterpret_cast<LeafLists *>(ws + L.status + 2 * L.status_pass);
     t.leaves = reinterpret_cast<SplitLeaf *>(ws + L.status + 2 * L.status_pass + 256);
-    // a segment of n items has at most n / kLeafAim + 1 buckets
-    t.leaf_capacity = static_cast<uint32_t>(L.capacity / kLeafAim + L.large_capacity);
+    // a segment of n items has at most n / leaf_aim + 1 buckets; one that is
+    // the whole array (32 tiles or more, so there is room) may have kBuckets
+    t.leaf_capacity = static_cast<uint32_t>(L.capacity / leaf_aim<uint64_t>() + L.large_capacity);
+    if (L.max_tiles >= 32) t.leaf_capacity = std::max<uint32_t>(t.leaf_capacity, kBuckets);
     return t;
 }
 static_assert(sizeof(LeafLists) <= 256, "the lists' header");
@@ -49,6 +51,11 @@ static_assert(sizeof(LeafLists) <= 256, "the lists' header");
 // one listed segment), or leaves, sorted from tk/tv into k/v or in place in
 // tk/tv.
 enum class SplitEnd { kNextPass, kLeavesBack, kLeavesInPlace };
+
+// Up to here the first of two passes samples 2048 keys of the array, not 8192:
+// its buckets may differ by half, as the second pass cuts them by their own
+// sizes and they stay far below the 2^20 items it makes full leaves of.
+constexpr size_t kSampleFew = static_cast<size_t>(1) << 26;
 
 // arrays: those the segments lie in.
 // One splitter pass over the tiled list of a SegLayout whose descriptors,
@@ -61,12 +68,17 @@ void launch_split_pass(const SegPointers &P, const SegLayout &L, uint32_t list_s
     const uint32_t *list = P.lists + static_cast<size_t>(kSegLarge) * list_stride;
     const uint32_t segs = std::max<uint32_t>(1u, L.large_capacity);
     const bool leaves = end != SplitEnd::kNextPass;
-    if (leaves)
+    // (a whole array's buckets may all be used, whatever its size)
+    const uint32_t fixed = sub != nullptr && segs == 1 ? static_cast<uint32_t>(kBuckets) : 0u;
+    if (fixed == 0u)
         hipLaunchKernelGGL((k_split_sample<256, 8, K>), dim3(split_grid(segs, cus * 6)), dim3(256), 0, stream, P.descs,
-                           list, P.header, P.first_tile, P.tile_seg, t.rows, 0u);
+                           list, P.header, P.first_tile, P.tile_seg, t.rows, fixed);
+    else if (!leaves && L.capacity <= kSampleFew)
+        hipLaunchKernelGGL((k_split_sample<512, 4, K>), dim3(segs), dim3(512), 0, stream, P.descs, list, P.header,
+                           P.first_tile, P.tile_seg, t.rows, fixed);
     else
         hipLaunchKernelGGL((k_split_sample<1024, 8, K>), dim3(segs), dim3(1024), 0, stream, P.descs, list, P.header,
-                           P.first_tile, P.tile_seg, t.rows, static_cast<uint32_t>(kBuckets));
+                           P.first_tile, P.tile_seg, t.rows, fixed);
     prof_mark(stream, RT_KIND_PROBE);
     const uint32_t tiles = (L.max_tiles + kChunks - 1) / kChunks * kChunks;
     hipLaunchKernelGGL((k_split_tile_count<512, K>), dim3(tiles), dim3(512), 0, stream, P.tile_seg, P.header, t.rows,
@@ -85,7 +97,7 @@ void launch_split_pass(const SegPointers &P, const SegLayout &L, uint32_t list_s
     prof_mark(stream, RT_KIND_PASS);
     if (!leaves) return;
     const int in_place = end == SplitEnd::kLeavesInPlace ? 1 : 0;
-    hipLaunchKernelGGL((k_split_leaves<256, 17, K, V, VALS>), dim3(split_grid(t.leaf_capacity, cus * 4)), dim3(256), 0,
+    hipLaunchKernelGGL((k_split_leaves<256, leaf_ipt<K>(), K, V, VALS>), dim3(split_grid(t.leaf_capacity, cus * 4)), dim3(256), 0,
                        stream, arrays, t.lists, t.leaves, in_place);
     hipLaunchKernelGGL((k_split_long_leaves<1024, sizeof(K) == 4 ? 16 : 8, K, V, VALS>), dim3(cus), dim3(1024), 0,
                        stream, arrays, t.lists, t.leaves, in_place);
@@ -112,17 +124,21 @@ inline SplitSortLayout make_split_sort_layout(size_t n, int block, int ipt) {
     return S;
 }
 
-// Sorts n items of keys/vals in place (n >= 2, n < 2^30).
+// Sorts n items of keys/vals in place (2 <= n < 2^30): one pass where its
+// buckets are leaves as they come.
 template <typename K, typename V, bool VALS>
 void launch_split_sort(K *keys, V *vals, uint32_t n, K *tk, V *tv, const SplitSortLayout &S, char *ws,
                        hipStream_t stream) {
     uint32_t *off = reinterpret_cast<uint32_t *>(ws + S.offsets);
     char *seg = ws + S.seg;
+    const int passes = n <= kBuckets * leaf_aim<K>() ? 1 : 2;
     prof_begin(stream);
-    for (int pass = 0; pass < 2; ++pass) {
+    for (int pass = 0; pass < passes; ++pass) {
         const SegLayout &L = pass == 0 ? S.first : S.second;
         const SegPointers P = seg_pointers(seg, L);
         const uint32_t num = pass == 0 ? 1u : static_cast<uint32_t>(kBuckets);
+        const SplitEnd end = pass == 1 ? SplitEnd::kLeavesInPlace
+                             : passes == 1 ? SplitEnd::kLeavesBack : SplitEnd::kNextPass;
         K *a_k = pass == 0 ? keys : tk, *b_k = pass == 0 ? tk : keys;
         V *a_v = pass == 0 ? vals : tv, *b_v = pass == 0 ? tv : vals;
         const SplitTables t = split_tables(seg, L);
@@ -131,8 +147,8 @@ void launch_split_sort(K *keys, V *vals, uint32_t n, K *tk, V *tv, const SplitSo
                            P.lists + static_cast<size_t>(kSegLarge) * num, P.first_tile, P.header, t.lists,
                            t.leaf_capacity);
         prof_mark(stream, RT_KIND_SEGMENTED);
-        launch_split_pass<SplitTile<K, V, VALS>, K, V, VALS>(P, L, num, pass == 0 ? SplitEnd::kNextPass : SplitEnd::kLeavesInPlace, off,
-                                      LeafArrays<K, V>{a_k, a_v, b_k, b_v}, seg, stream);
+        launch_split_pass<SplitTile<K, V, VALS>, K, V, VALS>(P, L, num, end, off, LeafArrays<K, V>{a_k, a_v, b_k, b_v},
+                                                             seg, stream);
     }
 }
 

@@ -54,9 +54,13 @@ struct LeafArrays {
     K *tk;
     V *tv;
 };
-// Leaf classes (kLeafClasses): what 256 x 17 blocks hold, what the largest
-// blocks hold, longer ones.
-constexpr uint32_t kLeafSmall = 256 * 17;
+// Leaf classes (kLeafClasses): what 256-thread blocks hold (17 items a thread;
+// 16 of 64-bit keys, so that three such blocks fit a CU's LDS), what the
+// largest blocks hold, longer ones.
+template <typename K>
+constexpr int leaf_ipt() {
+    return sizeof(K) == 4 ? 17 : 16;
+}
 template <typename K>
 constexpr uint32_t leaf_max() {
     return sizeof(K) == 4 ? 1024u * 16u : 1024u * 8u;
@@ -67,10 +71,14 @@ constexpr uint32_t leaf_max() {
 // to segments of 2^20 items.  Fuller leaves cost less per item (a leaf's bins
 // are scanned whole): 2^27 pairs in segments of up to 2^20 took 577 us in
 // leaves of 1536 to 3072 items.
-constexpr uint32_t kLeafAim = 3900;
+template <typename K>
+constexpr uint32_t leaf_aim() {
+    return sizeof(K) == 4 ? 3900u : 3650u;
+}
 
+template <typename K>
 __device__ __forceinline__ uint32_t split_bucket_count(uint32_t n) {
-    return min((n + kLeafAim - 1u) / kLeafAim, static_cast<uint32_t>(kBuckets));
+    return min((n + leaf_aim<K>() - 1u) / leaf_aim<K>(), static_cast<uint32_t>(kBuckets));
 }
 
 // Buckets of a segment's keys, held in a block.
@@ -121,18 +129,19 @@ struct SegSample {
     }
     __device__ __forceinline__ uint32_t val(uint32_t, uint32_t = 0) const { return 0u; }
 };
-template <typename K>
+// Takes the quantiles of the sorted sample, every EVERYth key and the last.
+template <typename K, uint32_t EVERY>
 struct QuantileSink {
     K *picked;
-    K *ends;
+    K *sorted;
     uint32_t buckets, m;
     __device__ __forceinline__ void put(uint32_t base, uint32_t i, K key, uint32_t) const {
         i += base;
         // the first key to complete q + 1 of the buckets' equal shares of m
         const uint32_t q = (i + 1u) * buckets / m;
         if (q != i * buckets / m && q < buckets) picked[q - 1u] = key;
-        if (i == 0) ends[0] = key;
-        if (i == m - 1u) ends[1] = key;
+        if (i % EVERY == 0) sorted[i / EVERY] = key;
+        if (i == m - 1u) sorted[m / EVERY] = key;
     }
 };
 
@@ -153,7 +162,8 @@ __global__ __launch_bounds__(BLOCK) void k_split_sample(const SegDesc *__restric
     constexpr uint32_t m = BLOCK * SIPT;
     __shared__ BlockSortLds<BLOCK, SIPT, K, uint32_t, false> sort;
     __shared__ K picked[kBuckets];
-    __shared__ K ends[2];
+    constexpr uint32_t EVERY = m * sizeof(K) > 32768 ? 2 : 1;  // (64 KB of LDS more would be too much)
+    __shared__ K sorted[m / EVERY + 1];
     __shared__ uint32_t hits[kBuckets];
     __shared__ SplitSeg seg;
     const uint32_t tid = threadIdx.x;
@@ -162,7 +172,8 @@ __global__ __launch_bounds__(BLOCK) void k_split_sample(const SegDesc *__restric
         const SegDesc d = descs[list[e]];
         const uint32_t n = d.n;
         char *row = rows + static_cast<size_t>(d.row) * kSplitRowBytes;
-        const uint32_t buckets = fixed_buckets ? fixed_buckets : split_bucket_count(n);
+        // (d.pass set: a segment of one key value)
+        const uint32_t buckets = d.pass ? 1u : fixed_buckets ? fixed_buckets : split_bucket_count<K>(n);
         {
             SegDesc t = d;
             t.pad = first_tile[e];
@@ -176,7 +187,7 @@ __global__ __launch_bounds__(BLOCK) void k_split_sample(const SegDesc *__restric
         }
         __syncthreads();
         if (buckets > 1)
-            block_sort<BLOCK, SIPT, K, uint32_t, false>(src, m, QuantileSink<K>{picked, ends, buckets, m},
+            block_sort<BLOCK, SIPT, K, uint32_t, false>(src, m, QuantileSink<K, EVERY>{picked, sorted, buckets, m},
                                                         false, sort);
         __syncthreads();
         if (tid == 0) {
@@ -187,14 +198,14 @@ __global__ __launch_bounds__(BLOCK) void k_split_sample(const SegDesc *__restric
             seg.pad[0] = seg.pad[1] = 0u;
             if (buckets > 1) {
                 // the sampled range, widened by a sample's mean distance
-                const uint64_t a = ends[0], b = ends[1], top = ~K(0);
+                const uint64_t a = sorted[0], b = sorted[m / EVERY], top = ~K(0);
                 const uint64_t w = (b - a) / m;
                 const uint64_t lo = a - min(a, w), hi = b + min(top - b, w);
                 const uint32_t bits = key_bits_of(hi - lo);
                 seg.shift = bits > 32u ? bits - 32u : 0u;
                 const uint64_t span = ((hi - lo) >> seg.shift) + 1u;
                 seg.lo = lo;
-                seg.linear = span >= (1u << 16) ? 1u : 0u;
+                seg.linear = span >= 16u * buckets ? 1u : 0u;  // else a stretch is a few values, and uneven
                 seg.scale = seg.linear ? static_cast<uint32_t>((static_cast<uint64_t>(buckets) << 32) / span) : 0u;
             }
         }
@@ -205,10 +216,10 @@ __global__ __launch_bounds__(BLOCK) void k_split_sample(const SegDesc *__restric
             f.scale = seg.scale;
             f.shift = seg.shift;
             f.last = buckets - 1u;
-            for (uint32_t i = tid; i < m; i += BLOCK) atomicAdd(&hits[f.stretch(src.key(i))], 1u);
+            for (uint32_t i = tid; i < m / EVERY; i += BLOCK) atomicAdd(&hits[f.stretch(sorted[i])], 1u);
             __syncthreads();
             // a share of mean s: 6 standard deviations, s + 6 sqrt(s)
-            const uint32_t s = m / buckets;
+            const uint32_t s = m / EVERY / buckets;
             if (tid < buckets && hits[tid] > s && (hits[tid] - s) * (hits[tid] - s) > 36u * s) seg.linear = 0u;
             __syncthreads();
         }
@@ -248,6 +259,11 @@ __global__ __launch_bounds__(BLOCK) void k_split_tile_count(const SegDesc *__res
     const uint32_t start = (tile - d.pad) * tile_items;
     const uint32_t valid = min(tile_items, d.n - start);
     const K *src = reinterpret_cast<const K *>(d.k) + start;
+    if (reinterpret_cast<const SplitSeg *>(rows + static_cast<size_t>(d.row) * kSplitRowBytes + kSplitSegAt)->buckets == 1u) {
+        for (uint32_t i = tid; i < static_cast<uint32_t>(kBuckets); i += BLOCK)
+            table[static_cast<size_t>(tile) * kBuckets + i] = i == 0 ? valid : 0u;
+        return;
+    }
     // the first keys are on their way while the splitters are read
     K k[U];
 #pragma unroll
@@ -347,23 +363,26 @@ static __global__ __launch_bounds__(1024) void k_split_scan(const uint32_t *__re
 
 // Per listed segment: its chunks' totals become prefix sums, its buckets'
 // totals go to its row, and where the buckets start: sub set (one segment):
-// to sub[0..kBuckets], the segments of the next pass; lists set: a leaf per
+// to sub[0..kBuckets], the segments of the next pass, and a bit for each that
+// holds one key value, from sub[kSubOnes]; lists set: a leaf per
 // bucket that is not in order as it stands (of every bucket, if `all`: the
 // leaves go to other arrays) to the list of its size.
+constexpr uint32_t kSubOnes = kBuckets + 4;
 template <typename K>
 __global__ __launch_bounds__(256) void k_split_starts(const SegDesc *__restrict__ descs,
                                                       const uint32_t *__restrict__ list,
-                                                      const SegHeader *__restrict__ h,
+                                                      SegHeader *__restrict__ h,
                                                       const uint32_t *__restrict__ first_tile, char *__restrict__ rows,
                                                       uint32_t *__restrict__ chunks, uint32_t *__restrict__ sub,
                                                       const K *k0, const K *tk0, LeafLists *__restrict__ lists,
                                                       SplitLeaf *__restrict__ leaves, uint32_t all) {
     __shared__ uint32_t s_wsum[4];
+    __shared__ uint32_t all_one;
     const uint32_t tid = threadIdx.x, lane = tid & 63u;
     const uint32_t count = h->count[kSegLarge];
+    if (tid == 0) all_one = 0u;
     for (uint32_t e = blockIdx.x; e < count; e += gridDim.x) {
-        const uint32_t s = list[e];
-        const SegDesc d = descs[s];
+        const SegDesc d = descs[list[e]];
         char *row = rows + static_cast<size_t>(d.row) * kSplitRowBytes;
         const uint32_t f = first_tile[e], tiles = first_tile[e + 1] - f;
         uint32_t c = 0;
@@ -375,22 +394,32 @@ __global__ __launch_bounds__(256) void k_split_starts(const SegDesc *__restrict_
         }
         reinterpret_cast<uint32_t *>(row)[tid] = c;
         const uint32_t start = block_exclusive_sum<256>(c, s_wsum);
+        const SplitSeg *seg = reinterpret_cast<const SplitSeg *>(row + kSplitSegAt);
+        const K *split = reinterpret_cast<const K *>(row + kSplittersAt);
+        uint32_t one = d.pass;  // the bucket holds one key value
+        if (!seg->linear && tid > 0)
+            one = tid + 1u < seg->buckets ? (static_cast<K>(split[tid] - split[tid - 1]) == K(1))
+                                          : (split[tid - 1] == ~K(0));
         if (sub != nullptr) {
-            sub[tid] = start;
-            if (tid == 255) sub[256] = d.n;
+            // one value in all: the segment is in order, nothing is left to do
+            if (one && c == d.n) all_one = 1u;
+            __syncthreads();
+            const bool done = all_one != 0u;
+            sub[tid] = done ? 0u : start;
+            if (tid == 255) sub[256] = done ? 0u : d.n;
+            const uint64_t ones = __builtin_amdgcn_ballot_w64(one != 0u);
+            if (lane == 0) {
+                sub[kSubOnes + tid / 32] = static_cast<uint32_t>(ones);
+                sub[kSubOnes + tid / 32 + 1] = static_cast<uint32_t>(ones >> 32);
+            }
+            if (done && tid == 0) h->total_tiles = 0u;
         }
         if (lists != nullptr) {
-            const SplitSeg *seg = reinterpret_cast<const SplitSeg *>(row + kSplitSegAt);
-            const K *split = reinterpret_cast<const K *>(row + kSplittersAt);
             const uint32_t at_k = static_cast<uint32_t>(reinterpret_cast<const K *>(d.k) - k0);
             const uint32_t at_tk = static_cast<uint32_t>(reinterpret_cast<const K *>(d.tk) - tk0);
-            uint32_t one = 0;  // the bucket holds one key value
-            if (!seg->linear && tid > 0)
-                one = tid + 1u < seg->buckets ? (static_cast<K>(split[tid] - split[tid - 1]) == K(1))
-                                              : (split[tid - 1] == ~K(0));
             int q = -1;
             if (c >= (all ? 1u : 2u) && (all || !one)) {  // (in place, one value is in order already)
-                q = c <= kLeafSmall ? 0 : c <= leaf_max<K>() ? 1 : 2;
+                q = c <= 256u * leaf_ipt<K>() ? 0 : c <= leaf_max<K>() ? 1 : 2;
             }
 #pragma unroll
             for (int i = 0; i < kLeafClasses; ++i) {
@@ -444,6 +473,13 @@ __global__ __launch_bounds__(BLOCK) void k_split_tile_scatter(const SegDesc *__r
     const V *src_v = reinterpret_cast<const V *>(d.v) + (VALS ? item0 : 0u);
     K *dst_k = reinterpret_cast<K *>(d.tk);
     V *dst_v = reinterpret_cast<V *>(d.tv);
+    if (reinterpret_cast<const SplitSeg *>(rows + static_cast<size_t>(d.row) * kSplitRowBytes + kSplitSegAt)->buckets == 1u) {
+        for (uint32_t i = tid; i < valid; i += BLOCK) {  // one bucket: a copy
+            dst_k[item0 + i] = src_k[i];
+            if constexpr (VALS) dst_v[item0 + i] = src_v[i];
+        }
+        return;
+    }
 
     K key[IPT];
     V val[VALS ? IPT : 1];
@@ -599,7 +635,7 @@ __global__ __launch_bounds__(BLOCK) void k_split_tile_scatter(const SegDesc *__r
 // wrote into the others, or in place.  The next leaf's bounds are read while
 // this one is sorted.
 template <int BLOCK, int IPT, typename K, typename V, bool VALS>
-__global__ __launch_bounds__(BLOCK, sizeof(K) == 4 ? 4 : 2) void k_split_leaves(LeafArrays<K, V> a,
+__global__ __launch_bounds__(BLOCK, sizeof(K) == 4 ? 4 : 3) void k_split_leaves(LeafArrays<K, V> a,
                                                                                const LeafLists *__restrict__ lists,
                                                                                const SplitLeaf *__restrict__ leaves,
                                                                                int in_place) {
@@ -662,7 +698,7 @@ __global__ __launch_bounds__(BLOCK) void k_split_long_leaves(LeafArrays<K, V> a,
 }
 
 // The segments of a pass of the two-pass sort, in one block: offsets off[0..
-// count] (count <= kBuckets; one segment of n items if off is NULL) become
+// count] (as k_split_starts leaves them; one segment of n items if NULL) become
 // descriptors, the tiled list, first tiles and the header, as k_seg_classify
 // and k_seg_tiles make them.  A one-item segment is copied to tk/tv here.
 template <typename K, typename V, bool VALS>
@@ -690,7 +726,7 @@ __global__ __launch_bounds__(256) void k_split_segments(const uint32_t *__restri
         d.tk = reinterpret_cast<uint32_t *>(tk + a);
         d.tv = VALS ? reinterpret_cast<uint32_t *>(tv + a) : nullptr;
         d.n = len;
-        d.pass = 0;
+        d.pass = off == nullptr ? 0u : (off[kSubOnes + s / 32] >> (s % 32)) & 1u;
         d.row = at;
         d.pad = t0;
         descs[at] = d;

@@ -1,7 +1,7 @@
-"""The two-pass splitter sort (arrays above 2^20 items with 32-bit keys, 2^19
-with 64-bit keys) against a stable host sort: tile and leaf edges, repeated
-keys (long buckets of one value), and keys that both passes' samples miss (a
-leaf no LDS holds)."""
+"""Arrays above 2^20 items (32-bit keys) and 2^19 items (64-bit keys, which take
+one splitter pass up to 934400 items and two from 2^22) against a stable host
+sort: tile and leaf edges, repeated keys (long buckets of one value), and keys
+that the passes' samples miss (a leaf no LDS holds)."""
 import numpy as np
 import pytest
 
@@ -13,23 +13,25 @@ from test_gpu_split import keys_of, sample_positions
 pytestmark = pytest.mark.gpu
 
 
-def missed_twice(n, seed, dtype):
-    """Nearly all keys in [2^30, 2^30 + 2^12), a range that no sampled key of
-    the first pass falls in, nor of the second, whose sample is of the one
-    bucket those keys make."""
-    m = 8192
-    u = inputs.uniform_keys(n, seed).astype(dtype)
-    top = dtype(np.iinfo(dtype).max)
-    k = u % dtype(1 << 12) + dtype(1 << 30)
+def missed(n, seed, m, twice):
+    """Nearly all keys in [2^30, 2^30 + 2^12), a range that none of the m keys
+    sampled first falls in, nor (twice) those of the second pass, whose sample
+    is of the one bucket those keys make."""
+    u = inputs.uniform_keys(n, seed).astype(np.uint64)
+    top = np.uint64((1 << 64) - 1)
+    span = np.uint64(1 << 28)
+    k = u % np.uint64(1 << 12) + np.uint64(1 << 30)
     at = sample_positions(n, m)
-    k[at] = np.where(np.arange(m) % 2 == 0, u[at] % dtype(1 << 28), top - u[at] % dtype(1 << 28))
+    k[at] = np.where(np.arange(m) % 2 == 0, u[at] % span, top - u[at] % span)
+    if not twice:
+        return k
     # the bucket those keys fall in, in input order: between two neighbours of
     # the sample's every (m / 256)-th key
     ordered = np.sort(k[at])
     rest = np.nonzero((k >= ordered[m // 2 - 1]) & (k < ordered[m // 2 + m // 256 - 1]))[0]
-    again = rest[np.unique(sample_positions(len(rest), 2048 if len(rest) < 1 << 19 else 4096))]
+    again = rest[np.unique(sample_positions(len(rest), 2048))]
     low = np.arange(len(again)) % 2 == 0
-    k[again] = np.where(low, dtype(1 << 29) + u[again] % dtype(1 << 28), dtype(1 << 31) - u[again] % dtype(1 << 28))
+    k[again] = np.where(low, np.uint64(1 << 29) + u[again] % span, np.uint64(1 << 31) - u[again] % span)
     return k
 
 
@@ -52,46 +54,30 @@ def check(keys, vdt, **kw):
 @pytest.mark.parametrize("kind", ["uniform", "sorted", "zipf16", "extremes", "one", "and4"])
 @pytest.mark.parametrize("n", [(1 << 20) + 1, 1_600_003, 1 << 22, 10_000_019])
 def test_large32(kind, n):
-    announce(f"two-pass split {kind} n={n}")
+    announce(f"large {kind} n={n}")
     keys = keys_of(kind, n, 40 + n % 13, np.uint32)
     check(keys, None)
     check(keys, np.int32)
 
 
 @pytest.mark.parametrize("kind", ["uniform", "zipf16", "extremes", "one", "and4"])
-@pytest.mark.parametrize("n", [(1 << 19) + 1, 3_000_017])
+@pytest.mark.parametrize("n", [(1 << 19) + 1, 934_400, 934_401, 3_000_017, 1 << 22, 5_000_011])
 def test_large64(kind, n):
-    announce(f"two-pass split64 {kind} n={n}")
+    announce(f"large64 {kind} n={n}")
     keys = keys_of(kind, n, 50 + n % 13, np.uint64)
     for vdt in (None, np.int32, np.int64):
         check(keys, vdt)
 
 
+@pytest.mark.parametrize("n", [700_001, 2_000_003, (1 << 22) + 3])
 @pytest.mark.parametrize("kind", ["small", "high", "low32"])
-def test_large64_in_some_bytes(kind):
-    announce(f"two-pass split64 {kind}")
-    check(inputs.keys64(kind, 2_000_003, 5), np.int32)
+def test_large64_in_some_bytes(kind, n):
+    announce(f"large64 {kind} n={n}")
+    check(inputs.keys64(kind, n, 5), np.int32)
 
 
-def test_large_with_a_leaf_no_lds_holds():
-    n = (1 << 20) + 4099
-    announce("two-pass split, both samples miss")
-    check(missed_twice(n, 3, np.uint32), np.int32)
-    check(missed_twice(n, 3, np.uint32), None)
-    check(missed_twice(600_011, 4, np.uint64), np.int64)
-
-
-def test_large_slices_and_a_workspace():
-    import torch
-    n = 1_500_001
-    announce("two-pass split of a slice in a caller's workspace")
-    base = inputs.uniform_keys(n + 2, 9)
-    k = torch.from_numpy(base.view(np.int32).copy()).cuda()
-    v = torch.arange(n + 2, dtype=torch.int32, device="cuda")
-    ws = torch.empty(rts.workspace_bytes(n, True), dtype=torch.uint8, device="cuda")
-    rts.sort_ex(k[1:n + 1], v[1:n + 1], None, ws)
-    sync()
-    order = np.argsort(base[1:n + 1], kind="stable") + 1
-    got, gv = k.cpu().numpy().view(np.uint32), v.cpu().numpy()
-    assert np.array_equal(got[1:n + 1], base[order]) and np.array_equal(gv[1:n + 1], order)
-    assert got[0] == base[0] and got[n + 1] == base[n + 1] and gv[0] == 0 and gv[n + 1] == n + 1
+@pytest.mark.parametrize("n,m,twice", [((1 << 19) + 4099, 8192, False), ((1 << 22) + 4099, 2048, True)])
+def test_large_with_a_leaf_no_lds_holds(n, m, twice):
+    announce(f"large64, the samples miss, n={n}")
+    check(missed(n, 3, m, twice), np.int32)
+    check(missed(n, 3, m, twice), None)
