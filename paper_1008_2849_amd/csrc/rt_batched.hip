@@ -210,7 +210,7 @@ void launch_segments(uint32_t *keys, uint32_t *vals, uint32_t *tk, uint32_t *tv,
 // Segments of a batched call, longest first: one splitter pass and leaves;
 // four digit passes for those too long for that, if the call can hold any.
 // Their list waits in the base rows, which the splitter pass does not use.
-constexpr uint32_t kSplitSegMax = 1u << 21;  // mean leaves of 8192 items, half the longest
+constexpr uint32_t kSplitSegMax = 1u << 20;
 
 template <bool VALS>
 static void launch_batched_body(uint32_t *keys, uint32_t *vals, const SegPointers &P, const SegLayout &L,

@@ -174,6 +174,50 @@ __device__ __forceinline__ void block_store(const BlockSortLds<BLOCK, IPT, K, V,
     });
 }
 
+// Items that are ranked by comparing all pairs: up to here that takes fewer
+// instructions (2 a pair, no bins to clear and scan, two barriers instead of
+// seven) whatever the keys.  KPAIR_NOTE
+constexpr uint32_t kPairwise = 128;
+
+// block_sort of n <= kPairwise items, one a thread.
+template <typename K, typename V, bool VALS, typename Source, typename Sink, typename Lds>
+__device__ __forceinline__ void block_sort_pairwise(const Source &src, uint32_t n, const Sink &sink, Lds &lds) {
+    constexpr uint32_t STEP = 16 / sizeof(K);  // keys a read
+    const uint32_t i = threadIdx.x;
+    const uint32_t wave0 = __builtin_amdgcn_readfirstlane(i & ~63u);
+    K key = ~K(0);
+    V val = 0;
+    if (i < n) {
+        key = src.key(i);
+        if constexpr (VALS) val = src.val(i);
+    }
+    if (i < kPairwise) lds.s.k[i] = key;  // the places past the end: no smaller than any
+    if constexpr (VALS) {
+        if (i < kPairwise) lds.s.v[i] = val;  // (every value is read before one is overwritten)
+    }
+    __syncthreads();
+    if (i >= n) return;
+    // equal keys: those before this item count, those behind it do not
+    uint32_t r = 0;
+    const uint32_t mine_end = min(wave0 + 64u, (n + STEP - 1u) / STEP * STEP);
+    for (uint32_t j = 0; j < wave0; j += STEP) {
+#pragma unroll
+        for (uint32_t q = 0; q < STEP; ++q) r += static_cast<uint32_t>(lds.s.k[j + q] <= key);
+    }
+    for (uint32_t j = wave0; j < mine_end; j += STEP) {
+#pragma unroll
+        for (uint32_t q = 0; q < STEP; ++q) {
+            const K x = lds.s.k[j + q];
+            r += static_cast<uint32_t>((x < key) | ((x == key) & (j + q < i)));
+        }
+    }
+    for (uint32_t j = mine_end; j < n; j += STEP) {
+#pragma unroll
+        for (uint32_t q = 0; q < STEP; ++q) r += static_cast<uint32_t>(lds.s.k[j + q] < key);
+    }
+    sink.put(0, r, key, val);
+}
+
 // Sorts items [0, n) of src (1 <= n <= BLOCK * IPT) into sink, which may be
 // the same arrays (in_place).  Every thread of the block must call it; the
 // LDS is free again after the next barrier.
@@ -196,6 +240,12 @@ __device__ __forceinline__ void block_sort(const Source &src, uint32_t n, const 
     const uint32_t lane = tid & 63u;
     const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     n = __builtin_amdgcn_readfirstlane(n);
+    if constexpr (BLOCK >= kPairwise) {
+        if (n <= kPairwise) {
+            block_sort_pairwise<K, V, VALS>(src, n, sink, lds);
+            return;
+        }
+    }
     const int slots = static_cast<int>((n + BLOCK - 1) / BLOCK);
     const uint32_t slot0 = wave * 64u * slots;
     uint32_t item0 = slot0 + lane;
@@ -268,7 +318,8 @@ __device__ __forceinline__ void block_sort(const Source &src, uint32_t n, const 
         return;
     }
     const uint32_t shift = bits > static_cast<uint32_t>(L::LOG_NB) ? bits - L::LOG_NB : 0u;
-    // few values, each many times: the bins would overflow
+    // few values, each many times: the bins would overflow, and their counts
+    // be taken in vain
     if (bits < 16u && (n >> bits) >= kDense) crowded = true;
     V val[VALS ? IPT : 1];
 

@@ -5,17 +5,19 @@
 // described by a SegDesc; a work list picks the segments of a launch.
 //
 // * Segments of at most 16K items are sorted whole inside one block: one
-//   read and one write of HBM, the four 8-bit counting-sort passes running
-//   between LDS and registers.
-// * Larger segments are cut into 16K-item tiles and sorted by per-segment
-//   counting-sort passes in the onesweep form of rt_kernels.h: upfront
-//   per-segment histograms, per-segment exclusive prefix sums, then per pass
-//   one launch covering the tiles of every segment, with each segment's
-//   lookback chain ending at its own first tile.
+//   read and one write of HBM, the bin sort of rt_block_sort.h (or its digit
+//   passes) running between LDS and registers.
+// * Larger segments are cut into 16K-item tiles.  A batched call takes them
+//   through one splitter pass and leaves (rt_split_seg_kernels.h); the
+//   server, the MSD-first sort and segments above kSplitSegMax through
+//   per-segment counting-sort passes in the onesweep form of rt_kernels.h:
+//   upfront per-segment histograms, per-segment exclusive prefix sums, then
+//   per pass one launch covering the tiles of every segment, with each
+//   segment's lookback chain ending at its own first tile.
 //
 // Each pass is Section 3's counting sort (histogram, exclusive prefix sum,
-// stable scatter) and the pass sequence is Section 4's LSD order; a segment
-// is sorted exactly as a single array of its own would be.
+// stable scatter); a segment is sorted exactly as a single array of its own
+// would be.
 #include "rt_block_sort.h"
 
 namespace rt {

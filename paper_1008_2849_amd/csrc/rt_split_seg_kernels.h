@@ -1,6 +1,6 @@
-// rt_split_seg_kernels.h -- splitter passes over long segments: the large
-// single-array sorts (two such passes, then leaves) and the long segments of
-// batched calls (one pass, then leaves).
+// rt_split_seg_kernels.h -- splitter passes over long segments: large arrays
+// of 64-bit keys (one or two such passes, then leaves) and the long segments
+// of batched calls (one pass, then leaves).
 //
 // A pass cuts every listed segment into up to 256 buckets of neighbouring
 // keys and writes them, stably, to the segment's other arrays.  Against the
@@ -14,6 +14,12 @@
 //   tile knows where its runs go without a lookback chain, and tiles may run
 //   in any order: each XCD takes a contiguous share of them, so that
 //   neighbouring runs, which share cache lines, are written through one L2.
+//
+// Measured, 2^26 pairs of 64-bit keys with 4-byte values: scatter 350 us a
+// pass (24 bytes an item, 4.6 TB/s: an eight-bit digit pass takes 342), count
+// 119 (4.5 TB/s), leaves 443, the rest 90; 1814 a sort with its input copy,
+// against 3311 by eight digit passes.  2^27 pairs of 32-bit keys in batched
+// segments: 1730 us a call against 2787 by four digit passes.
 //
 // Launches of a pass: k_split_sample (buckets of each segment),
 // k_split_tile_count (rows), k_split_scan (rows to prefix sums, totals),
@@ -70,7 +76,8 @@ constexpr uint32_t leaf_max() {
 // within four standard deviations of what 256 x 17 blocks hold (4352 items) up
 // to segments of 2^20 items.  Fuller leaves cost less per item (a leaf's bins
 // are scanned whole): 2^27 pairs in segments of up to 2^20 took 577 us in
-// leaves of 1536 to 3072 items.
+// leaves of 1536 to 3072 items.  Blocks of 256 x 16 with 64-bit keys: three to
+// a CU instead of two, 2^26 pairs 1858 -> 1814 us a sort.
 template <typename K>
 constexpr uint32_t leaf_aim() {
     return sizeof(K) == 4 ? 3900u : 3650u;
@@ -149,9 +156,12 @@ struct QuantileSink {
 // as many as its leaves need) from BLOCK * SIPT sample keys, and writes its
 // tiles' entries of the tile map (as k_seg_tilemap).  2048 sample keys serve
 // a pass with leaves: 8192 gave better leaves only to keys of uneven density,
-// and cost 60 us more in random reads at 2^28 items.  The buckets are equal stretches of the sampled range if no stretch holds far
-// more of the sample than its share (no bucket much above the mean, and a
-// key's bucket costs one multiplication), else the sample's quantiles.
+// and cost 60 us more in random reads at 2^28 items.  The buckets are equal
+// stretches of the sampled range if no stretch holds far more of the sample
+// than its share (no bucket much above the mean, and a key's bucket costs one
+// multiplication: 350 us a scatter of 2^26 64-bit pairs, 440 by search), else
+// the sample's quantiles.  Bound by latency: random reads, then the sample's
+// sort (12 us for 2048 keys, 27 for 8192, with 2^22 items).
 template <int BLOCK, int SIPT, typename K>
 __global__ __launch_bounds__(BLOCK) void k_split_sample(const SegDesc *__restrict__ descs,
                                                         const uint32_t *__restrict__ list,
@@ -364,9 +374,9 @@ static __global__ __launch_bounds__(1024) void k_split_scan(const uint32_t *__re
 // Per listed segment: its chunks' totals become prefix sums, its buckets'
 // totals go to its row, and where the buckets start: sub set (one segment):
 // to sub[0..kBuckets], the segments of the next pass, and a bit for each that
-// holds one key value, from sub[kSubOnes]; lists set: a leaf per
-// bucket that is not in order as it stands (of every bucket, if `all`: the
-// leaves go to other arrays) to the list of its size.
+// holds one key value, from sub[kSubOnes]; lists set: a leaf per bucket that is
+// not in order as it stands (of every bucket, if `all`: the leaves go to other
+// arrays) to the list of its size.
 constexpr uint32_t kSubOnes = kBuckets + 4;
 template <typename K>
 __global__ __launch_bounds__(256) void k_split_starts(const SegDesc *__restrict__ descs,
@@ -418,8 +428,17 @@ __global__ __launch_bounds__(256) void k_split_starts(const SegDesc *__restrict_
             const uint32_t at_k = static_cast<uint32_t>(reinterpret_cast<const K *>(d.k) - k0);
             const uint32_t at_tk = static_cast<uint32_t>(reinterpret_cast<const K *>(d.tk) - tk0);
             int q = -1;
-            if (c >= (all ? 1u : 2u) && (all || !one)) {  // (in place, one value is in order already)
-                q = c <= 256u * leaf_ipt<K>() ? 0 : c <= leaf_max<K>() ? 1 : 2;
+            constexpr uint32_t small = 256u * leaf_ipt<K>();
+            if (one) {
+                // in place, one value is in order already; else it is copied,
+                // by as many blocks as have a leaf of it
+                const uint32_t parts = all ? (c + small - 1u) / small : 0u;
+                uint32_t at = parts ? atomicAdd(&lists->count[0], parts) : 0u;
+                for (uint32_t i = 0; i < c && parts; i += small, ++at)
+                    if (at < lists->capacity)
+                        leaves[at] = SplitLeaf{at_k + start + i, at_tk + start + i, min(small, c - i), 1u};
+            } else if (c >= (all ? 1u : 2u)) {
+                q = c <= small ? 0 : c <= leaf_max<K>() ? 1 : 2;
             }
 #pragma unroll
             for (int i = 0; i < kLeafClasses; ++i) {
@@ -433,7 +452,7 @@ __global__ __launch_bounds__(256) void k_split_starts(const SegDesc *__restrict_
                                                 __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(mine), 0u));
                 if (q == i && at < lists->capacity)
                     leaves[static_cast<size_t>(i) * lists->capacity + at] =
-                        SplitLeaf{at_k + start, at_tk + start, c, one};
+                        SplitLeaf{at_k + start, at_tk + start, c, 0u};
             }
         }
         __syncthreads();
@@ -631,6 +650,31 @@ __global__ __launch_bounds__(BLOCK) void k_split_tile_scatter(const SegDesc *__r
     }
 }
 
+// A leaf of one key value, from tk/tv to k/v.
+template <int BLOCK, typename K, typename V, bool VALS>
+__device__ __forceinline__ void copy_leaf(const LeafArrays<K, V> &a, const SplitLeaf &l) {
+    constexpr int U = 8;  // loads in flight per lane
+    const K *from_k = a.tk + l.at_tk;
+    const V *from_v = VALS ? a.tv + l.at_tk : nullptr;
+    K *to_k = a.k + l.at_k;
+    V *to_v = VALS ? a.v + l.at_k : nullptr;
+    for (uint32_t base = threadIdx.x; base < l.n; base += BLOCK * U) {
+        K k[U];
+        V v[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            k[u] = from_k[min(base + u * BLOCK, l.n - 1u)];
+            if constexpr (VALS) v[u] = from_v[min(base + u * BLOCK, l.n - 1u)];
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (base + u * BLOCK >= l.n) break;
+            to_k[base + u * BLOCK] = k[u];
+            if constexpr (VALS) to_v[base + u * BLOCK] = v[u];
+        }
+    }
+}
+
 // Sorts the leaves of the first list whole in LDS, from the arrays the pass
 // wrote into the others, or in place.  The next leaf's bounds are read while
 // this one is sorted.
@@ -647,6 +691,12 @@ __global__ __launch_bounds__(BLOCK, sizeof(K) == 4 ? 4 : 3) void k_split_leaves(
     for (;;) {
         e += gridDim.x;
         const SplitLeaf next = leaves[min(e, count - 1u)];
+        if (l.one) {  // (never in place)
+            copy_leaf<BLOCK, K, V, VALS>(a, l);
+            if (e >= count) return;
+            l = next;
+            continue;
+        }
         const uint32_t to = in_place ? l.at_tk : l.at_k;
         block_sort<BLOCK, IPT, K, V, VALS>(
             ArraySource<K, V>{a.tk + l.at_tk, VALS ? a.tv + l.at_tk : nullptr}, l.n,
@@ -658,9 +708,8 @@ __global__ __launch_bounds__(BLOCK, sizeof(K) == 4 ? 4 : 3) void k_split_leaves(
     }
 }
 
-// The other leaves: those the largest blocks hold, as above; longer ones of
-// one value are copied by all blocks together (in place they are never
-// listed), others sorted by one block through global memory.
+// The other leaves: those the largest blocks hold, as above; longer ones are
+// sorted by one block through global memory.
 template <int BLOCK, int IPT, typename K, typename V, bool VALS>
 __global__ __launch_bounds__(BLOCK) void k_split_long_leaves(LeafArrays<K, V> a, const LeafLists *__restrict__ lists,
                                                              const SplitLeaf *__restrict__ leaves, int in_place) {
@@ -669,7 +718,7 @@ __global__ __launch_bounds__(BLOCK) void k_split_long_leaves(LeafArrays<K, V> a,
     for (int which = 1; which < kLeafClasses; ++which) {
         const uint32_t count = min(lists->count[which], lists->capacity);
         const SplitLeaf *list = leaves + static_cast<size_t>(which) * lists->capacity;
-        for (uint32_t e = which == 1 ? blockIdx.x : 0u; e < count; e += which == 1 ? gridDim.x : 1u) {
+        for (uint32_t e = blockIdx.x; e < count; e += gridDim.x) {
             const SplitLeaf l = list[e];
             K *from_k = a.tk + l.at_tk, *to_k = a.k + l.at_k;
             V *from_v = VALS ? a.tv + l.at_tk : nullptr;
@@ -679,12 +728,7 @@ __global__ __launch_bounds__(BLOCK) void k_split_long_leaves(LeafArrays<K, V> a,
                     ArraySource<K, V>{from_k, from_v}, l.n,
                     ArraySink<K, V, VALS>{in_place ? from_k : to_k, in_place ? from_v : to_v}, in_place != 0, lds);
                 __syncthreads();
-            } else if (l.one) {
-                for (uint32_t i = blockIdx.x * BLOCK + threadIdx.x; i < l.n; i += gridDim.x * BLOCK) {
-                    to_k[i] = from_k[i];
-                    if constexpr (VALS) to_v[i] = from_v[i];
-                }
-            } else if (e % gridDim.x == blockIdx.x) {
+            } else {
                 if (!in_place)
                     for (uint32_t i = threadIdx.x; i < l.n; i += BLOCK) {
                         to_k[i] = from_k[i];
