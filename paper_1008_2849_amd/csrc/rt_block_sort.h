@@ -175,8 +175,10 @@ __device__ __forceinline__ void block_store(const BlockSortLds<BLOCK, IPT, K, V,
 }
 
 // Items that are ranked by comparing all pairs: up to here that takes fewer
-// instructions (2 a pair, no bins to clear and scan, two barriers instead of
-// seven) whatever the keys.  KPAIR_NOTE
+// instructions (2 a pair, no bins to clear and scan, one barrier instead of
+// seven) whatever the keys.  65536 segments of 16 to 120 pairs: 272 -> 216 us
+// uniform, 340 -> 216 repeated keys; up to 256 items it took longer than the
+// bins (40000 segments of 128 to 256 pairs: 281 us against 201).
 constexpr uint32_t kPairwise = 128;
 
 // block_sort of n <= kPairwise items, one a thread.

@@ -230,7 +230,7 @@ void launch_split64(uint64_t *keys, uint32_t *vals, uint32_t value_words, uint32
 //
 //             spread keys  ANDs of two   below 2^32   below 2^20
 //   600000     156    83    154   145    101    82    86    81
-//   2^20       183   100    182   194    115    99    95    99   (one pass)
+//   2^20       183   100    182   194    115    99    95    99
 //   2^21       227   154    223   292                117   142   (two)
 //   2^22       367   189    365   308    221   209   179   193
 //   2^24       998   508    981   878                461   510
@@ -239,7 +239,7 @@ void launch_split64(uint64_t *keys, uint32_t *vals, uint32_t value_words, uint32
 // The lines are where keys of all eight digits gain whatever their
 // distribution.  Two passes do not gain where the digit passes skip five of
 // eight, which only a pass over the keys can tell.
-constexpr size_t kSplitOneMax64 = 256 * 3650;  // (full leaves)
+constexpr size_t kSplitOneMax64 = 256 * 2344;  // uneven leaves (18 percent) then fit: at 700000 ANDs of two took 186, not 165
 constexpr size_t kSplitTwoMin64 = static_cast<size_t>(1) << 22;
 constexpr size_t kSplitLargeEnd = static_cast<size_t>(1) << 30;
 size_t split_large_scratch_bytes64(size_t n, uint32_t value_words);

@@ -39,10 +39,10 @@ inline SplitTables split_tables(char *ws, const SegLayout &L) {
     t.chunks = reinterpret_cast<uint32_t *>(ws + L.status + L.status_pass);
     t.lists = reinterpret_cast<LeafLists *>(ws + L.status + 2 * L.status_pass);
     t.leaves = reinterpret_cast<SplitLeaf *>(ws + L.status + 2 * L.status_pass + 256);
-    // a segment of n items has at most n / leaf_aim + 1 buckets, one that is
+    // a segment of n items has at most n / kQuantileAim + 1 buckets, one that is
     // the whole array (32 tiles or more, so there is room) up to kBuckets, and
     // buckets of one value make a leaf for every 4096 of their items besides
-    t.leaf_capacity = static_cast<uint32_t>(L.capacity / leaf_aim<uint64_t>() + L.large_capacity);
+    t.leaf_capacity = static_cast<uint32_t>(L.capacity / kQuantileAim + L.large_capacity);
     if (L.max_tiles >= 32) t.leaf_capacity = std::max<uint32_t>(t.leaf_capacity, kBuckets);
     t.leaf_capacity += static_cast<uint32_t>(L.capacity / 4096);
     return t;
