@@ -30,7 +30,7 @@ def keys32(kind, n, seed):
 
 
 @pytest.mark.parametrize("kind", ["uniform", "one", "ends", "narrow", "cluster", "and4"])
-@pytest.mark.parametrize("n", [2, 3, 63, 64, 257, 1023, 1024, 1025, 4096, 4097, 8191, 8193, 16383, 16384, 16385])
+@pytest.mark.parametrize("n", [2, 3, 63, 64, 65, 127, 128, 129, 257, 1023, 1024, 1025, 4096, 4097, 8191, 8193, 16383, 16384, 16385])
 def test_small_sort(kind, n):
     announce(f"block sort {kind} n={n}")
     keys, vals = keys32(kind, n, 900 + n), inputs.index_values(n)
@@ -44,7 +44,7 @@ def test_small_sort(kind, n):
 
 
 @pytest.mark.parametrize("kind", ["uniform", "small", "high", "low32", "and2"])
-@pytest.mark.parametrize("n", [2, 65, 1024, 1025, 4097, 8191, 8192, 8193])
+@pytest.mark.parametrize("n", [2, 65, 127, 128, 129, 1024, 1025, 4097, 8191, 8192, 8193])
 def test_small_sort64(kind, n):
     import torch
     announce(f"block sort64 {kind} n={n}")
