@@ -285,7 +285,10 @@ __device__ __forceinline__ void block_sort_global(K *a_k, V *a_v, K *b_k, V *b_v
             }
             __syncthreads();
             if (i < m) {
-                const uint32_t p = whist[wave * 256 + d] + r;
+                // (clamped: a batched call's malformed offsets can give two
+                // blocks overlapping items, which change between the count
+                // and this read)
+                const uint32_t p = min(whist[wave * 256 + d] + r, m - 1u);
                 b_k[p] = k;
                 if constexpr (VALS) b_v[p] = a_v[i];
             }
