@@ -22,6 +22,7 @@
 // holds more than kBinLimit items.
 #pragma once
 
+#include <cstddef>
 #include <type_traits>
 #include <utility>
 
@@ -40,8 +41,10 @@ constexpr uint32_t kDense = 8;  // items per value of a small key range
 constexpr int floor_log2(int x) { return x <= 1 ? 0 : 1 + floor_log2(x / 2); }
 constexpr int ceil_log2(int x) { return x <= 1 ? 0 : 1 + floor_log2(x - 1); }
 
+// Aligned for its 16-byte accesses (the bins are cleared and scanned four at
+// a time), whatever stands beside it in a kernel's LDS.
 template <int BLOCK, int IPT, typename K, typename V, bool VALS>
-struct BlockSortLds {
+struct alignas(16) BlockSortLds {
     static constexpr int WAVES = BLOCK / 64;
     static constexpr int CAP = BLOCK * IPT;
     static constexpr int LOG_NB = floor_log2(CAP);
@@ -66,6 +69,13 @@ struct BlockSortLds {
     uint32_t wmax[WAVES];
     K wlo[WAVES], whi[WAVES];
 };
+typedef BlockSortLds<256, 17, uint32_t, uint32_t, true> BlockSortLds32;
+typedef BlockSortLds<256, 16, uint64_t, uint32_t, true> BlockSortLds64;
+static_assert(alignof(BlockSortLds32) >= alignof(uint4) && alignof(BlockSortLds64) >= alignof(uint4) &&
+                  offsetof(BlockSortLds32, b) == 0 && offsetof(BlockSortLds64, b) == 0,
+              "the bins are read as uint4");
+// three 256 x 16 blocks with 64-bit keys and 4-byte values share a CU's LDS
+static_assert(3 * sizeof(BlockSortLds64) <= kLdsBytesPerCu, "three blocks to a CU");
 
 __device__ __forceinline__ uint32_t key_bits_of(uint32_t span) { return 32u - __builtin_clz(span | 1u) - (span == 0u); }
 __device__ __forceinline__ uint32_t key_bits_of(uint64_t span) {
