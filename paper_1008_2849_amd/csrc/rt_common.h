@@ -224,7 +224,7 @@ void launch_split64(uint64_t *keys, uint32_t *vals, uint32_t value_words, uint32
                     char *scratch, hipStream_t stream);
 // The splitter passes over a large array of 64-bit keys
 // (rt_split_seg_kernels.h): one pass and leaves up to kSplitOneMax64, two and
-// leaves from kSplitTwoMin64 to kSplitLargeEnd.  scratch as above,
+// leaves from kSplitTwoMin64 to kSplitTwoMax64.  scratch as above,
 // split_large_scratch_bytes64() long.  us, the digit passes against these,
 // pairs with 4-byte values:
 //
@@ -236,12 +236,22 @@ void launch_split64(uint64_t *keys, uint32_t *vals, uint32_t value_words, uint32
 //   2^24       998   508    981   878                461   510
 //   2^26      3311  1814   3414  3096   2338  1830  1577  1814
 //
+// and without the input's copy:
+//
+//   2^27      5759  2847  5923  5302  3831  2854  2357  2806
+//   2^28     11311  6143 11825 11407  7568  6077  4659  6486
+//   1.25 2^28 13600 7954 13921 16340  9317  8007  5943  9609
+//   1.8 2^28 20242 10541 21551 33033 13178 10333  8445 19248
+//
 // The lines are where keys of all eight digits gain whatever their
 // distribution.  Two passes do not gain where the digit passes skip five of
-// eight, which only a pass over the keys can tell.
+// eight, which only a pass over the keys can tell.  They end where the mean
+// of their at most 65536 leaves (2^28: 4096 items) still leaves uneven cuts
+// room in the largest leaf (8192): above, leaves that no LDS holds are sorted
+// through global memory.
 constexpr size_t kSplitOneMax64 = 256 * 2344;  // uneven leaves (18 percent) then fit: at 700000 ANDs of two took 186, not 165
 constexpr size_t kSplitTwoMin64 = static_cast<size_t>(1) << 22;
-constexpr size_t kSplitLargeEnd = static_cast<size_t>(1) << 30;
+constexpr size_t kSplitTwoMax64 = static_cast<size_t>(1) << 28;
 size_t split_large_scratch_bytes64(size_t n, uint32_t value_words);
 void launch_split_large64(uint64_t *keys, uint32_t *vals, uint32_t value_words, uint32_t n, uint64_t *tk, uint32_t *tv,
                           char *scratch, hipStream_t stream);

@@ -426,7 +426,7 @@ extern "C" rt_status rt_sort64_ex(uint64_t *keys, void *vals, uint32_t value_byt
             launch_split64(keys, v, vw, static_cast<uint32_t>(n), tk, tv, w, stream);
             return finish_waited(cfg, stream, "rt_sort64_ex");
         }
-        const bool passes = n > kSplitMax64 && (n <= kSplitOneMax64 || n >= kSplitTwoMin64) && n < kSplitLargeEnd;
+        const bool passes = n > kSplitMax64 && (n <= kSplitOneMax64 || n >= kSplitTwoMin64) && n <= kSplitTwoMax64;
         if (passes && L.t2k != 0 &&
             split_large_scratch_bytes64(n, vw) <= L.total - L.t2k) {
             launch_split_large64(keys, v, vw, static_cast<uint32_t>(n), tk, tv, w + L.t2k, stream);

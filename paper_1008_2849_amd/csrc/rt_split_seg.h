@@ -126,8 +126,8 @@ inline SplitSortLayout make_split_sort_layout(size_t n, int block, int ipt) {
     return S;
 }
 
-// Sorts n items of keys/vals in place (2 <= n < 2^30): one pass where its
-// buckets are leaves as they come.
+// Sorts n items of keys/vals in place (2 <= n <= kSplitTwoMax64): one pass
+// where its buckets are leaves as they come.
 template <typename K, typename V, bool VALS>
 void launch_split_sort(K *keys, V *vals, uint32_t n, K *tk, V *tv, const SplitSortLayout &S, char *ws,
                        hipStream_t stream) {

@@ -1,5 +1,6 @@
 """The limits of the splitter passes: malformed batched offsets whose
-overlapping segments hold leaves that no LDS holds."""
+overlapping segments hold leaves that no LDS holds; the sizes on each side of
+the lines where a method begins or ends."""
 import numpy as np
 import pytest
 
@@ -45,3 +46,50 @@ def test_overlapping_long_leaves_stay_inside():
     order = np.argsort(keys[121000:171000], kind="stable")
     assert np.array_equal(gk[guard + 121000:guard + 171000], keys[121000:171000][order])
     assert np.array_equal(gv[guard + 121000:guard + 171000], vals[121000:171000][order])
+
+
+def digit_passes(call):
+    """The counting-sort passes (past the first) that the call launches."""
+    rts.profile_start()
+    call()
+    sync()
+    return sorted({kind - 16 for kind, _ in rts.profile_stop() if kind > 16})
+
+
+def words64(n, ands, seed):
+    import torch
+    g = torch.Generator(device="cuda")
+    g.manual_seed(seed)
+    k = torch.empty(n, dtype=torch.int64, device="cuda").random_(-(1 << 63), (1 << 63) - 1, generator=g)
+    for _ in range(ands - 1):
+        k &= torch.empty(n, dtype=torch.int64, device="cuda").random_(-(1 << 63), (1 << 63) - 1, generator=g)
+    return k
+
+
+def check_pairs64(k0, k, v):
+    """The properties that fix a stable sort of original indices."""
+    import torch
+    n = k0.numel()
+    s = k ^ (-(1 << 63))  # unsigned order as signed order
+    assert bool((s[1:] >= s[:-1]).all()), "keys ascend"
+    at = v.to(torch.int64)
+    assert bool((torch.bincount(at, minlength=n) == 1).all()), "values are a permutation"
+    assert bool(torch.equal(k0[at], k)), "each key arrives with its own index"
+    eq = k[1:] == k[:-1]
+    assert bool((at[1:][eq] > at[:-1][eq]).all()), "equal keys keep index order"
+
+
+@pytest.mark.parametrize("ands", [1, 2])
+@pytest.mark.parametrize("n,digits", [(1 << 28, False), ((1 << 28) + 1, True)])
+def test_where_two_passes_of_64_bit_keys_end(n, digits, ands):
+    """Two splitter passes up to 2^28 items, whose leaves the LDS holds; digit
+    passes above."""
+    import torch
+    announce(f"64-bit keys, the end of two passes, n={n} ands={ands}")
+    k0 = words64(n, ands, 7 + ands)
+    k, v = k0.clone(), torch.arange(n, dtype=torch.int32, device="cuda")
+    ran = digit_passes(lambda: rts.sort_pairs64(k, v))
+    assert (ran == list(range(1, 8))) == digits, ran
+    check_pairs64(k0, k, v)
+    del k0, k, v
+    torch.cuda.empty_cache()
