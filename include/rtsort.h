@@ -233,7 +233,7 @@ size_t rt_workspace_bytes64(size_t n, uint32_t value_bytes, const rt_config *cfg
  * must not overlap.  max_total bounds seg_offsets[num_segments] -
  * seg_offsets[0] and sizes the workspace (pass the total when known).
  * Segments of up to 16384 items are sorted whole in LDS, larger ones of up
- * to 2^21 by one pass into buckets of neighbouring keys and the buckets whole
+ * to 2^20 by one pass into buckets of neighbouring keys and the buckets whole
  * in LDS, longer ones by four 8-bit onesweep passes over 16K-item tiles.
  *
  * Errors: argument errors are returned before any device work.  A segment

@@ -93,3 +93,29 @@ def test_where_two_passes_of_64_bit_keys_end(n, digits, ands):
     check_pairs64(k0, k, v)
     del k0, k, v
     torch.cuda.empty_cache()
+
+
+M = 1 << 20  # the longest segment that takes a splitter pass
+
+
+@pytest.mark.parametrize("kind", ["uniform", "and4", "zipf16", "one"])
+@pytest.mark.parametrize("sizes", [[M], [M + 1], [M, M], [M + 1, M], [3 * M, M + 1], [M, 30_000, M + 1, 5, 16_385, M - 1],
+                                   [2 * M + 7, 100, 20_000, 70_000]], ids=str)
+def test_segments_around_the_longest_a_splitter_pass_takes(sizes, kind):
+    announce(f"batched segments {sizes} {kind}")
+    n = sum(sizes)
+    keys = {"uniform": lambda: inputs.uniform_keys(n, 71), "and4": lambda: inputs.and_keys(n, 4, 72),
+            "zipf16": lambda: inputs.zipf16_keys(n, 73), "one": lambda: np.full(n, 7, np.uint32)}[kind]()
+    off = (np.concatenate([[0], np.cumsum(sizes)]) + 3).astype(np.uint32)
+    base = np.concatenate([np.full(3, 9, np.uint32), keys, np.full(5, 9, np.uint32)])
+    vals = np.arange(len(base), dtype=np.uint32)
+    want_k, want_v = base.copy(), vals.copy()
+    for a, b in zip(off[:-1], off[1:]):
+        order = np.argsort(base[a:b], kind="stable")
+        want_k[a:b], want_v[a:b] = base[a:b][order], vals[a:b][order]
+    o, k, v, only = to_dev(off), to_dev(base), to_dev(vals), to_dev(base)
+    rts.sort_batched_ex(k, v, o, n, validate=True)
+    rts.sort_batched_ex(only, None, o, n, validate=True)
+    sync()
+    assert np.array_equal(to_host(k), want_k) and np.array_equal(to_host(v), want_v)
+    assert np.array_equal(to_host(only), want_k)
