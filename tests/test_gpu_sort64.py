@@ -140,6 +140,22 @@ def test_probed_size(dist, expected):
     check(gpu_sort64(k, v), oracle.lsd_sort64(k, v), dist)
 
 
+@pytest.mark.parametrize("vb", [0, 4])
+@pytest.mark.parametrize("dist,expected", [("uniform", 1), ("and2", 0), ("dict16", 0)])
+def test_probed_digit_passes(dist, expected, vb):
+    """The digit passes themselves at a size whose keys are sampled first,
+    asked for by their shape (the default takes splitter passes there): the
+    sample chooses chunks or one chain, and the sort that follows its choice
+    gives the oracle's result."""
+    n = (1 << 25) + 33
+    announce(f"64-bit keys probed digit passes dist={dist} vb={vb} n={n}")
+    cfg = Config((8,) * 8, 1024, 16, 0)
+    k = inputs.keys64("uniform", n, 741) if dist == "uniform" else _dists(n)[dist]
+    v = values(n, vb)
+    assert rts.chunk_decision(dev64(k), value_bytes=vb, cfg=cfg) == expected, dist
+    check(gpu_sort64(k, v, cfg), oracle.lsd_sort64(k, v), dist)
+
+
 CONFIGS = [((8,) * 8, 1024, 8), ((8,) * 8, 512, 16), ((11, 11, 11, 11, 10, 10), 512, 8),
            ((10, 9, 9, 9, 9, 9, 9), 512, 8), ((8, 8, 8, 8, 8, 8, 8, 8), 1024, 8),
            ((8,) * 8, 1024, 16), ((8,) * 8, 1024, 12)]
