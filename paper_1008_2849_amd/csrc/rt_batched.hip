@@ -116,37 +116,11 @@ static void launch_small_classes(const SegPointers &P, const SegLayout &L, uint3
     prof_mark(stream, RT_KIND_SEG_SMALL);
 }
 
-// Per-segment histograms and prefix sums, whole-in-LDS segments, and passes
-// 0..passes-1 (on digits digit0..digit0 + passes - 1) over the tiled
-// segments.  The lists and the tiled list's counter are already on the
-// device.  to_temp: the result is wanted in the temporaries (odd pass
-// counts), where the tiled passes leave it.  persistent: the passes run one
-// block per CU, each claiming tiles until none is left.
+// Passes 0..passes-1 on digits digit0.. over the tiles of the tile map.
 template <bool VALS, typename S>
-static void launch_seg_sort_body(const SegPointers &P, const SegLayout &L, uint32_t list_stride, int passes,
-                                 int to_temp, uint32_t nchunks, uint32_t digit0, bool persistent,
-                                 hipStream_t stream, int from = kSegLarge) {
+static void launch_digit_passes(const SegPointers &P, const SegLayout &L, int passes, uint32_t nchunks, uint32_t digit0,
+                                bool persistent, hipStream_t stream) {
     const uint32_t cus = static_cast<uint32_t>(device_cu_count());
-    uint32_t *large_list = P.lists + static_cast<size_t>(kSegLarge) * list_stride;
-    const bool huge = from == kSegHuge;
-    hipLaunchKernelGGL(k_seg_tiles, dim3(1), dim3(1024), 0, stream, P.descs, huge ? P.huge_list : large_list,
-                       P.first_tile, P.header, L.large_capacity, L.max_tiles, L.tile, from,
-                       huge ? large_list : nullptr, nullptr, 0u);
-    hipLaunchKernelGGL(k_seg_tilemap, dim3(cap_grid((L.max_tiles + 255) / 256, cus * 4)), dim3(256), 0, stream,
-                       P.descs, large_list, P.first_tile, P.header, P.tile_seg, nchunks);
-    prof_mark(stream, RT_KIND_SEGMENTED);
-    // the histogram rows and lookback words this call uses start at zero
-    hipLaunchKernelGGL(k_seg_clear, dim3(cus * 4), dim3(256), 0, stream, P.header, P.hist,
-                       reinterpret_cast<uint32_t *>(P.status), L.status_pass / 4, L.wide_status ? 2u : 1u, passes);
-    prof_mark(stream, RT_KIND_FILL);
-    hipLaunchKernelGGL((k_seg_histogram<512, 16>), dim3(cap_grid(L.max_tiles, cus * 2)), dim3(512), 0, stream,
-                       P.tile_seg, P.header, P.hist, L.tile,
-                       ((1u << passes) - 1u) << digit0);
-    prof_mark(stream, RT_KIND_HISTOGRAM);
-    hipLaunchKernelGGL(k_seg_plan, dim3(cap_grid(L.large_capacity, cus * 4)), dim3(256), 0, stream, P.descs,
-                       large_list, P.header, P.hist, P.base);
-    prof_mark(stream, RT_KIND_PLAN);
-    if (from == kSegLarge) launch_small_classes<VALS>(P, L, list_stride, passes, to_temp, stream);
     for (int p = 0; p < passes; ++p) {
         S *status = reinterpret_cast<S *>(reinterpret_cast<char *>(P.status) + p * L.status_pass);
         uint32_t *ctr = P.header_words + offsetof(SegHeader, chunk_ctr) / 4 + p * kChunks;
@@ -168,6 +142,38 @@ static void launch_seg_sort_body(const SegPointers &P, const SegLayout &L, uint3
     }
 }
 
+// Per-segment histograms and prefix sums, whole-in-LDS segments, and passes
+// 0..passes-1 (on digits digit0..digit0 + passes - 1) over the tiled
+// segments.  The lists and the tiled list's counter are already on the
+// device.  to_temp: the result is wanted in the temporaries (odd pass
+// counts), where the tiled passes leave it.  persistent: the passes run one
+// block per CU, each claiming tiles until none is left.
+template <bool VALS, typename S>
+static void launch_seg_sort_body(const SegPointers &P, const SegLayout &L, uint32_t list_stride, int passes,
+                                 int to_temp, uint32_t nchunks, uint32_t digit0, bool persistent,
+                                 hipStream_t stream) {
+    const uint32_t cus = static_cast<uint32_t>(device_cu_count());
+    uint32_t *large_list = P.lists + static_cast<size_t>(kSegLarge) * list_stride;
+    hipLaunchKernelGGL(k_seg_tiles, dim3(1), dim3(1024), 0, stream, P.descs, large_list, nullptr, P.first_tile, P.header,
+                       L.large_capacity, L.max_tiles, L.tile, nullptr, 0u);
+    hipLaunchKernelGGL(k_seg_tilemap, dim3(cap_grid((L.max_tiles + 255) / 256, cus * 4)), dim3(256), 0, stream,
+                       P.descs, large_list, P.first_tile, P.header, P.tile_seg, nchunks);
+    prof_mark(stream, RT_KIND_SEGMENTED);
+    // the histogram rows and lookback words this call uses start at zero
+    hipLaunchKernelGGL(k_seg_clear, dim3(cus * 4), dim3(256), 0, stream, P.header, P.hist,
+                       reinterpret_cast<uint32_t *>(P.status), L.status_pass / 4, L.wide_status ? 2u : 1u, passes);
+    prof_mark(stream, RT_KIND_FILL);
+    hipLaunchKernelGGL((k_seg_histogram<512, 16>), dim3(cap_grid(L.max_tiles, cus * 2)), dim3(512), 0, stream,
+                       P.tile_seg, P.header, P.hist, L.tile,
+                       ((1u << passes) - 1u) << digit0);
+    prof_mark(stream, RT_KIND_HISTOGRAM);
+    hipLaunchKernelGGL(k_seg_plan, dim3(cap_grid(L.large_capacity, cus * 4)), dim3(256), 0, stream, P.descs,
+                       large_list, P.header, P.hist, P.base);
+    prof_mark(stream, RT_KIND_PLAN);
+    launch_small_classes<VALS>(P, L, list_stride, passes, to_temp, stream);
+    launch_digit_passes<VALS, S>(P, L, passes, nchunks, digit0, persistent, stream);
+}
+
 SegPointers seg_pointers(char *ws, const SegLayout &L) {
     SegPointers P{};
     P.header = reinterpret_cast<SegHeader *>(ws + L.header);
@@ -178,7 +184,6 @@ SegPointers seg_pointers(char *ws, const SegLayout &L) {
     P.tile_seg = reinterpret_cast<SegDesc *>(ws + L.tile_seg);
     P.hist = reinterpret_cast<uint32_t *>(ws + L.hist);
     P.base = reinterpret_cast<uint32_t *>(ws + L.base);
-    P.huge_list = P.base;  // (moved out before the rows are written)
     P.status = ws + L.status;
     P.tk = reinterpret_cast<uint32_t *>(ws + L.tk);
     P.tv = L.tv ? reinterpret_cast<uint32_t *>(ws + L.tv) : nullptr;
@@ -193,7 +198,7 @@ void launch_segments(uint32_t *keys, uint32_t *vals, uint32_t *tk, uint32_t *tv,
     hipLaunchKernelGGL(k_seg_reset, dim3(1), dim3(64), 0, stream, P.header);
     hipLaunchKernelGGL(k_seg_classify, dim3((num_segments + 255) / 256), dim3(256), 0, stream, offsets,
                        num_segments, keys, vals, tk, vals_on ? tv : nullptr, L.capacity, L.large_capacity,
-                       to_temp, L.classes.limits(), P.descs, P.lists, P.header, 0u, nullptr);
+                       to_temp, L.classes.limits(), P.descs, P.lists, P.header, 0u);
     // XCD chunks of the tile list pay off for long segments only: with a few
     // tiles per segment (many partial tiles, short lookback chains) one
     // chunk measured faster.  The segments' mean size bounds their tiles.
@@ -207,22 +212,51 @@ void launch_segments(uint32_t *keys, uint32_t *vals, uint32_t *tk, uint32_t *tv,
     }
 }
 
-// Segments of a batched call, longest first: one splitter pass and leaves;
-// four digit passes for those too long for that, if the call can hold any.
-// Their list waits in the base rows, which the splitter pass does not use.
+// The longest segment that one splitter pass and leaves sort.
 constexpr uint32_t kSplitSegMax = 1u << 20;
+
+// Whether a batched call takes its tiled segments through splitter passes, and
+// through digit passes only those that are too long.  Not if they are too long
+// by their mean: the splitter pass's launches would find nothing (4 segments
+// of 2^20.1 to 2^21: 196 us, 217 with them).  And not from where a segment can
+// be too long, and the digit passes' launches are needed besides, up to where
+// the items outweigh them: us by digit passes and by both,
+//
+//                                 spread keys    ANDs of four     16 keys
+//   100 of 2^14.1 to 2^15 (2.2M)    120   119     120   161      119   168
+//   4 of 2^18 to 2^19.9 (1.6M)      115   111     117   163      116   120
+//   200 of 2^4 to 2^16 (1.2M)       153   153     202   241      196   245
+//   8 of 2^19.9 (8.3M)              210   174     207   251      204   180
+constexpr size_t kFewItems = static_cast<size_t>(1) << 22;
+static bool takes_splitters(const SegLayout &L, uint32_t num_segments) {
+    if (L.tile != kSegTile || L.wide_status) return false;
+    if (L.capacity > static_cast<size_t>(num_segments) * kSplitSegMax) return false;
+    return L.capacity <= kSplitSegMax || L.capacity > kFewItems;
+}
 
 template <bool VALS>
 static void launch_batched_body(uint32_t *keys, uint32_t *vals, const SegPointers &P, const SegLayout &L,
-                                uint32_t num_segments, char *ws, hipStream_t stream) {
+                                uint32_t num_segments, uint32_t nchunks, char *ws, hipStream_t stream) {
     launch_small_classes<VALS>(P, L, num_segments, kSegPasses, 0, stream);
     typedef SplitTile<uint32_t, uint32_t, VALS> T;
     static_assert(T::ITEMS == kSegTile, "the tile map is made for these tiles");
     if (L.large_capacity > 0)
         launch_split_pass<T, uint32_t, uint32_t, VALS>(P, L, num_segments, SplitEnd::kLeavesBack, nullptr,
                                                     LeafArrays<uint32_t, uint32_t>{keys, vals, P.tk, P.tv}, ws, stream);
-    if (L.capacity > kSplitSegMax)
-        launch_seg_sort_body<VALS, uint32_t>(P, L, num_segments, kSegPasses, 0, 1u, 0u, true, stream, kSegHuge);
+    if (L.capacity <= kSplitSegMax) return;
+    const uint32_t cus = static_cast<uint32_t>(device_cu_count());
+    hipLaunchKernelGGL(k_seg_digit_map, dim3(cus * 4), dim3(256), 0, stream, P.descs,
+                       P.lists + static_cast<size_t>(kSegLarge) * num_segments,
+                       P.lists + static_cast<size_t>(kSegHuge) * num_segments, P.first_tile, P.header, P.tile_seg,
+                       P.hist, reinterpret_cast<uint32_t *>(P.status), L.status_pass / 4, nchunks);
+    prof_mark(stream, RT_KIND_SEGMENTED);
+    hipLaunchKernelGGL((k_seg_histogram<512, 16>), dim3(cap_grid(L.max_tiles, cus * 2)), dim3(512), 0, stream,
+                       P.tile_seg, P.header, P.hist, L.tile, (1u << kSegPasses) - 1u);
+    prof_mark(stream, RT_KIND_HISTOGRAM);
+    hipLaunchKernelGGL(k_seg_plan, dim3(cap_grid(L.large_capacity, cus * 4)), dim3(256), 0, stream, P.descs, nullptr,
+                       P.header, P.hist, P.base);
+    prof_mark(stream, RT_KIND_PLAN);
+    launch_digit_passes<VALS, uint32_t>(P, L, kSegPasses, nchunks, 0u, true, stream);
 }
 
 void launch_batched(uint32_t *keys, uint32_t *vals, const uint32_t *offsets, uint32_t num_segments,
@@ -230,23 +264,25 @@ void launch_batched(uint32_t *keys, uint32_t *vals, const uint32_t *offsets, uin
     const SegPointers P = seg_pointers(ws, L);
     prof_begin(stream);
     uint32_t *tv = vals ? P.tv : nullptr;
-    if (L.tile != kSegTile || L.wide_status) {
+    if (!takes_splitters(L, num_segments)) {
         launch_segments(keys, vals, P.tk, tv, offsets, num_segments, L, ws, kSegPasses, 0, stream);
         return;
     }
+    const uint32_t nchunks = seg_chunk_count(L.capacity, num_segments, L.tile);
     hipLaunchKernelGGL(k_seg_reset, dim3(1), dim3(64), 0, stream, P.header);
     hipLaunchKernelGGL(k_seg_classify, dim3((num_segments + 255) / 256), dim3(256), 0, stream, offsets, num_segments,
                        keys, vals, P.tk, tv, L.capacity, L.large_capacity, 0, L.classes.limits(), P.descs, P.lists,
-                       P.header, kSplitSegMax, P.huge_list);
+                       P.header, kSplitSegMax);
     if (L.large_capacity > 0) {
         const SplitTables t = split_tables(ws, L);
         hipLaunchKernelGGL(k_seg_tiles, dim3(1), dim3(1024), 0, stream, P.descs,
-                           P.lists + static_cast<size_t>(kSegLarge) * num_segments, P.first_tile, P.header,
-                           L.large_capacity, L.max_tiles, L.tile, kSegLarge, nullptr, t.lists, t.leaf_capacity);
+                           P.lists + static_cast<size_t>(kSegLarge) * num_segments,
+                           P.lists + static_cast<size_t>(kSegHuge) * num_segments,
+                           P.first_tile, P.header, L.large_capacity, L.max_tiles, L.tile, t.lists, t.leaf_capacity);
         prof_mark(stream, RT_KIND_SEGMENTED);
     }
-    if (vals) launch_batched_body<true>(keys, vals, P, L, num_segments, ws, stream);
-    else launch_batched_body<false>(keys, vals, P, L, num_segments, ws, stream);
+    if (vals) launch_batched_body<true>(keys, vals, P, L, num_segments, nchunks, ws, stream);
+    else launch_batched_body<false>(keys, vals, P, L, num_segments, nchunks, ws, stream);
 }
 
 }  // namespace rt

@@ -177,7 +177,6 @@ struct SegPointers {
     SegDesc *tile_seg;  // per tile: its segment's descriptor, pad = the segment's first tile
     uint32_t *hist;
     uint32_t *base;
-    uint32_t *huge_list;
     char *status;
     uint32_t *tk;
     uint32_t *tv;

@@ -109,6 +109,10 @@ struct SegHeader {
     uint32_t count[kSegMaxClasses + 2];  // list lengths: whole-in-LDS classes, tiled, huge
     uint32_t total_tiles;                // tiles of the tiled list
     uint32_t error;
+    // the segments of the digit passes in a call of splitter passes:
+    // digit_large entries of the tiled list, then the huge ones; their first
+    // tiles start at first_tile[digit_first]
+    uint32_t digit_first, digit_large, digit_count, digit_tiles;
     // XCD chunks of the tile list, cut at segment ends: chunk x holds tiles
     // [chunk_start[x], chunk_start[x + 1]); kChunks tile counters per launch
     uint32_t chunk_start[kChunks + 1];

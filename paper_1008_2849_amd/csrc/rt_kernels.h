@@ -889,8 +889,11 @@ __device__ __forceinline__ void rank_items(const K (&key)[IPT], V (&val)[VALS ? 
 // through the same LDS: a tile whose keys and values would not fit the LDS
 // together (16K items of 64-bit keys with 4- or 8-byte values) keeps its
 // size at the cost of two more barriers.
+//
+// LOOP: for a block's loop over tiles: what follows from the thread's number
+// is derived again for each tile, not kept in registers across the loop.
 template <int BITS, int BLOCK, int IPT, typename K, typename V, bool VALS, bool NT, typename S, bool STAGE,
-          bool SMALL, bool FUSED = false, bool SEQ = false>
+          bool SMALL, bool FUSED = false, bool SEQ = false, bool LOOP = false>
 __device__ __forceinline__ void onesweep_tile(const TileJob<K, V> &job,
                                               OnesweepLds<BITS, BLOCK, IPT, K, V, VALS, FUSED, SEQ> &lds,
                                               S *__restrict__ status, uint32_t *__restrict__ error_flag) {
@@ -902,7 +905,8 @@ __device__ __forceinline__ void onesweep_tile(const TileJob<K, V> &job,
     constexpr int DT = RADIX / R;                            // owning threads
     using St = Status<S>;
 
-    const uint32_t tid = threadIdx.x;
+    uint32_t tid = threadIdx.x;
+    if constexpr (LOOP) asm volatile("" : "+v"(tid));
     const uint32_t lane = tid & 63u;
     const uint32_t wave = tid >> 6;
     const uint32_t shift = job.shift, width = job.width, valid = job.valid;

@@ -37,15 +37,15 @@ static __global__ __launch_bounds__(64) void k_seg_reset(SegHeader *__restrict__
 // past off[0] + capacity, is left untouched and raises kSegErrBounds.  When
 // the result is wanted in the temporaries (to_temp), a one-item segment is
 // copied there here, as no later kernel sees it.  Segments of more than
-// huge_min items go to huge_list (NULL: none do).  List slots are taken per
-// wave: one atomic per class and wave, each lane's slot found from the
-// class's ballot.
+// huge_min items (0: none) go to the huge list, which fills the tiled list's
+// array from its end.  List slots are taken per wave: one atomic per class and
+// wave, each lane's slot found from the class's ballot.
 static __global__ __launch_bounds__(256) void k_seg_classify(const uint32_t *__restrict__ off, uint32_t num_segments,
                                                       uint32_t *keys, uint32_t *vals, uint32_t *tk, uint32_t *tv,
                                                       size_t capacity, uint32_t large_capacity, int to_temp,
                                                       SegClassLimits classes, SegDesc *__restrict__ descs,
                                                       uint32_t *__restrict__ lists, SegHeader *__restrict__ h,
-                                                      uint32_t huge_min, uint32_t *__restrict__ huge_list) {
+                                                      uint32_t huge_min) {
     const uint32_t s = blockIdx.x * 256 + threadIdx.x;
     int c = -1;  // list of this lane's segment (-1: none)
     SegDesc d;
@@ -69,7 +69,7 @@ static __global__ __launch_bounds__(256) void k_seg_classify(const uint32_t *__r
             d.pass = 0;
             d.row = 0;
             d.pad = 0;
-            c = huge_list != nullptr && n > huge_min ? kSegHuge : kSegLarge;
+            c = huge_min != 0u && n > huge_min ? kSegHuge : kSegLarge;
 #pragma unroll
             for (int i = kSegMaxClasses - 1; i >= 0; --i)
                 if (i < static_cast<int>(classes.count) && n <= classes.max_n[i]) c = i;
@@ -98,8 +98,14 @@ static __global__ __launch_bounds__(256) void k_seg_classify(const uint32_t *__r
         d.row = at;
     }
     descs[s] = d;
-    if (c == kSegHuge) huge_list[at] = s;
+    if (c == kSegHuge) lists[static_cast<size_t>(kSegHuge) * num_segments - 1u - at] = s;
     else lists[static_cast<size_t>(c) * num_segments + at] = s;
+}
+
+// Entry i of the tiled list followed by the huge one, `large` entries of the
+// first (list to list_end: their array).
+__device__ __forceinline__ uint32_t seg_entry(const uint32_t *list, const uint32_t *list_end, uint32_t large, uint32_t i) {
+    return i < large ? list[i] : *(list_end - 1 - (i - large));
 }
 
 // The tiled list as the server builds it on the host has no counter on the
@@ -116,47 +122,83 @@ struct LeafLists {
 };
 
 // One block: first_tile[i] = tiles of list entries before i, and the total.
-// `from`: whose list it is (count[from]); its length, as far as the workspace
-// holds it, becomes count[kSegLarge], and moved (if set) takes its entries.
-// leaf_lists set: also empties them.
 // Well-formed offsets never list more than large_capacity segments nor more
 // than max_tiles tiles; overlapping (malformed) ones can, and then the list
 // is cut to what the workspace holds (or emptied) and the error is raised,
 // so that no later kernel indexes past the tables.
+//
+// leaf_lists set (a call of splitter passes): also empties them, and the same
+// for the segments of the digit passes (h->digit_*).  These are the huge ones;
+// if those hold three quarters of the tiles or more, or a quarter of few
+// tiles, every tiled segment, because the two methods run one after the other
+// and each has launches that little work does not fill.  12 segments of 2^6 to
+// 2^22 ANDs of four words: 300 us by both, 224 by digit passes; 20 of 2^10 to
+// 2^23 spread keys: 748 and 659; 50 of 2^6 to 2^22: 463 and 529.
+constexpr uint32_t kFewTiles = 256;
 static __global__ __launch_bounds__(1024) void k_seg_tiles(const SegDesc *__restrict__ descs,
                                                            const uint32_t *__restrict__ list,
+                                                           const uint32_t *__restrict__ list_end,
                                                            uint32_t *__restrict__ first_tile, SegHeader *__restrict__ h,
                                                            uint32_t large_capacity, uint32_t max_tiles, uint32_t tile,
-                                                           int from, uint32_t *__restrict__ moved,
                                                            LeafLists *__restrict__ leaf_lists,
                                                            uint32_t leaf_capacity) {
-    __shared__ uint32_t s_wsum[16];
-    const uint32_t listed = h->count[from];
+    __shared__ uint32_t s_wsum[2][16];
+    __shared__ uint32_t s_total[2];
+    const uint32_t tid = threadIdx.x;
+    // first[i] = start + the tiles before entry i, i up to count; returns the
+    // tiles.  which: 0 or 1, another one than the call before
+    const auto number = [&](uint32_t large, uint32_t count, uint32_t *first, uint32_t start, int which) {
+        const uint32_t per = (count + 1023u) / 1024u;
+        const uint32_t lo = min(count, tid * per), hi = min(count, lo + per);
+        uint32_t sum = 0;  // at most 256 entries of at most 2^19 tiles: no overflow
+        for (uint32_t i = lo; i < hi; ++i) sum += (descs[seg_entry(list, list_end, large, i)].n + tile - 1) / tile;
+        // saturate, so the block total stays exact up to max_tiles and cannot wrap
+        uint32_t run = block_exclusive_sum<1024>(min(sum, max_tiles + 1u), s_wsum[which]);
+        for (uint32_t i = lo; i < hi; ++i) {
+            first[i] = start + run;
+            run += (descs[seg_entry(list, list_end, large, i)].n + tile - 1) / tile;
+        }
+        if (tid == 1023) {
+            first[count] = start + run;
+            s_total[which] = run;
+        }
+        __syncthreads();
+        return s_total[which];
+    };
+    const uint32_t listed = h->count[kSegLarge], huge_listed = h->count[kSegHuge];
+    uint32_t large = min(listed, large_capacity), huge = min(huge_listed, large_capacity);
+    bool fits = listed == large && huge_listed == huge;
     if (leaf_lists != nullptr) {
-        if (threadIdx.x < kLeafClasses) leaf_lists->count[threadIdx.x] = 0u;
-        if (threadIdx.x == kLeafClasses) leaf_lists->capacity = leaf_capacity;
+        if (tid < kLeafClasses) leaf_lists->count[tid] = 0u;
+        if (tid == kLeafClasses) leaf_lists->capacity = leaf_capacity;
     }
-    const uint32_t count = min(listed, large_capacity);
-    const uint32_t per = (count + 1023u) / 1024u;
-    const uint32_t lo = min(count, threadIdx.x * per), hi = min(count, lo + per);
-    uint32_t sum = 0;  // at most 256 entries of at most 2^19 tiles: no overflow
-    for (uint32_t i = lo; i < hi; ++i) {
-        const uint32_t s = list[i];
-        sum += (descs[s].n + tile - 1) / tile;
-        if (moved != nullptr) moved[i] = s;
+    uint32_t tiles = number(large, large, first_tile, 0u, 0);
+    if (tiles > max_tiles) {
+        fits = false;
+        large = tiles = 0u;
     }
-    // saturate, so the block total stays exact up to max_tiles and cannot wrap
-    uint32_t run = block_exclusive_sum<1024>(min(sum, max_tiles + 1u), s_wsum);
-    for (uint32_t i = lo; i < hi; ++i) {
-        first_tile[i] = run;
-        run += (descs[list[i]].n + tile - 1) / tile;
+    uint32_t digit_first = 0, digit_large = 0, digit_tiles = 0;
+    if (huge > 0u) {
+        digit_first = large;  // (the entry that ends one list begins the other)
+        if (large + huge <= large_capacity) digit_tiles = number(0u, huge, first_tile + digit_first, tiles, 1);
+        if (digit_tiles == 0u || digit_tiles > max_tiles - tiles) {
+            fits = false;
+            huge = digit_tiles = 0u;
+        } else if (digit_tiles >= 3u * tiles || (tiles + digit_tiles <= kFewTiles && 3u * digit_tiles >= tiles)) {
+            digit_first = 0u;
+            digit_large = large;
+            digit_tiles = number(large, large + huge, first_tile, 0u, 0);
+            large = tiles = 0u;
+        }
     }
-    if (threadIdx.x == 1023) {
-        const bool fits = run <= max_tiles;
-        first_tile[count] = run;
-        h->count[kSegLarge] = fits ? count : 0u;
-        h->total_tiles = fits ? run : 0u;
-        if (!fits || listed != count) atomicOr(&h->error, kSegErrBounds);
+    if (tid == 0) {
+        h->count[kSegLarge] = large;
+        h->total_tiles = tiles;
+        h->digit_first = digit_first;
+        h->digit_large = digit_large;
+        h->digit_count = digit_large + huge;
+        h->digit_tiles = digit_tiles;
+        if (!fits) atomicOr(&h->error, kSegErrBounds);
     }
 }
 
@@ -178,6 +220,24 @@ static __global__ __launch_bounds__(256) void k_seg_clear(const SegHeader *__res
         for (size_t i = first; i < status_words; i += stride) status[p * status_pass_words + i] = 0u;
 }
 
+// Start of chunk x when the tile list (first_tile[0..count], numbered from
+// origin) is cut into nchunks chunks of about equal tile counts at segment
+// ends.
+__device__ __forceinline__ uint32_t seg_chunk_start(uint32_t x, uint32_t nchunks, const uint32_t *first_tile,
+                                                    uint32_t count, uint32_t total, uint32_t origin = 0u) {
+    if (x == 0) return 0u;
+    if (x >= nchunks || count == 0) return total;
+    // the first segment start at or after x / nchunks of the tiles
+    const uint32_t target = origin + static_cast<uint32_t>(static_cast<uint64_t>(x) * total / nchunks);
+    uint32_t lo = 0, hi = count;  // first_tile[count] = origin + total
+    while (lo < hi) {
+        const uint32_t mid = (lo + hi) / 2;
+        if (first_tile[mid] >= target) hi = mid;
+        else lo = mid + 1;
+    }
+    return first_tile[lo] - origin;
+}
+
 // tile_desc[t] = the descriptor of the segment that tile t belongs to, with
 // pad = that segment's first tile (first_tile is strictly increasing: every
 // listed segment has at least one tile), so that a tile's kernel reaches its
@@ -191,24 +251,8 @@ static __global__ __launch_bounds__(256) void k_seg_tilemap(const SegDesc *__res
                                                      SegDesc *__restrict__ tile_desc, uint32_t nchunks) {
     const uint32_t count = h->count[kSegLarge];
     const uint32_t total = h->total_tiles;
-    if (blockIdx.x == 0 && threadIdx.x <= kChunks) {
-        const uint32_t x = threadIdx.x;
-        uint32_t at = total;
-        if (x == 0) {
-            at = 0;
-        } else if (x < nchunks && count > 0) {
-            // the first segment start at or after x / kChunks of the tiles
-            const uint32_t target = static_cast<uint32_t>(static_cast<uint64_t>(x) * total / nchunks);
-            uint32_t lo = 0, hi = count;  // first_tile[count] = total
-            while (lo < hi) {
-                const uint32_t mid = (lo + hi) / 2;
-                if (first_tile[mid] >= target) hi = mid;
-                else lo = mid + 1;
-            }
-            at = first_tile[lo];
-        }
-        h->chunk_start[x] = at;
-    }
+    if (blockIdx.x == 0 && threadIdx.x <= kChunks)
+        h->chunk_start[threadIdx.x] = seg_chunk_start(threadIdx.x, nchunks, first_tile, count, total);
     for (uint32_t t = blockIdx.x * 256 + threadIdx.x; t < total; t += gridDim.x * 256) {
         uint32_t lo = 0, hi = count - 1;  // the last entry with first_tile <= t
         while (lo < hi) {
@@ -220,6 +264,47 @@ static __global__ __launch_bounds__(256) void k_seg_tilemap(const SegDesc *__res
         d.pad = first_tile[lo];
         tile_desc[t] = d;
     }
+}
+
+// The same for the digit passes of a call of splitter passes (h->digit_*),
+// which become the tiled list, entry e with row e; also clears what they use,
+// as k_seg_clear (a launch less for calls that have no such segments, which
+// only the device knows).
+static __global__ __launch_bounds__(256) void k_seg_digit_map(const SegDesc *__restrict__ descs,
+                                                       const uint32_t *__restrict__ list,
+                                                       const uint32_t *__restrict__ list_end,
+                                                       const uint32_t *__restrict__ first_tile,
+                                                       SegHeader *__restrict__ h, SegDesc *__restrict__ tile_desc,
+                                                       uint32_t *__restrict__ hist, uint32_t *__restrict__ status,
+                                                       size_t status_pass_words, uint32_t nchunks) {
+    const uint32_t total = h->digit_tiles, count = h->digit_count, large = h->digit_large;
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        h->count[kSegLarge] = count;
+        h->total_tiles = total;
+    }
+    if (total == 0u) return;
+    first_tile += h->digit_first;
+    const uint32_t origin = first_tile[0];
+    if (blockIdx.x == 0 && threadIdx.x <= kChunks)
+        h->chunk_start[threadIdx.x] = seg_chunk_start(threadIdx.x, nchunks, first_tile, count, total, origin);
+    const uint32_t stride = gridDim.x * 256, tid = blockIdx.x * 256 + threadIdx.x;
+    for (uint32_t t = tid; t < total; t += stride) {
+        uint32_t lo = 0, hi = count - 1u;  // the last entry with first_tile <= t
+        while (lo < hi) {
+            const uint32_t mid = (lo + hi + 1u) / 2u;
+            if (first_tile[mid] - origin <= t) lo = mid;
+            else hi = mid - 1u;
+        }
+        SegDesc d = descs[seg_entry(list, list_end, large, lo)];
+        d.row = lo;
+        d.pad = first_tile[lo] - origin;
+        tile_desc[t] = d;
+    }
+    const size_t hist_words = static_cast<size_t>(count) * kSegPasses * kSegRadix;
+    const size_t status_words = static_cast<size_t>(total) * kSegRadix;
+    for (size_t i = tid; i < hist_words; i += stride) hist[i] = 0u;
+    for (int p = 0; p < kSegPasses; ++p)
+        for (size_t i = tid; i < status_words; i += stride) status[p * status_pass_words + i] = 0u;
 }
 
 // ---------------------------------------------------------------------------
@@ -466,7 +551,8 @@ __global__ __launch_bounds__(BLOCK) void k_seg_histogram(const SegDesc *__restri
 }
 
 // base[row][p][d] = count of digits below d in pass p of the segment: one
-// block of 256 threads per tiled segment at a time.
+// block of 256 threads per tiled segment at a time.  list NULL: entry e has
+// row e.
 static __global__ __launch_bounds__(256) void k_seg_plan(const SegDesc *__restrict__ descs,
                                                   const uint32_t *__restrict__ list,
                                                   const SegHeader *__restrict__ h,
@@ -474,7 +560,7 @@ static __global__ __launch_bounds__(256) void k_seg_plan(const SegDesc *__restri
     __shared__ uint32_t s_wsum[4];
     const uint32_t count = h->count[kSegLarge];
     for (uint32_t e = blockIdx.x; e < count; e += gridDim.x) {
-        const size_t row = static_cast<size_t>(descs[list[e]].row) * kSegPasses * kSegRadix;
+        const size_t row = static_cast<size_t>(list != nullptr ? descs[list[e]].row : e) * kSegPasses * kSegRadix;
         for (int p = 0; p < kSegPasses; ++p) {
             const uint32_t c = hist[row + p * kSegRadix + threadIdx.x];
             base[row + p * kSegRadix + threadIdx.x] = block_exclusive_sum<256>(c, s_wsum);
@@ -538,8 +624,8 @@ __global__ __launch_bounds__(BLOCK) void k_seg_onesweep(const SegDesc *__restric
         job.first = first;
         job.valid = min(static_cast<uint32_t>(TILE), d.n - (tile - first) * static_cast<uint32_t>(TILE));
         job.bound = d.n;
-        onesweep_tile<kSegBits, BLOCK, IPT, uint32_t, uint32_t, VALS, false, S, true, SMALL>(job, lds, status,
-                                                                                            error_flag);
+        onesweep_tile<kSegBits, BLOCK, IPT, uint32_t, uint32_t, VALS, false, S, true, SMALL, false, false, PERSIST>(
+            job, lds, status, error_flag);
         if constexpr (!PERSIST) return;
         __syncthreads();  // the tile is out of the LDS before the next claim
     }

@@ -119,3 +119,71 @@ def test_segments_around_the_longest_a_splitter_pass_takes(sizes, kind):
     sync()
     assert np.array_equal(to_host(k), want_k) and np.array_equal(to_host(v), want_v)
     assert np.array_equal(to_host(only), want_k)
+
+
+def test_long_segments_of_two_streams_and_replays():
+    """Segments above 2^20 items among shorter ones: two streams at once, each
+    with a workspace of its own, then a captured call replayed on new keys."""
+    import torch
+    sizes = [M + 1, 40, 300_000, 2 * M + 16_385, 17_000, 0, 64, 5 * M]
+    n = sum(sizes)
+    off = np.concatenate([[0], np.cumsum(sizes)]).astype(np.uint32)
+    o = to_dev(off)
+
+    def expected(keys):
+        order = np.concatenate([a + np.argsort(keys[a:b], kind="stable") for a, b in zip(off[:-1], off[1:])])
+        return keys[order], order.astype(np.uint32)
+
+    streams = [torch.cuda.Stream() for _ in range(2)]
+    spaces = [torch.empty(rts.batched_workspace_bytes(len(sizes), n), dtype=torch.uint8, device="cuda") for _ in streams]
+    inp = [inputs.uniform_keys(n, 81), inputs.and_keys(n, 4, 82)]
+    want = [expected(x) for x in inp]
+    k0, v0 = [to_dev(x) for x in inp], to_dev(inputs.index_values(n))
+    k, v = [torch.empty_like(x) for x in k0], [torch.empty_like(v0) for _ in streams]
+    announce("batched, segments above 2^20 items on two streams")
+    sync()
+    for rep in range(5):
+        for i, s in enumerate(streams):
+            with torch.cuda.stream(s):
+                k[i].copy_(k0[i])
+                v[i].copy_(v0)
+                rts.sort_batched_ex(k[i], v[i], o, n, workspace=spaces[i], stream=s)
+        sync()
+        for i in range(2):
+            assert np.array_equal(to_host(k[i]), want[i][0]) and np.array_equal(to_host(v[i]), want[i][1]), (rep, i)
+    announce("the same, captured and replayed")
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=streams[0]):
+        rts.sort_batched_ex(k[0], v[0], o, n, workspace=spaces[0], stream=streams[0])
+    for rep in range(4):
+        k[0].copy_(k0[rep % 2])
+        v[0].copy_(v0)
+        sync()
+        g.replay()
+        sync()
+        got = want[rep % 2]
+        assert np.array_equal(to_host(k[0]), got[0]) and np.array_equal(to_host(v[0]), got[1]), rep
+
+
+@pytest.mark.parametrize("sizes,splitters,digits", [
+    ([20_000] * 52, True, False),                 # up to 2^20 items: no segment can be too long for a splitter pass
+    ([20_000] * 53, False, True),                 # up to 2^22: one method's launches, not both's
+    ([20_000] * 209, False, True),
+    ([20_000] * 210, True, True),                 # above: splitters, and digit passes for what is too long
+    ([2_000_000] * 3, False, True),               # too long by their mean
+    ([5_000_000, 300_000, 20_000] + [64] * 4, True, True),     # most items too long: all by digit passes
+    ([1_100_000] + [130_000] * 40 + [64] * 4, True, True),     # few of them
+], ids=lambda x: f"{len(x)}x{x[0]}" if isinstance(x, list) else None)
+def test_method_of_a_batched_call(sizes, splitters, digits):
+    announce(f"method of {len(sizes)} segments of {sizes[0]}")
+    n = sum(sizes)
+    off = np.concatenate([[0], np.cumsum(sizes)]).astype(np.uint32)
+    keys = inputs.and_keys(n, 2, 91)
+    order = np.concatenate([a + np.argsort(keys[a:b], kind="stable") for a, b in zip(off[:-1], off[1:])])
+    k, v, o = to_dev(keys), to_dev(inputs.index_values(n)), to_dev(off)
+    rts.profile_start()
+    rts.sort_batched_ex(k, v, o, n)
+    sync()
+    kinds = {kind for kind, _ in rts.profile_stop()}
+    assert (10 in kinds) == splitters and (17 in kinds) == digits, kinds
+    assert np.array_equal(to_host(k), keys[order]) and np.array_equal(to_host(v), order.astype(np.uint32))
