@@ -32,6 +32,9 @@ struct SplitTables {
     SplitLeaf *leaves;
     uint32_t leaf_capacity;
 };
+inline uint32_t quantile_aim(const SegLayout &L, size_t key_bytes) {
+    return key_bytes == 4 && L.capacity <= kFewLeafItems ? kQuantileAimFew : kQuantileAim;
+}
 inline SplitTables split_tables(char *ws, const SegLayout &L) {
     SplitTables t;
     t.rows = ws + L.hist;
@@ -39,10 +42,10 @@ inline SplitTables split_tables(char *ws, const SegLayout &L) {
     t.chunks = reinterpret_cast<uint32_t *>(ws + L.status + L.status_pass);
     t.lists = reinterpret_cast<LeafLists *>(ws + L.status + 2 * L.status_pass);
     t.leaves = reinterpret_cast<SplitLeaf *>(ws + L.status + 2 * L.status_pass + 256);
-    // a segment of n items has at most n / kQuantileAim + 1 buckets, one that is
+    // a segment of n items has at most n / kQuantileAimFew + 1 buckets, one that is
     // the whole array (32 tiles or more, so there is room) up to kBuckets, and
     // buckets of one value make a leaf for every 4096 of their items besides
-    t.leaf_capacity = static_cast<uint32_t>(L.capacity / kQuantileAim + L.large_capacity);
+    t.leaf_capacity = static_cast<uint32_t>(L.capacity / kQuantileAimFew + L.large_capacity);
     if (L.max_tiles >= 32) t.leaf_capacity = std::max<uint32_t>(t.leaf_capacity, kBuckets);
     t.leaf_capacity += static_cast<uint32_t>(L.capacity / 4096);
     return t;
@@ -72,15 +75,16 @@ void launch_split_pass(const SegPointers &P, const SegLayout &L, uint32_t list_s
     const bool leaves = end != SplitEnd::kNextPass;
     // (a whole array's buckets may all be used, whatever its size)
     const uint32_t fixed = sub != nullptr && segs == 1 ? static_cast<uint32_t>(kBuckets) : 0u;
+    const uint32_t aim = quantile_aim(L, sizeof(K));
     if (fixed == 0u)
         hipLaunchKernelGGL((k_split_sample<256, 8, K>), dim3(split_grid(segs, cus * 6)), dim3(256), 0, stream, P.descs,
-                           list, P.header, P.first_tile, P.tile_seg, t.rows, fixed);
+                           list, P.header, P.first_tile, P.tile_seg, t.rows, fixed, aim);
     else if (!leaves && L.capacity <= kSampleFew)
         hipLaunchKernelGGL((k_split_sample<512, 4, K>), dim3(segs), dim3(512), 0, stream, P.descs, list, P.header,
-                           P.first_tile, P.tile_seg, t.rows, fixed);
+                           P.first_tile, P.tile_seg, t.rows, fixed, aim);
     else
         hipLaunchKernelGGL((k_split_sample<1024, 8, K>), dim3(segs), dim3(1024), 0, stream, P.descs, list, P.header,
-                           P.first_tile, P.tile_seg, t.rows, fixed);
+                           P.first_tile, P.tile_seg, t.rows, fixed, aim);
     prof_mark(stream, RT_KIND_PROBE);
     const uint32_t tiles = (L.max_tiles + kChunks - 1) / kChunks * kChunks;
     hipLaunchKernelGGL((k_split_tile_count<512, K>), dim3(tiles), dim3(512), 0, stream, P.tile_seg, P.header, t.rows,

@@ -86,8 +86,15 @@ constexpr uint32_t leaf_aim() {
 // Quantiles of a sample are less even (30 sample keys a bucket of 2^18 items:
 // 18 percent), and a leaf that does not fit 256 threads costs most: items per
 // leaf of theirs.  2000 segments of 2^6 to 2^20 keys that are ANDs of four
-// words: 1504 -> 1407 us a call.
+// words: 1504 -> 1407 us a call.  Batched calls of few items take half of
+// that: each then has fewer leaves than the chip has blocks, and a leaf for
+// the largest blocks costs the call a launch with work in it (4 segments of
+// 2^16 to 2^18 repeated keys: 119.6 -> 88.2 us, by digit passes 91.9); with
+// 35 million items the smaller leaves cost more than they save (ANDs of four
+// words: 869 -> 929 us).
 constexpr uint32_t kQuantileAim = 2900;
+constexpr uint32_t kQuantileAimFew = 1500;
+constexpr size_t kFewLeafItems = static_cast<size_t>(1) << 24;
 
 __device__ __forceinline__ uint32_t split_bucket_count(uint32_t n, uint32_t aim) {
     return min((n + aim - 1u) / aim, static_cast<uint32_t>(kBuckets));
@@ -158,7 +165,7 @@ struct QuantileSink {
 };
 
 // Chooses every listed segment's buckets (fixed_buckets of them if set, else
-// as many as its leaves need) from BLOCK * SIPT sample keys, and writes its
+// as many as its leaves need, of quantile_aim items where quantiles cut them) from BLOCK * SIPT sample keys, and writes its
 // tiles' entries of the tile map (as k_seg_tilemap).  2048 sample keys serve
 // a pass with leaves: 8192 gave better leaves only to keys of uneven density,
 // and cost 60 us more in random reads at 2^28 items.  The buckets are equal
@@ -173,7 +180,7 @@ __global__ __launch_bounds__(BLOCK) void k_split_sample(const SegDesc *__restric
                                                         const SegHeader *__restrict__ h,
                                                         const uint32_t *__restrict__ first_tile,
                                                         SegDesc *__restrict__ tile_desc, char *__restrict__ rows,
-                                                        uint32_t fixed_buckets) {
+                                                        uint32_t fixed_buckets, uint32_t quantile_aim) {
     constexpr uint32_t m = BLOCK * SIPT;
     __shared__ BlockSortLds<BLOCK, SIPT, K, uint32_t, false> sort;
     __shared__ K picked[kBuckets];
@@ -189,7 +196,7 @@ __global__ __launch_bounds__(BLOCK) void k_split_sample(const SegDesc *__restric
         char *row = rows + static_cast<size_t>(d.row) * kSplitRowBytes;
         // (d.pass set: a segment of one key value)
         const uint32_t stretches = d.pass ? 1u : fixed_buckets ? fixed_buckets : split_bucket_count(n, leaf_aim<K>());
-        const uint32_t buckets = d.pass ? 1u : fixed_buckets ? fixed_buckets : split_bucket_count(n, kQuantileAim);
+        const uint32_t buckets = d.pass ? 1u : fixed_buckets ? fixed_buckets : split_bucket_count(n, quantile_aim);
         {
             SegDesc t = d;
             t.pad = first_tile[e];
