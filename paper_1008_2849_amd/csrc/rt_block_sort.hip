@@ -41,9 +41,15 @@ bool default_method(const rt_config *cfg) {
                               (cfg->flags & ~static_cast<uint32_t>(RT_FLAG_VALIDATE)) == 0);
 }
 
-rt_status finish_waited(const rt_config *cfg, hipStream_t stream, const char *what) {
+rt_status finish_waited(const rt_config *cfg, hipStream_t stream, const char *what, const void *error) {
     const rt_status s = finish_call(stream, what);
-    if (s != RT_OK || cfg == nullptr || !(cfg->flags & RT_FLAG_VALIDATE)) return s;
+    const bool wait = (cfg != nullptr && (cfg->flags & RT_FLAG_VALIDATE)) || (error != nullptr && debug_sync_enabled());
+    if (s != RT_OK || !wait) return s;
+    if (error != nullptr) {
+        uint32_t err = 0;
+        const rt_status r = read_device_word(error, stream, &err, what);
+        return r == RT_OK && err ? set_error(RT_ERR_HIP, "%s: device error word 0x%x", what, err) : r;
+    }
     const hipError_t e = hipStreamSynchronize(stream);
     return e == hipSuccess ? RT_OK : set_error(RT_ERR_HIP, "%s: %s", what, hipGetErrorString(e));
 }

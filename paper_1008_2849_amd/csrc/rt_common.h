@@ -217,6 +217,7 @@ void launch_block_sort64(uint64_t *keys, uint32_t *vals, uint32_t value_words, u
 constexpr size_t kSplitMax32 = static_cast<size_t>(1) << 20;
 constexpr size_t kSplitMax64 = static_cast<size_t>(1) << 19;
 size_t split_scratch_bytes(size_t n, size_t key_bytes);
+size_t split_error_at(size_t n);  // of its device error word, in the scratch
 void launch_split(uint32_t *keys, uint32_t *vals, uint32_t n, uint32_t *tk, uint32_t *tv, char *scratch,
                   hipStream_t stream);
 void launch_split64(uint64_t *keys, uint32_t *vals, uint32_t value_words, uint32_t n, uint64_t *tk, uint32_t *tv,
@@ -252,14 +253,16 @@ constexpr size_t kSplitOneMax64 = 256 * 2344;  // uneven leaves (18 percent) the
 constexpr size_t kSplitTwoMin64 = static_cast<size_t>(1) << 22;
 constexpr size_t kSplitTwoMax64 = static_cast<size_t>(1) << 28;
 size_t split_large_scratch_bytes64(size_t n, uint32_t value_words);
+size_t split_large_error_at64(size_t n, uint32_t value_words);
 void launch_split_large64(uint64_t *keys, uint32_t *vals, uint32_t value_words, uint32_t n, uint64_t *tk, uint32_t *tv,
                           char *scratch, hipStream_t stream);
 // Whether cfg leaves the method to the library: no digits, shape or flags
 // but RT_FLAG_VALIDATE.
 bool default_method(const rt_config *cfg);
-// The end of a call that ran no kernel which can raise a device error:
-// finish_call, and with RT_FLAG_VALIDATE the wait it asks for.
-rt_status finish_waited(const rt_config *cfg, hipStream_t stream, const char *what);
+// The end of a call that ran one of the methods above: finish_call, and with
+// RT_FLAG_VALIDATE the wait it asks for and what *error (device; NULL: the
+// call's kernels raise none) says.
+rt_status finish_waited(const rt_config *cfg, hipStream_t stream, const char *what, const void *error = nullptr);
 
 // Kernel timing marks (see rt_profile_start); cheap no-ops when disabled.
 void prof_begin(hipStream_t stream);

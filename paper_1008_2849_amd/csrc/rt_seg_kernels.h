@@ -115,11 +115,13 @@ static __global__ __launch_bounds__(64) void k_seg_set_count(SegHeader *__restri
 }
 
 // The leaf lists of a splitter pass (rt_split_seg_kernels.h).
-constexpr int kLeafClasses = 3;
+constexpr int kLeafClasses = 4;
 struct LeafLists {
     uint32_t count[kLeafClasses];
+    uint32_t words[3];  // GridWords of the longest
     uint32_t capacity;  // entries per list
 };
+constexpr uint32_t kLeafListsZero = kLeafClasses + 3;  // words that start at zero
 
 // One block: first_tile[i] = tiles of list entries before i, and the total.
 // Well-formed offsets never list more than large_capacity segments nor more
@@ -169,8 +171,8 @@ static __global__ __launch_bounds__(1024) void k_seg_tiles(const SegDesc *__rest
     uint32_t large = min(listed, large_capacity), huge = min(huge_listed, large_capacity);
     bool fits = listed == large && huge_listed == huge;
     if (leaf_lists != nullptr) {
-        if (tid < kLeafClasses) leaf_lists->count[tid] = 0u;
-        if (tid == kLeafClasses) leaf_lists->capacity = leaf_capacity;
+        if (tid < kLeafListsZero) reinterpret_cast<uint32_t *>(leaf_lists)[tid] = 0u;
+        if (tid == kLeafListsZero) leaf_lists->capacity = leaf_capacity;
     }
     uint32_t tiles = number(large, large, first_tile, 0u, 0);
     if (tiles > max_tiles) {

@@ -605,7 +605,8 @@ extern "C" rt_status rt_sort_pairs_ex(uint32_t *keys, uint32_t *vals, size_t n, 
         s = cached_workspace(L.total, stream, &ws);
         if (s != RT_OK) return s;
     }
-    if (try_split(keys, vals, n, cfg, L, ws, stream)) return finish_waited(cfg, stream, "rt_sort_pairs_ex");
+    if (try_split(keys, vals, n, cfg, L, ws, stream))
+        return finish_waited(cfg, stream, "rt_sort_pairs_ex", static_cast<char *>(ws) + split_error_at(n));
     launch_sort(keys, vals, static_cast<uint32_t>(n), r, L, static_cast<char *>(ws), false, nullptr, nullptr,
                 stream);
     s = finish_call(stream, "rt_sort_pairs_ex");
@@ -676,7 +677,8 @@ extern "C" rt_status rt_sort_pairs_noalloc(uint32_t *keys, uint32_t *vals, size_
     void *ws = nullptr;
     s = noalloc_scratch(&ws, "rt_sort_pairs_noalloc");
     if (s != RT_OK) return s;
-    if (try_split(keys, vals, n, cfg, L, ws, stream)) return finish_waited(cfg, stream, "rt_sort_pairs_noalloc");
+    if (try_split(keys, vals, n, cfg, L, ws, stream))
+        return finish_waited(cfg, stream, "rt_sort_pairs_noalloc", static_cast<char *>(ws) + split_error_at(n));
     // every region that must start at zero (histograms, lookback words,
     // tile counters, error word) is cleared by the sort's own kernels
     launch_sort(keys, vals, static_cast<uint32_t>(n), r, L, static_cast<char *>(ws), false, nullptr, nullptr,

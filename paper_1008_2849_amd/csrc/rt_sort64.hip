@@ -424,13 +424,13 @@ extern "C" rt_status rt_sort64_ex(uint64_t *keys, void *vals, uint32_t value_byt
         uint32_t *tv = vw ? reinterpret_cast<uint32_t *>(w + L.t1v) : nullptr;
         if (n <= kSplitMax64 && split_scratch_bytes(n, sizeof(uint64_t)) <= L.t1k) {
             launch_split64(keys, v, vw, static_cast<uint32_t>(n), tk, tv, w, stream);
-            return finish_waited(cfg, stream, "rt_sort64_ex");
+            return finish_waited(cfg, stream, "rt_sort64_ex", w + split_error_at(n));
         }
         const bool passes = n > kSplitMax64 && (n <= kSplitOneMax64 || n >= kSplitTwoMin64) && n <= kSplitTwoMax64;
         if (passes && L.t2k != 0 &&
             split_large_scratch_bytes64(n, vw) <= L.total - L.t2k) {
             launch_split_large64(keys, v, vw, static_cast<uint32_t>(n), tk, tv, w + L.t2k, stream);
-            return finish_waited(cfg, stream, "rt_sort64_ex");
+            return finish_waited(cfg, stream, "rt_sort64_ex", w + L.t2k + split_large_error_at64(n, vw));
         }
     }
     launch_sort64(keys, static_cast<uint32_t *>(vals), vw, static_cast<uint32_t>(n), r, L, static_cast<char *>(ws),

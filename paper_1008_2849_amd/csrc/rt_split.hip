@@ -1,4 +1,6 @@
 // rt_split.hip -- host side of the splitter sort: shapes by size and launches.
+#include <cstddef>
+
 #include "rt_common.h"
 #include "rt_split_kernels.h"
 
@@ -13,10 +15,18 @@ static uint32_t split_tile(size_t n) {
     return n <= (static_cast<size_t>(1) << 17) ? 1024u : n <= (static_cast<size_t>(1) << 18) ? 2048u : 4096u;
 }
 
+// The buckets' starts, then the leaves' counters.
+static size_t starts_bytes() { return align256((kBuckets + 1) * sizeof(uint32_t) + sizeof(GridWords)); }
+
 size_t split_scratch_bytes(size_t n, size_t key_bytes) {
     const size_t tiles = (n + split_tile(n) - 1) / split_tile(n);
-    return align256(tiles * kBuckets * sizeof(uint32_t)) + align256((kBuckets + 1) * sizeof(uint32_t)) +
+    return align256(tiles * kBuckets * sizeof(uint32_t)) + starts_bytes() +
            align256(kBuckets * key_bytes);
+}
+
+size_t split_error_at(size_t n) {
+    const size_t tiles = (n + split_tile(n) - 1) / split_tile(n);
+    return align256(tiles * kBuckets * sizeof(uint32_t)) + (kBuckets + 1) * sizeof(uint32_t) + offsetof(GridWords, error);
 }
 
 template <typename K, typename V, bool VALS>
@@ -25,7 +35,7 @@ static void launch(K *keys, V *vals, uint32_t n, K *tk, V *tv, char *scratch, hi
     uint32_t *table = reinterpret_cast<uint32_t *>(scratch);
     scratch += align256(static_cast<size_t>(tiles) * kBuckets * sizeof(uint32_t));
     uint32_t *starts = reinterpret_cast<uint32_t *>(scratch);
-    scratch += align256((kBuckets + 1) * sizeof(uint32_t));
+    scratch += starts_bytes();
     K *splitters = reinterpret_cast<K *>(scratch);
     prof_begin(stream);
 #define RT_SPLIT_TILES(BLK)                                                                                         \
@@ -43,7 +53,7 @@ static void launch(K *keys, V *vals, uint32_t n, K *tk, V *tv, char *scratch, hi
     // leaves that hold four times the mean bucket
 #define RT_SPLIT_LEAF(BLK, I)                                                                                       \
     hipLaunchKernelGGL((k_split_leaf<BLK, I, K, V, VALS>), dim3(kBuckets), dim3(BLK), 0, stream, tk, tv, keys, vals, \
-                       splitters, starts)
+                       splitters, starts, table, reinterpret_cast<GridWords *>(starts + kBuckets + 1))
     if (n <= (1u << 16)) RT_SPLIT_LEAF(256, 4);
     else if (n <= (1u << 18)) RT_SPLIT_LEAF(1024, 4);
     else if (n <= (1u << 19)) RT_SPLIT_LEAF(1024, 8);

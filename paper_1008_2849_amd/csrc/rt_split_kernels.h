@@ -19,8 +19,8 @@
 // repeated keys cost nothing extra.  The buckets of other values have about
 // n / kBuckets items, at most four times that but for a chance of about 1e-5
 // (a bucket of spread keys holds eight or more sample keys); one that does
-// not fit the leaf's LDS is sorted by its block through global memory, slowly
-// but with the same result.
+// not fit the leaf's LDS is sorted through global memory, slowly but with the
+// same result: by its block, and by all of them together if it is long.
 //
 // Measured (a pass, the input copy included; before: the four- or eight-pass
 // sort): 60001 pairs 62.9 -> 25.0 us, 2^20 keys 79.8 -> 43.2 us, 300007 64-bit
@@ -36,6 +36,11 @@
 namespace rt {
 
 constexpr int kBuckets = 256;
+
+// Counters of grid_sort_long, zero before the launch, and its error word.
+struct GridWords {
+    uint32_t claim, done, error;
+};
 
 // Splitters are searched in the order of a binary tree (node i's children
 // are 2i and 2i + 1, the root is 1): a level is a run of consecutive LDS
@@ -120,7 +125,7 @@ __global__ __launch_bounds__(BLOCK) void k_split_count(const K *__restrict__ key
 
 // Scatters tile blockIdx.x of the k_split_count with the same tiles by bucket
 // into out_k/out_v, stably.  Block 0 writes the buckets' starts
-// (kBuckets + 1 words).
+// (kBuckets + 1 words), and the leaves' counters after them start at zero.
 template <int BLOCK, int IPT, typename K, typename V, bool VALS>
 __global__ __launch_bounds__(BLOCK) void k_split_scatter(const K *__restrict__ keys, const V *__restrict__ vals,
                                                          uint32_t n, const K *__restrict__ splitters,
@@ -220,6 +225,7 @@ __global__ __launch_bounds__(BLOCK) void k_split_scatter(const K *__restrict__ k
         if (tile == 0) {
             starts[tid] = start;
             if (tid == kBuckets - 1) starts[kBuckets] = n;
+            if (tid < sizeof(GridWords) / 4) starts[kBuckets + 1 + tid] = 0u;
         }
     }
     __syncthreads();
@@ -243,14 +249,184 @@ __global__ __launch_bounds__(BLOCK) void k_split_scatter(const K *__restrict__ k
     }
 }
 
+// Moves items [base, min(base + BLOCK, end)) of a to b, stably, by the digit at
+// bit sh: next[d] (LDS) is where digit d's next item goes, and moves on.
+// Positions are clamped to [0, m): a batched call's malformed offsets can give
+// two blocks overlapping items, which change between the count and this read.
+template <int BLOCK, typename K, typename V, bool VALS>
+__device__ __forceinline__ void block_scatter_step(const K *a_k, const V *a_v, K *b_k, V *b_v, uint32_t base, uint32_t end,
+                                                   uint32_t m, uint32_t sh, uint32_t *next, uint32_t *whist) {
+    constexpr int WAVES = BLOCK / 64;
+    const uint32_t tid = threadIdx.x, wave = tid >> 6;
+    for (uint32_t i = tid; i < WAVES * 256; i += BLOCK) whist[i] = 0u;
+    __syncthreads();
+    const uint32_t i = base + tid;
+    const K k = i < end ? a_k[i] : K(0);
+    const uint32_t d = static_cast<uint32_t>(k >> sh) & 255u;
+    uint32_t lo, hi;
+    match_digit<8>(d, lo, hi);
+    const uint64_t live = __builtin_amdgcn_ballot_w64(i < end);
+    lo &= static_cast<uint32_t>(live);
+    hi &= static_cast<uint32_t>(live >> 32);
+    const uint32_t r = __builtin_amdgcn_mbcnt_hi(hi, __builtin_amdgcn_mbcnt_lo(lo, 0u));
+    if (i < end && r == 0) whist[wave * 256 + d] = __popc(lo) + __popc(hi);
+    __syncthreads();
+    if (tid < 256) {
+        uint32_t run = next[tid];
+        for (int w = 0; w < WAVES; ++w) {
+            const uint32_t x = whist[w * 256 + tid];
+            whist[w * 256 + tid] = run;
+            run += x;
+        }
+        next[tid] = run;
+    }
+    __syncthreads();
+    if (i < end) {
+        const uint32_t p = min(whist[wave * 256 + d] + r, m - 1u);
+        b_k[p] = k;
+        if constexpr (VALS) b_v[p] = a_v[i];
+    }
+    __syncthreads();
+}
+
+// Longest bucket that one block sorts through global memory (64-bit keys: 64
+// steps a digit, about 3 ms); longer ones take the whole grid.
+constexpr uint32_t kAloneMax = 1u << 16;
+constexpr uint32_t kGridTile = 1u << 14;  // items a block takes at a time then
+
+// A bucket of n items of k/v (`copied`: first copied there from tk/tv) to be
+// sorted in k/v, with tk/tv to work in.
+template <typename K, typename V>
+struct LongLeaf {
+    K *k;
+    V *v;
+    K *tk;
+    V *tv;
+    uint32_t n, copied;
+};
+
+// LSD passes (8-bit digits) of the whole grid over `count` buckets, leaf(i)
+// the i-th, for keys that the sample missed: whatever the keys, the time is
+// that of about two passes over the buckets a digit.  Per digit: counts of
+// each tile to its row of `table`, each bucket's rows to output positions, a
+// stable scatter of each tile.  One counter numbers the units of all phases
+// in order; a block that has claimed one waits until the units of the phases
+// before are done, which blocks that run have claimed, so it does not matter
+// which blocks of the grid are on the chip.  The wait is bounded as the
+// lookback's is (*error is raised then).  All threads call it; first: LDS, count + 1
+// words.
+template <int BLOCK, typename K, typename V, bool VALS, typename Leaves>
+__device__ __forceinline__ void grid_sort_long(const Leaves &leaf, uint32_t count, uint32_t *first, uint32_t *table,
+                                               GridWords *words, uint32_t *error, uint32_t *whist, uint32_t *wsum) {
+    __shared__ uint32_t next[256];  // counts, or where the digit's next item goes
+    __shared__ uint32_t shared;     // thread 0's word for the block
+    const uint32_t tid = threadIdx.x;
+    uint32_t tiles = 0;
+    for (uint32_t base = 0; base < count; base += BLOCK) {
+        const uint32_t c = base + tid < count ? (leaf(base + tid).n - 1u) / kGridTile + 1u : 0u;
+        const uint32_t at = block_exclusive_sum<BLOCK>(c, wsum);
+        if (base + tid < count) first[base + tid] = tiles + at;
+        if (tid == BLOCK - 1) shared = at + c;
+        __syncthreads();
+        tiles += shared;
+        __syncthreads();
+    }
+    if (tid == 0) first[count] = tiles;
+    constexpr uint32_t PHASES = 1 + 3 * sizeof(K);  // copies; per digit: counts, positions, scatter
+    uint32_t phase = 0, begin = 0, size = tiles, ready = 0;
+    for (;;) {
+        __syncthreads();
+        if (tid == 0) shared = atomicAdd(&words->claim, 1u);
+        __syncthreads();
+        const uint32_t unit = shared;
+        while (unit - begin >= size) {
+            begin += size;
+            if (++phase == PHASES) return;
+            size = phase % 3u == 2u ? count : tiles;
+        }
+        if (phase != ready) {
+            __syncthreads();
+            if (tid == 0) {
+                uint32_t polls = 0;
+                while (status_load(&words->done) < begin && ++polls <= kLookbackSpinLimit) backoff(16);
+                shared = polls <= kLookbackSpinLimit ? 1u : 0u;
+                if (!shared) atomicOr(error, kErrLookbackTimeout);
+                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+            }
+            __syncthreads();
+            if (!shared) return;
+            ready = phase;
+        }
+        uint32_t e = unit - begin;
+        if (phase % 3u == 2u) {  // one bucket's rows
+            uint32_t *row = table + static_cast<size_t>(first[e]) * 256u + (tid & 255u);
+            const uint32_t rows = first[e + 1] - first[e];
+            constexpr uint32_t U = 8;  // loads in flight
+            const auto load = [&](uint32_t t, uint32_t (&x)[U]) {
+#pragma unroll
+                for (uint32_t i = 0; i < U; ++i) x[i] = t + i < rows ? row[static_cast<size_t>(t + i) * 256u] : 0u;
+            };
+            uint32_t c = 0, x[U];
+            for (uint32_t t = 0; t < rows && tid < 256; t += U) {
+                load(t, x);
+#pragma unroll
+                for (uint32_t i = 0; i < U; ++i) c += x[i];
+            }
+            uint32_t run = block_exclusive_sum<BLOCK>(c, wsum);
+            for (uint32_t t = 0; t < rows && tid < 256; t += U) {
+                load(t, x);
+#pragma unroll
+                for (uint32_t i = 0; i < U; ++i) {
+                    if (t + i < rows) row[static_cast<size_t>(t + i) * 256u] = run;
+                    run += x[i];
+                }
+            }
+        } else {
+            const uint32_t tile = e;
+            uint32_t hi = count - 1u;  // the bucket: the last with first <= tile
+            for (e = 0; e < hi;) {
+                const uint32_t mid = (e + hi + 1u) / 2u;
+                if (first[mid] <= tile) e = mid;
+                else hi = mid - 1u;
+            }
+            const LongLeaf<K, V> l = leaf(e);
+            const uint32_t m = l.n, i0 = (tile - first[e]) * kGridTile, i1 = min(m, i0 + kGridTile);
+            const uint32_t digit = phase == 0u ? 0u : (phase - 1u) / 3u, sh = 8u * digit;
+            K *a_k = digit & 1u ? l.tk : l.k, *b_k = digit & 1u ? l.k : l.tk;
+            V *a_v = digit & 1u ? l.tv : l.v, *b_v = digit & 1u ? l.v : l.tv;
+            uint32_t *row = table + static_cast<size_t>(tile) * 256u;
+            if (phase == 0u) {
+                for (uint32_t i = i0 + tid; i < i1 && l.copied; i += BLOCK) {
+                    a_k[i] = b_k[i];
+                    if constexpr (VALS) a_v[i] = b_v[i];
+                }
+            } else if (phase % 3u == 1u) {
+                if (tid < 256) next[tid] = 0u;
+                __syncthreads();
+                for (uint32_t i = i0 + tid; i < i1; i += BLOCK) atomicAdd(&next[static_cast<uint32_t>(a_k[i] >> sh) & 255u], 1u);
+                __syncthreads();
+                if (tid < 256) row[tid] = next[tid];
+            } else {
+                if (tid < 256) next[tid] = row[tid];
+                for (uint32_t base = i0; base < i1; base += BLOCK) block_scatter_step<BLOCK, K, V, VALS>(a_k, a_v, b_k, b_v, base, i1, m, sh, next, whist);
+            }
+        }
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();
+        if (tid == 0) {
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+            atomicAdd(&words->done, 1u);
+        }
+    }
+}
+
 // LSD passes of one block over items [0, m) of a/b in global memory (8-bit
 // digits; an even number of passes, so the result ends in a): for a bucket
 // that no leaf holds.
 template <int BLOCK, typename K, typename V, bool VALS>
 __device__ __forceinline__ void block_sort_global(K *a_k, V *a_v, K *b_k, V *b_v, uint32_t m, uint32_t *whist, uint32_t *wsum) {
-    constexpr int WAVES = BLOCK / 64;
     __shared__ uint32_t next[256];  // where the digit's next item goes
-    const uint32_t tid = threadIdx.x, wave = tid >> 6;
+    const uint32_t tid = threadIdx.x;
     for (uint32_t sh = 0; sh < 8 * sizeof(K); sh += 8) {
         __syncthreads();
         if (tid < 256) next[tid] = 0u;
@@ -260,40 +436,8 @@ __device__ __forceinline__ void block_sort_global(K *a_k, V *a_v, K *b_k, V *b_v
         const uint32_t c = tid < 256 ? next[tid] : 0u;
         const uint32_t first = block_exclusive_sum<BLOCK>(c, wsum);
         if (tid < 256) next[tid] = first;
-        for (uint32_t base = 0; base < m; base += BLOCK) {
-            for (uint32_t i = tid; i < WAVES * 256; i += BLOCK) whist[i] = 0u;
-            __syncthreads();
-            const uint32_t i = base + tid;
-            const K k = i < m ? a_k[i] : K(0);
-            const uint32_t d = static_cast<uint32_t>(k >> sh) & 255u;
-            uint32_t lo, hi;
-            match_digit<8>(d, lo, hi);
-            const uint64_t live = __builtin_amdgcn_ballot_w64(i < m);
-            lo &= static_cast<uint32_t>(live);
-            hi &= static_cast<uint32_t>(live >> 32);
-            const uint32_t r = __builtin_amdgcn_mbcnt_hi(hi, __builtin_amdgcn_mbcnt_lo(lo, 0u));
-            if (i < m && r == 0) whist[wave * 256 + d] = __popc(lo) + __popc(hi);
-            __syncthreads();
-            if (tid < 256) {
-                uint32_t run = next[tid];
-                for (int w = 0; w < WAVES; ++w) {
-                    const uint32_t x = whist[w * 256 + tid];
-                    whist[w * 256 + tid] = run;
-                    run += x;
-                }
-                next[tid] = run;
-            }
-            __syncthreads();
-            if (i < m) {
-                // (clamped: a batched call's malformed offsets can give two
-                // blocks overlapping items, which change between the count
-                // and this read)
-                const uint32_t p = min(whist[wave * 256 + d] + r, m - 1u);
-                b_k[p] = k;
-                if constexpr (VALS) b_v[p] = a_v[i];
-            }
-            __syncthreads();
-        }
+        for (uint32_t base = 0; base < m; base += BLOCK)
+            block_scatter_step<BLOCK, K, V, VALS>(a_k, a_v, b_k, b_v, base, m, m, sh, next, whist);
         K *sk = a_k; a_k = b_k; b_k = sk;
         V *sv = a_v; a_v = b_v; b_v = sv;
     }
@@ -304,10 +448,12 @@ __device__ __forceinline__ void block_sort_global(K *a_k, V *a_v, K *b_k, V *b_v
 template <int BLOCK, int IPT, typename K, typename V, bool VALS>
 __global__ __launch_bounds__(BLOCK) void k_split_leaf(K *__restrict__ tk, V *__restrict__ tv, K *__restrict__ keys,
                                                       V *__restrict__ vals, const K *__restrict__ splitters,
-                                                      const uint32_t *__restrict__ starts) {
+                                                      const uint32_t *__restrict__ starts, uint32_t *table,
+                                                      GridWords *words) {
     constexpr uint32_t CAP = BLOCK * IPT;
     __shared__ BlockSortLds<BLOCK, IPT, K, V, VALS> lds;
-    __shared__ uint64_t big_mask[kBuckets / 64];
+    // buckets of one value, and buckets for the whole grid
+    __shared__ uint64_t big_mask[kBuckets / 64], long_mask[kBuckets / 64];
     const uint32_t tid = threadIdx.x, b = blockIdx.x;
     // one-value buckets too long for a leaf are in order: every block copies
     // its share of them
@@ -317,12 +463,17 @@ __global__ __launch_bounds__(BLOCK) void k_split_leaf(K *__restrict__ tk, V *__r
         if (m > CAP && tid > 0)
             copy = tid < kBuckets - 1 ? static_cast<K>(splitters[tid] - splitters[tid - 1]) == K(1)
                                       : splitters[tid - 1] == ~K(0);
-        const uint64_t mask = __builtin_amdgcn_ballot_w64(copy);
-        if ((tid & 63u) == 0) big_mask[tid >> 6] = mask;
+        const uint64_t mask = __builtin_amdgcn_ballot_w64(copy), grid = __builtin_amdgcn_ballot_w64(!copy && m > kAloneMax);
+        if ((tid & 63u) == 0) {
+            big_mask[tid >> 6] = mask;
+            long_mask[tid >> 6] = grid;
+        }
     }
     const uint32_t first = starts[b], m = starts[b + 1] - first;
     __syncthreads();
-    for (int q = 0; q < kBuckets / 64; ++q)
+    uint32_t longs = 0;
+    for (int q = 0; q < kBuckets / 64; ++q) {
+        longs += static_cast<uint32_t>(__popcll(long_mask[q]));
         for (uint64_t mask = big_mask[q]; mask != 0; mask &= mask - 1u) {
             const uint32_t x = q * 64 + __builtin_ctzll(mask);
             const uint32_t e = starts[x + 1];
@@ -331,19 +482,37 @@ __global__ __launch_bounds__(BLOCK) void k_split_leaf(K *__restrict__ tk, V *__r
                 if constexpr (VALS) vals[i] = tv[i];
             }
         }
-    if (m == 0 || ((big_mask[b / 64] >> (b % 64)) & 1u)) return;
-    if (m <= CAP) {
+    }
+    if (m != 0 && m <= CAP) {
         block_sort<BLOCK, IPT, K, V, VALS>(ArraySource<K, V>{tk + first, VALS ? tv + first : nullptr}, m,
                                            ArraySink<K, V, VALS>{keys + first, VALS ? vals + first : nullptr}, false,
                                            lds);
-        return;
+    } else if (m > CAP && m <= kAloneMax && !((big_mask[b / 64] >> (b % 64)) & 1u)) {
+        for (uint32_t i = tid; i < m; i += BLOCK) {
+            keys[first + i] = tk[first + i];
+            if constexpr (VALS) vals[first + i] = tv[first + i];
+        }
+        block_sort_global<BLOCK, K, V, VALS>(keys + first, VALS ? vals + first : nullptr, tk + first,
+                                             VALS ? tv + first : nullptr, m, lds.whist, lds.wsum);
     }
-    for (uint32_t i = tid; i < m; i += BLOCK) {
-        keys[first + i] = tk[first + i];
-        if constexpr (VALS) vals[first + i] = tv[first + i];
-    }
-    block_sort_global<BLOCK, K, V, VALS>(keys + first, VALS ? vals + first : nullptr, tk + first,
-                                         VALS ? tv + first : nullptr, m, lds.whist, lds.wsum);
+    if (longs == 0) return;
+    const auto leaf = [&](uint32_t i) {
+        uint32_t x = 0;  // the i-th long bucket
+        for (int q = 0; q < kBuckets / 64; ++q) {
+            uint64_t mask = long_mask[q];
+            const uint32_t c = static_cast<uint32_t>(__popcll(mask));
+            if (i < c) {
+                for (; i != 0; --i) mask &= mask - 1u;
+                x = q * 64 + __builtin_ctzll(mask);
+                break;
+            }
+            i -= c;
+        }
+        const uint32_t at = starts[x];
+        return LongLeaf<K, V>{keys + at, VALS ? vals + at : nullptr, tk + at, VALS ? tv + at : nullptr, starts[x + 1] - at, 1u};
+    };
+    __syncthreads();
+    grid_sort_long<BLOCK, K, V, VALS>(leaf, longs, lds.b.bin, table, words, &words->error, lds.whist, lds.wsum);
 }
 
 }  // namespace rt

@@ -14,6 +14,10 @@ static SplitSortLayout layout64(size_t n, uint32_t value_words) {
 
 size_t split_large_scratch_bytes64(size_t n, uint32_t value_words) { return layout64(n, value_words).total; }
 
+size_t split_large_error_at64(size_t n, uint32_t value_words) {
+    return split_sort_error_at(layout64(n, value_words), split_sort_passes<uint64_t>(n) == 2);
+}
+
 void launch_split_large64(uint64_t *keys, uint32_t *vals, uint32_t value_words, uint32_t n, uint64_t *tk, uint32_t *tv,
                           char *scratch, hipStream_t stream) {
     const SplitSortLayout S = layout64(n, value_words);

@@ -2,6 +2,8 @@
 // sequence, shapes by type, and the two-pass sort of a large array.
 #pragma once
 
+#include <cstddef>
+
 #include "rt_common.h"
 #include "rt_split_seg_kernels.h"
 
@@ -103,10 +105,13 @@ void launch_split_pass(const SegPointers &P, const SegLayout &L, uint32_t list_s
     prof_mark(stream, RT_KIND_PASS);
     if (!leaves) return;
     const int in_place = end == SplitEnd::kLeavesInPlace ? 1 : 0;
+    // (the table's rows and the chunk rows behind them: leaves of more than
+    // kAloneMax items have at most 5 / 4 of a row for kGridTile items)
+    GridWords *words = reinterpret_cast<GridWords *>(t.lists->words);
     hipLaunchKernelGGL((k_split_leaves<256, leaf_ipt<K>(), K, V, VALS>), dim3(split_grid(t.leaf_capacity, cus * 4)), dim3(256), 0,
                        stream, arrays, t.lists, t.leaves, in_place);
     hipLaunchKernelGGL((k_split_long_leaves<1024, sizeof(K) == 4 ? 16 : 8, K, V, VALS>), dim3(cus), dim3(1024), 0,
-                       stream, arrays, t.lists, t.leaves, in_place);
+                       stream, arrays, t.lists, t.leaves, in_place, t.table, words, sub ? &words->error : &P.header->error);
     prof_mark(stream, RT_KIND_SEG_SMALL);
 }
 
@@ -117,6 +122,11 @@ struct SplitSortLayout {
     size_t offsets, seg, total;
     SegLayout first, second;
 };
+// Where the error word of a sort of n items lies.
+inline size_t split_sort_error_at(const SplitSortLayout &S, bool two_passes) {
+    const SegLayout &L = two_passes ? S.second : S.first;
+    return S.seg + L.status + 2 * L.status_pass + offsetof(LeafLists, words) + offsetof(GridWords, error);
+}
 inline SplitSortLayout make_split_sort_layout(size_t n, int block, int ipt) {
     SplitSortLayout S{};
     SegClassTable t = seg_class_table();
@@ -130,6 +140,11 @@ inline SplitSortLayout make_split_sort_layout(size_t n, int block, int ipt) {
     return S;
 }
 
+template <typename K>
+inline int split_sort_passes(size_t n) {
+    return n <= kBuckets * leaf_aim<K>() ? 1 : 2;
+}
+
 // Sorts n items of keys/vals in place (2 <= n <= kSplitTwoMax64): one pass
 // where its buckets are leaves as they come.
 template <typename K, typename V, bool VALS>
@@ -137,7 +152,7 @@ void launch_split_sort(K *keys, V *vals, uint32_t n, K *tk, V *tv, const SplitSo
                        hipStream_t stream) {
     uint32_t *off = reinterpret_cast<uint32_t *>(ws + S.offsets);
     char *seg = ws + S.seg;
-    const int passes = n <= kBuckets * leaf_aim<K>() ? 1 : 2;
+    const int passes = split_sort_passes<K>(n);
     prof_begin(stream);
     for (int pass = 0; pass < passes; ++pass) {
         const SegLayout &L = pass == 0 ? S.first : S.second;

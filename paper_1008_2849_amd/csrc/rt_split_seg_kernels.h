@@ -62,7 +62,7 @@ struct LeafArrays {
 };
 // Leaf classes (kLeafClasses): what 256-thread blocks hold (17 items a thread;
 // 16 of 64-bit keys, so that three such blocks fit a CU's LDS), what the
-// largest blocks hold, longer ones.
+// largest blocks hold, longer ones, ones for the whole grid.
 template <typename K>
 constexpr int leaf_ipt() {
     return sizeof(K) == 4 ? 17 : 16;
@@ -454,7 +454,7 @@ __global__ __launch_bounds__(256) void k_split_starts(const SegDesc *__restrict_
                     if (at < lists->capacity)
                         leaves[at] = SplitLeaf{at_k + start + i, at_tk + start + i, min(small, c - i), 1u};
             } else if (c >= (all ? 1u : 2u)) {
-                q = c <= small ? 0 : c <= leaf_max<K>() ? 1 : 2;
+                q = c <= small ? 0 : c <= leaf_max<K>() ? 1 : c <= kAloneMax ? 2 : 3;
             }
 #pragma unroll
             for (int i = 0; i < kLeafClasses; ++i) {
@@ -725,13 +725,16 @@ __global__ __launch_bounds__(BLOCK, sizeof(K) == 4 ? 4 : 3) void k_split_leaves(
 }
 
 // The other leaves: those the largest blocks hold, as above; longer ones are
-// sorted by one block through global memory.
+// sorted by one block through global memory, and those above kAloneMax by the
+// whole grid (2^22 64-bit pairs, nearly all in one leaf: 1.0 ms a sort, 77 by
+// one block).
 template <int BLOCK, int IPT, typename K, typename V, bool VALS>
 __global__ __launch_bounds__(BLOCK) void k_split_long_leaves(LeafArrays<K, V> a, const LeafLists *__restrict__ lists,
-                                                             const SplitLeaf *__restrict__ leaves, int in_place) {
+                                                             const SplitLeaf *__restrict__ leaves, int in_place,
+                                                             uint32_t *table, GridWords *words, uint32_t *error) {
     __shared__ BlockSortLds<BLOCK, IPT, K, V, VALS> lds;
     static_assert(BLOCK * IPT == leaf_max<K>(), "the largest leaf");
-    for (int which = 1; which < kLeafClasses; ++which) {
+    for (int which = 1; which < 3; ++which) {
         const uint32_t count = min(lists->count[which], lists->capacity);
         const SplitLeaf *list = leaves + static_cast<size_t>(which) * lists->capacity;
         for (uint32_t e = blockIdx.x; e < count; e += gridDim.x) {
@@ -755,6 +758,21 @@ __global__ __launch_bounds__(BLOCK) void k_split_long_leaves(LeafArrays<K, V> a,
             }
         }
     }
+    // (fewer than 2^30 items, so fewer than that; their first tiles take the place of the block sort's words)
+    constexpr uint32_t MAX = (1u << 30) / kAloneMax;
+    static_assert(sizeof(lds.b.word) >= (MAX + 1) * sizeof(uint32_t), "room for the first tiles");
+    const uint32_t longs = min(min(lists->count[3], lists->capacity), MAX);
+    if (longs == 0) return;
+    const SplitLeaf *list = leaves + 3 * static_cast<size_t>(lists->capacity);
+    const auto leaf = [&](uint32_t i) {
+        const SplitLeaf l = list[i];
+        LongLeaf<K, V> x{a.k + l.at_k, VALS ? a.v + l.at_k : nullptr, a.tk + l.at_tk, VALS ? a.tv + l.at_tk : nullptr, l.n, 1u};
+        if (in_place) x = LongLeaf<K, V>{x.tk, x.tv, x.k, x.v, l.n, 0u};
+        return x;
+    };
+    __syncthreads();
+    grid_sort_long<BLOCK, K, V, VALS>(leaf, longs, reinterpret_cast<uint32_t *>(lds.b.word), table, words, error,
+                                      lds.whist, lds.wsum);
 }
 
 // The segments of a pass of the two-pass sort, in one block: offsets off[0..
@@ -798,8 +816,8 @@ __global__ __launch_bounds__(256) void k_split_segments(const uint32_t *__restri
         h->count[kSegLarge] = at + listed;
         h->total_tiles = t0 + tiles;
     }
-    if (s < kLeafClasses) leaf_lists->count[s] = 0u;
-    if (s == kLeafClasses) leaf_lists->capacity = leaf_capacity;
+    if (s < kLeafListsZero) reinterpret_cast<uint32_t *>(leaf_lists)[s] = 0u;
+    if (s == kLeafListsZero) leaf_lists->capacity = leaf_capacity;
 }
 
 }  // namespace rt

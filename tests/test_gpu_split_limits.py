@@ -8,7 +8,8 @@ import paper_1008_2849_amd as rts
 from paper_1008_2849_amd import inputs
 from paper_1008_2849_amd._lib import RT_ERR_INVALID_ARG, RtError
 from gpu_util import announce, sync, to_dev, to_host
-from test_gpu_split import sample_positions
+from test_gpu_split import keys_of, sample_positions
+from test_gpu_split_large import missed
 
 pytestmark = pytest.mark.gpu
 
@@ -187,3 +188,64 @@ def test_method_of_a_batched_call(sizes, splitters, digits):
     kinds = {kind for kind, _ in rts.profile_stop()}
     assert (10 in kinds) == splitters and (17 in kinds) == digits, kinds
     assert np.array_equal(to_host(k), keys[order]) and np.array_equal(to_host(v), order.astype(np.uint32))
+
+
+def timed(call):
+    """Milliseconds of a call, the second of two."""
+    import torch
+    for _ in range(2):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        call()
+        b.record()
+        sync()
+    return a.elapsed_time(b)
+
+
+@pytest.mark.parametrize("with_values", [True, False])
+@pytest.mark.parametrize("n", [(1 << 18) + 5, 1 << 20])
+def test_keys_the_sample_misses(n, with_values):
+    """Nearly all keys in one bucket, which the whole grid sorts: the result,
+    and a time that one block alone does not reach (9 ms at 2^20)."""
+    import torch
+    announce(f"missed by the sample, n={n} values={with_values}")
+    keys, vals = keys_of("missed", n, 31, np.uint32), inputs.index_values(n)
+    order = np.argsort(keys, kind="stable")
+    k0, v0 = to_dev(keys), to_dev(vals)
+    k, v = torch.empty_like(k0), torch.empty_like(v0) if with_values else None
+
+    def call():
+        k.copy_(k0)
+        if with_values:
+            v.copy_(v0)
+        rts.sort_ex(k, v, rts.Config(flags=4))
+    ms = timed(call)
+    assert np.array_equal(to_host(k), keys[order])
+    assert not with_values or np.array_equal(to_host(v), order.astype(np.uint32))
+    print(f"{ms:.3f} ms", flush=True)
+    assert ms < 4.0
+
+
+@pytest.mark.parametrize("vdt", [None, np.int32, np.int64])
+def test_64_bit_keys_both_samples_miss(vdt):
+    import torch
+    n = (1 << 22) + 11
+    announce(f"64-bit keys missed by both samples, n={n} values={vdt}")
+    keys = missed(n, 3, 2048, True)
+    order = np.argsort(keys, kind="stable")
+    k0 = torch.from_numpy(keys.view(np.int64).copy()).cuda()
+    k, v = torch.empty_like(k0), None
+    if vdt is not None:
+        v0 = torch.arange(n, device="cuda").to(torch.int32 if vdt == np.int32 else torch.int64)
+        v = torch.empty_like(v0)
+
+    def call():
+        k.copy_(k0)
+        if v is not None:
+            v.copy_(v0)
+        rts.sort64_ex(k, v, rts.Config(flags=4))
+    ms = timed(call)
+    assert np.array_equal(k.cpu().numpy().view(np.uint64), keys[order])
+    assert v is None or np.array_equal(v.cpu().numpy(), order.astype(vdt))
+    print(f"{ms:.3f} ms", flush=True)
+    assert ms < 20.0  # one block alone: 77 ms
