@@ -154,7 +154,7 @@ static void launch_seg_sort_body(const SegPointers &P, const SegLayout &L, uint3
                                  hipStream_t stream) {
     const uint32_t cus = static_cast<uint32_t>(device_cu_count());
     uint32_t *large_list = P.lists + static_cast<size_t>(kSegLarge) * list_stride;
-    hipLaunchKernelGGL(k_seg_tiles, dim3(1), dim3(1024), 0, stream, P.descs, large_list, nullptr, P.first_tile, P.header,
+    hipLaunchKernelGGL(k_seg_tiles<false>, dim3(1), dim3(1024), 0, stream, P.descs, large_list, nullptr, P.first_tile, P.header,
                        L.large_capacity, L.max_tiles, L.tile, nullptr, 0u);
     hipLaunchKernelGGL(k_seg_tilemap, dim3(cap_grid((L.max_tiles + 255) / 256, cus * 4)), dim3(256), 0, stream,
                        P.descs, large_list, P.first_tile, P.header, P.tile_seg, nchunks);
@@ -275,7 +275,7 @@ void launch_batched(uint32_t *keys, uint32_t *vals, const uint32_t *offsets, uin
                        P.header, kSplitSegMax);
     if (L.large_capacity > 0) {
         const SplitTables t = split_tables(ws, L);
-        hipLaunchKernelGGL(k_seg_tiles, dim3(1), dim3(1024), 0, stream, P.descs,
+        hipLaunchKernelGGL(k_seg_tiles<true>, dim3(1), dim3(1024), 0, stream, P.descs,
                            P.lists + static_cast<size_t>(kSegLarge) * num_segments,
                            P.lists + static_cast<size_t>(kSegHuge) * num_segments,
                            P.first_tile, P.header, L.large_capacity, L.max_tiles, L.tile, t.lists, t.leaf_capacity);

@@ -129,15 +129,16 @@ constexpr uint32_t kLeafListsZero = kLeafClasses + 3;  // words that start at ze
 // is cut to what the workspace holds (or emptied) and the error is raised,
 // so that no later kernel indexes past the tables.
 //
-// leaf_lists set (a call of splitter passes): also empties them, and the same
-// for the segments of the digit passes (h->digit_*).  These are the huge ones;
+// DIGIT_LISTS (a call of splitter passes): also empties the leaf lists, and the
+// same for the segments of the digit passes (h->digit_*).  These are the huge ones;
 // if those hold three quarters of the tiles or more, or a quarter of few
 // tiles, every tiled segment, because the two methods run one after the other
 // and each has launches that little work does not fill.  12 segments of 2^6 to
 // 2^22 ANDs of four words: 300 us by both, 224 by digit passes; 20 of 2^10 to
 // 2^23 spread keys: 748 and 659; 50 of 2^6 to 2^22: 463 and 529.
 constexpr uint32_t kFewTiles = 256;
-static __global__ __launch_bounds__(1024) void k_seg_tiles(const SegDesc *__restrict__ descs,
+template <bool DIGIT_LISTS>
+__global__ __launch_bounds__(1024) void k_seg_tiles(const SegDesc *__restrict__ descs,
                                                            const uint32_t *__restrict__ list,
                                                            const uint32_t *__restrict__ list_end,
                                                            uint32_t *__restrict__ first_tile, SegHeader *__restrict__ h,
@@ -153,12 +154,13 @@ static __global__ __launch_bounds__(1024) void k_seg_tiles(const SegDesc *__rest
         const uint32_t per = (count + 1023u) / 1024u;
         const uint32_t lo = min(count, tid * per), hi = min(count, lo + per);
         uint32_t sum = 0;  // at most 256 entries of at most 2^19 tiles: no overflow
-        for (uint32_t i = lo; i < hi; ++i) sum += (descs[seg_entry(list, list_end, large, i)].n + tile - 1) / tile;
+        const auto entry = [&](uint32_t i) { return DIGIT_LISTS ? seg_entry(list, list_end, large, i) : list[i]; };
+        for (uint32_t i = lo; i < hi; ++i) sum += (descs[entry(i)].n + tile - 1) / tile;
         // saturate, so the block total stays exact up to max_tiles and cannot wrap
         uint32_t run = block_exclusive_sum<1024>(min(sum, max_tiles + 1u), s_wsum[which]);
         for (uint32_t i = lo; i < hi; ++i) {
             first[i] = start + run;
-            run += (descs[seg_entry(list, list_end, large, i)].n + tile - 1) / tile;
+            run += (descs[entry(i)].n + tile - 1) / tile;
         }
         if (tid == 1023) {
             first[count] = start + run;
@@ -167,18 +169,27 @@ static __global__ __launch_bounds__(1024) void k_seg_tiles(const SegDesc *__rest
         __syncthreads();
         return s_total[which];
     };
-    const uint32_t listed = h->count[kSegLarge], huge_listed = h->count[kSegHuge];
-    uint32_t large = min(listed, large_capacity), huge = min(huge_listed, large_capacity);
-    bool fits = listed == large && huge_listed == huge;
-    if (leaf_lists != nullptr) {
-        if (tid < kLeafListsZero) reinterpret_cast<uint32_t *>(leaf_lists)[tid] = 0u;
-        if (tid == kLeafListsZero) leaf_lists->capacity = leaf_capacity;
-    }
+    const uint32_t listed = h->count[kSegLarge];
+    uint32_t large = min(listed, large_capacity);
+    bool fits = listed == large;
     uint32_t tiles = number(large, large, first_tile, 0u, 0);
     if (tiles > max_tiles) {
         fits = false;
         large = tiles = 0u;
     }
+    if constexpr (!DIGIT_LISTS) {
+        if (tid == 0) {
+            h->count[kSegLarge] = large;
+            h->total_tiles = tiles;
+            if (!fits) atomicOr(&h->error, kSegErrBounds);
+        }
+        return;
+    }
+    if (tid < kLeafListsZero) reinterpret_cast<uint32_t *>(leaf_lists)[tid] = 0u;
+    if (tid == kLeafListsZero) leaf_lists->capacity = leaf_capacity;
+    const uint32_t huge_listed = h->count[kSegHuge];
+    uint32_t huge = min(huge_listed, large_capacity);
+    fits = fits && huge_listed == huge;
     uint32_t digit_first = 0, digit_large = 0, digit_tiles = 0;
     if (huge > 0u) {
         digit_first = large;  // (the entry that ends one list begins the other)

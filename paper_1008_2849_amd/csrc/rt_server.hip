@@ -329,7 +329,7 @@ rt_status enqueue_step(rt_server *s, StepSlot &slot, const StepPlan &P) {
     if (P.fresh_tiled) {  // histograms and prefix sums of fresh tiled requests
         hipLaunchKernelGGL(k_srv_clear_rows, dim3(grid(P.fresh_tiled, cus * 4)), dim3(256), 0, st, d_descs, d_hlist,
                            d_hh, d_hist);
-        hipLaunchKernelGGL(k_seg_tiles, dim3(1), dim3(1024), 0, st, d_descs, d_hlist, nullptr, d_first_h, d_hh, stride,
+        hipLaunchKernelGGL(k_seg_tiles<false>, dim3(1), dim3(1024), 0, st, d_descs, d_hlist, nullptr, d_first_h, d_hh, stride,
                            m.max_tiles, static_cast<uint32_t>(kSegTile), nullptr, 0u);
         hipLaunchKernelGGL(k_seg_tilemap, dim3(grid((P.tiles + 255) / 256, cus * 4)), dim3(256), 0, st, d_descs,
                            d_hlist, d_first_h, d_hh, d_seg_h, 1u);
@@ -342,7 +342,7 @@ rt_status enqueue_step(rt_server *s, StepSlot &slot, const StepPlan &P) {
     if (P.tiled) {  // one pass of every tiled request, each at its own pass
         hipLaunchKernelGGL(k_fill_zero, dim3(grid((P.tiles * kSegRadix + 4095) / 4096, 4096)), dim3(256), 0, st,
                            d_status, P.tiles * kSegRadix, nullptr);
-        hipLaunchKernelGGL(k_seg_tiles, dim3(1), dim3(1024), 0, st, d_descs, d_plist, nullptr, d_first_p, d_hp, stride,
+        hipLaunchKernelGGL(k_seg_tiles<false>, dim3(1), dim3(1024), 0, st, d_descs, d_plist, nullptr, d_first_p, d_hp, stride,
                            m.max_tiles, static_cast<uint32_t>(kSegTile), nullptr, 0u);
         // XCD chunks when the step's tiled requests are long (see seg_chunk_count)
         const uint32_t nchunks = seg_chunk_count(P.tiles * kSegTile, P.tiled, kSegTile);

@@ -444,12 +444,42 @@ __device__ __forceinline__ void block_sort_global(K *a_k, V *a_v, K *b_k, V *b_v
     __syncthreads();
 }
 
+// The arguments of k_split_leaf, as they lie in memory (pointers, one after the
+// other).
+template <typename K, typename V>
+struct SplitLeafArgs {
+    K *tk;
+    V *tv;
+    K *keys;
+    V *vals;
+    const K *splitters;
+    const uint32_t *starts;
+    uint32_t *table;
+    GridWords *words;
+};
+
+// The kernel's arguments, from its first on, read again: what follows a long
+// phase then keeps no registers through it (with them, the leaves' sort spilled
+// twice as many and took 1 to 4 us longer).
+template <typename T>
+__device__ __forceinline__ T reread_args() {
+    static_assert(sizeof(T) % 8 == 0, "read in 8-byte words");
+    typedef const __attribute__((address_space(4))) uint64_t ct;
+    ct *p = (ct *)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(p));
+    uint64_t w[sizeof(T) / 8];
+#pragma unroll
+    for (uint32_t i = 0; i < sizeof(T) / 8; ++i) w[i] = p[i];
+    T x;
+    __builtin_memcpy(&x, w, sizeof x);
+    return x;
+}
+
 // Sorts bucket blockIdx.x of the temporary arrays into the caller's.
 template <int BLOCK, int IPT, typename K, typename V, bool VALS>
 __global__ __launch_bounds__(BLOCK) void k_split_leaf(K *__restrict__ tk, V *__restrict__ tv, K *__restrict__ keys,
                                                       V *__restrict__ vals, const K *__restrict__ splitters,
-                                                      const uint32_t *__restrict__ starts, uint32_t *table,
-                                                      GridWords *words) {
+                                                      const uint32_t *__restrict__ starts, uint32_t *, GridWords *) {
     constexpr uint32_t CAP = BLOCK * IPT;
     __shared__ BlockSortLds<BLOCK, IPT, K, V, VALS> lds;
     // buckets of one value, and buckets for the whole grid
@@ -471,9 +501,7 @@ __global__ __launch_bounds__(BLOCK) void k_split_leaf(K *__restrict__ tk, V *__r
     }
     const uint32_t first = starts[b], m = starts[b + 1] - first;
     __syncthreads();
-    uint32_t longs = 0;
-    for (int q = 0; q < kBuckets / 64; ++q) {
-        longs += static_cast<uint32_t>(__popcll(long_mask[q]));
+    for (int q = 0; q < kBuckets / 64; ++q)
         for (uint64_t mask = big_mask[q]; mask != 0; mask &= mask - 1u) {
             const uint32_t x = q * 64 + __builtin_ctzll(mask);
             const uint32_t e = starts[x + 1];
@@ -482,7 +510,6 @@ __global__ __launch_bounds__(BLOCK) void k_split_leaf(K *__restrict__ tk, V *__r
                 if constexpr (VALS) vals[i] = tv[i];
             }
         }
-    }
     if (m != 0 && m <= CAP) {
         block_sort<BLOCK, IPT, K, V, VALS>(ArraySource<K, V>{tk + first, VALS ? tv + first : nullptr}, m,
                                            ArraySink<K, V, VALS>{keys + first, VALS ? vals + first : nullptr}, false,
@@ -495,7 +522,10 @@ __global__ __launch_bounds__(BLOCK) void k_split_leaf(K *__restrict__ tk, V *__r
         block_sort_global<BLOCK, K, V, VALS>(keys + first, VALS ? vals + first : nullptr, tk + first,
                                              VALS ? tv + first : nullptr, m, lds.whist, lds.wsum);
     }
+    uint32_t longs = 0;
+    for (int q = 0; q < kBuckets / 64; ++q) longs += static_cast<uint32_t>(__popcll(long_mask[q]));
     if (longs == 0) return;
+    const SplitLeafArgs<K, V> g = reread_args<SplitLeafArgs<K, V>>();
     const auto leaf = [&](uint32_t i) {
         uint32_t x = 0;  // the i-th long bucket
         for (int q = 0; q < kBuckets / 64; ++q) {
@@ -508,11 +538,12 @@ __global__ __launch_bounds__(BLOCK) void k_split_leaf(K *__restrict__ tk, V *__r
             }
             i -= c;
         }
-        const uint32_t at = starts[x];
-        return LongLeaf<K, V>{keys + at, VALS ? vals + at : nullptr, tk + at, VALS ? tv + at : nullptr, starts[x + 1] - at, 1u};
+        const uint32_t at = g.starts[x];
+        return LongLeaf<K, V>{g.keys + at, VALS ? g.vals + at : nullptr, g.tk + at, VALS ? g.tv + at : nullptr,
+                              g.starts[x + 1] - at, 1u};
     };
     __syncthreads();
-    grid_sort_long<BLOCK, K, V, VALS>(leaf, longs, lds.b.bin, table, words, &words->error, lds.whist, lds.wsum);
+    grid_sort_long<BLOCK, K, V, VALS>(leaf, longs, lds.b.bin, g.table, g.words, &g.words->error, lds.whist, lds.wsum);
 }
 
 }  // namespace rt
