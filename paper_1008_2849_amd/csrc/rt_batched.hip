@@ -242,7 +242,8 @@ static void launch_batched_body(uint32_t *keys, uint32_t *vals, const SegPointer
     static_assert(T::ITEMS == kSegTile, "the tile map is made for these tiles");
     if (L.large_capacity > 0)
         launch_split_pass<T, uint32_t, uint32_t, VALS>(P, L, num_segments, SplitEnd::kLeavesBack, nullptr,
-                                                    LeafArrays<uint32_t, uint32_t>{keys, vals, P.tk, P.tv}, ws, stream);
+                                                    LeafArrays<uint32_t, uint32_t>{keys, vals, P.tk, P.tv}, ws, stream,
+                                                    &P.header->error);
     if (L.capacity <= kSplitSegMax) return;
     const uint32_t cus = static_cast<uint32_t>(device_cu_count());
     hipLaunchKernelGGL(k_seg_digit_map, dim3(cus * 4), dim3(256), 0, stream, P.descs,

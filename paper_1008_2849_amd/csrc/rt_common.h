@@ -245,17 +245,26 @@ void launch_split64(uint64_t *keys, uint32_t *vals, uint32_t value_words, uint32
 //
 // The lines are where keys of all eight digits gain whatever their
 // distribution.  Two passes do not gain where the digit passes skip five of
-// eight, which only a pass over the keys can tell.  They end where the mean
+// eight (the table is without the choice below).  They end where the mean
 // of their at most 65536 leaves (2^28: 4096 items) still leaves uneven cuts
 // room in the largest leaf (8192): above, leaves that no LDS holds are sorted
 // through global memory.
 constexpr size_t kSplitOneMax64 = 256 * 2344;  // uneven leaves (18 percent) then fit: at 700000 ANDs of two took 186, not 165
 constexpr size_t kSplitTwoMin64 = static_cast<size_t>(1) << 22;
 constexpr size_t kSplitTwoMax64 = static_cast<size_t>(1) << 28;
+// From here a sample of the keys chooses: keys that differ in at most
+// kNarrowBytes of their bytes take the digit passes.  The launches of both
+// methods are made, and those not chosen find nothing to do: 55 us of 2870 for
+// spread keys at 2^27, 90 of 2440 for keys below 2^20 (2820 by splitter passes;
+// 2^28: 4820 and 6490).  Below, spread keys would lose more by it than such keys gain.
+constexpr size_t kSplitGateMin64 = static_cast<size_t>(1) << 27;
+constexpr uint32_t kNarrowBytes = 3;
 size_t split_large_scratch_bytes64(size_t n, uint32_t value_words);
 size_t split_large_error_at64(size_t n, uint32_t value_words);
+// gate: they run if it is zero (see k_narrow_probe), or NULL; error: their
+// error word, or NULL (it is in the scratch then).
 void launch_split_large64(uint64_t *keys, uint32_t *vals, uint32_t value_words, uint32_t n, uint64_t *tk, uint32_t *tv,
-                          char *scratch, hipStream_t stream);
+                          char *scratch, hipStream_t stream, const uint32_t *gate, uint32_t *error);
 // Whether cfg leaves the method to the library: no digits, shape or flags
 // but RT_FLAG_VALIDATE.
 bool default_method(const rt_config *cfg);

@@ -64,6 +64,8 @@ struct PlanArgs {
     uint32_t *cbase;                  // kMaxPasses * kChunks * kChunkRadix words (chunked sorts)
     uint32_t *chunk_ctr;              // kMaxPasses * kChunks tile counters, or NULL (no chunk fields)
     const uint32_t *mode;             // with chunked: nonzero if the probe chose per-chunk counts (NULL: chosen)
+    uint32_t *gate;                   // whether any pass runs, or NULL (see k_narrow_probe)
+    uint32_t gate_passes;
     uint32_t *user_k;
     uint32_t *user_v;
     uint32_t *t1_k;

@@ -158,9 +158,11 @@ __device__ __forceinline__ void status_store(S *p, S v) {
 // fill
 // ---------------------------------------------------------------------------
 
-// one (if set): a word that starts at 1.
+// one (if set): a word that starts at 1.  gate: see k_narrow_probe.
 static __global__ __launch_bounds__(256) void k_fill_zero(uint32_t *__restrict__ p, size_t words,
-                                                          uint32_t *__restrict__ one = nullptr) {
+                                                          uint32_t *__restrict__ one = nullptr,
+                                                          const uint32_t *__restrict__ gate = nullptr) {
+    if (gate != nullptr && *gate == 0u) return;
     if (one != nullptr && blockIdx.x == 0 && threadIdx.x == 0) *one = 1u;
     const size_t stride = static_cast<size_t>(gridDim.x) * 256;
     for (size_t i = static_cast<size_t>(blockIdx.x) * 256 + threadIdx.x; i < words; i += stride)
@@ -351,7 +353,9 @@ __device__ __forceinline__ T wave_reduce(T v, F op) {
 // reason: one block for all passes, one after the other, took 27 us.
 template <int BLOCK, typename K = uint32_t>
 __global__ __launch_bounds__(BLOCK) void k_chunk_probe(const K *__restrict__ keys, uint32_t n, HistArgs ha,
-                                                       uint32_t *__restrict__ mode) {
+                                                       uint32_t *__restrict__ mode,
+                                                       const uint32_t *__restrict__ gate = nullptr) {
+    if (gate != nullptr && *gate == 0u) return;
     constexpr int WAVES = BLOCK / 64;
     constexpr int RUNS = static_cast<int>(kProbeSamples / 64);
     constexpr int PER = RUNS / WAVES;  // runs per wave = keys per lane
@@ -478,6 +482,9 @@ __device__ inline void plan_chunks(const PlanArgs &a, bool chunked, const uint32
 // all items fall in one chunk, so the rule holds for skipped passes too.)
 // Chunk x's output slot of digit d is the digit's start plus the counts of
 // d in chunks 0..x-1.  Without a.chunked every pass is one chunk.
+//
+// a.gate set (see k_narrow_probe): no pass runs if it is closed, or the counts
+// show more than a.gate_passes to run, and then it is closed here.
 static __global__ __launch_bounds__(256) void k_plan(PlanArgs a, const uint32_t *__restrict__ hist,
                                               uint32_t *__restrict__ base, SortPlan *__restrict__ plan,
                                               uint32_t *__restrict__ tile_counters, uint32_t direct) {
@@ -495,6 +502,11 @@ static __global__ __launch_bounds__(256) void k_plan(PlanArgs a, const uint32_t 
     if (tid == kMaxPasses) tile_counters[kMaxPasses] = 0u;  // the error word
     if (a.chunk_ctr != nullptr)
         for (uint32_t i = tid; i < kMaxPasses * kChunks; i += 256) a.chunk_ctr[i] = 0u;
+    if (a.gate != nullptr && *a.gate == 0u) {
+        if (tid < kMaxPasses) plan->pass[tid].active = 0u;
+        if (tid == 0) plan->executed = plan->copy_back = 0u;
+        return;
+    }
     uint32_t c[kMaxPasses][8];  // bins 8t..8t + 7, or chunks 0..7 of digit t
     static_assert(kChunks == 8, "a digit's chunk counts take a thread's bins");
 #pragma unroll
@@ -551,6 +563,10 @@ static __global__ __launch_bounds__(256) void k_plan(PlanArgs a, const uint32_t 
     uint32_t active = 0;  // bit p: pass p runs
     for (uint32_t p = 0; p < a.num_passes; ++p)
         if (direct || a.no_skip || !s_constant[p]) active |= 1u << p;
+    if (a.gate != nullptr && static_cast<uint32_t>(__popc(active)) > a.gate_passes) {
+        active = 0u;
+        if (tid == 0) *a.gate = 0u;
+    }
     const uint32_t executed = static_cast<uint32_t>(__popc(active));
     // Buffers: U = caller's arrays, A/B = temporaries.  The last executed pass
     // must write U: an even count alternates U->A->U...; an odd count >= 3
@@ -1101,8 +1117,11 @@ __device__ __forceinline__ void onesweep_tile(const TileJob<K, V> &job,
 // first and last tile can be partial.  The grid needs ctile[nchunks]
 // blocks; surplus blocks find every chunk exhausted and exit.  The plan's
 // pointers are reinterpreted as K keys and V values.
+//
+// PERSIST: the block claims tiles until none is left, for passes that mostly
+// do not run: a block per CU then starts to find that out, not one per tile.
 template <int BITS, int BLOCK, int IPT, typename K, typename V, bool VALS, bool NT, typename S, bool STAGE,
-          bool FUSED = false, bool SEQ = false>
+          bool FUSED = false, bool SEQ = false, bool PERSIST = false>
 __device__ __forceinline__ void onesweep_pass(OnesweepLds<BITS, BLOCK, IPT, K, V, VALS, FUSED, SEQ> &lds,
                                               const SortPlan *__restrict__ plan, int pass, uint32_t n,
                                               S *__restrict__ status, uint32_t *__restrict__ chunk_counter,
@@ -1113,31 +1132,35 @@ __device__ __forceinline__ void onesweep_pass(OnesweepLds<BITS, BLOCK, IPT, K, V
     constexpr bool SMALL = sizeof(S) == 4 && sizeof(K) == 4 && sizeof(V) == 4;
     const PassPlan *pp = plan->pass + pass;
     if (!pp->active) return;
-    // this wave's digit counters start at zero (and the fused counts)
-    for (uint32_t i = threadIdx.x & 63u; i < RADIX; i += 64) lds.whist[(threadIdx.x >> 6) * RADIX + i] = 0u;
-    if constexpr (FUSED)
-        for (uint32_t i = threadIdx.x; i < static_cast<uint32_t>(kFusedBins); i += BLOCK) lds.fused[i] = 0u;
-    if (threadIdx.x == 0)
-        claim_tile<TILE>(pp, chunk_counter, lds.claim[0], lds.claim[1], lds.claim[2], lds.claim[3], lds.claim[4]);
-    __syncthreads();
-    if (lds.claim[0] == kNoTile) return;
-    TileJob<K, V> job;
-    job.src_k = reinterpret_cast<const K *>(pp->src_k);
-    job.src_v = reinterpret_cast<const V *>(pp->src_v);
-    job.dst_k = reinterpret_cast<K *>(pp->dst_k);
-    job.dst_v = reinterpret_cast<V *>(pp->dst_v);
-    job.base = pp->cbase + lds.claim[2] * kChunkRadix;
-    job.item0 = lds.claim[3];
-    job.shift = pp->shift;
-    job.width = pp->width;
-    job.tile = lds.claim[0];
-    job.first = lds.claim[1];
-    job.valid = lds.claim[4];
-    job.bound = n;
-    job.next_hist = FUSED ? hist + (pass + 1) * kMaxRadix : nullptr;
-    job.next_shift = FUSED ? plan->pass[pass + 1].shift : 0u;
-    job.next_width = FUSED ? plan->pass[pass + 1].width : 0u;
-    onesweep_tile<BITS, BLOCK, IPT, K, V, VALS, NT, S, STAGE, SMALL, FUSED, SEQ>(job, lds, status, error_flag);
+    for (;;) {
+        // this wave's digit counters start at zero (and the fused counts)
+        for (uint32_t i = threadIdx.x & 63u; i < RADIX; i += 64) lds.whist[(threadIdx.x >> 6) * RADIX + i] = 0u;
+        if constexpr (FUSED)
+            for (uint32_t i = threadIdx.x; i < static_cast<uint32_t>(kFusedBins); i += BLOCK) lds.fused[i] = 0u;
+        if (threadIdx.x == 0)
+            claim_tile<TILE>(pp, chunk_counter, lds.claim[0], lds.claim[1], lds.claim[2], lds.claim[3], lds.claim[4]);
+        __syncthreads();
+        if (lds.claim[0] == kNoTile) return;
+        TileJob<K, V> job;
+        job.src_k = reinterpret_cast<const K *>(pp->src_k);
+        job.src_v = reinterpret_cast<const V *>(pp->src_v);
+        job.dst_k = reinterpret_cast<K *>(pp->dst_k);
+        job.dst_v = reinterpret_cast<V *>(pp->dst_v);
+        job.base = pp->cbase + lds.claim[2] * kChunkRadix;
+        job.item0 = lds.claim[3];
+        job.shift = pp->shift;
+        job.width = pp->width;
+        job.tile = lds.claim[0];
+        job.first = lds.claim[1];
+        job.valid = lds.claim[4];
+        job.bound = n;
+        job.next_hist = FUSED ? hist + (pass + 1) * kMaxRadix : nullptr;
+        job.next_shift = FUSED ? plan->pass[pass + 1].shift : 0u;
+        job.next_width = FUSED ? plan->pass[pass + 1].width : 0u;
+        onesweep_tile<BITS, BLOCK, IPT, K, V, VALS, NT, S, STAGE, SMALL, FUSED, SEQ, PERSIST>(job, lds, status, error_flag);
+        if constexpr (!PERSIST) return;
+        __syncthreads();  // the tile is out of the LDS before the next claim
+    }
 }
 
 // The pass over 32-bit keys (with 32-bit values when VALS).  FUSED: the

@@ -162,8 +162,9 @@ Layout64 make_layout64(size_t n, const Resolved &r, uint32_t value_words) {
     }
     off = align256(off);
     L.status_bytes = off - L.status;
-    // tile counters, the error word, kChunks tile counters per pass, the probe's choice
-    L.ctr = off;   off += align256(sizeof(uint32_t) * (kMaxPasses + 2 + kMaxPasses * kChunks));
+    // tile counters, the error word, kChunks tile counters per pass, the
+    // probe's choice, the gate
+    L.ctr = off;   off += align256(sizeof(uint32_t) * (kMaxPasses + 3 + kMaxPasses * kChunks));
     L.base = off;  off += align256(sizeof(uint32_t) * kMaxPasses * kMaxRadix);
     L.cbase = off; off += align256(sizeof(uint32_t) * kMaxPasses * kChunks * kChunkRadix);
     L.plan = off;  off += align256(sizeof(SortPlan));
@@ -212,7 +213,7 @@ void launch_histogram64_chunked(const uint64_t *keys, uint32_t n, const HistArgs
 
 template <int CC>
 void launch_histogram64_auto(const uint64_t *keys, uint32_t n, const HistArgs &hp, const HistArgs &hc,
-                             const uint32_t *mode, uint32_t *hist, hipStream_t stream) {
+                             const uint32_t *mode, uint32_t *hist, hipStream_t stream, const uint32_t *gate) {
     constexpr int kBlock = 512, kCP = 8;
     const size_t lds = std::max(static_cast<size_t>(kCP) * (hp.total_bins + 1),
                                 static_cast<size_t>(CC) * (hc.total_bins + 1)) * sizeof(uint32_t);
@@ -223,7 +224,7 @@ void launch_histogram64_auto(const uint64_t *keys, uint32_t n, const HistArgs &h
     });
     const uint32_t grid = grid_for(n, 4096, static_cast<uint32_t>(device_cu_count()) * 4);
     hipLaunchKernelGGL((k_histogram64_auto<kBlock, kCP, CC>), dim3(grid), dim3(kBlock), lds, stream, keys, n, hp, hc,
-                       mode, hist);
+                       mode, hist, gate);
 }
 
 template <int C>
@@ -242,10 +243,22 @@ void launch_histogram64_copies(const uint64_t *keys, uint32_t n, const HistArgs 
 
 template <int BITS, int BLOCK, int IPT>
 void launch_pass64_shape(const Layout64 &L, uint32_t vw, hipStream_t stream, const SortPlan *plan, int pass,
-                         uint32_t n, void *status, uint32_t *ctr) {
+                         uint32_t n, void *status, uint32_t *ctr, bool gated) {
     const dim3 grid(L.grid_tiles), block(BLOCK);
     uint32_t *err = ctr + kMaxPasses;
     uint32_t *chunk_ctr = ctr + kMaxPasses + 1 + pass * kChunks;
+    if constexpr (BITS == 8 && BLOCK == 1024 && IPT >= 12) {  // the default's shapes
+        if (gated && !L.wide_status) {
+            const dim3 few(std::min<uint32_t>(L.grid_tiles, static_cast<uint32_t>(device_cu_count())));
+#define RT_OS64_GATED(V)                                                                                             \
+    hipLaunchKernelGGL((k_onesweep64<BITS, BLOCK, IPT, V, uint32_t, true>), few, block, 0, stream, plan, pass, n, \
+                       static_cast<uint32_t *>(status), chunk_ctr, err)
+            if (vw == 2) RT_OS64_GATED(2); else if (vw == 1) RT_OS64_GATED(1); else RT_OS64_GATED(0);
+#undef RT_OS64_GATED
+            prof_mark(stream, RT_KIND_PASS + pass);
+            return;
+        }
+    }
 #define RT_OS64(V, S)                                                                                      \
     hipLaunchKernelGGL((k_onesweep64<BITS, BLOCK, IPT, V, S>), grid, block, 0, stream, plan, pass, n, \
                        static_cast<S *>(status), chunk_ctr, err)
@@ -259,31 +272,33 @@ void launch_pass64_shape(const Layout64 &L, uint32_t vw, hipStream_t stream, con
 }
 
 void launch_pass64(int bits_class, int block, int ipt, const Layout64 &L, uint32_t vw, hipStream_t stream,
-                   const SortPlan *plan, int pass, uint32_t n, void *status, uint32_t *ctr) {
+                   const SortPlan *plan, int pass, uint32_t n, void *status, uint32_t *ctr, bool gated) {
 #define RT_SHAPE_LAUNCH(B, BLK, I)                                                    \
     if (bits_class == B && block == BLK && ipt == I) {                                \
-        launch_pass64_shape<B, BLK, I>(L, vw, stream, plan, pass, n, status, ctr);    \
+        launch_pass64_shape<B, BLK, I>(L, vw, stream, plan, pass, n, status, ctr, gated); \
         return;                                                                       \
     }
     RT64_FOR_EACH_SHAPE(RT_SHAPE_LAUNCH)
 #undef RT_SHAPE_LAUNCH
 }
 
-void launch_sort64(uint64_t *keys, uint32_t *vals, uint32_t vw, uint32_t n, const Resolved &r, const Layout64 &L,
-                   char *ws, hipStream_t stream) {
+uint32_t *gate_word(char *ws, const Layout64 &L) {
+    return reinterpret_cast<uint32_t *>(ws + L.ctr) + kMaxPasses + 2 + kMaxPasses * kChunks;
+}
+
+// Up to the plan.  gate: whether the passes run (see k_narrow_probe), or NULL.
+void launch_plan64(uint64_t *keys, uint32_t *vals, uint32_t vw, uint32_t n, const Resolved &r, const Layout64 &L,
+                   char *ws, hipStream_t stream, uint32_t *gate) {
     uint32_t *hist = reinterpret_cast<uint32_t *>(ws + L.hist);
     uint32_t *ctr = reinterpret_cast<uint32_t *>(ws + L.ctr);
     uint32_t *base = reinterpret_cast<uint32_t *>(ws + L.base);
     SortPlan *plan = reinterpret_cast<SortPlan *>(ws + L.plan);
-    char *status = ws + L.status;
-    const uint32_t cus = static_cast<uint32_t>(device_cu_count());
-
-    prof_begin(stream);
+    if (gate == nullptr) prof_begin(stream);
     // histogram counters and lookback words, adjacent in the layout
     const size_t fill_words = (L.status + L.status_bytes - L.hist) / 4;
     uint32_t *mode = ctr + kMaxPasses + 1 + kMaxPasses * kChunks;
     hipLaunchKernelGGL(k_fill_zero, dim3(grid_for(fill_words, 256 * 16, 4096)), dim3(256), 0, stream, hist,
-                       fill_words, mode);
+                       fill_words, mode, gate);
     prof_mark(stream, RT_KIND_FILL);
 
     const HistArgs ha = hist_args(r, n, false);
@@ -293,13 +308,13 @@ void launch_sort64(uint64_t *keys, uint32_t *vals, uint32_t vw, uint32_t n, cons
     if (r.chunked) {
         const HistArgs hc = hist_args(r, n, true);
         if (sample_decides64(r, n)) {
-            hipLaunchKernelGGL((k_chunk_probe<1024, uint64_t>), dim3(hc.num_passes), dim3(1024), 0, stream, keys, n, hc, mode);
+            hipLaunchKernelGGL((k_chunk_probe<1024, uint64_t>), dim3(hc.num_passes), dim3(1024), 0, stream, keys, n, hc, mode, gate);
             prof_mark(stream, RT_KIND_PROBE);
             switch (copies64(hc.total_bins)) {
-                case 8: launch_histogram64_auto<8>(keys, n, ha, hc, mode, hist, stream); break;
-                case 4: launch_histogram64_auto<4>(keys, n, ha, hc, mode, hist, stream); break;
-                case 2: launch_histogram64_auto<2>(keys, n, ha, hc, mode, hist, stream); break;
-                default: launch_histogram64_auto<1>(keys, n, ha, hc, mode, hist, stream); break;
+                case 8: launch_histogram64_auto<8>(keys, n, ha, hc, mode, hist, stream, gate); break;
+                case 4: launch_histogram64_auto<4>(keys, n, ha, hc, mode, hist, stream, gate); break;
+                case 2: launch_histogram64_auto<2>(keys, n, ha, hc, mode, hist, stream, gate); break;
+                default: launch_histogram64_auto<1>(keys, n, ha, hc, mode, hist, stream, gate); break;
             }
             probed = true;
         } else {
@@ -334,6 +349,8 @@ void launch_sort64(uint64_t *keys, uint32_t *vals, uint32_t vw, uint32_t n, cons
     a.cbase = reinterpret_cast<uint32_t *>(ws + L.cbase);
     a.chunk_ctr = ctr + kMaxPasses + 1;
     a.mode = probed ? mode : nullptr;
+    a.gate = gate;
+    a.gate_passes = kNarrowBytes;
     a.user_k = reinterpret_cast<uint32_t *>(keys);
     a.user_v = vw ? vals : nullptr;
     a.t1_k = reinterpret_cast<uint32_t *>(ws + L.t1k);
@@ -342,17 +359,31 @@ void launch_sort64(uint64_t *keys, uint32_t *vals, uint32_t vw, uint32_t n, cons
     a.t2_v = (L.t2v && vw) ? reinterpret_cast<uint32_t *>(ws + L.t2v) : nullptr;
     hipLaunchKernelGGL(k_plan, dim3(1), dim3(256), 0, stream, a, hist, base, plan, ctr, 0u);
     prof_mark(stream, RT_KIND_PLAN);
+}
 
+void launch_passes64(uint64_t *keys, uint32_t *vals, uint32_t vw, uint32_t n, const Resolved &r, const Layout64 &L,
+                     char *ws, hipStream_t stream, bool gated) {
+    const SortPlan *plan = reinterpret_cast<const SortPlan *>(ws + L.plan);
+    const uint32_t cus = static_cast<uint32_t>(device_cu_count());
     for (uint32_t p = 0; p < r.num_passes; ++p)
         launch_pass64(bits_class_of(r.width[p]), r.block, r.ipt, L, vw, stream, plan, static_cast<int>(p), n,
-                      status + L.status_pass[p], ctr);
+                      ws + L.status + L.status_pass[p], reinterpret_cast<uint32_t *>(ws + L.ctr), gated);
 
     if (r.num_passes == 1 || !(r.flags & RT_FLAG_NO_SKIP)) {
         const uint32_t grid_c = grid_for(2 * static_cast<size_t>(n), 256 * 8, cus * 8);
-        hipLaunchKernelGGL(k_copy_back_words, dim3(grid_c), dim3(256), 0, stream, plan, a.t1_k, a.t1_v,
-                           a.user_k, a.user_v, 2 * static_cast<size_t>(n), static_cast<size_t>(vw) * n);
+        hipLaunchKernelGGL(k_copy_back_words, dim3(grid_c), dim3(256), 0, stream, plan,
+                           reinterpret_cast<const uint32_t *>(ws + L.t1k),
+                           vw ? reinterpret_cast<const uint32_t *>(ws + L.t1v) : nullptr,
+                           reinterpret_cast<uint32_t *>(keys), vw ? vals : nullptr, 2 * static_cast<size_t>(n),
+                           static_cast<size_t>(vw) * n);
         prof_mark(stream, RT_KIND_COPY_BACK);
     }
+}
+
+void launch_sort64(uint64_t *keys, uint32_t *vals, uint32_t vw, uint32_t n, const Resolved &r, const Layout64 &L,
+                   char *ws, hipStream_t stream) {
+    launch_plan64(keys, vals, vw, n, r, L, ws, stream, nullptr);
+    launch_passes64(keys, vals, vw, n, r, L, ws, stream, false);
 }
 
 rt_status check64(const uint64_t *keys, const void *vals, uint32_t value_bytes, size_t n, const char *what) {
@@ -429,8 +460,20 @@ extern "C" rt_status rt_sort64_ex(uint64_t *keys, void *vals, uint32_t value_byt
         const bool passes = n > kSplitMax64 && (n <= kSplitOneMax64 || n >= kSplitTwoMin64) && n <= kSplitTwoMax64;
         if (passes && L.t2k != 0 &&
             split_large_scratch_bytes64(n, vw) <= L.total - L.t2k) {
-            launch_split_large64(keys, v, vw, static_cast<uint32_t>(n), tk, tv, w + L.t2k, stream);
-            return finish_waited(cfg, stream, "rt_sort64_ex", w + L.t2k + split_large_error_at64(n, vw));
+            const uint32_t m = static_cast<uint32_t>(n);
+            char *scratch = w + L.t2k;
+            if (n < kSplitGateMin64) {
+                launch_split_large64(keys, v, vw, m, tk, tv, scratch, stream, nullptr, nullptr);
+                return finish_waited(cfg, stream, "rt_sort64_ex", scratch + split_large_error_at64(n, vw));
+            }
+            uint32_t *gate = gate_word(w, L), *error = reinterpret_cast<uint32_t *>(w + L.ctr) + kMaxPasses;
+            prof_begin(stream);
+            hipLaunchKernelGGL(k_narrow_probe<1024>, dim3(1), dim3(1024), 0, stream, keys, m, kNarrowBytes, gate);
+            prof_mark(stream, RT_KIND_PROBE);
+            launch_plan64(keys, v, vw, m, r, L, w, stream, gate);  // (clears the error word too)
+            launch_split_large64(keys, v, vw, m, tk, tv, scratch, stream, gate, error);
+            launch_passes64(keys, v, vw, m, r, L, w, stream, true);
+            return finish_waited(cfg, stream, "rt_sort64_ex", error);
         }
     }
     launch_sort64(keys, static_cast<uint32_t *>(vals), vw, static_cast<uint32_t>(n), r, L, static_cast<char *>(ws),

@@ -64,12 +64,13 @@ enum class SplitEnd { kNextPass, kLeavesBack, kLeavesInPlace };
 // sizes and they stay far below the 2^20 items it makes full leaves of.
 constexpr size_t kSampleFew = static_cast<size_t>(1) << 26;
 
-// arrays: those the segments lie in.
+// arrays: those the segments lie in.  error: the word that the leaves raise, or
+// NULL (their own, in the leaf lists' header).
 // One splitter pass over the tiled list of a SegLayout whose descriptors,
 // list, first tiles and leaf lists' header are on the device.
 template <typename T, typename K, typename V, bool VALS>
 void launch_split_pass(const SegPointers &P, const SegLayout &L, uint32_t list_stride, SplitEnd end, uint32_t *sub,
-                       const LeafArrays<K, V> &arrays, char *ws, hipStream_t stream) {
+                       const LeafArrays<K, V> &arrays, char *ws, hipStream_t stream, uint32_t *error) {
     const uint32_t cus = static_cast<uint32_t>(device_cu_count());
     const SplitTables t = split_tables(ws, L);
     const uint32_t *list = P.lists + static_cast<size_t>(kSegLarge) * list_stride;
@@ -111,7 +112,7 @@ void launch_split_pass(const SegPointers &P, const SegLayout &L, uint32_t list_s
     hipLaunchKernelGGL((k_split_leaves<256, leaf_ipt<K>(), K, V, VALS>), dim3(split_grid(t.leaf_capacity, cus * 4)), dim3(256), 0,
                        stream, arrays, t.lists, t.leaves, in_place);
     hipLaunchKernelGGL((k_split_long_leaves<1024, sizeof(K) == 4 ? 16 : 8, K, V, VALS>), dim3(cus), dim3(1024), 0,
-                       stream, arrays, t.lists, t.leaves, in_place, t.table, words, sub ? &words->error : &P.header->error);
+                       stream, arrays, t.lists, t.leaves, in_place, t.table, words, error ? error : &words->error);
     prof_mark(stream, RT_KIND_SEG_SMALL);
 }
 
@@ -149,11 +150,11 @@ inline int split_sort_passes(size_t n) {
 // where its buckets are leaves as they come.
 template <typename K, typename V, bool VALS>
 void launch_split_sort(K *keys, V *vals, uint32_t n, K *tk, V *tv, const SplitSortLayout &S, char *ws,
-                       hipStream_t stream) {
+                       hipStream_t stream, const uint32_t *gate, uint32_t *error) {
     uint32_t *off = reinterpret_cast<uint32_t *>(ws + S.offsets);
     char *seg = ws + S.seg;
     const int passes = split_sort_passes<K>(n);
-    prof_begin(stream);
+    if (gate == nullptr) prof_begin(stream);
     for (int pass = 0; pass < passes; ++pass) {
         const SegLayout &L = pass == 0 ? S.first : S.second;
         const SegPointers P = seg_pointers(seg, L);
@@ -166,10 +167,10 @@ void launch_split_sort(K *keys, V *vals, uint32_t n, K *tk, V *tv, const SplitSo
         hipLaunchKernelGGL((k_split_segments<K, V, VALS>), dim3(1), dim3(256), 0, stream, pass == 0 ? nullptr : off,
                            num, n, a_k, a_v, b_k, b_v, L.tile, P.descs,
                            P.lists + static_cast<size_t>(kSegLarge) * num, P.first_tile, P.header, t.lists,
-                           t.leaf_capacity);
+                           t.leaf_capacity, pass == 0 ? gate : nullptr, pass == 0 ? off : nullptr);
         prof_mark(stream, RT_KIND_SEGMENTED);
         launch_split_pass<SplitTile<K, V, VALS>, K, V, VALS>(P, L, num, end, off, LeafArrays<K, V>{a_k, a_v, b_k, b_v},
-                                                             seg, stream);
+                                                             seg, stream, error);
     }
 }
 

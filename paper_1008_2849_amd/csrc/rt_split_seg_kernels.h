@@ -779,14 +779,21 @@ __global__ __launch_bounds__(BLOCK) void k_split_long_leaves(LeafArrays<K, V> a,
 // count] (as k_split_starts leaves them; one segment of n items if NULL) become
 // descriptors, the tiled list, first tiles and the header, as k_seg_classify
 // and k_seg_tiles make them.  A one-item segment is copied to tk/tv here.
+// gate (if set): a gate that is open leaves this pass and the next, whose
+// segments are in `sub`, nothing to do (see k_narrow_probe).
 template <typename K, typename V, bool VALS>
 __global__ __launch_bounds__(256) void k_split_segments(const uint32_t *__restrict__ off, uint32_t count, uint32_t n,
                                                         K *k, V *v, K *tk, V *tv, uint32_t tile,
                                                         SegDesc *__restrict__ descs, uint32_t *__restrict__ list,
                                                         uint32_t *__restrict__ first_tile, SegHeader *__restrict__ h,
-                                                        LeafLists *__restrict__ leaf_lists, uint32_t leaf_capacity) {
+                                                        LeafLists *__restrict__ leaf_lists, uint32_t leaf_capacity,
+                                                        const uint32_t *__restrict__ gate, uint32_t *__restrict__ sub) {
     __shared__ uint32_t wsum[2][4];
     const uint32_t s = threadIdx.x;
+    if (gate != nullptr && *gate != 0u) {
+        count = 0u;
+        for (uint32_t i = s; i < kSubOnes + kBuckets / 32; i += 256) sub[i] = 0u;
+    }
     const uint32_t a = off == nullptr || s >= count ? 0u : off[s];
     const uint32_t e = s >= count ? 0u : off == nullptr ? n : off[s + 1];
     const uint32_t len = e - a;

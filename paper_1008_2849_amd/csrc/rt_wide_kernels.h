@@ -149,12 +149,54 @@ __global__ __launch_bounds__(BLOCK) void k_histogram64_chunked(const uint64_t *_
 template <int BLOCK, int CP, int CC>
 __global__ __launch_bounds__(BLOCK) void k_histogram64_auto(const uint64_t *__restrict__ keys, uint32_t n, HistArgs hp,
                                                             HistArgs hc, const uint32_t *__restrict__ mode,
-                                                            uint32_t *__restrict__ hist) {
+                                                            uint32_t *__restrict__ hist,
+                                                            const uint32_t *__restrict__ gate) {
     extern __shared__ uint32_t s_h[];
+    if (gate != nullptr && *gate == 0u) return;
     if (*mode != 0u)
         histogram64_body<BLOCK, CC, true>(keys, n, hc, hist, s_h);
     else
         histogram64_body<BLOCK, CP, false>(keys, n, hp, hist, s_h);
+}
+
+// ---------------------------------------------------------------------------
+// digit passes or splitter passes
+// ---------------------------------------------------------------------------
+
+// One block: *gate = 1 if the sampled keys differ in at most max_bytes of their
+// eight bytes, else 0.  Both methods are launched; the digit passes run if the
+// gate is open (until the plan finds more passes to run than that), the
+// splitter passes if it is closed.
+template <int BLOCK>
+__global__ __launch_bounds__(BLOCK) void k_narrow_probe(const uint64_t *__restrict__ keys, uint32_t n,
+                                                        uint32_t max_bytes, uint32_t *__restrict__ gate) {
+    constexpr int WAVES = BLOCK / 64, PER = 8, RUNS = WAVES * PER;  // runs of 64 consecutive keys
+    __shared__ uint32_t differ[2];
+    const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
+    if (tid < 2) differ[tid] = 0u;
+    __syncthreads();
+    const uint64_t k0 = keys[0];
+    uint64_t k[PER];
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+        const uint64_t start = static_cast<uint64_t>(wave * PER + j) * n / RUNS;
+        k[j] = keys[min(start + lane, static_cast<uint64_t>(n) - 1u)];
+    }
+    uint64_t d = 0;
+#pragma unroll
+    for (int j = 0; j < PER; ++j) d |= k[j] ^ k0;
+    const uint32_t lo = wave_reduce(static_cast<uint32_t>(d), [](uint32_t x, uint32_t y) { return x | y; });
+    const uint32_t hi = wave_reduce(static_cast<uint32_t>(d >> 32), [](uint32_t x, uint32_t y) { return x | y; });
+    if (lane == 0) {
+        atomicOr(&differ[0], lo);
+        atomicOr(&differ[1], hi);
+    }
+    __syncthreads();
+    if (tid != 0) return;
+    uint32_t bytes = 0;
+    for (int b = 0; b < 4; ++b)
+        bytes += ((differ[0] >> (8 * b)) & 255u ? 1u : 0u) + ((differ[1] >> (8 * b)) & 255u ? 1u : 0u);
+    *gate = bytes <= max_bytes ? 1u : 0u;
 }
 
 // ---------------------------------------------------------------------------
@@ -163,7 +205,7 @@ __global__ __launch_bounds__(BLOCK) void k_histogram64_auto(const uint64_t *__re
 
 // The pass over 64-bit keys with values of VW 32-bit words (0, 1 or 2):
 // the single-array pass of k_onesweep on wider items.
-template <int BITS, int BLOCK, int IPT, int VW, typename S>
+template <int BITS, int BLOCK, int IPT, int VW, typename S, bool PERSIST = false>
 __global__ __launch_bounds__(BLOCK) void k_onesweep64(const SortPlan *__restrict__ plan, int pass, uint32_t n,
                                                       S *__restrict__ status, uint32_t *__restrict__ chunk_counter,
                                                       uint32_t *__restrict__ error_flag) {
@@ -172,8 +214,8 @@ __global__ __launch_bounds__(BLOCK) void k_onesweep64(const SortPlan *__restrict
     // keys, then the values through the same space
     constexpr bool SEQ = VW > 0 && static_cast<size_t>(BLOCK) * IPT * (sizeof(uint64_t) + sizeof(V)) > 128 * 1024;
     __shared__ OnesweepLds<BITS, BLOCK, IPT, uint64_t, V, (VW > 0), false, SEQ> lds;
-    onesweep_pass<BITS, BLOCK, IPT, uint64_t, V, (VW > 0), false, S, true, false, SEQ>(lds, plan, pass, n, status,
-                                                                                       chunk_counter, error_flag);
+    onesweep_pass<BITS, BLOCK, IPT, uint64_t, V, (VW > 0), false, S, true, false, SEQ, PERSIST>(
+        lds, plan, pass, n, status, chunk_counter, error_flag);
 }
 
 // Moves the result of a sort with exactly one executed pass from the
