@@ -123,13 +123,14 @@ def split_calls(marks):
 
 def bench_workloads(rts, inputs, dev, names, K, W):
     """The other single-array workloads at full size (keys only at 2^28 and
-    2^20; the skewed 2^26-pair inputs): whole-sort Gkeys/s, the mean pass
-    time and its HBM fraction, the histogram time, and the last timed
+    2^20; the skewed 2^26-pair inputs), by the default method for their size:
+    whole-sort Gkeys/s, the mean pass time (digit passes, or the splitter
+    sort's scatter) and its HBM fraction, the histogram time, and the last timed
     output against the CPU oracle (bit for bit, timed single-threaded on
     one core: the CPU baseline of that workload)."""
     import numpy as np
     import torch
-    from paper_1008_2849_amd._lib import RT_KIND_HISTOGRAM, RT_KIND_PASS
+    from paper_1008_2849_amd._lib import RT_KIND_HISTOGRAM, RT_KIND_PASS, RT_KIND_SEG_SMALL
     out = []
     for name in names:
         w = inputs.WORKLOADS[name]
@@ -139,15 +140,15 @@ def bench_workloads(rts, inputs, dev, names, K, W):
         v0 = torch.from_numpy(v_h.view(np.int32)).to(dev) if v_h is not None else None
         tuned = rts.tuned_config(n, w.with_values)
         slots = [(k0.clone(), None if v0 is None else v0.clone()) for _ in range(K + W)]
-        ws = torch.empty(rts.workspace_bytes(n, w.with_values, tuned), dtype=torch.uint8, device=dev)
+        ws = torch.empty(rts.workspace_bytes(n, w.with_values), dtype=torch.uint8, device=dev)
         for i in range(W):
-            rts.sort_ex(slots[i][0], slots[i][1], tuned, ws)
+            rts.sort_ex(slots[i][0], slots[i][1], None, ws)
         torch.cuda.synchronize()
         # per-kernel times first (HIP events around every kernel), then the
         # same sorts of fresh copies timed without them
         rts.profile_start(max_marks=16 * K + 16)
         for i in range(W, W + K):
-            rts.sort_ex(slots[i][0], slots[i][1], tuned, ws)
+            rts.sort_ex(slots[i][0], slots[i][1], None, ws)
         torch.cuda.synchronize()
         marks = rts.profile_stop(capacity=16 * K + 16)
         for i in range(W, W + K):
@@ -157,11 +158,12 @@ def bench_workloads(rts, inputs, dev, names, K, W):
         torch.cuda.synchronize()
         t0 = time.perf_counter()
         for i in range(W, W + K):
-            rts.sort_ex(slots[i][0], slots[i][1], tuned, ws)
+            rts.sort_ex(slots[i][0], slots[i][1], None, ws)
         torch.cuda.synchronize()
         wall = time.perf_counter() - t0
         passes = [ms for kind, ms in marks if RT_KIND_PASS <= kind < RT_KIND_PASS + 8]
         hist = [ms for kind, ms in marks if kind == RT_KIND_HISTOGRAM]
+        digits = all(kind != RT_KIND_SEG_SMALL for kind, _ in marks)
         ko, vo = slots[W + K - 1]
         out_k = ko.cpu().numpy().view(np.uint32)
         out_v = None if vo is None else vo.cpu().numpy().view(np.uint32)
@@ -176,8 +178,9 @@ def bench_workloads(rts, inputs, dev, names, K, W):
                     "pass_ms": round(pm, 4), "pass_GBps": round(2 * item * n / pm / 1e6, 1),
                     "pass_frac_of_peak": round(2 * item * n / pm / 1e6 / PEAK_HBM_GBPS, 4),
                     "histogram_ms": round(float(np.mean(hist)), 4) if hist else None,
+                    "method": "digit passes" if digits else "splitter sort",
                     "config": {"digit_bits": list(tuned.digit_bits), "block_threads": tuned.block_threads,
-                               "items_per_thread": tuned.items_per_thread},
+                               "items_per_thread": tuned.items_per_thread} if digits else None,
                     "matches_oracle_bit_exact": same,
                     "cpu_oracle": {"seconds": round(dt, 4), "Gkeys/s": round(n / dt / 1e9, 5), "cores": 1,
                                    "pinned_core": core}})
@@ -216,7 +219,8 @@ def bench_batched(rts, inputs, dev, K, W, single_gkeys):
     wall = time.perf_counter() - t0
     calls = split_calls(rts.profile_stop(capacity=32 * K + 32))
     per_call = [c[0] for c in calls]
-    pass_ms = [ms for c in calls for kind, ms in c[1] if RT_KIND_PASS <= kind < RT_KIND_PASS + 8]
+    # the splitter scatter; the digit passes behind it find no segment too long
+    pass_ms = [max(ms for kind, ms in c[1] if kind == RT_KIND_PASS) for c in calls]
     eager_wall = wall
     # the same calls captured as graphs (one per staged copy), then replayed
     for k, v in slots:
@@ -272,7 +276,7 @@ def bench_batched(rts, inputs, dev, K, W, single_gkeys):
             "replay_p99_ms": round(float(np.percentile(replay_ms, 99)), 4),
             "eager_call_p50_ms": round(float(np.percentile(per_call, 50)), 4),
             "eager_call_p99_ms": round(float(np.percentile(per_call, 99)), 4),
-            "tiled_pass_ms": round(float(np.mean(pass_ms)), 4) if pass_ms else None,
+            "scatter_ms": round(float(np.mean(pass_ms)), 4),
             "size_classes": [list(c) + [b] for c, b in zip(rts.segment_classes(), rts.segment_config()[0])],
             "tiled_tile": list(rts.segment_config()[1]),
             "frac_of_single_array": round(gk / single_gkeys, 4), "parity_properties_ok": ok}
@@ -340,11 +344,11 @@ def bench_msd_first(rts, dev, k0, v0, slots, K, W, single_gkeys, ref_k, ref_v):
 
 
 def bench_sort64(rts, inputs, dev, K, W):
-    """64-bit keys: 2^28 uniform u64 keys carrying u32 index values, eight
-    8-bit passes, each timed call on its own pre-staged copy."""
+    """64-bit keys: 2^28 uniform u64 keys carrying u32 index values (two
+    splitter passes and leaves), each timed call on its own pre-staged copy."""
     import numpy as np
     import torch
-    from paper_1008_2849_amd._lib import RT_KIND_HISTOGRAM, RT_KIND_PASS
+    from paper_1008_2849_amd._lib import RT_KIND_HISTOGRAM, RT_KIND_PASS, RT_KIND_SEG_SMALL
     w = inputs.WORKLOADS["pairs64_256m_uniform"]
     n = w.n
     k_h, _ = inputs.make_workload(w)
@@ -363,8 +367,11 @@ def bench_sort64(rts, inputs, dev, K, W):
     torch.cuda.synchronize()
     wall = time.perf_counter() - t0
     calls = split_calls(rts.profile_stop(capacity=32 * K + 32))
-    pass_ms = [ms for c in calls for kind, ms in c[1] if RT_KIND_PASS <= kind < RT_KIND_PASS + 8]
-    hist_ms = [ms for c in calls for kind, ms in c[1] if kind == RT_KIND_HISTOGRAM]
+    # per call: the launches with work in them (the digit passes' find none)
+    def longest(kind_, count):
+        return [ms for c in calls for ms in sorted(ms for kind, ms in c[1] if kind == kind_)[-count:]]
+    pass_ms, hist_ms = longest(RT_KIND_PASS, 2), longest(RT_KIND_HISTOGRAM, 2)
+    leaves_ms = [sum(ms for kind, ms in c[1] if kind == RT_KIND_SEG_SMALL) for c in calls]
     ko, vo = slots[W + K - 1]
     # properties that fix a stable sort of original indices (unsigned order
     # through the sign flip)
@@ -379,11 +386,11 @@ def bench_sort64(rts, inputs, dev, K, W):
     pm = float(np.mean(pass_ms))
     pass_bytes = 2.0 * 12 * n
     gk = n / (wall / K) / 1e9
-    return {"workload": w.name, "n": n, "key_bits": 64, "value_bytes": 4, "digit_bits": [8] * 8,
+    return {"workload": w.name, "n": n, "key_bits": 64, "value_bytes": 4, "method": "two splitter passes and leaves",
             "Gkeys/s": round(gk, 3), "ms_per_call": round(1e3 * wall / K, 4),
-            "pass_ms": round(pm, 4), "pass_GBps": round(pass_bytes / pm / 1e6, 1),
-            "pass_frac_of_peak": round(pass_bytes / pm / 1e6 / PEAK_HBM_GBPS, 4),
-            "histogram_ms": round(float(np.mean(hist_ms)), 4) if hist_ms else None,
+            "scatter_ms": round(pm, 4), "scatter_GBps": round(pass_bytes / pm / 1e6, 1),
+            "scatter_frac_of_peak": round(pass_bytes / pm / 1e6 / PEAK_HBM_GBPS, 4),
+            "count_ms": round(float(np.mean(hist_ms)), 4), "leaves_ms": round(float(np.mean(leaves_ms)), 4),
             "parity_properties_ok": ok}
 
 
