@@ -102,7 +102,14 @@ typedef enum rt_status {
 #define RT_FLAG_MSD_TWO_LEVELS 0x100u
 
 /*
- * Sort configuration.  Zero-initialised fields mean "tuned default".
+ * Sort configuration.  Zero-initialised fields mean "tuned default".  A
+ * default call (no configuration, or one of zeros but for RT_FLAG_VALIDATE)
+ * leaves the method to the library too.  32-bit keys: up to 16384 items one
+ * block sorts the array in its LDS, up to 2^20 the array is cut into buckets of
+ * neighbouring keys that blocks sort in theirs; the LSD digit passes above, and
+ * where a loaded tuning table sets them (rt_load_tuning).  64-bit keys: see
+ * rt_sort64_ex.  A configuration that sets digits, a tile shape or another flag
+ * asks for digit passes.
  * digit_bits[p] is the width of pass p's digit, least significant first
  * (Section 4: digits are processed from the least significant one upward);
  * the widths must sum to 32 and each lies in 1..RT_MAX_DIGIT_BITS.
@@ -127,8 +134,9 @@ typedef struct rt_config {
  * --------------------------------------------------------------------- */
 
 /*
- * Sort n keys in place (stable LSD radix sort, Section 4; each pass the
- * counting sort of Section 3).  keys: device u32[n].
+ * Sort n keys in place (stable; method: see rt_config.  The digit passes are
+ * Section 4's LSD radix sort, each pass the counting sort of Section 3).
+ * keys: device u32[n].
  */
 rt_status rt_sort_keys(uint32_t *keys, size_t n, hipStream_t stream);
 
@@ -181,9 +189,9 @@ rt_status rt_sort_pairs_noalloc(uint32_t *keys, uint32_t *vals, size_t n, const 
  * --------------------------------------------------------------------- */
 
 /*
- * Sort n 64-bit unsigned keys in place, ascending and stable, by the same
- * LSD radix sort on K = 64-bit keys (Section 4; each pass Section 3's
- * counting sort).  The paper sorts 32-bit keys and notes that its items may
+ * Sort n 64-bit unsigned keys in place, ascending and stable (methods: see
+ * rt_sort64_ex; its digit passes are the same LSD radix sort on K = 64-bit
+ * keys, Section 4, each pass Section 3's counting sort).  The paper sorts 32-bit keys and notes that its items may
  * be wider than one 64-bit key-value word; this is that variant.
  * keys: device u64[n], 8-byte aligned.
  */
@@ -199,9 +207,13 @@ rt_status rt_sort_pairs64(uint64_t *keys, uint32_t *vals, size_t n, hipStream_t 
 /*
  * Explicit form.  value_bytes: 0 (keys only, vals ignored), 4 or 8 bytes per
  * item; vals is then a device array of n such values, aligned to
- * value_bytes.  cfg (NULL = built-in default: eight 8-bit digits, in
- * 16K-item tiles from 2^24 items (12K with 8-byte values) and 8K-item tiles
- * below): digit_bits must sum to 64, each 1..RT_MAX_DIGIT_BITS; tile shapes
+ * value_bytes.  A default call (cfg NULL, or zeros but for RT_FLAG_VALIDATE)
+ * sorts up to 8192 items in one block, up to 600064 by one pass into buckets of
+ * neighbouring keys and the buckets in LDS, and 2^22 to 2^28 by two such passes
+ * (from 2^27 by digit passes if the keys differ in at most three bytes); other
+ * sizes by eight 8-bit digit passes, in 16K-item tiles from 2^24 items (12K
+ * with 8-byte values) and 8K-item tiles below, as does a cfg that sets anything
+ * else.  cfg: digit_bits must sum to 64, each 1..RT_MAX_DIGIT_BITS; tile shapes
  * built are 1024x16, 1024x12, 1024x8 and 512x16 for digits of up to 8 bits
  * and 512x8 for wider ones (correct, but several times slower than 8-bit
  * digits); flags: RT_FLAG_NO_SKIP, RT_FLAG_ONE_CHAIN, RT_FLAG_CHUNKS (XCD
@@ -232,9 +244,12 @@ size_t rt_workspace_bytes64(size_t n, uint32_t value_bytes, const rt_config *cfg
  * one-item segments are fine.  vals may be NULL (keys only); keys and vals
  * must not overlap.  max_total bounds seg_offsets[num_segments] -
  * seg_offsets[0] and sizes the workspace (pass the total when known).
- * Segments of up to 16384 items are sorted whole in LDS, larger ones of up
- * to 2^20 by one pass into buckets of neighbouring keys and the buckets whole
- * in LDS, longer ones by four 8-bit onesweep passes over 16K-item tiles.
+ * Segments of up to 16384 items are sorted whole in LDS.  Larger ones of up
+ * to 2^20 take one pass into buckets of neighbouring keys and the buckets whole
+ * in LDS, in calls of up to 2^20 or more than 2^22 items (max_total); in other
+ * calls, in calls whose mean segment is longer than 2^20 items or whose tile is
+ * tuned to 512 x 16, and if they are longer, four 8-bit onesweep passes over
+ * tiles.
  *
  * Errors: argument errors are returned before any device work.  A segment
  * whose offsets decrease or reach past seg_offsets[0] + max_total is left
@@ -316,9 +331,10 @@ rt_status rt_digit_histograms(const uint32_t *keys, size_t n, const rt_config *c
                               uint32_t *hist, hipStream_t stream);
 
 /*
- * The XCD-chunk decision that rt_sort_pairs_ex (with_values != 0) or
- * rt_sort_keys-style calls (with_values == 0) make for these n keys under
- * cfg (NULL = tuned default), written to *mode (device u32): 1 = the passes
+ * The XCD-chunk decision that the digit passes of rt_sort_pairs_ex
+ * (with_values != 0) or rt_sort_keys-style calls (with_values == 0) make for
+ * these n keys under cfg (NULL = tuned default; whether a default call takes
+ * digit passes is another matter, see rt_config), written to *mode (device u32): 1 = the passes
  * run in XCD chunks, 0 = one lookback chain per pass.  Where the sort
  * samples its keys (see RT_FLAG_CHUNKS) this runs the same sample kernel on
  * the same keys; otherwise it writes what the size, the digit widths and the
@@ -329,8 +345,8 @@ rt_status rt_digit_histograms(const uint32_t *keys, size_t n, const rt_config *c
 rt_status rt_chunk_decision(const uint32_t *keys, size_t n, int with_values, const rt_config *cfg,
                             uint32_t *mode, hipStream_t stream);
 
-/* The same for a sort of 64-bit keys with value_bytes of 0, 4 or 8
- * (rt_sort64_ex's decision). */
+/* The same for the digit passes of 64-bit keys with value_bytes of 0, 4 or 8
+ * (rt_sort64_ex). */
 rt_status rt_chunk_decision64(const uint64_t *keys, size_t n, uint32_t value_bytes, const rt_config *cfg,
                               uint32_t *mode, hipStream_t stream);
 
@@ -522,8 +538,10 @@ rt_status rt_server_destroy(rt_server *s);
 
 /*
  * Load a tuning table (JSON written by the autotuner).  Its "keys" and
- * "pairs" entries map single-array sorts of n in [min_n, max_n] to digit
- * widths, block size, items per thread and flags; its "segments" entries
+ * "pairs" entries map single-array sorts of n in [min_n, max_n] to the digit
+ * passes' widths, block size, items per thread and flags; default calls they
+ * apply to take those, except for n up to the table's "own_methods_max_n" (0
+ * if it has none), where the library's own methods stand (see rt_config).  Its "segments" entries
  * (increasing max_n, at most 4, each at most 16384 and within its shape,
  * digits 8,8,8,8 or 11,11,10) are the whole-in-LDS size classes of the
  * segmented sort (see rt_segment_classes), and a "segments_tiled" entry
@@ -533,7 +551,8 @@ rt_status rt_server_destroy(rt_server *s);
  */
 rt_status rt_load_tuning(const char *json_path);
 
-/* Tuned configuration the library would use for n items. */
+/* Tuned configuration of the digit passes for n items (a default call may take
+ * another method, see rt_config). */
 rt_status rt_tuned_config(size_t n, int with_values, rt_config *out);
 
 /*

@@ -7,7 +7,8 @@ GPU and writes the tuning table that rt_load_tuning() reads.
 Single-array sorts ("keys", "pairs"): at each measured size it times every
 (digit widths, tile shape, store flavour) the library has kernels for and
 keeps the fastest; entries cover size ranges split at the geometric
-midpoints between measured sizes.  Each candidate's output is checked
+midpoints between measured sizes.  The table says that default calls of at
+most OWN_METHODS_MAX_N items do not take them.  Each candidate's output is checked
 against a stable argsort of the same keys on the device before its time
 counts, so a configuration can only win by sorting correctly.
 
@@ -41,6 +42,10 @@ SHAPES = {8: [(256, 16), (512, 16), (1024, 8), (1024, 12), (1024, 16), (512, 32)
           11: [(256, 16), (512, 8), (512, 16)]}
 WIDTHS = [(8, 8, 8, 8), (11, 11, 10)]
 SIZES = [1 << 16, 1 << 20, 1 << 24, 1 << 28]
+# up to here a default call keeps the library's methods for small arrays (one
+# to three launches, faster than any digit passes); the entries below serve
+# calls that ask for digit passes with the tuned shape
+OWN_METHODS_MAX_N = 1 << 20
 
 
 def candidates():
@@ -382,7 +387,7 @@ def main(argv=None) -> int:
     report = [r for r in old.get("measurements", []) if r.get("op") not in tuned] + report
     table = {"arch": "gfx950", "device": torch.cuda.get_device_name(0),
              "cus": torch.cuda.get_device_properties(0).multi_processor_count,
-             "library": api.version(), "entries": entries, "measurements": report}
+             "library": api.version(), "own_methods_max_n": OWN_METHODS_MAX_N, "entries": entries, "measurements": report}
     with open(args.out, "w") as f:
         json.dump(table, f, indent=1)
     api.load_tuning(args.out)  # the library accepts what was written

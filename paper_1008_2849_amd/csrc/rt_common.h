@@ -268,6 +268,8 @@ void launch_split_large64(uint64_t *keys, uint32_t *vals, uint32_t value_words, 
 // Whether cfg leaves the method to the library: no digits, shape or flags
 // but RT_FLAG_VALIDATE.
 bool default_method(const rt_config *cfg);
+// Whether the tuning table sets the digit passes of a default call of n items.
+bool tuned_digits(size_t n, int with_values);
 // The end of a call that ran one of the methods above: finish_call, and with
 // RT_FLAG_VALIDATE the wait it asks for and what *error (device; NULL: the
 // call's kernels raise none) says.

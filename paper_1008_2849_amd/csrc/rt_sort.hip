@@ -570,11 +570,17 @@ static rt_status check_ranges(const uint32_t *keys, const uint32_t *vals, size_t
     return RT_OK;
 }
 
+// Whether the method is the library's to choose: neither cfg nor the tuning
+// table sets the digit passes.
+static bool own_method(const rt_config *cfg, size_t n, const uint32_t *vals) {
+    return default_method(cfg) && !tuned_digits(n, vals != nullptr);
+}
+
 // Takes the splitter sort where the method is the library's to choose and the
 // size suits it: the first temporary is its temporary, the tables lie below.
 static bool try_split(uint32_t *keys, uint32_t *vals, size_t n, const rt_config *cfg, const Layout &L, void *ws,
                       hipStream_t stream) {
-    if (!default_method(cfg) || n > kSplitMax32 || split_scratch_bytes(n, sizeof(uint32_t)) > L.t1k) return false;
+    if (n > kSplitMax32 || !own_method(cfg, n, vals) || split_scratch_bytes(n, sizeof(uint32_t)) > L.t1k) return false;
     char *w = static_cast<char *>(ws);
     launch_split(keys, vals, static_cast<uint32_t>(n), reinterpret_cast<uint32_t *>(w + L.t1k),
                  vals ? reinterpret_cast<uint32_t *>(w + L.t1v) : nullptr, w, stream);
@@ -597,7 +603,7 @@ extern "C" rt_status rt_sort_pairs_ex(uint32_t *keys, uint32_t *vals, size_t n, 
         if (reinterpret_cast<uintptr_t>(ws) & 255u)
             return set_error(RT_ERR_INVALID_ARG, "rt_sort_pairs_ex: workspace must be 256-byte aligned");
     }
-    if (default_method(cfg) && n <= kBlockSortMax32) {
+    if (n <= kBlockSortMax32 && own_method(cfg, n, vals)) {
         launch_block_sort(keys, vals, static_cast<uint32_t>(n), stream);
         return finish_waited(cfg, stream, "rt_sort_pairs_ex");
     }
@@ -670,7 +676,7 @@ extern "C" rt_status rt_sort_pairs_noalloc(uint32_t *keys, uint32_t *vals, size_
                          "rt_sort_pairs_noalloc: %zu items need %zu bytes of workspace; the static scratch holds %zu "
                          "(use rt_sort_pairs_ex)",
                          n, L.total, kNoAllocScratchBytes);
-    if (default_method(cfg) && n <= kBlockSortMax32) {
+    if (n <= kBlockSortMax32 && own_method(cfg, n, vals)) {
         launch_block_sort(keys, vals, static_cast<uint32_t>(n), stream);
         return finish_waited(cfg, stream, "rt_sort_pairs_noalloc");
     }

@@ -2,11 +2,14 @@
 // written by the autotuner (paper_1008_2849_amd/autotune.py).
 //
 // Table format:
-//   {"arch": "gfx950", "entries": [
+//   {"arch": "gfx950", "own_methods_max_n": M, "entries": [
 //      {"op": "keys"|"pairs"|"segments"|"segments_tiled", "min_n": N0, "max_n": N1,
 //       "digit_bits": [w0, w1, ...], "block": B, "ipt": I, "flags": F}, ...]}
 // A "keys" or "pairs" entry applies to single-array sorts of n in
-// [min_n, max_n]; the first matching entry wins.  The "segments" entries, in
+// [min_n, max_n]; the first matching entry wins.  It sets the digit passes, so
+// a default call it applies to takes them, unless n is at most M (0 if the
+// table does not say): there the library's own methods for small arrays stand,
+// as they do where no entry applies.  The "segments" entries, in
 // increasing max_n, are the whole-in-LDS size classes of the segmented sort
 // (batched calls, the MSD-first sort's buckets, small server requests): each
 // sorts the segments of up to max_n items (and more than the previous
@@ -136,6 +139,7 @@ struct Entry {
 
 std::mutex g_mu;
 std::vector<Entry> g_table;
+double g_own_methods_max = 0;
 bool g_seg_tuned = false;
 SegClassTable g_seg;
 
@@ -178,6 +182,15 @@ void tuned_config_op(size_t n, int op, rt_config *out) {
     builtin(n, op, out);
 }
 
+bool tuned_digits(size_t n, int with_values) {
+    std::lock_guard<std::mutex> lk(g_mu);
+    if (static_cast<double>(n) <= g_own_methods_max) return false;
+    for (const Entry &e : g_table)
+        if (e.op == (with_values ? 1 : 0) && static_cast<double>(n) >= e.min_n && static_cast<double>(n) <= e.max_n)
+            return true;
+    return false;
+}
+
 void tuned_config(size_t n, int with_values, rt_config *out) { tuned_config_op(n, with_values ? 1 : 0, out); }
 
 SegClassTable seg_class_table() {
@@ -211,6 +224,9 @@ extern "C" rt_status rt_load_tuning(const char *json_path) {
     const JValue *entries = root.get("entries");
     if (!entries || entries->kind != JValue::Array)
         return set_error(RT_ERR_INVALID_ARG, "rt_load_tuning: no \"entries\" array");
+    const JValue *own = root.get("own_methods_max_n");
+    if (own != nullptr && own->kind != JValue::Number)
+        return set_error(RT_ERR_INVALID_ARG, "rt_load_tuning: \"own_methods_max_n\" is not a number");
     std::vector<Entry> table;
     SegClassTable seg{};
     for (size_t i = 0; i < entries->arr.size(); ++i) {
@@ -289,6 +305,7 @@ extern "C" rt_status rt_load_tuning(const char *json_path) {
     }
     std::lock_guard<std::mutex> lk(g_mu);
     g_table.swap(table);
+    g_own_methods_max = own != nullptr ? own->num : 0;
     g_seg_tuned = seg.count > 0;
     g_seg = seg;
     return RT_OK;

@@ -281,3 +281,33 @@ def test_64_bit_keys_both_samples_miss(vdt):
     assert v is None or np.array_equal(v.cpu().numpy(), order.astype(vdt))
     print(f"{ms:.3f} ms", flush=True)
     assert ms < 20.0  # one block alone: 77 ms
+
+
+@pytest.mark.parametrize("own,digits", [(None, True), (50_000, True), (1 << 20, False)])
+def test_tuning_table_entry_of_a_small_size(own, digits, tmp_path):
+    """A loaded table's entry sets the digit passes of default calls, unless the
+    table leaves that size to the library's own methods."""
+    import json
+    n = 100_003
+    announce(f"tuned shape at n={n}, own methods up to {own}")
+    table = {"entries": [{"op": "pairs", "min_n": 0, "max_n": 1 << 20, "digit_bits": [8, 8, 8, 8], "block": 512,
+                          "ipt": 16, "flags": 0}]}
+    if own is not None:
+        table["own_methods_max_n"] = own
+    path = tmp_path / "t.json"
+    path.write_text(json.dumps(table))
+    keys, vals = inputs.uniform_keys(n, 19), inputs.index_values(n)
+    order = np.argsort(keys, kind="stable")
+    try:
+        rts.load_tuning(str(path))
+        for with_values, by_digits in ((True, digits), (False, False)):  # (no entry for keys alone)
+            k, v = to_dev(keys), to_dev(vals)
+            rts.profile_start()
+            rts.sort_ex(k, v if with_values else None)
+            sync()
+            kinds = {kind for kind, _ in rts.profile_stop()}
+            assert (19 in kinds) == by_digits and (8 in kinds) != by_digits, kinds
+            assert np.array_equal(to_host(k), keys[order])
+            assert not with_values or np.array_equal(to_host(v), order.astype(np.uint32))
+    finally:
+        rts.load_default_tuning()
