@@ -59,9 +59,11 @@ static_assert(sizeof(LeafLists) <= 256, "the lists' header");
 // tk/tv.
 enum class SplitEnd { kNextPass, kLeavesBack, kLeavesInPlace };
 
-// Up to here the first of two passes samples 2048 keys of the array, not 8192:
-// its buckets may differ by half, as the second pass cuts them by their own
-// sizes and they stay far below the 2^20 items it makes full leaves of.
+// Up to here the first of two passes samples 2048 keys of the array, not 8192
+// (12 us against 28): its buckets may differ by half, as the second pass cuts
+// them by their own sizes and they stay far below the 2^20 items it makes full
+// leaves of.  Above, 16 us are less than 0.6 percent of the sort, and the
+// longest of the buckets comes near those.
 constexpr size_t kSampleFew = static_cast<size_t>(1) << 26;
 
 // arrays: those the segments lie in.  error: the word that the leaves raise, or
