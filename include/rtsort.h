@@ -575,10 +575,10 @@ rt_status rt_tuned_config(size_t n, int with_values, rt_config *out);
 #define RT_KIND_COPY 5u
 #define RT_KIND_GENERATE 6u
 #define RT_KIND_SEGMENTED 7u /* segmented sort: tile lists of the tiled segments */
-#define RT_KIND_SEG_SMALL 8u /* segmented sort: segments sorted whole in LDS */
+#define RT_KIND_SEG_SMALL 8u /* segments, buckets or whole arrays sorted in LDS */
 #define RT_KIND_MSD_PASS 9u  /* MSD-first sort: the partition pass on the top digit */
-#define RT_KIND_PROBE 10u    /* sample of the keys that chooses XCD chunks or one chain */
-#define RT_KIND_PASS 16u     /* + pass index: one counting-sort pass (onesweep) */
+#define RT_KIND_PROBE 10u    /* sample of the keys: XCD chunks or one chain, buckets, the method */
+#define RT_KIND_PASS 16u     /* + pass index: one counting-sort pass (onesweep); 16: a splitter pass's scatter too */
 rt_status rt_profile_start(uint32_t max_marks);
 rt_status rt_profile_stop(uint32_t *kinds, float *ms, uint32_t capacity, uint32_t *count);
 

@@ -154,11 +154,15 @@ def test_segments_around_the_longest_a_splitter_pass_takes(sizes, kind):
     assert np.array_equal(to_host(only), want_k)
 
 
-def test_long_segments_of_two_streams_and_replays():
+@pytest.mark.parametrize("sizes", [
+    [M + 1, 40, 300_000, 2 * M + 16_385, 17_000, 0, 64, 5 * M],           # too long by their mean
+    [M + 1, 40, 300_000, 2 * M + 16_385, 17_000, 0, 64, 5 * M] + [9] * 4,  # most items too long
+    [300_000] * 9 + [M + 1, 40, 17_000] + [260_000] * 9,                  # few of them
+], ids=len)
+def test_long_segments_of_two_streams_and_replays(sizes):
     """Segments above 2^20 items among shorter ones: two streams at once, each
     with a workspace of its own, then a captured call replayed on new keys."""
     import torch
-    sizes = [M + 1, 40, 300_000, 2 * M + 16_385, 17_000, 0, 64, 5 * M]
     n = sum(sizes)
     off = np.concatenate([[0], np.cumsum(sizes)]).astype(np.uint32)
     o = to_dev(off)
@@ -281,6 +285,29 @@ def test_64_bit_keys_both_samples_miss(vdt):
     assert v is None or np.array_equal(v.cpu().numpy(), order.astype(vdt))
     print(f"{ms:.3f} ms", flush=True)
     assert ms < 20.0  # one block alone: 77 ms
+
+
+def test_keys_that_samples_miss_on_two_streams():
+    """Two sorts whose leaves take the whole grid, at once: each goes on with
+    whatever blocks of it are on the chip."""
+    import torch
+    a, b = keys_of("missed", 1 << 20, 33, np.uint32), missed((1 << 22) + 11, 5, 2048, True)
+    ka, kb = to_dev(a), torch.from_numpy(b.view(np.int64).copy()).cuda()
+    streams = [torch.cuda.Stream() for _ in range(2)]
+    x, y = [torch.empty_like(ka) for _ in range(4)], torch.empty_like(kb)
+    announce("two sorts of missed keys at once")
+    sync()
+    for rep in range(3):
+        with torch.cuda.stream(streams[0]):
+            for k in x:
+                k.copy_(ka)
+                rts.sort_keys(k, stream=streams[0])
+        with torch.cuda.stream(streams[1]):
+            y.copy_(kb)
+            rts.sort_keys64(y, stream=streams[1])
+        sync()
+        assert all(np.array_equal(to_host(k), np.sort(a)) for k in x), rep
+        assert np.array_equal(y.cpu().numpy().view(np.uint64), np.sort(b)), rep
 
 
 @pytest.mark.parametrize("own,digits", [(None, True), (50_000, True), (1 << 20, False)])
